@@ -526,11 +526,14 @@ __global__ __launch_bounds__(BKT_THREADS) void k_bucket_scatter(int64_t n, const
 // (window << L | bit) of the set bits of its LDS bitmap, written to
 // out[boff[b] ...] below limit.  Reads every key of the bucket before
 // writing, so out may be keys (the buckets are disjoint ranges).  The bitmap
-// is read in blocks of 64 words; the ids of a block are written 64 at a
-// time, lane l taking the block's (r * 64 + l)-th set bit, so that a
-// wavefront's stores go to consecutive positions.
+// is read in blocks of 64 words, one word per lane of a wavefront: each lane
+// walks its word's set bits and puts their ids at their ranks in a stage in
+// LDS, which the wavefront then stores to consecutive positions, BM_STAGE ids
+// at a time (the LDS that the bitmap leaves of a CU's 160 KB, over the 16
+// wavefronts).
 constexpr int BM_WORDS_MAX = (1 << SORT_LBITS) >> 5;
 constexpr int BM_BLOCKS_MAX = BM_WORDS_MAX / 64;
+constexpr int BM_STAGE = 448;
 
 __global__ __launch_bounds__(BKT_THREADS) void k_bucket_bitmap(int nb, const uint32_t *boff, const uint32_t *keys,
                                                                int L, int H, uint32_t *out, int64_t limit)
@@ -538,11 +541,13 @@ __global__ __launch_bounds__(BKT_THREADS) void k_bucket_bitmap(int nb, const uin
     extern __shared__ uint32_t bm[];            // 2^L bits, whole blocks of 64 words
     __shared__ uint32_t btot[BM_BLOCKS_MAX];    // set bits per block, then the blocks' offsets
     __shared__ uint32_t wsum[BKT_THREADS / 64];
+    __shared__ uint32_t stages[BKT_THREADS / 64][BM_STAGE];
     const int nw = ((1 << L) >> 5) > 0 ? (1 << L) >> 5 : 1;
     const int nbk = (nw + 63) / 64;
     const uint32_t lmask = (1u << L) - 1u;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     constexpr int NWAVE = BKT_THREADS / 64;
+    uint32_t *stage = stages[wv];
     for (int b = blockIdx.x; b < nb; b += gridDim.x) {
         const uint32_t s = boff[b], e = boff[b + 1];
         if (s == e || (int64_t)s >= limit) continue;   // uniform over the workgroup
@@ -589,33 +594,29 @@ __global__ __launch_bounds__(BKT_THREADS) void k_bucket_bitmap(int nb, const uin
         __syncthreads();
         const uint32_t hi = (H > 0) ? ((uint32_t)b & ((1u << H) - 1u)) << L : 0u;
         for (int k = wv; k < nbk; k += NWAVE) {
-            const uint32_t word = bm[k * 64 + lane];
+            uint32_t word = bm[k * 64 + lane];
             const uint32_t c = (uint32_t)__popc(word);
             uint32_t incl = c;
+#pragma unroll
             for (int d = 1; d < 64; d <<= 1) {
                 const uint32_t t = __shfl_up(incl, d, 64);
                 if (lane >= d) incl += t;
             }
-            const uint32_t excl = incl - c;
             const uint32_t T = (uint32_t)__shfl((int)incl, 63, 64);
             const int64_t base = (int64_t)s + btot[k];
-            for (uint32_t r0 = 0; r0 < T; r0 += 64) {
-                const uint32_t o = r0 + (uint32_t)lane;
-                // the word holding set bit o of the block: the last lane whose
-                // exclusive count is <= o
-                int at = 0;
-                for (int step = 32; step >= 1; step >>= 1) {
-                    const uint32_t ex = (uint32_t)__shfl((int)excl, at + step < 64 ? at + step : 63, 64);
-                    if (at + step < 64 && ex <= o) at += step;
+            const uint32_t first = hi | ((uint32_t)(k * 64 + lane) << 5);
+            uint32_t at = incl - c;   // rank of this lane's next set bit in the block
+            for (uint32_t r0 = 0; r0 < T; r0 += BM_STAGE) {
+                const uint32_t m = min(T - r0, (uint32_t)BM_STAGE);
+                while (word != 0u && at < r0 + m) {
+                    stage[at - r0] = first | (uint32_t)(__ffs(word) - 1);
+                    word &= word - 1u;
+                    ++at;
                 }
-                uint32_t w = (uint32_t)__shfl((int)word, at, 64);
-                const uint32_t ex_at = (uint32_t)__shfl((int)excl, at, 64);
-                if (o < T) {
-                    for (uint32_t skip = o - ex_at; skip; --skip) w &= w - 1u;
-                    const int bit = __ffs(w) - 1;
-                    const int64_t pos = base + o;
-                    if (pos < limit) out[pos] = hi | ((uint32_t)(k * 64 + at) << 5) | (uint32_t)bit;
-                }
+                __builtin_amdgcn_wave_barrier();
+                for (uint32_t o = (uint32_t)lane; o < m; o += 64)
+                    if (base + r0 + o < limit) out[base + r0 + o] = stage[o];
+                __builtin_amdgcn_wave_barrier();
             }
         }
         __syncthreads();
