@@ -316,7 +316,7 @@ def leg_c4(ctx, dx, dy, table):
                              "autotune": {"pixels_per_vertex": bppv,
                                           "trial_ms": {str(k): round(v, 1) for k, v in btrials.items()}},
                              "chunk_query_overlaps": overlaps,
-                             "roofline": roofline("k_batch_select (count pass)", BYTES_PER_POINT * CHUNK_POINTS * overlaps,
+                             "roofline": roofline("k_batch_hits (probe pass)", BYTES_PER_POINT * CHUNK_POINTS * overlaps,
                                                   count_ms,
                                                   bytes_rule="16 B per point-query test: every overlap of a 4096-point "
                                                              "table chunk with a query's canvas box")}

@@ -16,6 +16,7 @@
 #include "lookup.h"
 
 #include <hipcub/hipcub.hpp>
+#include <rocprim/warp/warp_scan.hpp>
 
 #include <algorithm>
 #include <cstdlib>
@@ -279,264 +280,303 @@ __device__ uint32_t chunk_word(const CanvasView &v, const double4 cb)
     return (__syncthreads_and(same) && w0 != full) ? w0 : NO_WORD;
 }
 
+// Inclusive prefix sum over the wavefront (rocPRIM's cross-lane warp scan).
+__device__ __forceinline__ uint32_t wave_incl_sum(uint32_t v)
+{
+    uint32_t r;
+    typename rocprim::warp_scan<uint32_t, 64>::storage_type storage;
+    rocprim::warp_scan<uint32_t, 64>().inclusive_scan(v, r, storage, rocprim::plus<uint32_t>());
+    return r;
+}
+
+// ------------------------------------------------------------ wavefront tasks
+//
+// A table chunk is probed by wavefronts of their own: a task is BW_PTS words
+// of 64 consecutive table points, one point per lane and word, and needs no
+// barrier.  The table is in Z order, so a task's box is small: most of the
+// (task, canvas) tests end at the box or at the canvas's coarse blocks under
+// it.  Few points per lane keep the registers low enough for eight
+// five or six wavefronts per SIMD, which is what hides the chain of dependent
+// reads (descriptor, coarse word, canvas word, record, edges) that bounds a
+// probe.
+constexpr int BW_PTS = 4;                        // words of 64 points per task
+constexpr int BW_TASKS = CHUNK / (64 * BW_PTS);  // tasks per chunk
+constexpr int BW_WORDS = CHUNK / 64;             // result words per chunk
+
+__device__ __forceinline__ double uniform_f64(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// Exact box of a task's points (NaN: no point); (min x, min y, max x, max y),
+// the same in every lane.  Without points it is inverted.
+__device__ __forceinline__ double4 task_box(const double *xs, const double *ys)
+{
+    double x0 = INFINITY, x1 = -INFINITY, y0 = INFINITY, y1 = -INFINITY;
+#pragma unroll
+    for (int u = 0; u < BW_PTS; ++u) {
+        x0 = fmin(x0, xs[u]); x1 = fmax(x1, xs[u]);
+        y0 = fmin(y0, ys[u]); y1 = fmax(y1, ys[u]);
+    }
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) {
+        x0 = fmin(x0, __shfl_xor(x0, d, 64)); x1 = fmax(x1, __shfl_xor(x1, d, 64));
+        y0 = fmin(y0, __shfl_xor(y0, d, 64)); y1 = fmax(y1, __shfl_xor(y1, d, 64));
+    }
+    return make_double4(uniform_f64(x0), uniform_f64(y0), uniform_f64(x1), uniform_f64(y1));
+}
+
+// The canvas word of every point of a task, when one word holds for all of
+// them: 0 when the points' exact box misses the canvas's half-open box;
+// otherwise the box lies inside it and every coarse block its pixels can fall
+// in (at most 64 are looked at, one per lane) is uniform with that word (the
+// pixel map is monotonic, so the box's corner pixels bound every point's
+// pixel).  Else NO_WORD.  Called by the whole wavefront; the result is uniform.
+__device__ __forceinline__ uint32_t task_word(const CanvasView &v, const double4 cb, int lane)
+{
+    if (!(cb.z >= v.bx0 && cb.x < v.bx1 && cb.w >= v.by0 && cb.y < v.by1)) return 0u;
+    if (!(v.bx0 <= cb.x && cb.z < v.bx1 && v.by0 <= cb.y && cb.w < v.by1)) return NO_WORD;
+    auto col = [&](double x) { return min((int)__dmul_rn(__dsub_rn(x, v.X0), v.sx), v.W - 1) >> v.blog; };
+    auto row = [&](double y) { return min((int)__dmul_rn(__dsub_rn(y, v.Y0), v.sy), v.H - 1) >> v.blog; };
+    const int c0 = col(cb.x), c1 = col(cb.z), r0 = row(cb.y), r1 = row(cb.w);
+    const int nbx = c1 - c0 + 1, nb = nbx * (r1 - r0 + 1);
+    if (nb > 64) return NO_WORD;
+    const int t = lane < nb ? lane : 0;
+    const int i = (r0 + t / nbx) * v.Wc + c0 + t % nbx;
+    const uint32_t w = v.cbyte ? (uint32_t)((const uint8_t *)v.coarse)[i] : (uint32_t)v.coarse[i];
+    const uint32_t w0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)w);
+    const uint32_t full = v.cbyte ? COARSE_BYTE_FULL : (uint32_t)COARSE_FULL;
+    return (__all(w == w0) && w0 != full) ? w0 : NO_WORD;
+}
+
 // ------------------------------------------------------------ batch select
 
-// Pass 1 (EMIT = false): matches per pair into pcount (64-bit, so that the
-// scan of the counts accumulates in 64 bits) and, when hits is given, each
-// thread's matches as a bit mask (hits[pair * BT_THREADS + thread], bit u
-// for the thread's point u).  Pass 2 (EMIT): for
-// the pairs of queries q0 <= q < q1 only, the 32-bit keys
-// ((query - qrun0[query]) << idbits | point id) of the matching points at
-// out[pbase[pair] - kbase ...]: every query's keys land in its own output
-// range, and a sort of each run of queries (qrun0: a query's run's first
-// query) orders them.
-template <bool EMIT>
-__global__ __launch_bounds__(BT_THREADS) void k_batch_select(SetArgs S, int64_t nfin, int64_t nchunk,
-                                                             const double *X, const double *Y,
-                                                             const uint32_t *ids, const unsigned int *cbase,
-                                                             const uint32_t *plist, const uint32_t *pq,
-                                                             unsigned long long *pcount, const unsigned long long *pbase,
-                                                             uint32_t *out, uint32_t q0, uint32_t q1,
-                                                             unsigned long long kbase, const uint32_t *qrun0,
-                                                             int idbits, uint16_t *hits, const double4 *chunk_bb)
+// Probe pass: hits[(p - p0) * BW_WORDS + j] = the points 64 j + lane of pair
+// p's chunk (bit = lane) that lie in its query's polygon, for the pairs p0 <=
+// p < p1.  Bound by the latency of its gathers: 3.0 ms for 130,574 (chunk,
+// query) pairs, 35 us for 805.  With 16 points per thread of a 256-thread
+// workgroup (158 registers, 2.2 wavefronts per SIMD, two barriers per pair)
+// it took 5.0 ms and 158 us.
+__global__ __launch_bounds__(BT_THREADS) void k_batch_hits(SetArgs S, int64_t nfin, int64_t nchunk, const double *X,
+                                                           const double *Y, const unsigned int *cbase,
+                                                           const uint32_t *plist, const uint32_t *pq, uint32_t p0,
+                                                           uint32_t p1, unsigned long long *hits)
 {
-    static_assert(BT_PER <= 16, "a thread's matches are kept as 16 bits");
-    __shared__ uint32_t wsum[BT_THREADS / 64];
-    for (int64_t c = blockIdx.x; c < nchunk; c += gridDim.x) {
-        const int64_t b = c * CHUNK;
-        double xs[BT_PER], ys[BT_PER];
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int64_t ntask = nchunk * BW_TASKS;
+    for (int64_t task = (int64_t)blockIdx.x * (BT_THREADS / 64) + wv; task < ntask;
+         task += (int64_t)gridDim.x * (BT_THREADS / 64)) {
+        const int64_t c = task / BW_TASKS;
+        const int part = (int)(task % BW_TASKS);
+        const uint32_t t0 = cbase[c], t1 = cbase[c + 1];
+        if (t0 == t1) continue;
+        double xs[BW_PTS], ys[BW_PTS];
+        unsigned long long valid[BW_PTS];
 #pragma unroll
-        for (int u = 0; u < BT_PER; ++u) {
-            const int64_t i = b + (int64_t)u * BT_THREADS + threadIdx.x;   // coalesced
+        for (int u = 0; u < BW_PTS; ++u) {
+            const int64_t i = c * CHUNK + part * (64 * BW_PTS) + 64 * u + lane;
             xs[u] = i < nfin ? X[i] : NAN;
             ys[u] = i < nfin ? Y[i] : NAN;
+            valid[u] = __ballot(i < nfin);
         }
-        for (uint32_t t = cbase[c]; t < cbase[c + 1]; ++t) {
+        const double4 cb = task_box(xs, ys);
+        for (uint32_t t = t0; t < t1; ++t) {
             const uint32_t p = plist[t];
-            const uint32_t qy = pq[p];
-            if (EMIT && (qy < q0 || qy >= q1)) continue;   // uniform over the workgroup
-            const CanvasDesc d = S.cds[qy];
+            if (p < p0 || p >= p1) continue;
+            const CanvasDesc d = S.cds[pq[p]];
             const CanvasView v = set_view(d, S.cells, S.coarse, S.cands, S.ledges, S.pspan);
-            uint32_t hit = 0;
-            const uint32_t cw = chunk_word(v, chunk_bb[c]);
+            unsigned long long m[BW_PTS];
+            const uint32_t cw = task_word(v, cb, lane);
             if (cw != NO_WORD) {
-                // one word for the whole chunk: all of its points or none
-                if (cw != 0u) {
 #pragma unroll
-                    for (int u = 0; u < BT_PER; ++u)
-                        if (b + (int64_t)u * BT_THREADS + threadIdx.x < nfin) hit |= 1u << u;
-                }
+                for (int u = 0; u < BW_PTS; ++u) m[u] = cw != 0u ? valid[u] : 0ull;
             } else {
+                Look lk[BW_PTS];
+                uint32_t ws[BW_PTS];
 #pragma unroll
-                for (int u = 0; u < BT_PER; ++u) {
-                    const uint32_t w = lookup(v, v.coarse, xs[u], ys[u]);
-                    bool in = false;
-                    if (w & BFLAG) {
-                        uint32_t rec = w & ~BFLAG;
+                for (int u = 0; u < BW_PTS; ++u) lk[u] = look_coarse(v, v.coarse, xs[u], ys[u]);
+#pragma unroll
+                for (int u = 0; u < BW_PTS; ++u) ws[u] = lk[u].full ? ((gu32p)v.cells)[lk[u].fidx] : lk[u].word;
+#pragma unroll
+                for (int u = 0; u < BW_PTS; ++u) {
+                    bool in = ws[u] != 0u;
+                    if (ws[u] & BFLAG) {
+                        in = false;
+                        uint32_t rec = ws[u] & ~BFLAG;
                         while (true) {
                             const Cand cd = v.cands[rec];
                             if (cand_inside(v, cd, xs[u], ys[u])) in = true;
                             if (cd.meta & CAND_LAST) break;
                             ++rec;
                         }
-                    } else {
-                        in = w != 0u;
                     }
-                    hit |= (in ? 1u : 0u) << u;
+                    m[u] = __ballot(in);
                 }
             }
-            // block-wide exclusive scan of the per-thread match counts
-            const uint32_t cnt = (uint32_t)__popc(hit);
-            const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-            uint32_t inc = cnt;
+            unsigned long long mine = m[0];
 #pragma unroll
-            for (int dd = 1; dd < 64; dd <<= 1) {
-                const uint32_t tt = __shfl_up(inc, dd, 64);
-                if (lane >= dd) inc += tt;
-            }
-            if (lane == 63) wsum[wv] = inc;
-            __syncthreads();
-            uint32_t pre = 0, tot = 0;
-#pragma unroll
-            for (int q = 0; q < BT_THREADS / 64; ++q) {
-                if (q < wv) pre += wsum[q];
-                tot += wsum[q];
-            }
-            __syncthreads();
-            if (!EMIT) {
-                if (threadIdx.x == 0) pcount[p] = tot;
-                if (hits) hits[(size_t)p * BT_THREADS + threadIdx.x] = (uint16_t)hit;
-            } else if (hit) {
-                unsigned long long pos = pbase[p] - kbase + pre + inc - cnt;
-                const uint32_t qk = (qy - qrun0[qy]) << idbits;
-#pragma unroll
-                for (int u = 0; u < BT_PER; ++u)
-                    if (hit & (1u << u)) out[pos++] = qk | ids[b + (int64_t)u * BT_THREADS + threadIdx.x];
-            }
+            for (int u = 1; u < BW_PTS; ++u) mine = lane == u ? m[u] : mine;
+            if (lane < BW_PTS) hits[(size_t)(p - p0) * BW_WORDS + part * BW_PTS + lane] = mine;
         }
     }
 }
 
-// The write pass from the count pass's match masks: no second probe.  Each
-// workgroup takes pairs p0 <= p < p1 (the pairs of a run of queries, which
-// are contiguous in query-major order), gathers the keys of its matches
-// into LDS and stores them as one contiguous block at out[pbase[p] - kbase].
-__global__ __launch_bounds__(BT_THREADS) void k_batch_emit_hits(int64_t p0, int64_t p1, const uint32_t *pq,
-                                                                const uint32_t *pc, const uint16_t *hits,
-                                                                const unsigned long long *pbase, const uint32_t *ids,
-                                                                const uint32_t *qrun0, int idbits, uint32_t *out,
-                                                                unsigned long long kbase)
+// Ordering the ids of the hit words.  A bucket is a query and a window of 2^L
+// consecutive ids; the buckets, query by query, are in output order.  A tile
+// is up to TILE_PAIRS pairs of one query: its ids are put in window order in
+// LDS and stored as one block, with the start of every window in it.  Bucket
+// totals come from those starts, a scan of them gives every bucket its output
+// range, and every bucket is ordered with a bitmap of its window in LDS,
+// filled from the query's tiles, whose set bits, read in order, are its ids.
+//
+// An id costs one 4-byte gather, one coalesced store and load, one coalesced
+// store of the result and four LDS operations: 5.7 ns per 1,000 ids (340M ids
+// of 128 stars over 50M points: tiles 0.90 ms, buckets 1.05 ms), bound by
+// instruction issue in the buckets and by the gathers in the tiles.  Keys
+// written query by query, counted per bucket and scattered with 4-byte stores
+// took 14 ns.
+constexpr int TILE_PAIRS = 4;
+constexpr int TILE_IDS = TILE_PAIRS * CHUNK;
+constexpr int TILE_THREADS = 1024;
+constexpr int TILE_BINS = 4096;                 // windows of a query (2^31 ids at most)
+constexpr int SORT_LBITS = 19;                  // largest window: a 64 KB LDS bitmap, two workgroups per CU
+constexpr int SORT_LMIN = 16;                   // smallest one taken to spread few ids over the chip
+
+__global__ __launch_bounds__(TILE_THREADS, 8) void k_hit_tiles(int nq, const uint32_t *tfirst,
+                                                            const unsigned long long *qbase, uint32_t p0,
+                                                            const uint32_t *pc, const unsigned long long *hits,
+                                                            const uint32_t *ids, int L, int nbins, uint32_t *keys,
+                                                            uint16_t *starts)
 {
-    __shared__ uint32_t stage[CHUNK];
-    __shared__ uint32_t wsum[BT_THREADS / 64];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    for (int64_t p = p0 + blockIdx.x; p < p1; p += gridDim.x) {
-        const uint32_t hit = hits[(size_t)p * BT_THREADS + threadIdx.x];
-        const uint32_t cnt = (uint32_t)__popc(hit);
-        uint32_t inc = cnt;
-#pragma unroll
-        for (int dd = 1; dd < 64; dd <<= 1) {
-            const uint32_t tt = __shfl_up(inc, dd, 64);
-            if (lane >= dd) inc += tt;
-        }
-        if (lane == 63) wsum[wv] = inc;
-        __syncthreads();
-        uint32_t pre = 0, tot = 0;
-#pragma unroll
-        for (int q = 0; q < BT_THREADS / 64; ++q) {
-            if (q < wv) pre += wsum[q];
-            tot += wsum[q];
-        }
-        if (tot) {
-            const uint32_t qy = pq[p];
-            const uint32_t qk = (qy - qrun0[qy]) << idbits;
-            const int64_t b = (int64_t)pc[p] * CHUNK;
-            uint32_t at = pre + inc - cnt;
-#pragma unroll
-            for (int u = 0; u < BT_PER; ++u)
-                if (hit & (1u << u)) stage[at++] = qk | ids[b + (int64_t)u * BT_THREADS + threadIdx.x];
-            __syncthreads();
-            uint32_t *dst = out + (pbase[p] - kbase);
-            for (uint32_t i = threadIdx.x; i < tot; i += BT_THREADS) dst[i] = stage[i];
-        }
-        __syncthreads();
+    constexpr int PER = TILE_IDS / TILE_THREADS;   // words of a wavefront
+    static_assert(PER * (TILE_THREADS / 64) == TILE_PAIRS * BW_WORDS, "a wavefront takes whole words of one pair");
+    extern __shared__ uint32_t tl[];
+    __shared__ uint32_t wsum[TILE_THREADS / 64];
+    uint32_t *bins = tl, *sorted = tl + ((nbins + 127) & ~63);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t tile = blockIdx.x;
+    // the tile's query: the last one that starts at or before it
+    int lo = 0, hi = nq - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (tfirst[mid] <= tile) lo = mid; else hi = mid - 1;
     }
-}
-
-// Ordering a run's keys without a radix sort.  A key is (query - first
-// query of the run) << idbits | id, unique within the run.  Its top bits,
-// key >> L with L = min(idbits, 20), name a bucket: a query and a window of
-// 2^L consecutive ids.  Buckets are counted, the keys scattered into bucket
-// order (when a query has more than one window), and each bucket is then
-// ordered with a bitmap of its window in LDS: the set bits, read in order,
-// are the bucket's ids ascending.
-constexpr int SORT_LBITS = 20;                  // window bits: a 128 KB LDS bitmap
-constexpr int BUCKETS_MAX = 4096;               // buckets of a run when a query has several windows
-constexpr int BKT_THREADS = 1024;
-constexpr int SCAT_PER = 8;                     // keys per thread of the scatter
-
-__global__ __launch_bounds__(BKT_THREADS) void k_bucket_hist(int64_t n, const uint32_t *keys, int L,
-                                                             uint32_t *hist)
-{
-    __shared__ uint32_t h[BUCKETS_MAX];
-    for (int b = threadIdx.x; b < BUCKETS_MAX; b += BKT_THREADS) h[b] = 0u;
+    constexpr int WPP = BW_WORDS / PER;            // wavefronts per pair
+    const uint32_t p = (uint32_t)qbase[lo] + (tile - tfirst[lo]) * TILE_PAIRS + (uint32_t)(wv / WPP);
+    const bool any = p < (uint32_t)qbase[lo + 1];
+    uint32_t v[PER], rb[PER], on = 0u;
+    for (int b = tid; b < nbins; b += TILE_THREADS) bins[b] = 0u;
+    const int j0 = (wv % WPP) * PER;
+    const unsigned long long *h = hits + (size_t)((any ? p : p0) - p0) * BW_WORDS + j0;
+    const uint32_t *id0 = ids + (int64_t)(any ? pc[p] : 0u) * CHUNK + 64 * j0;
+    if (any)
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const unsigned long long w = h[k];
+            const uint32_t half = lane < 32 ? (uint32_t)w : (uint32_t)(w >> 32);
+            on |= ((half >> (lane & 31)) & 1u) << k;
+        }
+#pragma unroll
+    for (int k = 0; k < PER; ++k) v[k] = (on >> k) & 1u ? id0[64 * k + lane] : 0u;
     __syncthreads();
-    const int64_t nth = (int64_t)gridDim.x * BKT_THREADS;
-    for (int64_t i0 = (int64_t)blockIdx.x * BKT_THREADS + threadIdx.x; i0 < n; i0 += 8 * nth) {
-        uint32_t kk[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) kk[u] = i0 + u * nth < n ? keys[i0 + u * nth] : 0u;
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-            if (i0 + u * nth < n) atomicAdd(&h[kk[u] >> L], 1u);
-    }
-    __syncthreads();
-    for (int b = threadIdx.x; b < BUCKETS_MAX; b += BKT_THREADS)
-        if (h[b]) atomicAdd(&hist[b], h[b]);
-}
-
-// Exclusive scan of nb <= BUCKETS_MAX counts (one workgroup); boff[nb] = total.
-__global__ __launch_bounds__(BKT_THREADS) void k_bucket_scan(int nb, const uint32_t *hist, uint32_t *boff)
-{
-    constexpr int PER = BUCKETS_MAX / BKT_THREADS;
-    __shared__ uint32_t wsum[BKT_THREADS / 64];
-    uint32_t v[PER], tot = 0;
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
-        const int b = threadIdx.x * PER + k;
-        v[k] = b < nb ? hist[b] : 0u;
-        tot += v[k];
+        // window and rank in it (below 2^14) in one word; a lane without a
+        // hit counts in a bin of its own, past the windows
+        const uint32_t bin = (on >> k) & 1u ? v[k] >> L : (uint32_t)(nbins + lane);
+        rb[k] = (bin << 14) | (atomicAdd(&bins[bin], 1u) & 0x3fffu);
     }
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    uint32_t inc = tot;
-    for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t t = __shfl_up(inc, d, 64);
-        if (lane >= d) inc += t;
-    }
+#pragma unroll
+    for (int k = 0; k < PER; ++k) asm volatile("" : "+v"(rb[k]));   // one register each, not its parts
+    __syncthreads();
+    // the windows' starts: an exclusive scan of the counts, a few per thread
+    const int per = (nbins + TILE_THREADS - 1) / TILE_THREADS, b0 = min(nbins, tid * per), b1 = min(nbins, b0 + per);
+    uint32_t mine = 0u;
+#pragma nounroll
+    for (int b = b0; b < b1; ++b) mine += bins[b];
+    const uint32_t inc = wave_incl_sum(mine);
     if (lane == 63) wsum[wv] = inc;
     __syncthreads();
-    uint32_t pre = 0, all = 0;
-    for (int w = 0; w < BKT_THREADS / 64; ++w) {
-        if (w < wv) pre += wsum[w];
-        all += wsum[w];
+    uint32_t at = inc - mine, total = 0u;
+#pragma nounroll
+    for (int w = 0; w < TILE_THREADS / 64; ++w) {
+        const uint32_t n = wsum[w];
+        if (w < wv) at += n;
+        total += n;
     }
-    uint32_t at = pre + inc - tot;
+    uint16_t *st = starts + (size_t)tile * (nbins + 1);
+#pragma nounroll
+    for (int b = b0; b < b1; ++b) {
+        const uint32_t n = bins[b];
+        bins[b] = at;
+        st[b] = (uint16_t)at;
+        at += n;
+    }
+    if (tid == 0) st[nbins] = (uint16_t)total;
+    __syncthreads();
 #pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        const int b = threadIdx.x * PER + k;
-        if (b < nb) boff[b] = at;
-        at += v[k];
-    }
-    if (threadIdx.x == 0) boff[nb] = all;
+    for (int k = 0; k < PER; ++k)
+        if ((on >> k) & 1u) sorted[bins[rb[k] >> 14] + (rb[k] & 0x3fffu)] = v[k];
+    __syncthreads();
+    if (!keys) return;   // counts only
+    uint32_t *dst = keys + (size_t)tile * TILE_IDS;
+    for (uint32_t i = tid; i < total; i += TILE_THREADS) dst[i] = sorted[i];
 }
 
-// Keys into bucket order: each workgroup takes a tile of keys, counts its
-// buckets in LDS, reserves each bucket's share with one atomic, then places
-// its keys (cursor: nb zeros on entry).
-__global__ __launch_bounds__(BKT_THREADS) void k_bucket_scatter(int64_t n, const uint32_t *keys, int L,
-                                                                const uint32_t *boff, uint32_t *cursor,
-                                                                uint32_t *out)
+// Bucket totals: tot[q * nbins + b] = ids of query q in window b, summed over
+// the query's tiles (64 windows by 16 slices of the tiles per workgroup).
+__global__ __launch_bounds__(TILE_THREADS) void k_bucket_tot(int nq, const uint32_t *tfirst, const uint16_t *starts,
+                                                             int nbins, unsigned long long *tot)
 {
-    __shared__ uint32_t h[BUCKETS_MAX];
-    constexpr int64_t TILE = (int64_t)BKT_THREADS * SCAT_PER;
-    for (int64_t t0 = (int64_t)blockIdx.x * TILE; t0 < n; t0 += (int64_t)gridDim.x * TILE) {
-        for (int b = threadIdx.x; b < BUCKETS_MAX; b += BKT_THREADS) h[b] = 0u;
-        __syncthreads();
-        uint32_t k[SCAT_PER];
-#pragma unroll
-        for (int u = 0; u < SCAT_PER; ++u) {
-            const int64_t i = t0 + (int64_t)u * BKT_THREADS + threadIdx.x;
-            k[u] = i < n ? keys[i] : 0u;
-            if (i < n) atomicAdd(&h[k[u] >> L], 1u);
+    constexpr int SL = TILE_THREADS / 64;
+    __shared__ uint32_t s[SL][64];
+    const int lane = threadIdx.x & 63, sl = threadIdx.x >> 6;
+    const int b = blockIdx.x * 64 + lane;
+    for (int q = blockIdx.y; q < nq; q += gridDim.y) {
+        const uint32_t t0 = tfirst[q], t1 = tfirst[q + 1];
+        uint32_t n = 0u;
+        if (b < nbins) {
+#pragma unroll 4
+            for (uint32_t t = t0 + sl; t < t1; t += SL) {
+                const uint16_t *st = starts + (size_t)t * (nbins + 1) + b;
+                n += (uint32_t)st[1] - (uint32_t)st[0];
+            }
         }
+        s[sl][lane] = n;
         __syncthreads();
-        for (int b = threadIdx.x; b < BUCKETS_MAX; b += BKT_THREADS)
-            if (h[b]) h[b] = boff[b] + atomicAdd(&cursor[b], h[b]);
-        __syncthreads();
+        if (sl == 0) {
 #pragma unroll
-        for (int u = 0; u < SCAT_PER; ++u) {
-            const int64_t i = t0 + (int64_t)u * BKT_THREADS + threadIdx.x;
-            if (i < n) out[atomicAdd(&h[k[u] >> L], 1u)] = k[u];
+            for (int k = 1; k < SL; ++k) n += s[k][lane];
+            if (b < nbins) tot[(size_t)q * nbins + b] = n;
         }
         __syncthreads();
     }
 }
 
-// Bucket b's keys keys[boff[b], boff[b+1]) in ascending id order: the ids
-// (window << L | bit) of the set bits of its LDS bitmap, written to
-// out[boff[b] ...] below limit.  Reads every key of the bucket before
-// writing, so out may be keys (the buckets are disjoint ranges).  The bitmap
+// Buckets b < nb in ascending id order: bucket b's ids, its window's run in
+// each of its query's tiles, become the ids (window << L | bit) of the set
+// bits of its LDS bitmap, written to out[offs[b] ...] below limit.  The bitmap
 // is read in blocks of 64 words, one word per lane of a wavefront: each lane
 // walks its word's set bits and puts their ids at their ranks in a stage in
 // LDS, which the wavefront then stores to consecutive positions, BM_STAGE ids
-// at a time (the LDS that the bitmap leaves of a CU's 160 KB, over the 16
-// wavefronts).
+// at a time.  The phases of a bucket (clear, fill, count, store) wait on one
+// another, so the window is half of what one workgroup's LDS would hold and
+// two workgroups share a CU.
+constexpr int BKT_THREADS = 1024;
 constexpr int BM_WORDS_MAX = (1 << SORT_LBITS) >> 5;
 constexpr int BM_BLOCKS_MAX = BM_WORDS_MAX / 64;
-constexpr int BM_STAGE = 448;
+constexpr int BM_STAGE = 192;
+constexpr int BM_FLY = 4;                       // tiles' runs in flight per wavefront, two loads each
 
-__global__ __launch_bounds__(BKT_THREADS) void k_bucket_bitmap(int nb, const uint32_t *boff, const uint32_t *keys,
-                                                               int L, int H, uint32_t *out, int64_t limit)
+__global__ __launch_bounds__(BKT_THREADS, 8) void k_bucket_bitmap(int64_t nb, const unsigned long long *offs,
+                                                               const uint32_t *tfirst, const uint16_t *starts,
+                                                               const uint32_t *keys, int L, int nbins, uint32_t *out,
+                                                               int64_t limit)
 {
     extern __shared__ uint32_t bm[];            // 2^L bits, whole blocks of 64 words
     __shared__ uint32_t btot[BM_BLOCKS_MAX];    // set bits per block, then the blocks' offsets
@@ -545,36 +585,57 @@ __global__ __launch_bounds__(BKT_THREADS) void k_bucket_bitmap(int nb, const uin
     const int nw = ((1 << L) >> 5) > 0 ? (1 << L) >> 5 : 1;
     const int nbk = (nw + 63) / 64;
     const uint32_t lmask = (1u << L) - 1u;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     constexpr int NWAVE = BKT_THREADS / 64;
     uint32_t *stage = stages[wv];
-    for (int b = blockIdx.x; b < nb; b += gridDim.x) {
-        const uint32_t s = boff[b], e = boff[b + 1];
-        if (s == e || (int64_t)s >= limit) continue;   // uniform over the workgroup
+    auto mark = [&](uint32_t id) {
+        const uint32_t lo = id & lmask;
+        atomicOr(&bm[lo >> 5], 1u << (lo & 31));
+    };
+    for (int64_t b = blockIdx.x; b < nb; b += gridDim.x) {
+        const unsigned long long s0 = offs[b];
+        if (offs[b + 1] == s0 || (int64_t)s0 >= limit) continue;   // uniform over the workgroup
+        const int q = (int)(b / nbins), win = (int)(b % nbins);
         for (int w = threadIdx.x; w < nbk * 64; w += BKT_THREADS) bm[w] = 0u;
         __syncthreads();
-        // eight keys of each thread in flight at a time
-        for (uint32_t i0 = s; i0 < e; i0 += 8 * BKT_THREADS) {
-            uint32_t kk[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const uint32_t i = i0 + (uint32_t)(u * BKT_THREADS) + threadIdx.x;
-                kk[u] = i < e ? keys[i] : 0u;
+        // each wavefront takes every NWAVE-th tile; the runs of 64 of its
+        // tiles are looked up at once, one per lane
+        const uint32_t t0 = tfirst[q], t1 = tfirst[q + 1];
+        for (uint32_t tb = t0 + wv; tb < t1; tb += 64 * NWAVE) {
+            const uint32_t tl = tb + (uint32_t)lane * NWAVE;
+            uint32_t rs = 0u, rn = 0u;
+            if (tl < t1) {
+                const uint16_t *st = starts + (size_t)tl * (nbins + 1) + win;
+                rs = st[0];
+                rn = (uint32_t)st[1] - rs;
             }
+            const int nt = (int)min(64u, (t1 - tb + NWAVE - 1) / NWAVE);
+            for (int k0 = 0; k0 < nt; k0 += BM_FLY) {
+                uint32_t a[BM_FLY], c[BM_FLY], len[BM_FLY];
+                const uint32_t *src[BM_FLY];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                if (i0 + (uint32_t)(u * BKT_THREADS) + threadIdx.x >= e) continue;
-                const uint32_t lo = kk[u] & lmask;
-                atomicOr(&bm[lo >> 5], 1u << (lo & 31));
+                for (int u = 0; u < BM_FLY; ++u) {
+                    const int k = min(k0 + u, 63);
+                    len[u] = k0 + u < nt ? (uint32_t)__builtin_amdgcn_readlane((int)rn, k) : 0u;
+                    src[u] = keys + (size_t)(tb + (uint32_t)k * NWAVE) * TILE_IDS +
+                             (uint32_t)__builtin_amdgcn_readlane((int)rs, k);
+                    a[u] = (uint32_t)lane < len[u] ? src[u][lane] : 0u;
+                    c[u] = (uint32_t)lane + 64 < len[u] ? src[u][lane + 64] : 0u;
+                }
+#pragma unroll
+                for (int u = 0; u < BM_FLY; ++u) {
+                    if ((uint32_t)lane < len[u]) mark(a[u]);
+                    if ((uint32_t)lane + 64 < len[u]) mark(c[u]);
+                    for (uint32_t i = (uint32_t)lane + 128; i < len[u]; i += 64) mark(src[u][i]);
+                }
             }
         }
         __syncthreads();
         // set bits per block of 64 words
         for (int k = wv; k < nbk; k += NWAVE) {
-            uint32_t c = (uint32_t)__popc(bm[k * 64 + lane]);
-#pragma unroll
-            for (int d = 32; d >= 1; d >>= 1) c += __shfl_xor(c, d, 64);
-            if (lane == 0) btot[k] = c;
+            const uint32_t c = wave_incl_sum((uint32_t)__popc(bm[k * 64 + lane]));
+            if (lane == 63) btot[k] = c;
         }
         __syncthreads();
         // exclusive scan of the block totals (nbk <= BKT_THREADS)
@@ -592,18 +653,13 @@ __global__ __launch_bounds__(BKT_THREADS) void k_bucket_bitmap(int nb, const uin
             if (threadIdx.x < nbk) btot[threadIdx.x] = pre + inc - v;
         }
         __syncthreads();
-        const uint32_t hi = (H > 0) ? ((uint32_t)b & ((1u << H) - 1u)) << L : 0u;
+        const uint32_t hi = (uint32_t)win << L;
         for (int k = wv; k < nbk; k += NWAVE) {
             uint32_t word = bm[k * 64 + lane];
             const uint32_t c = (uint32_t)__popc(word);
-            uint32_t incl = c;
-#pragma unroll
-            for (int d = 1; d < 64; d <<= 1) {
-                const uint32_t t = __shfl_up(incl, d, 64);
-                if (lane >= d) incl += t;
-            }
-            const uint32_t T = (uint32_t)__shfl((int)incl, 63, 64);
-            const int64_t base = (int64_t)s + btot[k];
+            const uint32_t incl = wave_incl_sum(c);
+            const uint32_t T = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+            const int64_t base = (int64_t)s0 + btot[k];
             const uint32_t first = hi | ((uint32_t)(k * 64 + lane) << 5);
             uint32_t at = incl - c;   // rank of this lane's next set bit in the block
             for (uint32_t r0 = 0; r0 < T; r0 += BM_STAGE) {
@@ -621,6 +677,13 @@ __global__ __launch_bounds__(BKT_THREADS) void k_bucket_bitmap(int nb, const uin
         }
         __syncthreads();
     }
+}
+
+// Query starts from the bucket offsets: qoff[q] = offs[q * nbins], qoff[nq] = the total.
+__global__ void k_query_off(int nq, int nbins, const unsigned long long *offs, unsigned long long *qoff)
+{
+    const int q = blockIdx.x * blockDim.x + threadIdx.x;
+    if (q <= nq) qoff[q] = offs[(size_t)q * nbins];
 }
 
 // ------------------------------------------------------------ batch join pairs
@@ -733,19 +796,6 @@ __global__ void k_split_pairs(int64_t n, const unsigned long long *keys, int pbi
         pt[i] = (uint32_t)(k >> pbits);
         pg[i] = (uint32_t)(k & m);
     }
-}
-
-// Query starts from pair bases: qoff[q] = pbase[first pair of q], qoff[nq] =
-// pbase[np] = the total.
-__global__ void k_query_off(int nq, const unsigned long long *qbase, const unsigned long long *pbase, int64_t np,
-                            unsigned long long *qoff)
-{
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q > nq) return;
-    const unsigned long long total = pbase[np];
-    if (q == nq) { qoff[nq] = total; return; }
-    const unsigned long long p = qbase[q];
-    qoff[q] = (p < (unsigned long long)np) ? pbase[p] : total;
 }
 
 // ------------------------------------------------------------ batch join-count
@@ -874,6 +924,7 @@ struct Pairs {
     uint32_t *pq = nullptr, *pc = nullptr, *plist = nullptr;
     unsigned int *cbase = nullptr;
     unsigned long long *qbase = nullptr;
+    std::vector<int64_t> qfirst;   // host: first pair of every query, then the total
 };
 
 static int make_pairs(spade_ctx *ctx, const spade_canvas *set, const spade_table *t, Pairs &P)
@@ -904,10 +955,12 @@ static int make_pairs(spade_ctx *ctx, const spade_canvas *set, const spade_table
     SPADE_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(nullptr, tb, qcount, qbase, nq + 1, st));
     if (ensure(ctx, cub, tb)) return SPADE_E_NOMEM;
     SPADE_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(cub.p, tb, qcount, qbase, nq + 1, st));
-    unsigned long long *h = (unsigned long long *)ensure_pinned(ctx, 64);
-    SPADE_HIP(ctx, hipMemcpyAsync(h, qbase + nq, 8, hipMemcpyDeviceToHost, st));
+    unsigned long long *h = (unsigned long long *)ensure_pinned(ctx, 8 * (size_t)(nq + 1));
+    if (!h) return set_error(ctx, SPADE_E_NOMEM, "pinned staging allocation failed");
+    SPADE_HIP(ctx, hipMemcpyAsync(h, qbase, 8 * (size_t)(nq + 1), hipMemcpyDeviceToHost, st));
     SPADE_HIP(ctx, hipStreamSynchronize(st));
-    const int64_t np = (int64_t)h[0];
+    P.qfirst.assign(h, h + nq + 1);
+    const int64_t np = P.qfirst[(size_t)nq];
     if (np >= (int64_t)INT32_MAX) return set_error(ctx, SPADE_E_UNSUPPORTED, "too many (chunk, query) pairs in one batch");
     DevBuf &bp = ctx->scratch[S_VALS];
     if (ensure(ctx, bp, sizeof(uint32_t) * 3 * (size_t)std::max<int64_t>(np, 1))) return SPADE_E_NOMEM;
@@ -1132,199 +1185,123 @@ int spade_batch_select(spade_ctx *ctx, const spade_canvas *set, const spade_tabl
     Pairs P;
     int rc = make_pairs(ctx, set, t, P);
     if (rc) return rc;
-    const int64_t np = P.np;
-    DevBuf &bc = ctx->scratch[S_VALS2];
-    DevBuf &bo = ctx->scratch[S_ENTC];
-    if (ensure(ctx, bc, sizeof(unsigned long long) * (size_t)(np + 1) + sizeof(unsigned long long) * (size_t)(np + 1) +
-                            sizeof(unsigned long long) * (size_t)(nq + 2) + 64))
-        return SPADE_E_NOMEM;
-    // 64-bit counts: hipCUB's scan accumulates in the input's type, and a
-    // batch may select more than 2^32 ids in total
-    unsigned long long *pcount = (unsigned long long *)bc.p;
-    unsigned long long *pbase = pcount + (np + 1);
-    unsigned long long *qoff = pbase + (np + 1);
     const SetArgs S = set_args(set);
-    const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(t->nchunk, (int64_t)num_cus_of(ctx->device) * 8));
-    // the count pass keeps every pair's match masks (2 bytes per point slot)
-    // when they fit the limit (SPADE_HIT_MASK_LIMIT bytes, default 16 GiB);
-    // the write pass then reads them instead of probing again
-    size_t hits_max = (size_t)16 << 30;
-    if (const char *e = getenv("SPADE_HIT_MASK_LIMIT")) hits_max = (size_t)strtoull(e, nullptr, 10);
-    DevBuf &bh = ctx->scratch[S_KEYS2];
-    const size_t hbytes = sizeof(uint16_t) * BT_THREADS * (size_t)std::max<int64_t>(np, 1);
-    uint16_t *hits = nullptr;
-    if (cap > 0 && hbytes <= hits_max) {
-        if (ensure(ctx, bh, hbytes) == SPADE_OK) hits = (uint16_t *)bh.p;
-        else ctx->err.clear();   // probe twice instead
-    }
-    hipLaunchKernelGGL(k_zero64, dim3(1), dim3(64), 0, st, (int64_t)1, pcount + np);
-    if (ctx->timing) SPADE_HIP(ctx, hipEventRecord(ctx->ev[2], st));
-    if (np > 0) {
-        hipLaunchKernelGGL(k_batch_select<false>, dim3(grid), dim3(BT_THREADS), 0, st, S, t->nfin, t->nchunk,
-                           (const double *)t->x.p, (const double *)t->y.p, (const uint32_t *)t->ids.p, P.cbase,
-                           P.plist, P.pq, pcount, nullptr, nullptr, 0u, (uint32_t)nq, 0ull, nullptr, 0, hits,
-                           (const double4 *)t->chunk_bb.p);
-        SPADE_HIP(ctx, hipGetLastError());
-    }
-    // the timed probe of a batch selection is its count pass
-    if (ctx->timing) SPADE_HIP(ctx, hipEventRecord(ctx->ev[3], st));
-    DevBuf &cub = ctx->scratch[S_CUBTMP];
-    size_t tb = 0;
-    SPADE_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(nullptr, tb, pcount, pbase, (int)(np + 1), st));
-    if (ensure(ctx, cub, tb)) return SPADE_E_NOMEM;
-    SPADE_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(cub.p, tb, pcount, pbase, (int)(np + 1), st));
-    // one readback: the queries' output offsets and their first pairs
-    unsigned long long *h =
-        (unsigned long long *)ensure_pinned(ctx, sizeof(unsigned long long) * 2 * (size_t)(nq + 1) + 64);
-    if (!h) return set_error(ctx, SPADE_E_NOMEM, "pinned staging allocation failed");
-    hipLaunchKernelGGL(k_query_off, dim3((nq + 1 + 255) / 256), dim3(256), 0, st, nq, P.qbase, pbase, np, qoff);
-    SPADE_HIP(ctx, hipGetLastError());
-    SPADE_HIP(ctx, hipMemcpyAsync(h, qoff, sizeof(unsigned long long) * (size_t)(nq + 1), hipMemcpyDeviceToHost, st));
-    SPADE_HIP(ctx, hipMemcpyAsync(h + nq + 1, P.qbase, sizeof(unsigned long long) * (size_t)(nq + 1),
-                                  hipMemcpyDeviceToHost, st));
-    SPADE_HIP(ctx, hipStreamSynchronize(st));
-    for (int q = 0; q <= nq; ++q) out_off[q] = (int64_t)h[q];
-    const unsigned long long total = h[nq];
-    const std::vector<unsigned long long> hq(h + nq + 1, h + 2 * (nq + 1));
-    // a buffer that is too small still receives the first cap ids in the
-    // canonical order (two-step Map); the call then reports the shortfall
-    const bool short_cap = (int64_t)total > cap;
-    if (total == 0 || cap == 0) {
-        if (short_cap) return set_error(ctx, SPADE_E_CAPACITY, "output capacity too small");
-        return SPADE_OK;
-    }
-    // Each query's ids are ordered per run of consecutive queries (at most
-    // 2^(32 - idbits) queries and 2^30 keys a run; a larger query alone),
-    // keyed by the 32-bit key (query - first query of its run) << idbits |
-    // id.  One write pass puts every key of the runs that end within cap at
-    // its final position in out_ids; each such run is then put in bucket
-    // order (query, window of 2^L ids) through scratch when a query spans
-    // several windows, and every bucket ordered with an LDS bitmap of its
-    // window, which writes the ids themselves.  The run that crosses cap, if
-    // any, is written to scratch by a pass of its own and only its first ids
-    // are written out; runs from cap on are not evaluated.
+    // Windows of the id buckets: the largest, or smaller ones while the
+    // buckets are too few to fill the chip (a single served selection).
+    const int cus = num_cus_of(ctx->device);
     const int idbits = std::max(1, bits_of((uint64_t)std::max<int64_t>(t->n - 1, 1)));
-    const int LB = std::min(idbits, SORT_LBITS);
-    const int HB = idbits - LB;
-    const int64_t QMAX = (int64_t)1 << (32 - idbits);
-    const int64_t GROUP = (int64_t)1 << 30;
-    struct Run { int q0, q1; int64_t k0, k1; };
-    std::vector<Run> runs;
-    {
-        int qb = 0;
-        for (int q = 0; q < nq; ++q)
-            if (q > qb && (q - qb >= QMAX || out_off[q + 1] - out_off[qb] > GROUP)) {
-                runs.push_back({qb, q, out_off[qb], out_off[q]});
-                qb = q;
+    int L = std::min(idbits, SORT_LBITS);
+    auto bins_at = [&](int l) { return (int)(((uint64_t)std::max<int64_t>(t->n - 1, 0) >> l) + 1); };
+    while (L > SORT_LMIN && (int64_t)nq * bins_at(L) < 2 * cus && bins_at(L - 1) <= TILE_BINS) --L;
+    const int nbins = bins_at(L);
+    // The queries are taken in groups: the hit words of a group's pairs (512
+    // bytes each) fit the limit (SPADE_HIT_MASK_LIMIT bytes, default 512 MiB:
+    // 2^20 pairs, whose tiles then take 16 GiB) and its buckets 2^26, or it is
+    // one query.  Nearly always one group.
+    size_t hits_max = (size_t)512 << 20;
+    if (const char *e = getenv("SPADE_HIT_MASK_LIMIT")) hits_max = (size_t)strtoull(e, nullptr, 10);
+    constexpr size_t PAIR_BYTES = sizeof(unsigned long long) * BW_WORDS;
+    constexpr int64_t BUCKETS = (int64_t)1 << 26;
+    DevBuf &bh = ctx->scratch[S_KEYS2], &bo = ctx->scratch[S_ENTF], &bs = ctx->scratch[S_LOOKBACK];
+    const std::vector<int64_t> &hq = P.qfirst;   // first pair of every query
+    std::vector<int> gq;                         // first query of every group, then nq
+    std::vector<uint32_t> tfirst((size_t)nq + 1);   // first tile of every query, in its group
+    int64_t pmost, tmost;                        // most pairs and tiles of a group
+    int gmost;                                   // most queries of one
+    auto tiles_of = [&](int q) { return (hq[(size_t)q + 1] - hq[(size_t)q] + TILE_PAIRS - 1) / TILE_PAIRS; };
+    auto group_by = [&](size_t limit) {
+        gq.assign(1, 0);
+        pmost = tmost = gmost = 1;
+        int64_t tiles = 0;
+        for (int q = 0; q < nq; ++q) {
+            const int qb = gq.back();
+            if (q > qb && ((size_t)(hq[(size_t)q + 1] - hq[(size_t)qb]) * PAIR_BYTES > limit ||
+                           (int64_t)(q + 1 - qb) * nbins > BUCKETS)) {
+                gq.push_back(q);
+                tiles = 0;
             }
-        runs.push_back({qb, nq, out_off[qb], out_off[nq]});
-    }
-    std::vector<uint32_t> hrun0((size_t)nq);
-    int qdone = 0;                       // queries of the runs that end within cap
-    int64_t gmax = 0, cross = -1;        // largest run ordered; index of the run crossing cap
-    size_t nbmax = 1;                    // most buckets of a run
-    for (size_t r = 0; r < runs.size(); ++r) {
-        const Run &R = runs[r];
-        for (int q = R.q0; q < R.q1; ++q) hrun0[(size_t)q] = (uint32_t)R.q0;
-        if (R.k1 <= cap) qdone = R.q1;
-        else if (R.k0 < cap && cross < 0) cross = (int64_t)r;
-        if (R.k0 < cap) {
-            gmax = std::max(gmax, R.k1 - R.k0);
-            nbmax = std::max(nbmax, (size_t)(R.q1 - R.q0) << HB);
+            tiles += tiles_of(q);
+            pmost = std::max(pmost, hq[(size_t)q + 1] - hq[(size_t)gq.back()]);
+            tmost = std::max(tmost, tiles);
+            gmost = std::max(gmost, q + 1 - gq.back());
         }
+        gq.push_back(nq);
+    };
+    auto room = [&]() {
+        return ensure(ctx, bh, PAIR_BYTES * (size_t)pmost) ||
+               (cap > 0 && ensure(ctx, bo, sizeof(uint32_t) * TILE_IDS * (size_t)tmost)) ||
+               ensure(ctx, bs, sizeof(uint16_t) * (size_t)(nbins + 1) * (size_t)tmost + 4 * ((size_t)gmost + 1));
+    };
+    group_by(hits_max);
+    if (room()) {
+        ctx->err.clear();   // one query at a time needs the least
+        group_by(0);
+        if (room()) return SPADE_E_NOMEM;
     }
-    DevBuf &br = ctx->scratch[S_LOOKBACK];
-    DevBuf &bo2 = ctx->scratch[S_ENTF];
-    const int64_t nbo = cross >= 0 ? runs[(size_t)cross].k1 - runs[(size_t)cross].k0 : 0;
-    // br: qrun0 [nq] | bucket counts [nbmax] | bucket offsets [nbmax + 1] | cursors [nbmax]
-    if (ensure(ctx, br, sizeof(uint32_t) * ((size_t)nq + 3 * nbmax + 1)) ||
-        ensure(ctx, bo2, 4 * (size_t)std::max<int64_t>(HB > 0 ? gmax : 1, 1)) ||
-        ensure(ctx, bo, 4 * (size_t)std::max<int64_t>(nbo, 1)))
-        return SPADE_E_NOMEM;
-    uint32_t *qrun0 = (uint32_t *)br.p;
-    uint32_t *bhist = qrun0 + nq, *boff = bhist + nbmax, *bcur = boff + nbmax + 1;
-    SPADE_HIP(ctx, hipMemcpyAsync(qrun0, hrun0.data(), sizeof(uint32_t) * (size_t)nq, hipMemcpyHostToDevice, st));
+    unsigned long long *hits = (unsigned long long *)bh.p;
+    uint32_t *keys = cap > 0 ? (uint32_t *)bo.p : nullptr, *dtf = (uint32_t *)bs.p;
+    uint16_t *starts = (uint16_t *)(dtf + gmost + 1);
+    // bc: bucket counts [nbmax + 1] | offsets [nbmax + 1] | query offsets [gmost + 1]
+    const size_t nbmax = (size_t)gmost * nbins;
+    DevBuf &bc = ctx->scratch[S_VALS2], &cub = ctx->scratch[S_CUBTMP];
+    if (ensure(ctx, bc, sizeof(unsigned long long) * (2 * (nbmax + 1) + (size_t)gmost + 1))) return SPADE_E_NOMEM;
+    unsigned long long *tot = (unsigned long long *)bc.p, *offs = tot + (nbmax + 1), *qoff = offs + (nbmax + 1);
+    unsigned long long *h = (unsigned long long *)ensure_pinned(ctx, 12 * ((size_t)gmost + 1));
+    if (!h) return set_error(ctx, SPADE_E_NOMEM, "pinned staging allocation failed");
+    uint32_t *htf = (uint32_t *)(h + gmost + 1);
     // the bitmap in whole blocks of 64 words
-    const size_t bm_lds = sizeof(uint32_t) * 64 * (size_t)((std::max(1, (1 << LB) >> 5) + 63) / 64);
+    const size_t bm_lds = sizeof(uint32_t) * 64 * (size_t)((std::max(1, (1 << L) >> 5) + 63) / 64);
+    const size_t tile_lds = sizeof(uint32_t) * ((size_t)((nbins + 127) & ~63) + TILE_IDS);
     SPADE_HIP(ctx, hipFuncSetAttribute((const void *)k_bucket_bitmap, hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)bm_lds));
-    // with one window per query, a run's buckets are its queries: their
-    // offsets come from out_off (one host array for all runs, so that no
-    // copy reads a slice that is being rewritten)
-    std::vector<uint32_t> hoff;
-    if (HB == 0)
-        for (const auto &R : runs)
-            for (int q = R.q0; q <= R.q1; ++q) hoff.push_back((uint32_t)(out_off[q] - R.k0));
-    size_t hoff_at = 0;
-    // orders the keys keys[0, k1 - k0) of run R; the ids end in dst[0, nwrite)
-    auto sort_run = [&](const Run &R, uint32_t *keys, uint32_t *dst, int64_t nwrite) -> int {
-        const int64_t n = R.k1 - R.k0;
-        const int nb = (R.q1 - R.q0) << HB;
-        const int cus = num_cus_of(ctx->device);
-        const uint32_t *src = keys;
-        if (HB == 0) {
-            // one bucket per query: the keys are in bucket order already
-            size_t at = 0;
-            for (const auto &Q : runs) {
-                if (Q.q0 == R.q0) break;
-                at += (size_t)(Q.q1 - Q.q0) + 1;
-            }
-            SPADE_HIP(ctx, hipMemcpyAsync(boff, hoff.data() + at, sizeof(uint32_t) * ((size_t)nb + 1),
-                                          hipMemcpyHostToDevice, st));
-        } else {
-            hipLaunchKernelGGL(k_zero32, dim3(grid_of(nb, 1024)), dim3(256), 0, st, (int64_t)nb, bhist);
-            hipLaunchKernelGGL(k_zero32, dim3(grid_of(nb, 1024)), dim3(256), 0, st, (int64_t)nb, bcur);
-            const int hg = (int)std::max<int64_t>(1, std::min<int64_t>((n + BKT_THREADS * 16 - 1) / (BKT_THREADS * 16),
-                                                                       (int64_t)cus * 2));
-            hipLaunchKernelGGL(k_bucket_hist, dim3(hg), dim3(BKT_THREADS), 0, st, n, keys, LB, bhist);
-            hipLaunchKernelGGL(k_bucket_scan, dim3(1), dim3(BKT_THREADS), 0, st, nb, bhist, boff);
-            const int sg = (int)std::max<int64_t>(1, std::min<int64_t>((n + BKT_THREADS * SCAT_PER - 1) /
-                                                                           (BKT_THREADS * SCAT_PER),
-                                                                       (int64_t)cus * 4));
-            hipLaunchKernelGGL(k_bucket_scatter, dim3(sg), dim3(BKT_THREADS), 0, st, n, keys, LB, boff, bcur,
-                               (uint32_t *)bo2.p);
-            src = (const uint32_t *)bo2.p;
+    SPADE_HIP(ctx, hipFuncSetAttribute((const void *)k_hit_tiles, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)tile_lds));
+    out_off[0] = 0;
+    // the timed probe of a batch selection is its probe pass (its first group's)
+    if (ctx->timing) SPADE_HIP(ctx, hipEventRecord(ctx->ev[2], st));
+    for (size_t k = 0; k + 1 < gq.size(); ++k) {
+        const int q0 = gq[k], q1 = gq[k + 1], ng = q1 - q0;
+        const uint32_t p0 = (uint32_t)hq[(size_t)q0], p1 = (uint32_t)hq[(size_t)q1];
+        const int64_t nb = (int64_t)ng * nbins;
+        htf[0] = 0;
+        for (int q = 0; q < ng; ++q) htf[q + 1] = htf[q] + (uint32_t)tiles_of(q0 + q);
+        const uint32_t ntile = htf[ng];
+        if (ntile == 0) {
+            for (int q = q0; q < q1; ++q) out_off[q + 1] = out_off[q0];
+            continue;
         }
+        SPADE_HIP(ctx, hipMemcpyAsync(dtf, htf, 4 * ((size_t)ng + 1), hipMemcpyHostToDevice, st));
+        const int64_t wgs = t->nchunk * BW_TASKS / (BT_THREADS / 64);
+        hipLaunchKernelGGL(k_batch_hits, dim3((unsigned)std::min<int64_t>(wgs, 1 << 20)), dim3(BT_THREADS), 0, st, S,
+                           t->nfin, t->nchunk, (const double *)t->x.p, (const double *)t->y.p, P.cbase, P.plist, P.pq,
+                           p0, p1, hits);
         SPADE_HIP(ctx, hipGetLastError());
-        hipLaunchKernelGGL(k_bucket_bitmap, dim3((unsigned)std::min<int64_t>(nb, (int64_t)cus * 4)),
-                           dim3(BKT_THREADS), bm_lds, st, nb, boff, src, LB, HB, dst, nwrite);
+        if (ctx->timing && k == 0) SPADE_HIP(ctx, hipEventRecord(ctx->ev[3], st));
+        hipLaunchKernelGGL(k_hit_tiles, dim3(ntile), dim3(TILE_THREADS), tile_lds, st, ng, (const uint32_t *)dtf,
+                           (const unsigned long long *)P.qbase + q0, p0, P.pc, hits, (const uint32_t *)t->ids.p, L,
+                           nbins, keys, starts);
+        hipLaunchKernelGGL(k_bucket_tot, dim3((nbins + 63) / 64, std::min(ng, 32768)), dim3(TILE_THREADS), 0, st, ng,
+                           (const uint32_t *)dtf, (const uint16_t *)starts, nbins, tot);
+        hipLaunchKernelGGL(k_zero64, dim3(1), dim3(64), 0, st, (int64_t)1, tot + nb);
         SPADE_HIP(ctx, hipGetLastError());
-        return SPADE_OK;
-    };
-    // the keys of queries [q0, q1) at out[pbase[pair] - kbase ...]
-    auto write_keys = [&](int q0, int q1, uint32_t *out, int64_t kbase) -> int {
-        if (hits) {
-            const int64_t p0 = (int64_t)hq[q0], p1 = (int64_t)hq[q1];
-            if (p1 > p0) {
-                const int eg = (int)std::min<int64_t>(p1 - p0, (int64_t)num_cus_of(ctx->device) * 8);
-                hipLaunchKernelGGL(k_batch_emit_hits, dim3(eg), dim3(BT_THREADS), 0, st, p0, p1, P.pq, P.pc, hits,
-                                   (const unsigned long long *)pbase, (const uint32_t *)t->ids.p, qrun0, idbits,
-                                   out, (unsigned long long)kbase);
-            }
-        } else {
-            hipLaunchKernelGGL(k_batch_select<true>, dim3(grid), dim3(BT_THREADS), 0, st, S, t->nfin, t->nchunk,
-                               (const double *)t->x.p, (const double *)t->y.p, (const uint32_t *)t->ids.p, P.cbase,
-                               P.plist, P.pq, nullptr, (const unsigned long long *)pbase, out, (uint32_t)q0,
-                               (uint32_t)q1, (unsigned long long)kbase, qrun0, idbits, nullptr,
-                               (const double4 *)t->chunk_bb.p);
-        }
+        size_t tb = 0;
+        SPADE_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(nullptr, tb, tot, offs, (int)(nb + 1), st));
+        if (ensure(ctx, cub, tb)) return SPADE_E_NOMEM;
+        SPADE_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(cub.p, tb, tot, offs, (int)(nb + 1), st));
+        hipLaunchKernelGGL(k_query_off, dim3((ng + 256) / 256), dim3(256), 0, st, ng, nbins, offs, qoff);
+        // ids beyond cap are not written (a buffer that is too small still
+        // receives the first cap ids)
+        const int64_t base = out_off[q0];   // ids of the groups before
+        if (base < cap)
+            hipLaunchKernelGGL(k_bucket_bitmap, dim3((unsigned)std::min<int64_t>(nb, 65536)), dim3(BKT_THREADS), bm_lds,
+                               st, nb, offs, (const uint32_t *)dtf, (const uint16_t *)starts, (const uint32_t *)keys, L,
+                               nbins, out_ids + base, cap - base);
         SPADE_HIP(ctx, hipGetLastError());
-        return SPADE_OK;
-    };
-    if (qdone > 0) {
-        if ((rc = write_keys(0, qdone, out_ids, 0))) return rc;
-        for (const auto &R : runs) {
-            if (R.q1 > qdone) break;
-            if (R.k1 > R.k0 && (rc = sort_run(R, out_ids + R.k0, out_ids + R.k0, R.k1 - R.k0))) return rc;
-        }
+        SPADE_HIP(ctx, hipMemcpyAsync(h, qoff, sizeof(unsigned long long) * (size_t)(ng + 1), hipMemcpyDeviceToHost, st));
+        SPADE_HIP(ctx, hipStreamSynchronize(st));
+        for (int q = q0; q <= q1; ++q) out_off[q] = base + (int64_t)h[q - q0];
     }
-    if (cross >= 0) {
-        const Run &R = runs[(size_t)cross];
-        if ((rc = write_keys(R.q0, R.q1, (uint32_t *)bo.p, R.k0))) return rc;
-        if ((rc = sort_run(R, (uint32_t *)bo.p, out_ids + R.k0, cap - R.k0))) return rc;
-    }
-    SPADE_HIP(ctx, hipStreamSynchronize(st));
-    if (short_cap) return set_error(ctx, SPADE_E_CAPACITY, "output capacity too small");
+    if (out_off[nq] > cap) return set_error(ctx, SPADE_E_CAPACITY, "output capacity too small");
     return SPADE_OK;
 }
 
