@@ -46,8 +46,8 @@ struct spade_table {
     int G = 1;
     double X0 = 0, Y0 = 0, sx = 0, sy = 0;
     int64_t nchunk = 0;
-    spade::DevBuf x, y, ids, cell_off, chunk_bb;
-    size_t bytes() const { return x.cap + y.cap + ids.cap + cell_off.cap + chunk_bb.cap; }
+    spade::DevBuf x, y, ids, chunk_bb;
+    size_t bytes() const { return x.cap + y.cap + ids.cap + chunk_bb.cap; }
 };
 
 namespace spade {
@@ -143,15 +143,16 @@ __global__ void k_pt_gather(int64_t n, const uint32_t *perm, const double *X, co
     }
 }
 
-// cell_off[c] = first sorted point of cell code c (c = 0 .. ncell + 1).
-__global__ void k_cell_off(int64_t n, const uint32_t *skeys, int64_t ncell, uint32_t *cell_off)
+// The sorted points with a cell: the keys below nfkey (non-finite points
+// have it).
+__global__ void k_count_finite(int64_t n, const uint32_t *skeys, uint32_t nfkey, uint32_t *nfin)
 {
-    const int64_t nth = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i <= n; i += nth) {
-        const int64_t ki = (i < n) ? (int64_t)skeys[i] : ncell;
-        const int64_t kp = (i == 0) ? -1 : (int64_t)skeys[i - 1];
-        for (int64_t c = kp + 1; c <= ki; ++c) cell_off[c] = (uint32_t)i;
+    int64_t lo = 0, hi = n;
+    while (lo < hi) {
+        const int64_t mid = (lo + hi) >> 1;
+        if (skeys[mid] < nfkey) lo = mid + 1; else hi = mid;
     }
+    *nfin = (uint32_t)lo;
 }
 
 // Exact bounding box of every chunk of the finite prefix (one wave per chunk).
@@ -705,18 +706,22 @@ __global__ void k_query_off(int nq, int nbins, const unsigned long long *offs, u
 // of 64-bit keys, 181M pairs of 20M points with 260 polygons in 43 layers took
 // 2.8 + 6.2 + 5.5 + 0.5 ms.
 
-// fn(u, label) for every match of the task's points (xs, ys; `valid` where a
-// point exists) with the polygons of canvas v.
+constexpr int PW_BYTES = 4096;                          // LDS pool of a wavefront of the write pass
+constexpr uint32_t PW_LONG = PW_BYTES / sizeof(uint32_t);   // lists that may not fit it
+constexpr size_t PAIR_HITS_MAX = (size_t)16 << 30;
+
+// fn(u, w) for every word u of the task's points (xs, ys; `valid` where a
+// point exists), w being each lane's canvas word in v.  fn is called by the
+// whole wavefront.
 template <int PTS, typename Fn>
-__device__ __forceinline__ void task_matches(const CanvasView &v, const double4 cb, const double *xs, const double *ys,
-                                             const bool *valid, int lane, Fn fn)
+__device__ __forceinline__ void task_words(const CanvasView &v, const double4 cb, const double *xs, const double *ys,
+                                           const bool *valid, int lane, Fn fn)
 {
     const uint32_t cw = task_word(v, cb, lane);
     if (cw != NO_WORD) {
         if (cw != 0u)
 #pragma unroll
-            for (int u = 0; u < PTS; ++u)
-                if (valid[u]) fn(u, cw - 1u);
+            for (int u = 0; u < PTS; ++u) fn(u, valid[u] ? cw : 0u);
         return;
     }
     Look lk[PTS];
@@ -726,28 +731,22 @@ __device__ __forceinline__ void task_matches(const CanvasView &v, const double4 
 #pragma unroll
     for (int u = 0; u < PTS; ++u) ws[u] = lk[u].full ? ((gu32p)v.cells)[lk[u].fidx] : lk[u].word;
 #pragma unroll
-    for (int u = 0; u < PTS; ++u) {
-        if (ws[u] == 0u) continue;
-        if (!(ws[u] & BFLAG)) { fn(u, ws[u] - 1u); continue; }
-        uint32_t rec = ws[u] & ~BFLAG;
-        while (true) {
-            const Cand cd = v.cands[rec];
-            if (cand_inside(v, cd, xs[u], ys[u])) fn(u, cd.poly);
-            if (cd.meta & CAND_LAST) break;
-            ++rec;
-        }
-    }
+    for (int u = 0; u < PTS; ++u) fn(u, ws[u]);
 }
 
-__global__ __launch_bounds__(BT_THREADS) void k_batch_pcount(SetArgs S, int64_t nfin, int64_t nchunk, const double *X,
-                                                             const double *Y, const uint32_t *ids,
+// Count pass over chunks [c0, c1).  hits, when given, keeps the points that
+// matched: hits[(t - cbase[c0]) * BW_WORDS + j] for entry t of the chunks'
+// query lists and word j.  *longest is raised to the longest list.
+__global__ __launch_bounds__(BT_THREADS) void k_batch_pcount(SetArgs S, int64_t nfin, int64_t c0, int64_t c1,
+                                                             const double *X, const double *Y, const uint32_t *ids,
                                                              const unsigned int *cbase, const uint32_t *plist,
-                                                             const uint32_t *pq, uint32_t *pcnt)
+                                                             const uint32_t *pq, uint32_t *pcnt,
+                                                             unsigned long long *hits, uint32_t *longest)
 {
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int64_t ntask = nchunk * BW_TASKS;
-    for (int64_t task = (int64_t)blockIdx.x * (BT_THREADS / 64) + wv; task < ntask;
+    const uint32_t tb = cbase[c0];
+    for (int64_t task = c0 * BW_TASKS + (int64_t)blockIdx.x * (BT_THREADS / 64) + wv; task < c1 * BW_TASKS;
          task += (int64_t)gridDim.x * (BT_THREADS / 64)) {
         const int64_t c = task / BW_TASKS;
         const uint32_t t0 = cbase[c], t1 = cbase[c + 1];
@@ -767,35 +766,61 @@ __global__ __launch_bounds__(BT_THREADS) void k_batch_pcount(SetArgs S, int64_t 
         for (uint32_t t = t0; t < t1; ++t) {
             const CanvasDesc d = S.cds[pq[plist[t]]];
             const CanvasView v = set_view(d, S.cells, S.coarse, S.cands, S.ledges, S.pspan);
-            task_matches<BW_PTS>(v, cb, xs, ys, valid, lane, [&](int u, uint32_t) { ++cnt[u]; });
+            unsigned long long mine = 0ull;   // lane u: the points of word u with a match
+            auto took = [&](int u, uint32_t got) {
+                cnt[u] += got;
+                const unsigned long long m = __ballot(got != 0u);
+                mine = lane == u ? m : mine;
+            };
+            task_words<BW_PTS>(v, cb, xs, ys, valid, lane, [&](int u, uint32_t w) {
+                uint32_t got = w != 0u ? 1u : 0u;
+                if (w & BFLAG) {
+                    got = 0u;
+                    uint32_t rec = w & ~BFLAG;
+                    while (true) {
+                        const Cand cd = v.cands[rec];
+                        got += cand_inside(v, cd, xs[u], ys[u]) ? 1u : 0u;
+                        if (cd.meta & CAND_LAST) break;
+                        ++rec;
+                    }
+                }
+                took(u, got);
+            });
+            if (hits && lane < BW_PTS) hits[(size_t)(t - tb) * BW_WORDS + (task % BW_TASKS) * BW_PTS + lane] = mine;
         }
 #pragma unroll
-        for (int u = 0; u < BW_PTS; ++u)
+        for (int u = 0; u < BW_PTS; ++u) {
             if (cnt[u]) pcnt[ids[i0 + 64 * u]] = cnt[u];
+            if (cnt[u] > PW_LONG) atomicMax(longest, cnt[u]);
+        }
     }
 }
 
-// Write pass: a wavefront takes 64 table points, one per lane, whose lists
-// are gathered in its pool of PW_POOL entries in LDS, in ascending polygon id
-// (an insertion per match), as many points at a time as the pool holds.  A
-// list longer than the pool is gathered in place in the output.  Positions at
-// or beyond cap are not written.
-constexpr int PW_BYTES = 4096;   // a wavefront's pool: 32 wavefronts per CU
-
-template <typename T>
-__global__ __launch_bounds__(BT_THREADS) void k_batch_pwrite(SetArgs S, int64_t nfin, int64_t nchunk, const double *X,
-                                                             const double *Y, const uint32_t *ids,
+// Write pass over chunks [c0, c1), from the count pass's hit words: a
+// wavefront takes 64 table points, one per lane, whose lists are gathered in
+// its pool in LDS in ascending polygon id (an insertion per match), as many
+// points at a time as the pool holds, and stored.  Only the points that
+// matched look their canvas word up again, and the only record of a boundary
+// pixel is then the match without another test.  LONG: the lists longer than
+// the pool, gathered in place in the output by a launch of their own (which
+// ends at once when there is none, so that the usual launch needs no
+// registers for it).  Positions at or beyond cap are not written.
+template <typename T, bool LONG>
+__global__ __launch_bounds__(BT_THREADS) void k_batch_pwrite(SetArgs S, int64_t nfin, int64_t c0, int64_t c1,
+                                                             const double *X, const double *Y, const uint32_t *ids,
                                                              const unsigned int *cbase, const uint32_t *plist,
-                                                             const uint32_t *pq, const unsigned long long *offs,
+                                                             const uint32_t *pq, const unsigned long long *hits,
+                                                             const unsigned long long *offs, const uint32_t *longest,
                                                              uint32_t *out_poly, int64_t cap)
 {
     constexpr uint32_t POOL = PW_BYTES / sizeof(T);
+    if (LONG && *longest <= POOL) return;
     __shared__ T pools[BT_THREADS / 64][POOL];
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     T *pool = pools[wv];
-    const int64_t nword = nchunk * BW_WORDS;
-    for (int64_t word = (int64_t)blockIdx.x * (BT_THREADS / 64) + wv; word < nword;
+    const uint32_t tb = cbase[c0];
+    for (int64_t word = c0 * BW_WORDS + (int64_t)blockIdx.x * (BT_THREADS / 64) + wv; word < c1 * BW_WORDS;
          word += (int64_t)gridDim.x * (BT_THREADS / 64)) {
         const int64_t c = word / BW_WORDS;
         const uint32_t t0 = cbase[c], t1 = cbase[c + 1];
@@ -810,44 +835,36 @@ __global__ __launch_bounds__(BT_THREADS) void k_batch_pwrite(SetArgs S, int64_t 
             o = (int64_t)offs[id];
             n = o < cap ? (uint32_t)(offs[id + 1] - (unsigned long long)o) : 0u;
         }
-        const double4 cb = task_box<1>(&x, &y);
-        auto matches = [&](auto fn) {
+        // fn(polygon id) for every match of the points `of`
+        auto matches = [&](unsigned long long of, auto fn) {
             for (uint32_t t = t0; t < t1; ++t) {
-                const CanvasDesc d = S.cds[pq[plist[t]]];
+                const unsigned long long m = hits[(size_t)(t - tb) * BW_WORDS + word % BW_WORDS] & of;
+                if (m == 0ull) continue;
+                const CanvasDesc &d = S.cds[pq[plist[t]]];
                 const CanvasView v = set_view(d, S.cells, S.coarse, S.cands, S.ledges, S.pspan);
-                task_matches<1>(v, cb, &x, &y, &valid, lane,
-                                [&](int, uint32_t label) { fn(caller_id(S, d.poly_base + label)); });
+                if (!((m >> lane) & 1ull)) continue;
+                const uint32_t w = lookup(v, v.coarse, x, y);
+                uint32_t rec = w & ~BFLAG, label = w - 1u;
+                bool more = (w & BFLAG) != 0, first = true, in = true;
+                do {
+                    if (more) {
+                        const Cand cd = v.cands[rec++];
+                        label = cd.poly;
+                        more = !(cd.meta & CAND_LAST);
+                        in = (first && !more) || cand_inside(v, cd, x, y);
+                        first = false;
+                    }
+                    if (in) fn(caller_id(S, d.poly_base + label));
+                } while (more);
             }
         };
-        const bool big = n > POOL;
-        const uint32_t np = big ? 0u : n;
-        const uint32_t excl = wave_incl_sum(np) - np;
-        unsigned long long todo = __ballot(np != 0u);
-        while (todo) {
-            const uint32_t base = (uint32_t)__builtin_amdgcn_readlane((int)excl, __ffsll((long long)todo) - 1);
-            const bool now = ((todo >> lane) & 1ull) && excl + np - base <= POOL;
-            T *list = pool + (now ? excl - base : 0u);
-            uint32_t j = 0u;
-            matches([&](uint32_t id) {
-                if (!now || j >= np) return;
-                uint32_t at = j++;
-                while (at > 0u && (uint32_t)list[at - 1] > id) {
-                    list[at] = list[at - 1];
-                    --at;
-                }
-                list[at] = (T)id;
-            });
-            if (now)
-                for (uint32_t k = 0; k < np && o + k < cap; ++k) out_poly[o + k] = (uint32_t)list[k];
-            todo &= ~__ballot(now);
-        }
-        if (__ballot(big)) {
+        if (LONG) {
+            const bool mine = n > POOL;
+            if (!__ballot(mine)) continue;
             // the smallest of a list that cap cuts off are kept
             const uint32_t keep = (uint32_t)min<int64_t>(n, cap - o);
-            uint32_t j = 0u;
-            matches([&](uint32_t id) {
-                if (!big) return;
-                uint32_t *list = out_poly + o;
+            uint32_t *list = out_poly + o, j = 0u;
+            matches(__ballot(mine), [&](uint32_t id) {
                 uint32_t at = j;
                 if (j < keep) ++j;
                 else if (list[keep - 1] > id) at = keep - 1;
@@ -858,6 +875,29 @@ __global__ __launch_bounds__(BT_THREADS) void k_batch_pwrite(SetArgs S, int64_t 
                 }
                 list[at] = id;
             });
+            continue;
+        }
+        const uint32_t np = n > POOL ? 0u : n;
+        const uint32_t excl = wave_incl_sum(np) - np;
+        unsigned long long todo = __ballot(np != 0u);
+        while (todo) {
+            const uint32_t base = (uint32_t)__builtin_amdgcn_readlane((int)excl, __ffsll((long long)todo) - 1);
+            const bool now = ((todo >> lane) & 1ull) && excl + np - base <= POOL;
+            T *list = pool + (now ? excl - base : 0u);
+            uint32_t j = 0u;
+            const unsigned long long of = __ballot(now);
+            matches(of, [&](uint32_t id) {
+                if (j >= np) return;
+                uint32_t at = j++;
+                while (at > 0u && (uint32_t)list[at - 1] > id) {
+                    list[at] = list[at - 1];
+                    --at;
+                }
+                list[at] = (T)id;
+            });
+            if (now)
+                for (uint32_t k = 0; k < np && o + k < cap; ++k) out_poly[o + k] = (uint32_t)list[k];
+            todo &= ~of;
         }
     }
 }
@@ -1155,8 +1195,7 @@ int spade_table_create(spade_ctx *ctx, const spade_points *pts, spade_table **ou
     const int64_t ncell = P * P;
     // sort by cell
     DevBuf &dk = ctx->scratch[S_KEYS], &dk2 = ctx->scratch[S_KEYS2], &dv = ctx->scratch[S_VALS];
-    if (ensure(ctx, dk, 4 * ns) || ensure(ctx, dk2, 4 * ns) || ensure(ctx, dv, 4 * ns) ||
-        ensure(ctx, t->cell_off, 4 * ((size_t)ncell + 2)))
+    if (ensure(ctx, dk, 4 * ns) || ensure(ctx, dk2, 4 * ns) || ensure(ctx, dv, 4 * ns))
         return fail(SPADE_E_NOMEM);
     if (n > 0) {
         hipLaunchKernelGGL(k_pt_key, dim3(grid_of(n)), dim3(256), 0, st, n, pts->x, pts->y, t->X0, t->Y0, t->sx, t->sy,
@@ -1172,11 +1211,11 @@ int spade_table_create(spade_ctx *ctx, const spade_points *pts, spade_table **ou
                                                           (const uint32_t *)dv.p, (uint32_t *)t->ids.p, (int)n, 0, kb, st));
         hipLaunchKernelGGL(k_pt_gather, dim3(grid_of(n)), dim3(256), 0, st, n, (const uint32_t *)t->ids.p, pts->x, pts->y,
                            (double *)t->x.p, (double *)t->y.p);
-        hipLaunchKernelGGL(k_cell_off, dim3(grid_of(n + 1)), dim3(256), 0, st, n, (const uint32_t *)dk2.p, ncell,
-                           (uint32_t *)t->cell_off.p);
+        hipLaunchKernelGGL(k_count_finite, dim3(1), dim3(1), 0, st, n, (const uint32_t *)dk2.p, (uint32_t)ncell,
+                           (uint32_t *)bb.p);
         SPADE_HIP(ctx, hipGetLastError());
         uint32_t *hf = (uint32_t *)ensure_pinned(ctx, 64);
-        SPADE_HIP(ctx, hipMemcpyAsync(hf, (uint32_t *)t->cell_off.p + ncell, 4, hipMemcpyDeviceToHost, st));
+        SPADE_HIP(ctx, hipMemcpyAsync(hf, bb.p, 4, hipMemcpyDeviceToHost, st));
         SPADE_HIP(ctx, hipStreamSynchronize(st));
         t->nfin = hf[0];
     }
@@ -1199,7 +1238,6 @@ void spade_table_destroy(spade_table *t)
     free_buf(t->x);
     free_buf(t->y);
     free_buf(t->ids);
-    free_buf(t->cell_off);
     free_buf(t->chunk_bb);
     delete t;
 }
@@ -1580,9 +1618,9 @@ int spade_batch_join_pairs(spade_ctx *ctx, const spade_canvas *set, const spade_
     // 2^32 pairs)
     const int64_t n = t->n;
     DevBuf &bc = ctx->scratch[S_VALS2], &bo = ctx->scratch[S_ENTC], &cub = ctx->scratch[S_CUBTMP];
-    if (ensure(ctx, bc, sizeof(uint32_t) * (size_t)(n + 1)) || ensure(ctx, bo, sizeof(unsigned long long) * (size_t)(n + 1)))
+    if (ensure(ctx, bc, sizeof(uint32_t) * (size_t)(n + 2)) || ensure(ctx, bo, sizeof(unsigned long long) * (size_t)(n + 1)))
         return SPADE_E_NOMEM;
-    uint32_t *pcnt = (uint32_t *)bc.p;
+    uint32_t *pcnt = (uint32_t *)bc.p, *longest = pcnt + (n + 1);
     unsigned long long *offs = (unsigned long long *)bo.p;
     const auto counts64 = rocprim::make_transform_iterator((const uint32_t *)pcnt, Widen());
     size_t tb = 0;
@@ -1591,26 +1629,58 @@ int spade_batch_join_pairs(spade_ctx *ctx, const spade_canvas *set, const spade_
     if (ensure(ctx, cub, std::max<size_t>(tb, 1))) return SPADE_E_NOMEM;
     unsigned long long *h = (unsigned long long *)ensure_pinned(ctx, 64);
     if (!h) return set_error(ctx, SPADE_E_NOMEM, "pinned staging allocation failed");
-    hipLaunchKernelGGL(k_zero32, dim3(grid_of(n + 1, 4096)), dim3(256), 0, st, n + 1, (unsigned int *)pcnt);
+    // The count pass keeps every pair's matching points (512 bytes) for the
+    // write pass.  Should they exceed 16 GiB, the chunks are taken in groups
+    // whose words do not (a chunk has at most one pair per canvas), and each
+    // group is counted again right before it is written.
+    const int64_t per_chunk = (int64_t)sizeof(unsigned long long) * BW_WORDS * set->nc;
+    int64_t group = t->nchunk;
+    size_t hbytes = sizeof(unsigned long long) * BW_WORDS * (size_t)std::max<int64_t>(P.np, 1);
+    DevBuf &bh = ctx->scratch[S_KEYS2];
+    if (cap > 0 && (hbytes > PAIR_HITS_MAX || ensure(ctx, bh, hbytes))) {
+        ctx->err.clear();
+        size_t room = PAIR_HITS_MAX;
+        group = std::max<int64_t>(1, (int64_t)(room / (size_t)per_chunk));
+        while (ensure(ctx, bh, (size_t)(group * per_chunk))) {
+            if (group == 1) return SPADE_E_NOMEM;
+            ctx->err.clear();
+            group = std::max<int64_t>(1, group / 4);
+        }
+    }
+    unsigned long long *hits = cap > 0 ? (unsigned long long *)bh.p : nullptr;
+    hipLaunchKernelGGL(k_zero32, dim3(grid_of(n + 2, 4096)), dim3(256), 0, st, n + 2, (unsigned int *)pcnt);
     if (ctx->timing) SPADE_HIP(ctx, hipEventRecord(ctx->ev[2], st));
-    const auto task_grid = [&](int tasks) {
-        return dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>(t->nchunk * tasks / (BT_THREADS / 64), 1 << 20)));
+    const auto task_grid = [&](int64_t chunks, int tasks) {
+        return dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>(chunks * tasks / (BT_THREADS / 64), 1 << 20)));
     };
-    hipLaunchKernelGGL(k_batch_pcount, task_grid(BW_TASKS), dim3(BT_THREADS), 0, st, S, t->nfin, t->nchunk,
-                       (const double *)t->x.p, (const double *)t->y.p, (const uint32_t *)t->ids.p, P.cbase, P.plist, P.pq,
-                       pcnt);
+    auto count = [&](int64_t c0, int64_t c1, unsigned long long *keep) {
+        hipLaunchKernelGGL(k_batch_pcount, task_grid(c1 - c0, BW_TASKS), dim3(BT_THREADS), 0, st, S, t->nfin, c0, c1,
+                           (const double *)t->x.p, (const double *)t->y.p, (const uint32_t *)t->ids.p, P.cbase, P.plist,
+                           P.pq, pcnt, keep, longest);
+    };
+    count(0, t->nchunk, group == t->nchunk ? hits : nullptr);
     SPADE_HIP(ctx, hipGetLastError());
     SPADE_HIP(ctx, rocprim::exclusive_scan(cub.p, tb, counts64, offs, 0ull, (size_t)(n + 1),
                                            rocprim::plus<unsigned long long>(), st));
     if (cap > 0) {
-        // 16-bit lists hold the polygon ids of at most 2^16 polygons
-        auto write = [&](auto kern) {
-            hipLaunchKernelGGL(kern, task_grid(BW_WORDS), dim3(BT_THREADS), 0, st, S, t->nfin, t->nchunk,
-                               (const double *)t->x.p, (const double *)t->y.p, (const uint32_t *)t->ids.p, P.cbase,
-                               P.plist, P.pq, (const unsigned long long *)offs, out_poly, cap);
-        };
-        if (M <= 65536) write(k_batch_pwrite<uint16_t>);
-        else write(k_batch_pwrite<uint32_t>);
+        for (int64_t c0 = 0; c0 < t->nchunk; c0 += group) {
+            const int64_t c1 = std::min(t->nchunk, c0 + group);
+            if (group < t->nchunk) count(c0, c1, hits);
+            auto write = [&](auto kern) {
+                hipLaunchKernelGGL(kern, task_grid(c1 - c0, BW_WORDS), dim3(BT_THREADS), 0, st, S, t->nfin, c0, c1,
+                                   (const double *)t->x.p, (const double *)t->y.p, (const uint32_t *)t->ids.p, P.cbase,
+                                   P.plist, P.pq, (const unsigned long long *)hits, (const unsigned long long *)offs,
+                                   (const uint32_t *)longest, out_poly, cap);
+            };
+            // 16-bit lists hold the polygon ids of at most 2^16 polygons
+            if (M <= 65536) {
+                write(k_batch_pwrite<uint16_t, false>);
+                write(k_batch_pwrite<uint16_t, true>);
+            } else {
+                write(k_batch_pwrite<uint32_t, false>);
+                write(k_batch_pwrite<uint32_t, true>);
+            }
+        }
         hipLaunchKernelGGL(k_pair_points, dim3(grid_of(n)), dim3(256), 0, st, n, (const unsigned long long *)offs, out_pt,
                            cap);
         SPADE_HIP(ctx, hipGetLastError());
