@@ -710,30 +710,6 @@ constexpr int PW_BYTES = 4096;                          // LDS pool of a wavefro
 constexpr uint32_t PW_LONG = PW_BYTES / sizeof(uint32_t);   // lists that may not fit it
 constexpr size_t PAIR_HITS_MAX = (size_t)16 << 30;
 
-// fn(u, w) for every word u of the task's points (xs, ys; `valid` where a
-// point exists), w being each lane's canvas word in v.  fn is called by the
-// whole wavefront.
-template <int PTS, typename Fn>
-__device__ __forceinline__ void task_words(const CanvasView &v, const double4 cb, const double *xs, const double *ys,
-                                           const bool *valid, int lane, Fn fn)
-{
-    const uint32_t cw = task_word(v, cb, lane);
-    if (cw != NO_WORD) {
-        if (cw != 0u)
-#pragma unroll
-            for (int u = 0; u < PTS; ++u) fn(u, valid[u] ? cw : 0u);
-        return;
-    }
-    Look lk[PTS];
-    uint32_t ws[PTS];
-#pragma unroll
-    for (int u = 0; u < PTS; ++u) lk[u] = look_coarse(v, v.coarse, xs[u], ys[u]);
-#pragma unroll
-    for (int u = 0; u < PTS; ++u) ws[u] = lk[u].full ? ((gu32p)v.cells)[lk[u].fidx] : lk[u].word;
-#pragma unroll
-    for (int u = 0; u < PTS; ++u) fn(u, ws[u]);
-}
-
 // Count pass over chunks [c0, c1).  hits, when given, keeps the points that
 // matched: hits[(t - cbase[c0]) * BW_WORDS + j] for entry t of the chunks'
 // query lists and word j.  *longest is raised to the longest list.
@@ -753,39 +729,55 @@ __global__ __launch_bounds__(BT_THREADS) void k_batch_pcount(SetArgs S, int64_t 
         if (t0 == t1) continue;
         const int64_t i0 = c * CHUNK + (task % BW_TASKS) * (64 * BW_PTS) + lane;
         double xs[BW_PTS], ys[BW_PTS];
-        bool valid[BW_PTS];
+        unsigned long long valid[BW_PTS];
         uint32_t cnt[BW_PTS];
 #pragma unroll
         for (int u = 0; u < BW_PTS; ++u) {
-            valid[u] = i0 + 64 * u < nfin;
-            xs[u] = valid[u] ? X[i0 + 64 * u] : NAN;
-            ys[u] = valid[u] ? Y[i0 + 64 * u] : NAN;
+            const int64_t i = i0 + 64 * u;
+            xs[u] = i < nfin ? X[i] : NAN;
+            ys[u] = i < nfin ? Y[i] : NAN;
+            valid[u] = __ballot(i < nfin);
             cnt[u] = 0u;
         }
         const double4 cb = task_box<BW_PTS>(xs, ys);
         for (uint32_t t = t0; t < t1; ++t) {
             const CanvasDesc d = S.cds[pq[plist[t]]];
             const CanvasView v = set_view(d, S.cells, S.coarse, S.cands, S.ledges, S.pspan);
-            unsigned long long mine = 0ull;   // lane u: the points of word u with a match
-            auto took = [&](int u, uint32_t got) {
-                cnt[u] += got;
-                const unsigned long long m = __ballot(got != 0u);
-                mine = lane == u ? m : mine;
-            };
-            task_words<BW_PTS>(v, cb, xs, ys, valid, lane, [&](int u, uint32_t w) {
-                uint32_t got = w != 0u ? 1u : 0u;
-                if (w & BFLAG) {
-                    got = 0u;
-                    uint32_t rec = w & ~BFLAG;
-                    while (true) {
-                        const Cand cd = v.cands[rec];
-                        got += cand_inside(v, cd, xs[u], ys[u]) ? 1u : 0u;
-                        if (cd.meta & CAND_LAST) break;
-                        ++rec;
-                    }
+            unsigned long long m[BW_PTS];   // the points of word u with a match
+            const uint32_t cw = task_word(v, cb, lane);
+            if (cw != NO_WORD) {
+#pragma unroll
+                for (int u = 0; u < BW_PTS; ++u) {
+                    m[u] = cw != 0u ? valid[u] : 0ull;
+                    cnt[u] += (uint32_t)((m[u] >> lane) & 1ull);
                 }
-                took(u, got);
-            });
+            } else {
+                Look lk[BW_PTS];
+                uint32_t ws[BW_PTS];
+#pragma unroll
+                for (int u = 0; u < BW_PTS; ++u) lk[u] = look_coarse(v, v.coarse, xs[u], ys[u]);
+#pragma unroll
+                for (int u = 0; u < BW_PTS; ++u) ws[u] = lk[u].full ? ((gu32p)v.cells)[lk[u].fidx] : lk[u].word;
+#pragma unroll
+                for (int u = 0; u < BW_PTS; ++u) {
+                    uint32_t got = ws[u] != 0u ? 1u : 0u;
+                    if (ws[u] & BFLAG) {
+                        got = 0u;
+                        uint32_t rec = ws[u] & ~BFLAG;
+                        while (true) {
+                            const Cand cd = v.cands[rec];
+                            got += cand_inside(v, cd, xs[u], ys[u]) ? 1u : 0u;
+                            if (cd.meta & CAND_LAST) break;
+                            ++rec;
+                        }
+                    }
+                    cnt[u] += got;
+                    m[u] = __ballot(got != 0u);
+                }
+            }
+            unsigned long long mine = m[0];
+#pragma unroll
+            for (int u = 1; u < BW_PTS; ++u) mine = lane == u ? m[u] : mine;
             if (hits && lane < BW_PTS) hits[(size_t)(t - tb) * BW_WORDS + (task % BW_TASKS) * BW_PTS + lane] = mine;
         }
 #pragma unroll
