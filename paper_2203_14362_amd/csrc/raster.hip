@@ -808,10 +808,10 @@ struct RowData {
                       // entries, high 16 bits non-horizontal entries (0: none)
     uint32_t *pre;    // inclusive row prefix: partial count (bits 0..30, sum) and
                       // spanning parity (bit 31, xor)
-    uint32_t *ihead;  // footprint-union intervals of the runs: run start, run end,
-    uint32_t *iend;   // first column, inclusive prefix of interval lengths
-    uint32_t *icol;
-    uint32_t *ilen;
+    uint32_t *rstart; // runs (maximal blocks of entries of one polygon): first entry
+    uint32_t *irun;   // footprint-union intervals of the runs: run,
+    uint32_t *icol;   // first column,
+    uint32_t *ilen;   // column after the last, then inclusive prefix of interval lengths
     int n;
 };
 
@@ -821,10 +821,7 @@ struct RowShared {
     int32_t *sb;        // claim counts -> per-column fill counters
     void *sx;           // claimant xor -> pixel class (16 or 32 bits per column)
     uint32_t *locfill;  // row-local fill counter of the local-edge array
-    uint32_t *nint;     // number of footprint-union intervals of the row
-    uint32_t *nlong;    // long runs deferred to whole waves, and their starts
-    uint32_t *longq;
-    const unsigned long long *nrec;   // records of the row (set by the count phase)
+    int nrun, nint;     // runs and footprint-union intervals of the row
     int W;              // width of the row's canvas
     bool cls16;        // sx in 16 bits: labels + 1 below 2^15, boundary flag in bit 15
 
@@ -845,11 +842,6 @@ struct RowShared {
         else atomicXor((uint32_t *)sx + e, v);
     }
 };
-
-// Runs longer than this are processed by a whole wave (lane-parallel scans)
-// instead of one thread; up to LONGQ of them per row, the rest serially.
-constexpr int LONG_RUN = 8;
-constexpr int LONGQ = 128;
 
 __device__ __forceinline__ size_t tile_index(int Wt, int c, int r)
 {
@@ -894,19 +886,13 @@ __device__ __forceinline__ uint64_t rec_slot(const RowShared &L, int col, uint64
 // with S the parity of the run's spanning entries starting right of col,
 // partial-right entries those partial entries starting right of col, and
 // local entries the non-horizontal entries whose footprint contains col.
+// sp is the run's first entry whose footprint starts right of col (je: none).
 template <bool EMIT>
 __device__ __forceinline__ void column_record(const RowArgs &A, const RowData &D, const RowShared &L,
-                                              int i, int je, int col, uint64_t rec_base_r,
+                                              int i, int je, int sp, int col, uint64_t rec_base_r,
                                               uint64_t loc_base_r, uint64_t part_base_r,
                                               uint64_t &nloc_tot)
 {
-    // sp: first entry of the run whose footprint starts right of col
-    int lo = i, hi = je;
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if ((int)(D.c[mid] & 0xffff) <= col) lo = mid + 1; else hi = mid;
-    }
-    const int sp = lo;
     if (sp == i || (int)(D.pm[sp - 1] & 0xffff) <= col) return;   // col outside the run's footprints
     const uint32_t pe = pre_excl(D, je), ps = pre_excl(D, sp);
     const uint32_t S = ((pe ^ ps) >> 31) & 1u;
@@ -1012,28 +998,29 @@ __device__ void claimant_walk(const RowArgs &A, const RowData &D, const RowShare
     }
 }
 
-// Calls fn(i, je) for every run (maximal block of entries of one polygon)
-// whose first entry this thread owns.
-template <typename Fn>
-__device__ __forceinline__ void for_each_run(const RowData &D, Fn fn)
+// First entry after run r.
+__device__ __forceinline__ int run_end(const RowData &D, const RowShared &L, int r)
 {
-    for (int i = threadIdx.x; i < D.n; i += row_threads()) {
-        const uint32_t k = D.poly[i];
-        if (i != 0 && D.poly[i - 1] == k) continue;
-        int je = i + 1;
-        while (je < D.n && D.poly[je] == k) ++je;
-        fn(i, je);
-    }
+    return r + 1 < L.nrun ? (int)D.rstart[r + 1] : D.n;
+}
+
+// Calls fn(i, je) for every run; a thread per run.
+template <typename Fn>
+__device__ __forceinline__ void for_each_run(const RowData &D, const RowShared &L, Fn fn)
+{
+    for (int r = threadIdx.x; r < L.nrun; r += row_threads()) fn((int)D.rstart[r], run_end(D, L, r));
 }
 
 // The five inclusive scans of phase 2 in one pass: footprint counts (sum),
 // claim counts (sum) and claimant xor over the row's columns, the per-entry
-// partial/spanning prefix (pre_op) and the interval lengths (sum).  Each
+// partial/spanning prefix (pre_op) and the interval lengths (sum, from the
+// intervals' columns).  Each
 // thread takes a contiguous chunk of every array: chunk totals first (loads
 // only, so they overlap), wave scans of the five totals, one barrier, then
 // the chunks rewritten from their running prefixes.  wt holds 5 words per
 // wave.
-__device__ void row_scans(const RowShared &L, int W, uint32_t *pre, int n, uint32_t *ilen, int ni, uint32_t *wt)
+__device__ void row_scans(const RowShared &L, int W, uint32_t *pre, int n, const uint32_t *icol, uint32_t *ilen,
+                          int ni, uint32_t *wt)
 {
     int32_t *sa = L.sa, *sb = L.sb;
     const int NW = row_threads() >> 6;
@@ -1050,7 +1037,7 @@ __device__ void row_scans(const RowShared &L, int W, uint32_t *pre, int n, uint3
         tx ^= L.sx_get(cix(c));
     }
     for (int q = qb; q < qe; ++q) tp = pre_op(tp, pre[q]);
-    for (int q = ib; q < ie; ++q) ti += ilen[q];
+    for (int q = ib; q < ie; ++q) ti += ilen[q] - icol[q];
     // inclusive wave scans of the chunk totals
     uint32_t ia = ta, ibb = tb, ix = tx, ip = tp, ii = ti;
 #pragma unroll
@@ -1078,29 +1065,67 @@ __device__ void row_scans(const RowShared &L, int W, uint32_t *pre, int n, uint3
         sa[cix(c)] = (int32_t)ra; sb[cix(c)] = (int32_t)rb; L.sx_set(cix(c), rx);
     }
     for (int q = qb; q < qe; ++q) { rp = pre_op(rp, pre[q]); pre[q] = rp; }
-    for (int q = ib; q < ie; ++q) { ri += ilen[q]; ilen[q] = ri; }
+    for (int q = ib; q < ie; ++q) { ri += ilen[q] - icol[q]; ilen[q] = ri; }
     __syncthreads();
 }
 
 // Runs every (run, footprint column) item of the row through column_record.
+// The count phase keeps where it found a thread's first ROW_ITEMS items
+// (interval and sp, two searches of dependent LDS reads each) for the emit
+// phase.
+constexpr int ROW_ITEMS = 4;
+
 template <bool EMIT>
 __device__ void all_column_records(const RowArgs &A, const RowData &D, const RowShared &L,
                                    uint64_t rec_base_r, uint64_t loc_base_r, uint64_t part_base_r,
-                                   uint64_t &nloc_tot)
+                                   uint64_t &nloc_tot, uint32_t (&at)[ROW_ITEMS])
 {
-    const int ni = (int)*L.nint;
+    const int ni = L.nint;
     if (ni == 0) return;
     const uint32_t total = D.ilen[ni - 1];
-    for (uint32_t t = threadIdx.x; t < total; t += row_threads()) {
-        int lo = 0, hi = ni - 1;            // first interval with prefix > t
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (D.ilen[mid] > t) hi = mid; else lo = mid + 1;
+    const bool keep = D.n < 65536;
+    auto item = [&](uint32_t t, uint32_t &slot, bool kept) {
+        int lo, sp, i, je, col;
+        auto bounds = [&]() {
+            const uint32_t before = lo ? D.ilen[lo - 1] : 0u;
+            const int r = (int)D.irun[lo];
+            col = (int)D.icol[lo] + (int)(t - before);
+            i = (int)D.rstart[r];
+            je = run_end(D, L, r);
+        };
+        if (EMIT && kept) {
+            lo = (int)(slot >> 16);
+            sp = (int)(slot & 0xffffu);
+            bounds();
+        } else {
+            lo = 0;
+            int hi = ni - 1;            // first interval with prefix > t
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (D.ilen[mid] > t) hi = mid; else lo = mid + 1;
+            }
+            bounds();
+            sp = i;
+            hi = je;
+            while (sp < hi) {
+                const int mid = (sp + hi) >> 1;
+                if ((int)(D.c[mid] & 0xffff) <= col) sp = mid + 1; else hi = mid;
+            }
+            slot = ((uint32_t)lo << 16) | (uint32_t)sp;
         }
-        const uint32_t before = lo ? D.ilen[lo - 1] : 0u;
-        const int col = (int)D.icol[lo] + (int)(t - before);
-        column_record<EMIT>(A, D, L, (int)D.ihead[lo], (int)D.iend[lo], col, rec_base_r, loc_base_r,
-                            part_base_r, nloc_tot);
+        column_record<EMIT>(A, D, L, i, je, sp, col, rec_base_r, loc_base_r, part_base_r, nloc_tot);
+    };
+    int k = 0;
+#pragma nounroll
+    for (uint32_t t = threadIdx.x; t < total; t += row_threads(), ++k) {
+        uint32_t slot = k == 0 ? at[0] : k == 1 ? at[1] : k == 2 ? at[2] : at[3];
+        item(t, slot, keep && k < ROW_ITEMS);
+        if (!EMIT) {
+            at[0] = k == 0 ? slot : at[0];
+            at[1] = k == 1 ? slot : at[1];
+            at[2] = k == 2 ? slot : at[2];
+            at[3] = k == 3 ? slot : at[3];
+        }
     }
 }
 
@@ -1116,175 +1141,116 @@ __host__ __device__ inline size_t row_lds_bytes(int W, int cap, bool cls16)
     return (size_t)(2 * cw + sx_words(cw, cls16)) * 4 + (size_t)cap * 37 + 32;
 }
 
-// Phase 1 for one run by one thread: footprint counts, interior spans with
-// their claimant xor, running footprint maxima, footprint-union intervals.
-__device__ void run_serial(const RowData &D, const RowShared &L, int i, int je, int W)
+// Elementwise maximum of two pairs of 16-bit values.
+__device__ __forceinline__ uint32_t pkmax(uint32_t a, uint32_t b)
 {
-    const uint32_t lab = D.poly[i] + 1;
-    uint32_t wtot = 0;
-    for (int q = i; q < je; ++q) wtot ^= (D.f[q] & F_W) ? 1u : 0u;
-    uint32_t par = wtot;
-    int mx = -1;
-    uint32_t mall = 0, mnh = 0;
-    const int c0first = (int)(D.c[i] & 0xffff);
-    if (par && c0first > 0) {
-        atomicAdd(&L.sb[cix(0)], 1); atomicSub(&L.sb[cix(c0first)], 1);
-        L.sx_xor(cix(0), lab); L.sx_xor(cix(c0first), lab);
-    }
-    for (int q = i; q < je; ++q) {
-        const uint32_t c = D.c[q];
-        const int c0 = (int)(c & 0xffff), c1 = (int)(c >> 16);
-        const uint8_t f = D.f[q];
-        atomicAdd(&L.sa[cix(c0)], 1);
-        atomicSub(&L.sa[cix(c1 + 1)], 1);
-        mx = max(mx, c1);
-        mall = max(mall, (uint32_t)c1 + 1u);
-        if (!(f & F_HORIZ)) mnh = max(mnh, (uint32_t)c1 + 1u);
-        D.pm[q] = mall | (mnh << 16);
-        if (f & F_W) par ^= 1u;
-        const int nc0 = (q + 1 < je) ? (int)(D.c[q + 1] & 0xffff) : W;
-        const int lo = max(c0, mx + 1), hi = nc0 - 1;
-        if (par && lo <= hi) {
-            atomicAdd(&L.sb[cix(lo)], 1); atomicSub(&L.sb[cix(hi + 1)], 1);
-            L.sx_xor(cix(lo), lab); L.sx_xor(cix(hi + 1), lab);
-        }
-    }
-    // footprint-union intervals of the run
-    int ulo = c0first, uhi = (int)(D.c[i] >> 16);
-    for (int q = i + 1; q <= je; ++q) {
-        const int c0 = q < je ? (int)(D.c[q] & 0xffff) : W + 1;
-        if (q < je && c0 <= uhi + 1) { uhi = max(uhi, (int)(D.c[q] >> 16)); continue; }
-        const uint32_t j = atomicAdd(L.nint, 1u);
-        D.ihead[j] = (uint32_t)i;
-        D.iend[j] = (uint32_t)je;
-        D.icol[j] = (uint32_t)ulo;
-        D.ilen[j] = (uint32_t)(uhi - ulo + 1);
-        if (q < je) { ulo = c0; uhi = (int)(D.c[q] >> 16); }
-    }
+    return max(a & 0xffffu, b & 0xffffu) | max(a & 0xffff0000u, b & 0xffff0000u);
 }
 
-__device__ __forceinline__ int wave_incl_max(int v)
+// Phase 1: the row's runs, and per entry the footprint counts, the interior
+// spans behind it with their claimant xor, the running footprint maxima and
+// the footprint-union intervals.  One entry per thread, row_threads() at a
+// time, with segmented scans over the runs (by lane masks in a wavefront, a
+// few words per wavefront in wt across them), so that a run's length does not
+// matter: the single run of a row of a one-polygon canvas used to be found
+// and walked by one thread or wavefront of the workgroup.  A polygon's rings
+// are closed, so the parity behind its last entry is even.
+__device__ void row_runs(const RowData &D, RowShared &L, int W, uint32_t *wt)
 {
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int t = __shfl_up(v, d, 64);
-        if (lane >= d) v = max(v, t);
-    }
-    return v;
-}
-
-__device__ __forceinline__ uint32_t wave_incl_xor(uint32_t v)
-{
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t t = __shfl_up(v, d, 64);
-        if (lane >= d) v ^= t;
-    }
-    return v;
-}
-
-// Phase 1 for one long run by a whole wave, 64 entries at a time: the
-// serial recurrences (parity after each entry, running maxima, interval
-// starts) become wave scans with carries between chunks.  Same results as
-// run_serial.
-__device__ void run_wave(const RowData &D, const RowShared &L, int i, int W)
-{
-    const int lane = threadIdx.x & 63;
-    const uint32_t k = D.poly[i];
-    const uint32_t lab = k + 1;
-    int je = D.n;
-    for (int b = i;; b += 64) {
-        const int q = b + lane;
-        const bool same = q < D.n && D.poly[q] == k;
-        const unsigned long long m = __ballot(!same);
-        if (m) { je = b + __ffsll((long long)m) - 1; break; }
-    }
-    uint32_t nw = 0;
-    for (int b = i; b < je; b += 64) {
-        const int q = b + lane;
-        nw += (uint32_t)__popcll(__ballot(q < je && (D.f[q] & F_W)));
-    }
-    const uint32_t wtot = nw & 1u;
-    const int c0first = (int)(D.c[i] & 0xffff);
-    if (lane == 0 && wtot && c0first > 0) {
-        atomicAdd(&L.sb[cix(0)], 1); atomicSub(&L.sb[cix(c0first)], 1);
-        L.sx_xor(cix(0), lab); L.sx_xor(cix(c0first), lab);
-    }
-    uint32_t par_c = wtot;
-    int mx_c = -1, mall_c = 0, mnh_c = 0, ulo_c = c0first;
-    for (int b = i; b < je; b += 64) {
-        const int q = b + lane;
-        const bool valid = q < je;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int NW = row_threads() >> 6;
+    const unsigned long long le = lane == 63 ? ~0ull : (2ull << lane) - 1ull;   // lanes up to this one
+    uint32_t runs = 0u, ints = 0u;        // before the current entries
+    uint32_t open_v = 0u, open_p = 0u;    // of the run open before them: maxima, parity
+    for (int b = 0; b < D.n; b += row_threads()) {
+        const int q = b + tid;
+        const bool valid = q < D.n;
+        const uint32_t k = valid ? D.poly[q] : 0u;
         const uint32_t c = valid ? D.c[q] : 0u;
-        const int c0 = (int)(c & 0xffff), c1 = (int)(c >> 16);
         const uint8_t f = valid ? D.f[q] : (uint8_t)0;
-        if (valid) { atomicAdd(&L.sa[cix(c0)], 1); atomicSub(&L.sa[cix(c1 + 1)], 1); }
-        const uint32_t par = par_c ^ wave_incl_xor((f & F_W) ? 1u : 0u);
-        const int mxs = wave_incl_max(valid ? c1 : -1);
-        const int mx = max(mx_c, mxs);
-        const int mall = max(mall_c, wave_incl_max(valid ? c1 + 1 : 0));
-        const int mnh = max(mnh_c, wave_incl_max(valid && !(f & F_HORIZ) ? c1 + 1 : 0));
-        if (valid) D.pm[q] = (uint32_t)mall | ((uint32_t)mnh << 16);
-        const int nc0 = (q + 1 < je) ? (int)(D.c[q + 1] & 0xffff) : W;
-        const int lo = max(c0, mx + 1), hi = nc0 - 1;
-        if (valid && par && lo <= hi) {
-            atomicAdd(&L.sb[cix(lo)], 1); atomicSub(&L.sb[cix(hi + 1)], 1);
-            L.sx_xor(cix(lo), lab); L.sx_xor(cix(hi + 1), lab);
+        const int c0 = (int)(c & 0xffff), c1 = (int)(c >> 16);
+        const bool head = valid && (q == 0 || D.poly[q - 1] != k);
+        const bool last = valid && (q + 1 == D.n || D.poly[q + 1] != k);
+        const int nc0 = valid && !last ? (int)(D.c[q + 1] & 0xffff) : W;
+        const unsigned long long hm = __ballot(head), wm = __ballot((f & F_W) != 0);
+        const unsigned long long hb = hm & le;
+        const int sl = hb ? 63 - __clzll((long long)hb) : -1;   // first lane of this lane's run, -1: before the wavefront
+        // running maxima over the run of c1 + 1: low half all entries, high half non-horizontal ones
+        uint32_t v = valid ? (uint32_t)(c1 + 1) | ((f & F_HORIZ) ? 0u : (uint32_t)(c1 + 1) << 16) : 0u;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint32_t t = __shfl_up(v, d, 64);
+            if (lane - d >= max(sl, 0)) v = pkmax(v, t);
         }
-        // footprint-union intervals: an entry starts one when it begins more
-        // than a column right of every earlier footprint of the run
-        const int prev = __shfl_up(mxs, 1, 64);
-        const int mx_excl = lane ? max(mx_c, prev) : mx_c;
-        const bool start = valid && (q == i || c0 > mx_excl + 1);
-        const int ulo = max(ulo_c, wave_incl_max(start ? c0 : -1));
-        const bool last = valid && (q + 1 == je || nc0 > mx + 1);
-        if (last) {
-            const uint32_t j = atomicAdd(L.nint, 1u);
-            D.ihead[j] = (uint32_t)i;
-            D.iend[j] = (uint32_t)je;
-            D.icol[j] = (uint32_t)ulo;
-            D.ilen[j] = (uint32_t)(mx - ulo + 1);
+        uint32_t par = (uint32_t)__popcll(wm & le & ~(sl > 0 ? (1ull << sl) - 1ull : 0ull)) & 1u;
+        if (lane == 63) {
+            wt[wv] = (uint32_t)__popcll(hm);
+            wt[NW + wv] = v;
+            wt[2 * NW + wv] = par;
         }
-        par_c = __shfl(par, 63, 64);
-        mx_c = __shfl(mx, 63, 64);
-        mall_c = __shfl(mall, 63, 64);
-        mnh_c = __shfl(mnh, 63, 64);
-        ulo_c = __shfl(ulo, 63, 64);
+        __syncthreads();
+        uint32_t r0 = 0u, in_v = 0u, in_p = 0u;   // as runs, open_v, open_p, before this wavefront
+        for (int w = 0; w < NW; ++w) {
+            if (w == wv) { r0 = runs; in_v = open_v; in_p = open_p; }
+            const uint32_t h = wt[w], tv = wt[NW + w], tp = wt[2 * NW + w];
+            runs += h;
+            open_v = h ? tv : pkmax(open_v, tv);
+            open_p = h ? tp : open_p ^ tp;
+        }
+        if (sl < 0) { v = pkmax(v, in_v); par ^= in_p; }
+        uint32_t prev = __shfl_up(v, 1, 64);
+        if (lane == 0) prev = in_v;
+        const int mx = (int)(v & 0xffffu) - 1;
+        // an interval starts where an entry begins more than a column right of
+        // every earlier footprint of its run, and ends before the next start
+        const bool start = valid && (head || c0 > (int)(prev & 0xffffu));
+        const unsigned long long sm = __ballot(start);
+        if (lane == 0) wt[3 * NW + wv] = (uint32_t)__popcll(sm);
+        __syncthreads();
+        uint32_t j0 = 0u;
+        for (int w = 0; w < NW; ++w) {
+            if (w == wv) j0 = ints;
+            ints += wt[3 * NW + w];
+        }
+        if (valid) {
+            const uint32_t r = r0 + (uint32_t)__popcll(hb) - 1u, j = j0 + (uint32_t)__popcll(sm & le) - 1u;
+            if (head) D.rstart[r] = (uint32_t)q;
+            if (start) { D.icol[j] = (uint32_t)c0; D.irun[j] = r; }
+            if (last || nc0 > mx + 1) D.ilen[j] = (uint32_t)(mx + 1);
+            D.pm[q] = v;
+            D.pre[q] = pre_own(f);
+            atomicAdd(&L.sa[cix(c0)], 1);
+            atomicSub(&L.sa[cix(c1 + 1)], 1);
+            const int lo = max(c0, mx + 1), hi = nc0 - 1;
+            if (par && lo <= hi) {
+                const uint32_t lab = k + 1;
+                atomicAdd(&L.sb[cix(lo)], 1); atomicSub(&L.sb[cix(hi + 1)], 1);
+                L.sx_xor(cix(lo), lab); L.sx_xor(cix(hi + 1), lab);
+            }
+        }
     }
+    L.nrun = (int)runs;
+    L.nint = (int)ints;
+    __syncthreads();
 }
 
 template <bool EMIT>
-__device__ void process_row(const RowArgs &A, const RowData &D, const RowShared &L, int64_t r, int W,
+__device__ void process_row(const RowArgs &A, const RowData &D, RowShared &L, int64_t r, int W,
                             int Wt, uint32_t *cells_q, int r_local,
                             int32_t *wtoti, uint32_t *wtotu, uint32_t *s_nbp, uint32_t *s_multi,
-                            unsigned long long *s_nloc, unsigned long long *s_nrec,
-                            unsigned long long *s_base)
+                            unsigned long long *s_nloc, unsigned long long *s_base)
 {
     const int tid = threadIdx.x;
 
-    // phase 1: per run, footprints (boundary counts), interior claims, the
-    //          running footprint maxima and the run list; per entry, the
+    // phase 1: runs, footprints (boundary counts), interior claims, running
+    //          footprint maxima, footprint intervals; per entry, the
     //          partial / spanning indicators to be scanned
-    for (int q = tid; q < D.n; q += row_threads()) D.pre[q] = pre_own(D.f[q]);
-    for_each_run(D, [&](int i, int je) {
-        if (je - i > LONG_RUN) {
-            const uint32_t j = atomicAdd(L.nlong, 1u);
-            if (j < (uint32_t)LONGQ) { L.longq[j] = (uint32_t)i; return; }
-        }
-        run_serial(D, L, i, je, W);
-    });
-    __syncthreads();
-    {
-        const uint32_t nl = min(*L.nlong, (uint32_t)LONGQ);
-        for (uint32_t k = (uint32_t)(tid >> 6); k < nl; k += (row_threads() >> 6)) run_wave(D, L, (int)L.longq[k], W);
-    }
-    __syncthreads();
+    row_runs(D, L, W, wtotu);
 
     // phase 2: prefix scans -> per-pixel boundary count, claim count,
-    //          claimant; per-entry partial/spanning prefixes; run spans
-    row_scans(L, W, D.pre, D.n, D.ilen, (int)*L.nint, wtotu);
+    //          claimant; per-entry partial/spanning prefixes; interval lengths
+    row_scans(L, W, D.pre, D.n, D.icol, D.ilen, L.nint, wtotu);
 
     // phase 3: classify pixels.  sx := 0 (no polygon), label + 1, or for a
     // boundary pixel BFLAG | (label + 1 of its single interior claimant, or 0);
@@ -1312,28 +1278,27 @@ __device__ void process_row(const RowArgs &A, const RowData &D, const RowShared 
 
     // phase 4: count records per column (and local-edge totals)
     uint64_t nloc = 0;
-    all_column_records<false>(A, D, L, 0, 0, 0, nloc);
-    if (rmulti) for_each_run(D, [&](int i, int je) { claimant_walk<false>(A, D, L, i, je, 0, W); });
+    uint32_t at[ROW_ITEMS] = {0u, 0u, 0u, 0u};
+    all_column_records<false>(A, D, L, 0, 0, 0, nloc, at);
+    if (rmulti) for_each_run(D, L, [&](int i, int je) { claimant_walk<false>(A, D, L, i, je, 0, W); });
     atomicAdd(s_nloc, (unsigned long long)nloc);
     __syncthreads();
 
-    {
-        uint32_t nrec = 0;
-        for (int c = tid; c < W; c += row_threads()) nrec += (uint32_t)L.sa[cix(c)];
-        atomicAdd(s_nrec, (unsigned long long)nrec);
-        __syncthreads();
-    }
+    // record ranges of the row's columns: sa := inclusive prefix of the
+    // per-column record counts (column c owns [sa[c-1], sa[c]))
+    block_scan(L.sa, W, wtoti, [](int32_t a, int32_t b) { return a + b; }, 0);
+    const unsigned long long nrec = (unsigned long long)L.sa[cix(W - 1)];
     const uint32_t npart_r = D.n ? (D.pre[D.n - 1] & 0x7fffffffu) : 0u;
     if (EMIT && A.alloc) {
         // reserve this row's output ranges; an overflow abandons the row and
         // the host redoes the canvas with exact sizes
         if (tid == 0) {
             const int sh = (int)(r % NSHARD);
-            const unsigned long long b0 = atomicAdd(&A.gctr[gctr_at(sh, 0)], *s_nrec);
+            const unsigned long long b0 = atomicAdd(&A.gctr[gctr_at(sh, 0)], nrec);
             const unsigned long long b1 = atomicAdd(&A.gctr[gctr_at(sh, 1)], *s_nloc);
             const unsigned long long b2 = atomicAdd(&A.gctr[gctr_at(sh, 2)], (unsigned long long)npart_r);
             atomicAdd(&A.gctr[gctr_at(sh, 3)], (unsigned long long)*s_nbp);
-            const bool over = b0 + *s_nrec > A.cap_rec || b1 + *s_nloc > A.cap_loc || b2 + npart_r > A.cap_part;
+            const bool over = b0 + nrec > A.cap_rec || b1 + *s_nloc > A.cap_loc || b2 + npart_r > A.cap_part;
             if (over) atomicOr(A.errflags, 32u);
             s_base[0] = (unsigned long long)sh * A.cap_rec + b0;
             s_base[1] = (unsigned long long)sh * A.cap_loc + b1;
@@ -1350,7 +1315,7 @@ __device__ void process_row(const RowArgs &A, const RowData &D, const RowShared 
     }
     if (!EMIT) {
         if (tid == 0) {
-            A.row_nrec[r] = *s_nrec;
+            A.row_nrec[r] = nrec;
             A.row_nloc[r] = *s_nloc;
             A.row_npart[r] = npart_r;
             A.row_nbp[r] = *s_nbp;
@@ -1358,20 +1323,14 @@ __device__ void process_row(const RowArgs &A, const RowData &D, const RowShared 
         return;
     }
 
-    // record ranges of the row's columns: sa := inclusive prefix of the
-    // per-column record counts (column c owns [sa[c-1], sa[c])), sb := 0
-    block_scan(L.sa, W, wtoti, [](int32_t a, int32_t b) { return a + b; }, 0);
-    for (int c = tid; c < W; c += row_threads()) L.sb[cix(c)] = 0;
-    __syncthreads();
-
     // phase 5: records, local edges, partial spans (in row entry order)
     const uint64_t rec_base_r = A.alloc ? s_base[0] : A.rec_base[r];
     const uint64_t loc_base_r = A.alloc ? s_base[1] : A.loc_base[r];
     const uint64_t part_base_r = A.alloc ? s_base[2] : A.part_base[r];
     {
         uint64_t dummy = 0;
-        all_column_records<true>(A, D, L, rec_base_r, loc_base_r, part_base_r, dummy);
-        if (rmulti) for_each_run(D, [&](int i, int je) { claimant_walk<true>(A, D, L, i, je, rec_base_r, W); });
+        all_column_records<true>(A, D, L, rec_base_r, loc_base_r, part_base_r, dummy, at);
+        if (rmulti) for_each_run(D, L, [&](int i, int je) { claimant_walk<true>(A, D, L, i, je, rec_base_r, W); });
         else
             for (int c = tid; c < W; c += row_threads()) {
                 const uint32_t w = L.sx_get(cix(c));
@@ -1414,9 +1373,8 @@ __global__ __launch_bounds__(ROW_THREADS_MAX) void k_rows(RowArgs A)
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int32_t wtoti[ROW_THREADS_MAX / 64];
     __shared__ uint32_t wtotu[5 * (ROW_THREADS_MAX / 64)];
-    __shared__ uint32_t s_locfill, s_nint, s_nbp, s_multi, s_nlong;
-    __shared__ uint32_t s_longq[LONGQ];
-    __shared__ unsigned long long s_nloc, s_nrec, s_base[4];
+    __shared__ uint32_t s_locfill, s_nbp, s_multi;
+    __shared__ unsigned long long s_nloc, s_base[4];
     const int cap = A.cap;
     const int cwmax = col_words(A.maxW);
     RowShared L;
@@ -1425,10 +1383,7 @@ __global__ __launch_bounds__(ROW_THREADS_MAX) void k_rows(RowArgs A)
     L.sx = (void *)(L.sb + cwmax);
     L.cls16 = A.cls16 != 0;
     L.locfill = &s_locfill;
-    L.nint = &s_nint;
-    L.nlong = &s_nlong;
-    L.longq = s_longq;
-    L.nrec = &s_nrec;
+    L.nrun = L.nint = 0;
     uint32_t *lpoly = (uint32_t *)(L.sb + cwmax) + sx_words(cwmax, L.cls16);
     uint32_t *lc = lpoly + cap;
     uint32_t *ledge = lc + cap;
@@ -1463,18 +1418,18 @@ __global__ __launch_bounds__(ROW_THREADS_MAX) void k_rows(RowArgs A)
             }
         }
         for (int c = tid; c < cw; c += row_threads()) { L.sa[c] = 0; L.sb[c] = 0; L.sx_set(c, 0u); }
-        if (tid == 0) { s_locfill = 0; s_nint = 0; s_nbp = 0; s_multi = 0; s_nloc = 0; s_nrec = 0; s_nlong = 0; }
+        if (tid == 0) { s_locfill = 0; s_nbp = 0; s_multi = 0; s_nloc = 0; }
         __syncthreads();
         if (n <= cap) {
             const RowData D{lpoly, lc, lf, ledge, lpm, lpre, lih, lie, lic, lil, n};
             process_row<EMIT>(A, D, L, r, W, Wt, cells_q, r_local, wtoti, wtotu, &s_nbp, &s_multi, &s_nloc,
-                              &s_nrec, s_base);
+                              s_base);
         } else {
             uint32_t *g = A.gaux + (size_t)6 * s;
             const RowData D{A.spoly + s, A.sc + s, A.sf + s, A.sedge + s, g, g + n, g + 2 * n, g + 3 * n,
                             g + 4 * n, g + 5 * n, n};
             process_row<EMIT>(A, D, L, r, W, Wt, cells_q, r_local, wtoti, wtotu, &s_nbp, &s_multi, &s_nloc,
-                              &s_nrec, s_base);
+                              s_base);
         }
         __syncthreads();
     }
