@@ -155,7 +155,7 @@ __global__ __launch_bounds__(256) void k_validate(int64_t M, int64_t R, const in
 // Each thread reduces a run of BB_SPAN consecutive vertices, flushing when
 // the canvas changes; a wave whose runs all end in one canvas merges them
 // before its atomics, so one canvas of many vertices costs few atomics.
-constexpr int BB_SPAN = 32;
+constexpr int BB_SPAN = 8;
 
 __device__ __forceinline__ void bb_flush(unsigned long long *bb, int q, const unsigned long long k[4])
 {
@@ -447,7 +447,12 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_rowscan(int64_t Htot, const ui
 #pragma unroll
         for (int k = 0; k < RS_REG; ++k) tot += rc[k];
     } else {
-        for (int64_t r = b; r < e; ++r) tot += rcount[r * rstride];
+        for (int64_t r = b; r < e; r += RS_REG) {   // RS_REG loads in flight
+#pragma unroll
+            for (int k = 0; k < RS_REG; ++k) rc[k] = r + k < e ? rcount[(r + k) * rstride] : 0u;
+#pragma unroll
+            for (int k = 0; k < RS_REG; ++k) tot += rc[k];
+        }
     }
     long long off = block_excl_sum(tot, wtot);
     int mx = 0;
@@ -464,7 +469,13 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_rowscan(int64_t Htot, const ui
         for (int k = 0; k < RS_REG; ++k)
             if (b + k < e) visit(b + k, rc[k]);
     } else {
-        for (int64_t r = b; r < e; ++r) visit(r, rcount[r * rstride]);
+        for (int64_t r = b; r < e; r += RS_REG) {
+#pragma unroll
+            for (int k = 0; k < RS_REG; ++k) rc[k] = r + k < e ? rcount[(r + k) * rstride] : 0u;
+#pragma unroll
+            for (int k = 0; k < RS_REG; ++k)
+                if (r + k < e) visit(r + k, rc[k]);
+        }
     }
     atomicMax(&s_max, mx);
     __syncthreads();
@@ -625,78 +636,103 @@ __global__ __launch_bounds__(256) void k_entries_rows(int64_t V, const Edge *edg
     }
 }
 
-// Longest row the in-row sort takes (its keys twice in LDS).
+// Longest row the in-row sort takes; rows of more than the row stage's `cap`
+// entries (at most SORT_CAP) are listed and sorted by workgroups of SORT_LONG
+// threads, the others by smaller ones.
 constexpr int ROWSORT_MAX = 4096;
-constexpr int SORT_THREADS = 1024;
-constexpr int SORT_CHUNKS = ROWSORT_MAX / SORT_THREADS;
+constexpr int SORT_LONG = 1024;
+constexpr int SORT_SHORT = 256;
+constexpr int SORT_CAP = 2048;
+constexpr int SORT_CHUNK = 64;                               // keys ranked against each other directly
+constexpr size_t SORT_KEY_BYTES = sizeof(uint64_t) + sizeof(uint16_t);
+
+struct SortArgs {
+    const uint32_t *row_off;
+    const uint64_t *ukey;
+    const uint32_t *uc;
+    const uint8_t *uf;
+    int pshift;
+    uint64_t emask;
+    uint32_t *s_poly, *s_edge, *s_c;
+    uint8_t *s_f;
+};
+
+// Sorts the n keys of the row at s, at most PER per thread (kk, src: LDS).
+// Every thread of the workgroup calls it (barriers).
+template <int PER, int nt>
+__device__ __forceinline__ void sort_row(const SortArgs &A, uint64_t *kk, uint16_t *src, uint32_t s, int n)
+{
+    const int t = threadIdx.x;
+    for (int i = t; i < n; i += nt) kk[i] = A.ukey[s + i];
+    __syncthreads();
+    uint64_t x[PER];
+    int at[PER];
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const int i = j * nt + t;
+        if (j * nt >= n) break;
+        x[j] = i < n ? kk[i] : ~0ull;
+        const int cb = i & ~(SORT_CHUNK - 1), ce = min(n, cb + SORT_CHUNK);
+        int rank = 0;
+#pragma unroll 8
+        for (int q = cb; q < ce; ++q) rank += (kk[q] < x[j]) ? 1 : 0;
+        at[j] = cb + rank;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const int i = j * nt + t;
+        if (i >= n) break;
+        kk[at[j]] = x[j];
+        src[at[j]] = (uint16_t)i;
+    }
+    __syncthreads();
+    for (int i = t; i < n; i += nt) {
+        const uint64_t key = kk[i];
+        const int own = i & ~(SORT_CHUNK - 1);
+        int g = i - own;
+#pragma unroll 4
+        for (int ob = 0; ob < n; ob += SORT_CHUNK) {
+            // smaller keys of the chunk at ob
+            int lo = 0;
+#pragma unroll
+            for (int st = SORT_CHUNK / 2; st > 0; st >>= 1)
+                if (ob + lo + st <= n && kk[ob + lo + st - 1] < key) lo += st;
+            if (ob + lo < n && kk[ob + lo] < key) ++lo;
+            g += ob == own ? 0 : lo;
+        }
+        const uint32_t from = s + src[i];
+        A.s_poly[s + g] = (uint32_t)(key >> A.pshift);
+        A.s_edge[s + g] = (uint32_t)(key & A.emask);
+        A.s_c[s + g] = A.uc[from];
+        A.s_f[s + g] = A.uf[from];
+    }
+    __syncthreads();
+}
 
 // Sorts every row's entries by key and writes them in that order: polygon
 // and edge from the key, footprint and flags from the source slot.  Keys
-// are unique.  The row is cut into chunks of one key per thread; a key's
-// rank in its chunk is the count of smaller keys there (the chunk is then
-// stored sorted), and its rank in the row adds, for every other chunk, the
-// count of smaller keys found by binary search.  The listed long rows
-// (nB + nC of them, with more than `cap` entries) come first, so that the
-// longest sorts do not start last.
-__global__ __launch_bounds__(SORT_THREADS) void k_rowsort(int64_t Htot, const uint32_t *row_off,
-                                                          const uint64_t *ukey, const uint32_t *uc,
-                                                          const uint8_t *uf, int pshift, uint64_t emask,
-                                                          uint32_t *s_poly, uint32_t *s_edge, uint32_t *s_c,
-                                                          uint8_t *s_f, int pmax, const uint32_t *longrows,
-                                                          int64_t nB, int64_t nC, int cap)
+// are unique.  A row is cut into chunks of SORT_CHUNK keys; a key's rank in
+// its chunk is the count of smaller keys there (the chunk is then stored
+// sorted, in place), and its rank in the row adds, for every other chunk, the
+// count of smaller keys found by binary search: about 64 compares plus 6 per
+// 64 keys.
+template <bool LONG>
+__global__ __launch_bounds__(LONG ? SORT_LONG : SORT_SHORT) void k_rowsort(int64_t Htot, SortArgs A, int pmax,
+                                                                        const uint32_t *longrows, int64_t nB,
+                                                                        int64_t nC, int cap)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    uint64_t *kk = (uint64_t *)smem;      // keys in bucket order
-    uint64_t *sk = kk + pmax;             // keys, each chunk sorted
-    const int tid = threadIdx.x;
-    const int64_t items = nC + nB + Htot;
+    uint64_t *kk = (uint64_t *)smem;             // keys in bucket order, then each chunk sorted
+    uint16_t *src = (uint16_t *)(kk + pmax);     // their slots in the bucket
+    const int64_t items = LONG ? nC + nB : Htot;
     for (int64_t k = blockIdx.x; k < items; k += gridDim.x) {
-        const int64_t r = k < nC ? (int64_t)longrows[Htot + k] : k < nC + nB ? (int64_t)longrows[k - nC] : k - nC - nB;
-        const uint32_t s = row_off[r];
-        const int n = (int)(row_off[r + 1] - s);
-        if (n == 0 || (k >= nC + nB && n > cap)) continue;
-        const int C = (n + SORT_THREADS - 1) / SORT_THREADS;
-        for (int i = tid; i < n; i += SORT_THREADS) kk[i] = ukey[s + i];
-        __syncthreads();
-        int lr[SORT_CHUNKS];
-#pragma unroll
-        for (int c = 0; c < SORT_CHUNKS; ++c) {
-            const int i = c * SORT_THREADS + tid;
-            lr[c] = 0;
-            if (c < C && i < n) {
-                const uint64_t x = kk[i];
-                const int cb = c * SORT_THREADS, ce = min(n, cb + SORT_THREADS);
-                int rank = 0;
-#pragma unroll 8
-                for (int q = cb; q < ce; ++q) rank += (kk[q] < x) ? 1 : 0;
-                lr[c] = rank;
-                sk[cb + rank] = x;
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int c = 0; c < SORT_CHUNKS; ++c) {
-            const int i = c * SORT_THREADS + tid;
-            if (c < C && i < n) {
-                const uint64_t x = kk[i];
-                int g = lr[c];
-                for (int o = 0; o < C; ++o) {
-                    if (o == c) continue;
-                    int lo = o * SORT_THREADS, hi = min(n, lo + SORT_THREADS);   // at most 1024 keys
-                    const int b = lo;
-                    while (lo < hi) {
-                        const int mid = (lo + hi) >> 1;
-                        if (sk[mid] < x) lo = mid + 1; else hi = mid;
-                    }
-                    g += lo - b;
-                }
-                s_poly[s + g] = (uint32_t)(x >> pshift);
-                s_edge[s + g] = (uint32_t)(x & emask);
-                s_c[s + g] = uc[s + i];
-                s_f[s + g] = uf[s + i];
-            }
-        }
-        __syncthreads();
+        const int64_t r = !LONG ? k : k < nC ? (int64_t)longrows[Htot + k] : (int64_t)longrows[k - nC];
+        const uint32_t s = A.row_off[r];
+        const int n = (int)(A.row_off[r + 1] - s);
+        if (n == 0 || (!LONG && n > cap)) continue;
+        if (LONG) sort_row<ROWSORT_MAX / SORT_LONG, SORT_LONG>(A, kk, src, s, n);
+        else sort_row<SORT_CAP / SORT_SHORT, SORT_SHORT>(A, kk, src, s, n);
     }
 }
 
@@ -1984,7 +2020,7 @@ int build_set(spade_ctx *ctx, const spade_polys *polys, int nc, const int64_t *p
     const bool cls16 = maxM_all < 0x8000;
     const size_t col_bytes = row_lds_bytes(W, 0, cls16);
     const size_t target = (col_bytes <= 40 * 1024) ? 38 * 1024 : (col_bytes <= 60 * 1024) ? 78 * 1024 : 150 * 1024;
-    const int cap = (int)std::max<size_t>(256, (target - std::min(target - 256 * 37, col_bytes)) / 37);
+    const int cap = (int)std::min<size_t>(SORT_CAP, std::max<size_t>(256, (target - std::min(target - 256 * 37, col_bytes)) / 37));
     // rows up to capB entries run in the launch over all rows, taken first,
     // their entries and auxiliary words in global memory; longer ones get a
     // launch of their own with a stage for the longest
@@ -2058,15 +2094,25 @@ int build_set(spade_ctx *ctx, const spade_polys *polys, int nc, const int64_t *p
     DevBuf &cub = ctx->scratch[S_CUBTMP];
     size_t tbytes = 0, tscan = 0;
     const int pmax = (int)std::max<uint64_t>(1, maxrow);
-    const size_t sort_lds = (size_t)pmax * 16 + 16;
+    const size_t sort_lds = (size_t)pmax * SORT_KEY_BYTES + 16;
     if (bucketed)
-        SPADE_HIP(ctx, hipFuncSetAttribute((const void *)k_rowsort, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sort_lds));
+        SPADE_HIP(ctx, hipFuncSetAttribute((const void *)k_rowsort<true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sort_lds));
     if (!bucketed) {
         SPADE_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(nullptr, tscan, nrows, eoff, (int)(V + 1), st));
         SPADE_HIP(ctx, hipcub::DeviceRadixSort::SortPairs(nullptr, tbytes, (const uint64_t *)dk.p,
                                                           (uint64_t *)dk2.p, (const uint32_t *)perm,
                                                           perm2, (int)T, 0, kbits, st));
         if (ensure(ctx, cub, std::max(tbytes, tscan))) return SPADE_E_NOMEM;
+    }
+    // internal stream for the launches over the listed long rows, which run
+    // beside the launches over all rows
+    const int64_t nlist = (int64_t)(nlistB + nlistC);
+    if (nlist > 0 && !ctx->side2) {
+        if (!ctx->side) SPADE_HIP(ctx, hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking));
+        SPADE_HIP(ctx, hipStreamCreateWithFlags(&ctx->side2, hipStreamNonBlocking));
+        if (!ctx->fork) SPADE_HIP(ctx, hipEventCreateWithFlags(&ctx->fork, hipEventDisableTiming));
+        if (!ctx->join) SPADE_HIP(ctx, hipEventCreateWithFlags(&ctx->join, hipEventDisableTiming));
+        SPADE_HIP(ctx, hipEventCreateWithFlags(&ctx->join2, hipEventDisableTiming));
     }
     auto enqueue_entries = [&]() -> hipError_t {
         hipError_t e;
@@ -2078,12 +2124,23 @@ int build_set(spade_ctx *ctx, const spade_polys *polys, int nc, const int64_t *p
                                    (const unsigned long long *)nullptr, (uint64_t)0);
                 if ((e = hipGetLastError()) != hipSuccess) return e;
             }
-            const int64_t sort_items = H + (int64_t)nlistB + (int64_t)nlistC;
-            hipLaunchKernelGGL(k_rowsort, dim3((unsigned)std::min<int64_t>(sort_items, 65535)), dim3(SORT_THREADS), sort_lds,
-                               qs, H, (const uint32_t *)row_off, (const uint64_t *)dk.p, (const uint32_t *)ent_c,
-                               (const uint8_t *)ent_f, cbits + ebits, (1ULL << ebits) - 1, s_poly, s_edge, s_c,
-                               s_f, pmax, (const uint32_t *)longrows, (int64_t)nlistB, (int64_t)nlistC, cap);
-            return hipGetLastError();
+            const SortArgs sa{row_off, (const uint64_t *)dk.p, ent_c, ent_f, cbits + ebits, (1ULL << ebits) - 1,
+                              s_poly, s_edge, s_c, s_f};
+            if (nlist > 0) {
+                if ((e = hipEventRecord(ctx->fork, qs)) != hipSuccess) return e;
+                if ((e = hipStreamWaitEvent(ctx->side2, ctx->fork, 0)) != hipSuccess) return e;
+                hipLaunchKernelGGL(k_rowsort<true>, dim3((unsigned)std::min<int64_t>(nlist, 65535)), dim3(SORT_LONG), sort_lds,
+                                   ctx->side2, H, sa, pmax, (const uint32_t *)longrows, (int64_t)nlistB, (int64_t)nlistC,
+                                   cap);
+                if ((e = hipGetLastError()) != hipSuccess) return e;
+                if ((e = hipEventRecord(ctx->join2, ctx->side2)) != hipSuccess) return e;
+            }
+            const int pshort = (int)std::min<uint64_t>((uint64_t)pmax, (uint64_t)cap);
+            hipLaunchKernelGGL(k_rowsort<false>, dim3((unsigned)std::min<int64_t>(H, 65535)), dim3(SORT_SHORT),
+                               (size_t)pshort * SORT_KEY_BYTES + 16, qs, H, sa, pshort, (const uint32_t *)longrows,
+                               (int64_t)nlistB, (int64_t)nlistC, cap);
+            if ((e = hipGetLastError()) != hipSuccess) return e;
+            return nlist > 0 ? hipStreamWaitEvent(qs, ctx->join2, 0) : hipSuccess;
         }
         size_t tb1 = tscan;
         e = hipcub::DeviceScan::ExclusiveSum(cub.p, tb1, nrows, eoff, (int)(V + 1), qs);
@@ -2144,13 +2201,6 @@ int build_set(spade_ctx *ctx, const spade_polys *polys, int nc, const int64_t *p
     // latency).  That launch takes the mid-length rows first, so that their
     // slower global-memory passes start at once.
     const bool bigrows = nlistC > 0;
-    if (bigrows && !ctx->side2) {
-        if (!ctx->side) SPADE_HIP(ctx, hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking));
-        SPADE_HIP(ctx, hipStreamCreateWithFlags(&ctx->side2, hipStreamNonBlocking));
-        if (!ctx->fork) SPADE_HIP(ctx, hipEventCreateWithFlags(&ctx->fork, hipEventDisableTiming));
-        if (!ctx->join) SPADE_HIP(ctx, hipEventCreateWithFlags(&ctx->join, hipEventDisableTiming));
-        SPADE_HIP(ctx, hipEventCreateWithFlags(&ctx->join2, hipEventDisableTiming));
-    }
     // a stage that leaves room for at most two workgroups per CU gets 512
     // threads per row instead of 256, so the CU still runs 16 waves
     auto row_threads_for = [](size_t lds) {
