@@ -549,6 +549,9 @@ __global__ __launch_bounds__(256) void k_entries(int64_t V, const Edge *edges, c
     }
 }
 
+constexpr int ESPREAD_MAX = 5;
+constexpr int64_t ESPREAD_LANES = 1 << 18;   // entries are latency-bound: 10,000 edges of 250 rows 121 us at 4 lanes, 93 at 32
+
 // Entries written straight into their row's bucket with the key
 // (polygon, first column, edge id) that orders them inside the row.  A
 // workgroup reserves, per row it touches, one range of slots with one
@@ -557,7 +560,7 @@ __global__ __launch_bounds__(256) void k_entries(int64_t V, const Edge *edges, c
 __global__ __launch_bounds__(256) void k_entries_rows(int64_t V, const Edge *edges, const uint32_t *epoly,
                                                       const int32_t *erow0, const uint64_t *nrows,
                                                       const CanvasDesc *cds, int nc, int ebits,
-                                                      int ckshift, uint32_t *cursor, int rstride,
+                                                      int ckshift, int espread, uint32_t *cursor, int rstride,
                                                       uint64_t *ukey, uint32_t *uc, uint8_t *uf,
                                                       const unsigned long long *tinfo, uint64_t tcap)
 {
@@ -580,12 +583,11 @@ __global__ __launch_bounds__(256) void k_entries_rows(int64_t V, const Edge *edg
         uc[pos] = (uint32_t)c0 | ((uint32_t)c1 << 16);
         uf[pos] = (span ? F_SPAN : 0) | (w ? F_W : 0) | (horiz ? F_HORIZ : 0);
     };
-    // one edge per fourth lane: four times the waves, a quarter of the
-    // entries per wave
-    const int64_t per = nth >> 2;
+    // one edge per 2^espread lanes: more waves, fewer entries per wave
+    const int64_t per = nth >> espread;
     const int64_t iters = (V + per - 1) / per;   // the same for every thread (block barriers)
     for (int64_t it = 0; it < iters; ++it) {
-        const int64_t j = (lane & 3) ? V : it * per + (((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 2);
+        const int64_t j = (lane & ((1 << espread) - 1)) ? V : it * per + (((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> espread);
         const int nr = j < V ? (int)nrows[j] : 0;
         int64_t g0 = 0;
         int q = 0;
@@ -2047,6 +2049,8 @@ int build_set(spade_ctx *ctx, const spade_polys *polys, int nc, const int64_t *p
     const int pbits = std::max(1, bits_for((uint64_t)(maxM - 1)));
     const int rbits = std::max(1, bits_for((uint64_t)H - 1));
     const int ebits = std::max(1, bits_for((uint64_t)V - 1));
+    int espread = 2;
+    while (espread < ESPREAD_MAX && (V << espread) < ESPREAD_LANES) ++espread;
     DevBuf &dk = ctx->scratch[S_KEYS], &dk2 = ctx->scratch[S_KEYS2];
     DevBuf &dv = ctx->scratch[S_VALS], &dv2 = ctx->scratch[S_VALS2];
     DevBuf &dc = ctx->scratch[S_ENTC], &df = ctx->scratch[S_ENTF];
@@ -2056,8 +2060,8 @@ int build_set(spade_ctx *ctx, const spade_polys *polys, int nc, const int64_t *p
     const uint64_t tcap = std::min(std::min(dk.cap / 8, dc.cap / 20), df.cap >= 16 ? (df.cap - 16) / 2 : 0);
     const bool spec = tcap > 0 && pbits + cbits + ebits <= 63;
     if (spec) {
-        hipLaunchKernelGGL(k_entries_rows, dim3(grid_for(4 * V)), dim3(256), 0, st, V, (const Edge *)cv->edges.p,
-                           epoly, erow0, nrows, d_cds, nc, ebits, cbits + ebits, cursor, rstride,
+        hipLaunchKernelGGL(k_entries_rows, dim3(grid_for(V << espread)), dim3(256), 0, st, V, (const Edge *)cv->edges.p,
+                           epoly, erow0, nrows, d_cds, nc, ebits, cbits + ebits, espread, cursor, rstride,
                            (uint64_t *)dk.p, (uint32_t *)dc.p, (uint8_t *)df.p,
                            (const unsigned long long *)rinfo, tcap);
         SPADE_HIP(ctx, hipGetLastError());
@@ -2118,9 +2122,9 @@ int build_set(spade_ctx *ctx, const spade_polys *polys, int nc, const int64_t *p
         hipError_t e;
         if (bucketed) {
             if (!entries_done) {
-                hipLaunchKernelGGL(k_entries_rows, dim3(grid_for(4 * V)), dim3(256), 0, qs, V,
+                hipLaunchKernelGGL(k_entries_rows, dim3(grid_for(V << espread)), dim3(256), 0, qs, V,
                                    (const Edge *)cv->edges.p, epoly, erow0, nrows, d_cds, nc, ebits, cbits + ebits,
-                                   cursor, rstride, (uint64_t *)dk.p, ent_c, ent_f,
+                                   espread, cursor, rstride, (uint64_t *)dk.p, ent_c, ent_f,
                                    (const unsigned long long *)nullptr, (uint64_t)0);
                 if ((e = hipGetLastError()) != hipSuccess) return e;
             }
