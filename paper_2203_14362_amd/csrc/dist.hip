@@ -19,6 +19,8 @@
 #include "wavewalk.h"
 
 #include <hipcub/hipcub.hpp>
+#include <rocprim/warp/warp_reduce.hpp>
+#include <rocprim/warp/warp_scan.hpp>
 
 #include <algorithm>
 #include <cmath>
@@ -562,34 +564,108 @@ __device__ __forceinline__ bool in_circle_pow2(double x, double y, double px, do
 // those outside circle KNN_JMAX.  The FP64 squared distance only gives the
 // first guess at j (4^j <= d2 up to rounding); the exact test settles it,
 // usually with two tests: j is outside, j + 1 inside.
-// Only bins that were hit are added to the global counts.
+// Only bins that were hit are added to the global counts.  wmin keeps the
+// innermost circle of every 64 consecutive points, so that the selection that
+// follows reads only the points it can take: the pass runs at the rate of a
+// plain read (100M points in 0.25 ms), and a second one over all points cost
+// as much again.
+constexpr int16_t KNN_NONE = 0x7fff;   // 64 points without a finite one
+constexpr int KNN_PER = 2;             // points per thread in flight
+
 __global__ __launch_bounds__(KNN_THREADS) void k_knn_pow2(int64_t n, const double *X, const double *Y, double px,
-                                                          double py, unsigned long long *bins)
+                                                          double py, unsigned long long *bins, int16_t *wmin)
 {
     __shared__ unsigned int h[KNN_BINS];
     for (int k = threadIdx.x; k < KNN_BINS; k += KNN_THREADS) h[k] = 0;
     __syncthreads();
-    for (int64_t i = (int64_t)blockIdx.x * KNN_THREADS + threadIdx.x; i < n; i += (int64_t)gridDim.x * KNN_THREADS) {
-        const double x = __builtin_nontemporal_load(X + i), y = __builtin_nontemporal_load(Y + i);
-        if (!(fabs(x) <= 1.7976931348623157e308 && fabs(y) <= 1.7976931348623157e308)) continue;
-        const double dx = x - px, dy = y - py;
-        const double d2 = dx * dx + dy * dy;
-        int j;
-        if (!(d2 > 0.0)) j = KNN_JMIN;
-        else if (!(d2 <= 1.7976931348623157e308)) j = KNN_JMAX + 1;
-        else j = min(max(ilogb(d2) >> 1, KNN_JMIN), KNN_JMAX + 1);   // 4^j <= d2 up to rounding
-        if (j <= KNN_JMAX && !in_circle_pow2(x, y, px, py, j)) {
-            do ++j;
-            while (j <= KNN_JMAX && !in_circle_pow2(x, y, px, py, j));
-        } else {
-            // in circle j (or j past the last one): move inwards while inside
-            while (j > KNN_JMIN && in_circle_pow2(x, y, px, py, j - 1)) --j;
+    const int64_t step = (int64_t)gridDim.x * KNN_THREADS * KNN_PER;
+    for (int64_t b = (int64_t)blockIdx.x * KNN_THREADS * KNN_PER; b < n; b += step) {
+        double xs[KNN_PER], ys[KNN_PER];
+#pragma unroll
+        for (int u = 0; u < KNN_PER; ++u) {
+            const int64_t i = b + u * KNN_THREADS + threadIdx.x;
+            xs[u] = i < n ? __builtin_nontemporal_load(X + i) : NAN;
+            ys[u] = i < n ? __builtin_nontemporal_load(Y + i) : NAN;
         }
-        atomicAdd(&h[j - KNN_JMIN], 1u);
+#pragma unroll
+        for (int u = 0; u < KNN_PER; ++u) {
+            const int64_t i = b + u * KNN_THREADS + threadIdx.x;
+            const double x = xs[u], y = ys[u];
+            int j = KNN_NONE;
+            if (fabs(x) <= 1.7976931348623157e308 && fabs(y) <= 1.7976931348623157e308) {
+                const double dx = x - px, dy = y - py;
+                const double d2 = dx * dx + dy * dy;
+                if (!(d2 > 0.0)) j = KNN_JMIN;
+                else if (!(d2 <= 1.7976931348623157e308)) j = KNN_JMAX + 1;
+                else j = min(max(ilogb(d2) >> 1, KNN_JMIN), KNN_JMAX + 1);   // 4^j <= d2 up to rounding
+                if (j <= KNN_JMAX && !in_circle_pow2(x, y, px, py, j)) {
+                    do ++j;
+                    while (j <= KNN_JMAX && !in_circle_pow2(x, y, px, py, j));
+                } else {
+                    // in circle j (or j past the last one): move inwards while inside
+                    while (j > KNN_JMIN && in_circle_pow2(x, y, px, py, j - 1)) --j;
+                }
+                atomicAdd(&h[j - KNN_JMIN], 1u);
+            }
+            int low;
+            typename rocprim::warp_reduce<int, 64>::storage_type storage;
+            rocprim::warp_reduce<int, 64>().reduce(j, low, storage, rocprim::minimum<int>());
+            if ((threadIdx.x & 63) == 0 && i < n) wmin[i >> 6] = (int16_t)low;
+        }
     }
     __syncthreads();
     for (int k = threadIdx.x; k < KNN_BINS; k += KNN_THREADS)
         if (h[k]) atomicAdd(&bins[k], (unsigned long long)h[k]);
+}
+
+// The points of circle 2^J from the words whose innermost circle reaches it,
+// in no particular order: ids and keys (FP64 squared distance).  A wavefront
+// looks at 64 words, one per lane; one global atomic per workgroup.
+__global__ __launch_bounds__(KNN_THREADS) void k_knn_take(int64_t n, const double *X, const double *Y, double px,
+                                                          double py, int J, const int16_t *wmin, uint32_t *count,
+                                                          uint32_t cap, uint32_t *ids, unsigned long long *keys)
+{
+    __shared__ uint32_t wsum[KNN_THREADS / 64];
+    __shared__ uint32_t s_base;
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int64_t nw = (n + 63) >> 6;
+    const int64_t w0 = ((int64_t)blockIdx.x * (KNN_THREADS / 64) + wv) * 64;
+    const bool reach = w0 + lane < nw && wmin[w0 + lane] <= J;
+    unsigned long long mine = 0ull;   // the points of this lane's word that are taken
+    for (unsigned long long m = __ballot(reach); m; m &= m - 1) {
+        const int w = __ffsll((long long)m) - 1;
+        const int64_t i = (w0 + w) * 64 + lane;
+        const bool in = i < n && in_circle_pow2(X[i], Y[i], px, py, J);
+        const unsigned long long t = __ballot(in);
+        if (lane == w) mine = t;
+    }
+    const uint32_t c = (uint32_t)__popcll(mine);
+    uint32_t incl;
+    typename rocprim::warp_scan<uint32_t, 64>::storage_type storage;
+    rocprim::warp_scan<uint32_t, 64>().inclusive_scan(c, incl, storage, rocprim::plus<uint32_t>());
+    if (lane == 63) wsum[wv] = incl;
+    __syncthreads();
+    uint32_t pre = 0u, total = 0u;
+#pragma unroll
+    for (int w = 0; w < KNN_THREADS / 64; ++w) {
+        if (w < wv) pre += wsum[w];
+        total += wsum[w];
+    }
+    if (total == 0u) return;   // uniform over the workgroup
+    if (threadIdx.x == 0) s_base = atomicAdd(count, total);
+    __syncthreads();
+    const uint32_t first = s_base + pre + incl - c;   // of this lane's word
+    for (unsigned long long m = __ballot(mine != 0ull); m; m &= m - 1) {
+        const int w = __ffsll((long long)m) - 1;
+        const unsigned long long t = (unsigned long long)__shfl((long long)mine, w, 64);
+        const uint32_t at = (uint32_t)__shfl((int)first, w, 64) + (uint32_t)__popcll(t & ((1ull << lane) - 1ull));
+        if (((t >> lane) & 1ull) && at < cap) {
+            const int64_t i = (w0 + w) * 64 + lane;
+            ids[at] = (uint32_t)i;
+            keys[at] = (unsigned long long)__double_as_longlong(dist2(X[i], Y[i], px, py));
+        }
+    }
 }
 
 // Candidate keys: FP64 squared distance (non-negative, so its bits order it)
@@ -636,6 +712,62 @@ __global__ void k_knn_fix(int64_t m, int64_t upto, const unsigned long long *key
     }
 }
 
+// Few candidates (m <= KS_MAX) are ordered by one workgroup in LDS: a bitonic
+// sort of (key, id), the runs of keys too close to tell apart as in k_knn_fix,
+// and the first kk ids written out.  The library sort and the kernels around
+// it took five launches for the 1,000 to 4,000 candidates of k = 1,000.
+constexpr int KS_THREADS = 1024;
+constexpr int KS_MAX = 4096;
+
+__global__ __launch_bounds__(KS_THREADS) void k_knn_order(int m, int kk, const unsigned long long *keys,
+                                                          const uint32_t *ids, const double *X, const double *Y,
+                                                          double px, double py, uint32_t *out)
+{
+    __shared__ unsigned long long sk[KS_MAX];
+    __shared__ uint32_t sid[KS_MAX];
+    const int t = threadIdx.x;
+    int P = 2;
+    while (P < m) P <<= 1;
+    for (int i = t; i < P; i += KS_THREADS) {
+        sk[i] = i < m ? keys[i] : ~0ull;   // past every distance
+        sid[i] = i < m ? ids[i] : 0xffffffffu;
+    }
+    __syncthreads();
+    for (int k = 2; k <= P; k <<= 1)
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            for (int e = t; e < P / 2; e += KS_THREADS) {
+                const int a = ((e & ~(j - 1)) << 1) | (e & (j - 1)), b = a + j;
+                const unsigned long long ka = sk[a], kb = sk[b];
+                const uint32_t ia = sid[a], ib = sid[b];
+                const bool gt = ka > kb || (ka == kb && ia > ib);
+                if (gt == ((a & k) == 0)) {
+                    sk[a] = kb; sk[b] = ka;
+                    sid[a] = ib; sid[b] = ia;
+                }
+            }
+            __syncthreads();
+        }
+    for (int i = t; i < m && i <= kk; i += KS_THREADS) {
+        if (i > 0 && knn_close(sk[i - 1], sk[i])) continue;   // not a run start
+        int e = i + 1;
+        while (e < m && knn_close(sk[e - 1], sk[e])) ++e;
+        for (int a = i + 1; a < e; ++a) {
+            const uint32_t v = sid[a];
+            int b = a;
+            while (b > i) {
+                const uint32_t u = sid[b - 1];
+                const int c = dist_cmp(X[u], Y[u], X[v], Y[v], px, py);
+                if (c < 0 || (c == 0 && u < v)) break;
+                sid[b] = u;
+                --b;
+            }
+            sid[b] = v;
+        }
+    }
+    __syncthreads();
+    for (int i = t; i < kk; i += KS_THREADS) out[i] = sid[i];
+}
+
 int knn_select(spade_ctx *ctx, const spade_points *pts, double px, double py, int64_t k, uint32_t *out_ids,
                int64_t *n_out)
 {
@@ -650,13 +782,17 @@ int knn_select(spade_ctx *ctx, const spade_points *pts, double px, double py, in
     // circles r_j = 2^j: bins of the innermost containing circle
     DevBuf &bb = ctx->scratch[S_BLOCKRED];
     const size_t bin_bytes = 8 * (size_t)KNN_BINS;
-    if (ensure(ctx, bb, std::max<size_t>(bin_bytes, 64 + 8 * (KNN_LEVELS + 1) + 16 * (KNN_LEVELS + 1))))
+    if (ensure(ctx, bb, std::max<size_t>(bin_bytes + 8, 64 + 8 * (KNN_LEVELS + 1) + 16 * (KNN_LEVELS + 1))))
         return SPADE_E_NOMEM;
     unsigned long long *dbins = (unsigned long long *)bb.p;
-    hipLaunchKernelGGL(k_dj_zero, dim3(4), dim3(256), 0, st, (int64_t)KNN_BINS, dbins);
+    // (the word past the bins: the number of candidates taken)
+    DevBuf &bw = ctx->scratch[S_NEXTP];
+    if (ensure(ctx, bw, sizeof(int16_t) * (size_t)((n + 63) / 64))) return SPADE_E_NOMEM;
+    int16_t *wmin = (int16_t *)bw.p;
+    hipLaunchKernelGGL(k_dj_zero, dim3(5), dim3(256), 0, st, (int64_t)KNN_BINS + 1, dbins);
     if (ctx->timing) SPADE_HIP(ctx, hipEventRecord(ctx->ev[2], st));
-    hipLaunchKernelGGL(k_knn_pow2, dim3((unsigned)std::min<int64_t>((n + KNN_THREADS - 1) / KNN_THREADS, cus * 8)),
-                       dim3(KNN_THREADS), 0, st, n, pts->x, pts->y, px, py, dbins);
+    hipLaunchKernelGGL(k_knn_pow2, dim3((unsigned)std::min<int64_t>((n + KNN_THREADS * KNN_PER - 1) / (KNN_THREADS * KNN_PER), cus * 8)),
+                       dim3(KNN_THREADS), 0, st, n, pts->x, pts->y, px, py, dbins, wmin);
     SPADE_HIP(ctx, hipGetLastError());
     unsigned long long *hb = (unsigned long long *)ensure_pinned(ctx, bin_bytes + 16 * (KNN_LEVELS + 8));
     if (!hb) return set_error(ctx, SPADE_E_NOMEM, "pinned staging allocation failed");
@@ -668,10 +804,12 @@ int knn_select(spade_ctx *ctx, const spade_points *pts, double px, double py, in
     const int64_t want = std::min<int64_t>(k, total);
     int64_t cum = 0;
     double rsel = -1.0;
+    int jsel = KNN_JMAX + 1;
     for (int b = 0; b + 1 < KNN_BINS; ++b) {
         cum += (int64_t)hb[b];
         if (cum >= want) {
-            rsel = std::ldexp(1.0, KNN_JMIN + b);
+            jsel = KNN_JMIN + b;
+            rsel = std::ldexp(1.0, jsel);
             break;
         }
     }
@@ -728,21 +866,39 @@ int knn_select(spade_ctx *ctx, const spade_points *pts, double px, double py, in
         }
         rsel = C.r[sel];
     }
-    // distance selection with circle sel: the candidates, ascending ids
-    int64_t m = 0;
-    DevBuf &bc = ctx->scratch[S_VALS2];
-    if (ensure(ctx, bc, 4 * (size_t)std::max<int64_t>(cum, 1))) return SPADE_E_NOMEM;
-    int rc = select_disk(ctx, pts, px, py, rsel, (uint32_t *)bc.p, cum, &m);
-    if (rc) return rc;
-    if (m != cum) return set_error(ctx, SPADE_E_HIP, "internal: circle count and selection disagree");
-    // order by distance, exactly; the first k are the result
-    DevBuf &bk = ctx->scratch[S_KEYS], &bk2 = ctx->scratch[S_KEYS2], &bi = ctx->scratch[S_VALS];
-    if (ensure(ctx, bk, 8 * (size_t)std::max<int64_t>(m, 1)) || ensure(ctx, bk2, 8 * (size_t)std::max<int64_t>(m, 1)) ||
-        ensure(ctx, bi, 4 * (size_t)std::max<int64_t>(m, 1)))
+    // The candidates: the points of that circle, with their keys.  Few of them
+    // (one in 32 points) come from the words of points that reach the circle;
+    // more, and the circles of the bounding box, from a distance selection
+    // over all points.
+    int64_t m = cum;
+    DevBuf &bc = ctx->scratch[S_VALS2], &bk = ctx->scratch[S_KEYS];
+    if (ensure(ctx, bc, 4 * (size_t)std::max<int64_t>(cum, 1)) || ensure(ctx, bk, 8 * (size_t)std::max<int64_t>(cum, 1)))
         return SPADE_E_NOMEM;
-    hipLaunchKernelGGL(k_knn_keys, dim3(dj_grid(m)), dim3(256), 0, st, m, (const uint32_t *)bc.p, pts->x, pts->y, px,
-                       py, (unsigned long long *)bk.p);
+    if (jsel <= KNN_JMAX && cum <= n / 32) {
+        hipLaunchKernelGGL(k_knn_take, dim3((unsigned)((n + 64 * KNN_THREADS - 1) / (64 * KNN_THREADS))), dim3(KNN_THREADS),
+                           0, st, n, pts->x, pts->y, px, py, jsel, (const int16_t *)wmin, (uint32_t *)(dbins + KNN_BINS),
+                           (uint32_t)cum, (uint32_t *)bc.p, (unsigned long long *)bk.p);
+    } else {
+        int rc = select_disk(ctx, pts, px, py, rsel, (uint32_t *)bc.p, cum, &m);
+        if (rc) return rc;
+        if (m != cum) return set_error(ctx, SPADE_E_HIP, "internal: circle count and selection disagree");
+        hipLaunchKernelGGL(k_knn_keys, dim3(dj_grid(m)), dim3(256), 0, st, m, (const uint32_t *)bc.p, pts->x, pts->y, px,
+                           py, (unsigned long long *)bk.p);
+    }
     SPADE_HIP(ctx, hipGetLastError());
+    // order by distance, exactly; the first k are the result
+    const int64_t kk = std::min<int64_t>(k, m);
+    if (m <= KS_MAX) {
+        hipLaunchKernelGGL(k_knn_order, dim3(1), dim3(KS_THREADS), 0, st, (int)m, (int)kk,
+                           (const unsigned long long *)bk.p, (const uint32_t *)bc.p, pts->x, pts->y, px, py, out_ids);
+        SPADE_HIP(ctx, hipGetLastError());
+        if (ctx->timing) SPADE_HIP(ctx, hipEventRecord(ctx->ev[3], st));
+        SPADE_HIP(ctx, hipStreamSynchronize(st));
+        *n_out = kk;
+        return SPADE_OK;
+    }
+    DevBuf &bk2 = ctx->scratch[S_KEYS2], &bi = ctx->scratch[S_VALS];
+    if (ensure(ctx, bk2, 8 * (size_t)m) || ensure(ctx, bi, 4 * (size_t)m)) return SPADE_E_NOMEM;
     DevBuf &cub = ctx->scratch[S_CUBTMP];
     size_t tb = 0;
     SPADE_HIP(ctx, hipcub::DeviceRadixSort::SortPairs(nullptr, tb, (const unsigned long long *)bk.p,
@@ -752,7 +908,6 @@ int knn_select(spade_ctx *ctx, const spade_points *pts, double px, double py, in
     SPADE_HIP(ctx, hipcub::DeviceRadixSort::SortPairs(cub.p, tb, (const unsigned long long *)bk.p,
                                                       (unsigned long long *)bk2.p, (const uint32_t *)bc.p,
                                                       (uint32_t *)bi.p, (int)m, 0, 64, st));
-    const int64_t kk = std::min<int64_t>(k, m);
     hipLaunchKernelGGL(k_knn_fix, dim3(dj_grid(kk + 1)), dim3(256), 0, st, m, kk + 1,
                        (const unsigned long long *)bk2.p, (uint32_t *)bi.p, pts->x, pts->y, px, py);
     SPADE_HIP(ctx, hipGetLastError());
