@@ -186,42 +186,101 @@ __device__ __forceinline__ bool overlaps(const double4 &b, const CanvasDesc &d)
     return !d.empty && b.z >= d.bx0 && b.x < d.bx1 && b.w >= d.by0 && b.y < d.by1;
 }
 
-// Pass 1 counts overlapping chunks per canvas, pass 2 lists them (query-major).
+// The (chunk, query) pairs, in query-major order with chunk-major lists of
+// them.  A thread takes a chunk and PAIR_Q queries (blockIdx.y); FILL = false
+// counts per query and per chunk, FILL lists them (the order of a query's
+// pairs and of a chunk's list is not fixed).
+constexpr int PAIR_Q = 32;
+
 template <bool FILL>
 __global__ __launch_bounds__(256) void k_pairs(int nq, int64_t nchunk, const double4 *bb, const CanvasDesc *cds,
-                                               unsigned long long *qcount, const unsigned long long *qbase,
-                                               unsigned long long *qfill, uint32_t *pq, uint32_t *pc)
+                                               unsigned long long *qn, const unsigned long long *qbase,
+                                               unsigned int *cn, const unsigned int *cbase, uint32_t *pq, uint32_t *pc,
+                                               uint32_t *plist)
 {
-    for (int q = blockIdx.y; q < nq; q += gridDim.y) {
-        const CanvasDesc d = cds[q];
-        uint32_t mine = 0;
-        for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < nchunk;
-             c += (int64_t)gridDim.x * blockDim.x) {
-            if (!overlaps(bb[c], d)) continue;
-            if (!FILL) { ++mine; continue; }
-            const unsigned long long p = qbase[q] + atomicAdd(&qfill[q], 1ull);
-            pq[p] = (uint32_t)q;
-            pc[p] = (uint32_t)c;
+    const int lane = threadIdx.x & 63;
+    const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const double4 b = c < nchunk ? bb[c] : make_double4(INFINITY, INFINITY, -INFINITY, -INFINITY);
+    for (int q0 = blockIdx.y * PAIR_Q; q0 < nq; q0 += gridDim.y * PAIR_Q) {
+        const int q1 = min(nq, q0 + PAIR_Q);
+        uint32_t mine = 0u;   // the queries of this chunk, bit q - q0
+        for (int q = q0; q < q1; ++q) {
+            const bool on = overlaps(b, cds[q]);
+            const unsigned long long m = __ballot(on);
+            mine |= (on ? 1u : 0u) << (q - q0);
+            if (!FILL && m && lane == 0) atomicAdd(&qn[q], (unsigned long long)__popcll(m));
         }
-        if (!FILL && mine) atomicAdd(&qcount[q], (unsigned long long)mine);
+        if (!FILL) {
+            if (mine) atomicAdd(&cn[c], (unsigned int)__popc(mine));
+            continue;
+        }
+        uint32_t at = mine ? cbase[c] + atomicAdd(&cn[c], (unsigned int)__popc(mine)) : 0u;
+        for (int q = q0; q < q1; ++q) {
+            const bool on = (mine >> (q - q0)) & 1u;
+            const unsigned long long m = __ballot(on);
+            if (!m) continue;
+            unsigned long long first = 0ull;
+            if (lane == 0) first = atomicAdd(&qn[q], (unsigned long long)__popcll(m));
+            const unsigned long long p =
+                qbase[q] + (unsigned long long)__shfl((long long)first, 0, 64) + __popcll(m & ((1ull << lane) - 1ull));
+            if (on) {
+                pq[p] = (uint32_t)q;
+                pc[p] = (uint32_t)c;
+                plist[at++] = (uint32_t)p;
+            }
+        }
     }
 }
 
-// Chunk-major lists of pair ids (counting sort by chunk).
-__global__ void k_pair_chunk_count(int64_t np, const uint32_t *pc, unsigned int *ccount)
+// One workgroup: exclusive scans of the per-query and per-chunk counts
+// (qbase[nq], cbase[nchunk] = total), the first tile of every query, the
+// counts cleared to serve as cursors, and qbase copied to the host's words.
+constexpr int PS_THREADS = 1024;
+
+template <typename T, typename Get, typename Put>
+__device__ void scan_block(int64_t n, T *wsum, Get get, Put put)
 {
-    const int64_t nth = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < np; p += nth) atomicAdd(&ccount[pc[p]], 1u);
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int64_t per = (n + PS_THREADS - 1) / PS_THREADS, b = min(n, tid * per), e = min(n, b + per);
+    T mine = 0;
+#pragma unroll 4
+    for (int64_t i = b; i < e; ++i) mine += get(i);
+    T inc = mine;
+    for (int d = 1; d < 64; d <<= 1) {
+        const T t = __shfl_up(inc, d, 64);
+        if (lane >= d) inc += t;
+    }
+    if (lane == 63) wsum[wv] = inc;
+    __syncthreads();
+    T at = inc - mine;
+    for (int w = 0; w < wv; ++w) at += wsum[w];
+#pragma unroll 4
+    for (int64_t i = b; i < e; ++i) {
+        const T v = get(i);
+        put(i, at);
+        at += v;
+    }
+    if (tid == PS_THREADS - 1) put(n, at);
+    __syncthreads();
 }
 
-__global__ void k_pair_chunk_fill(int64_t np, const uint32_t *pc, const unsigned int *cbase, unsigned int *cfill,
-                                  uint32_t *plist)
+__global__ __launch_bounds__(PS_THREADS) void k_pair_scan(int nq, int64_t nchunk, unsigned long long *qn,
+                                                          unsigned long long *qbase, unsigned int *cn,
+                                                          unsigned int *cbase, int tile, uint32_t *tfirst,
+                                                          unsigned long long *hbase)
 {
-    const int64_t nth = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < np; p += nth) {
-        const uint32_t c = pc[p];
-        plist[cbase[c] + atomicAdd(&cfill[c], 1u)] = (uint32_t)p;
-    }
+    __shared__ unsigned long long ws[PS_THREADS / 64];
+    __shared__ uint32_t wt[PS_THREADS / 64];
+    scan_block<unsigned long long>(nq, ws, [&](int64_t q) { return qn[q]; }, [&](int64_t q, unsigned long long at) {
+        qbase[q] = at;
+        __hip_atomic_store(&hbase[q], at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    });
+    scan_block<uint32_t>(nq, wt, [&](int64_t q) { return (uint32_t)((qn[q] + tile - 1) / tile); },
+                         [&](int64_t q, uint32_t at) { tfirst[q] = at; });
+    scan_block<uint32_t>(nchunk, wt, [&](int64_t c) { return cn[c]; }, [&](int64_t c, uint32_t at) { cbase[c] = at; });
+    for (int64_t q = threadIdx.x; q < nq; q += PS_THREADS) qn[q] = 0ull;
+    for (int64_t c = threadIdx.x; c < nchunk; c += PS_THREADS) cn[c] = 0u;
+    __threadfence_system();
 }
 
 // Canvas q of a set as a probe view (descriptor in device memory).
@@ -470,10 +529,10 @@ __global__ __launch_bounds__(TILE_THREADS, 8) void k_hit_tiles(int nq, const uin
     int lo = 0, hi = nq - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
-        if (tfirst[mid] <= tile) lo = mid; else hi = mid - 1;
+        if (tfirst[mid] - tfirst[0] <= tile) lo = mid; else hi = mid - 1;
     }
     constexpr int WPP = BW_WORDS / PER;            // wavefronts per pair
-    const uint32_t p = (uint32_t)qbase[lo] + (tile - tfirst[lo]) * TILE_PAIRS + (uint32_t)(wv / WPP);
+    const uint32_t p = (uint32_t)qbase[lo] + (tile - (tfirst[lo] - tfirst[0])) * TILE_PAIRS + (uint32_t)(wv / WPP);
     const bool any = p < (uint32_t)qbase[lo + 1];
     uint32_t v[PER], rb[PER], on = 0u;
     for (int b = tid; b < nbins; b += TILE_THREADS) bins[b] = 0u;
@@ -544,7 +603,7 @@ __global__ __launch_bounds__(TILE_THREADS) void k_bucket_tot(int nq, const uint3
     const int lane = threadIdx.x & 63, sl = threadIdx.x >> 6;
     const int b = blockIdx.x * 64 + lane;
     for (int q = blockIdx.y; q < nq; q += gridDim.y) {
-        const uint32_t t0 = tfirst[q], t1 = tfirst[q + 1];
+        const uint32_t t0 = tfirst[q] - tfirst[0], t1 = tfirst[q + 1] - tfirst[0];
         uint32_t n = 0u;
         if (b < nbins) {
 #pragma unroll 4
@@ -607,7 +666,7 @@ __global__ __launch_bounds__(BKT_THREADS, 8) void k_bucket_bitmap(int64_t nb, co
         __syncthreads();
         // each wavefront takes every NWAVE-th tile; the runs of 64 of its
         // tiles are looked up at once, one per lane
-        const uint32_t t0 = tfirst[q], t1 = tfirst[q + 1];
+        const uint32_t t0 = tfirst[q] - tfirst[0], t1 = tfirst[q + 1] - tfirst[0];
         for (uint32_t tb = t0 + wv; tb < t1; tb += 64 * NWAVE) {
             const uint32_t tl = tb + (uint32_t)lane * NWAVE;
             uint32_t rs = 0u, rn = 0u;
@@ -685,11 +744,27 @@ __global__ __launch_bounds__(BKT_THREADS, 8) void k_bucket_bitmap(int64_t nb, co
     }
 }
 
-// Query starts from the bucket offsets: qoff[q] = offs[q * nbins], qoff[nq] = the total.
-__global__ void k_query_off(int nq, int nbins, const unsigned long long *offs, unsigned long long *qoff)
+// Query starts from the bucket offsets, into the host's words: hoff[q] =
+// offs[q * nbins], hoff[nq] = the total.
+__global__ void k_query_off(int nq, int nbins, const unsigned long long *offs, unsigned long long *hoff)
 {
     const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q <= nq) qoff[q] = offs[(size_t)q * nbins];
+    if (q <= nq) __hip_atomic_store(&hoff[q], offs[(size_t)q * nbins], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __threadfence_system();
+}
+
+// Both at once for few buckets (one workgroup): offs = exclusive scan of tot.
+constexpr int64_t BUCKET_SCAN_MAX = 32768;   // 32 per thread; a library scan takes three launches
+
+__global__ __launch_bounds__(PS_THREADS) void k_bucket_scan(int nq, int nbins, const unsigned long long *tot,
+                                                            unsigned long long *offs, unsigned long long *hoff)
+{
+    __shared__ unsigned long long ws[PS_THREADS / 64];
+    scan_block<unsigned long long>((int64_t)nq * nbins, ws, [&](int64_t i) { return tot[i]; },
+                                   [&](int64_t i, unsigned long long at) { offs[i] = at; });
+    for (int q = threadIdx.x; q <= nq; q += PS_THREADS)
+        __hip_atomic_store(&hoff[q], offs[(size_t)q * nbins], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __threadfence_system();
 }
 
 // ------------------------------------------------------------ batch join pairs
@@ -1054,6 +1129,7 @@ struct Pairs {
     uint32_t *pq = nullptr, *pc = nullptr, *plist = nullptr;
     unsigned int *cbase = nullptr;
     unsigned long long *qbase = nullptr;
+    uint32_t *tfirst = nullptr;    // first tile of every query (tiles of TILE_PAIRS pairs)
     std::vector<int64_t> qfirst;   // host: first pair of every query, then the total
 };
 
@@ -1063,31 +1139,27 @@ static int make_pairs(spade_ctx *ctx, const spade_canvas *set, const spade_table
     const int nq = set->nc;
     const int64_t nchunk = t->nchunk;
     DevBuf &bq = ctx->scratch[S_KEYS];
-    if (ensure(ctx, bq, sizeof(unsigned long long) * (3 * (size_t)nq + 3) + sizeof(unsigned int) * 2 * ((size_t)nchunk + 2)))
-        return SPADE_E_NOMEM;
-    unsigned long long *qcount = (unsigned long long *)bq.p;
-    unsigned long long *qbase = qcount + (nq + 1);
-    unsigned long long *qfill = qbase + (nq + 1);
-    unsigned int *ccount = (unsigned int *)(qfill + (nq + 1));
-    unsigned int *cbase = ccount + (nchunk + 1);
-    hipLaunchKernelGGL(k_zero64, dim3(grid_of(3 * nq + 3, 1024)), dim3(256), 0, st, (int64_t)(3 * nq + 3), qcount);
-    hipLaunchKernelGGL(k_zero32, dim3(grid_of(2 * nchunk + 2, 4096)), dim3(256), 0, st, (int64_t)(2 * nchunk + 2), ccount);
+    // 8-byte words: qn [nq] | qbase [nq + 1]; 4-byte: cn [nchunk] | cbase [nchunk + 1] | tfirst [nq + 1]
+    const int64_t words = 2 * (int64_t)nq + 1;
+    if (ensure(ctx, bq, 8 * (size_t)words + 4 * (size_t)(2 * nchunk + 1 + nq + 1))) return SPADE_E_NOMEM;
+    unsigned long long *qn = (unsigned long long *)bq.p, *qbase = qn + nq;
+    unsigned int *cn = (unsigned int *)(qn + words), *cbase = cn + nchunk;
+    P.tfirst = cbase + nchunk + 1;
+    unsigned long long *h = (unsigned long long *)ensure_pinned(ctx, 8 * (size_t)(nq + 1));
+    if (!h) return set_error(ctx, SPADE_E_NOMEM, "pinned staging allocation failed");
+    // (the counters, and the words between them)
+    hipLaunchKernelGGL(k_zero32, dim3(grid_of(2 * words + nchunk, 4096)), dim3(256), 0, st, 2 * words + nchunk,
+                       (unsigned int *)bq.p);
     SPADE_HIP(ctx, hipGetLastError());
     const CanvasDesc *cds = (const CanvasDesc *)set->dcds.p;
     const double4 *bb = (const double4 *)t->chunk_bb.p;
-    dim3 g((unsigned)std::max<int64_t>(1, std::min<int64_t>((nchunk + 255) / 256, 64)), (unsigned)std::min(nq, 32768));
-    if (nchunk > 0) {
-        hipLaunchKernelGGL(k_pairs<false>, g, dim3(256), 0, st, nq, nchunk, bb, cds, qcount, nullptr, nullptr, nullptr, nullptr);
-        SPADE_HIP(ctx, hipGetLastError());
-    }
-    DevBuf &cub = ctx->scratch[S_CUBTMP];
-    size_t tb = 0;
-    SPADE_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(nullptr, tb, qcount, qbase, nq + 1, st));
-    if (ensure(ctx, cub, tb)) return SPADE_E_NOMEM;
-    SPADE_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(cub.p, tb, qcount, qbase, nq + 1, st));
-    unsigned long long *h = (unsigned long long *)ensure_pinned(ctx, 8 * (size_t)(nq + 1));
-    if (!h) return set_error(ctx, SPADE_E_NOMEM, "pinned staging allocation failed");
-    SPADE_HIP(ctx, hipMemcpyAsync(h, qbase, 8 * (size_t)(nq + 1), hipMemcpyDeviceToHost, st));
+    const dim3 g((unsigned)std::max<int64_t>(1, (nchunk + 255) / 256), (unsigned)std::min((nq + PAIR_Q - 1) / PAIR_Q, 32768));
+    if (nchunk > 0)
+        hipLaunchKernelGGL(k_pairs<false>, g, dim3(256), 0, st, nq, nchunk, bb, cds, qn, nullptr, cn, nullptr, nullptr,
+                           nullptr, nullptr);
+    hipLaunchKernelGGL(k_pair_scan, dim3(1), dim3(PS_THREADS), 0, st, nq, nchunk, qn, qbase, cn, cbase, TILE_PAIRS, P.tfirst,
+                       h);
+    SPADE_HIP(ctx, hipGetLastError());
     SPADE_HIP(ctx, hipStreamSynchronize(st));
     P.qfirst.assign(h, h + nq + 1);
     const int64_t np = P.qfirst[(size_t)nq];
@@ -1102,17 +1174,8 @@ static int make_pairs(spade_ctx *ctx, const spade_canvas *set, const spade_table
     P.cbase = cbase;
     P.qbase = qbase;
     if (np > 0) {
-        hipLaunchKernelGGL(k_pairs<true>, g, dim3(256), 0, st, nq, nchunk, bb, cds, nullptr, qbase, qfill, P.pq, P.pc);
-        hipLaunchKernelGGL(k_pair_chunk_count, dim3(grid_of(np)), dim3(256), 0, st, np, P.pc, ccount);
-        SPADE_HIP(ctx, hipGetLastError());
-    }
-    tb = 0;
-    SPADE_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(nullptr, tb, ccount, cbase, (int)(nchunk + 1), st));
-    if (ensure(ctx, cub, tb)) return SPADE_E_NOMEM;
-    SPADE_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(cub.p, tb, ccount, cbase, (int)(nchunk + 1), st));
-    if (np > 0) {
-        hipLaunchKernelGGL(k_zero32, dim3(grid_of(nchunk + 1, 4096)), dim3(256), 0, st, nchunk + 1, ccount);
-        hipLaunchKernelGGL(k_pair_chunk_fill, dim3(grid_of(np)), dim3(256), 0, st, np, P.pc, cbase, ccount, P.plist);
+        hipLaunchKernelGGL(k_pairs<true>, g, dim3(256), 0, st, nq, nchunk, bb, cds, qn, (const unsigned long long *)qbase, cn,
+                           (const unsigned int *)cbase, P.pq, P.pc, P.plist);
         SPADE_HIP(ctx, hipGetLastError());
     }
     return SPADE_OK;
@@ -1333,7 +1396,6 @@ int spade_batch_select(spade_ctx *ctx, const spade_canvas *set, const spade_tabl
     DevBuf &bh = ctx->scratch[S_KEYS2], &bo = ctx->scratch[S_ENTF], &bs = ctx->scratch[S_LOOKBACK];
     const std::vector<int64_t> &hq = P.qfirst;   // first pair of every query
     std::vector<int> gq;                         // first query of every group, then nq
-    std::vector<uint32_t> tfirst((size_t)nq + 1);   // first tile of every query, in its group
     int64_t pmost, tmost;                        // most pairs and tiles of a group
     int gmost;                                   // most queries of one
     auto tiles_of = [&](int q) { return (hq[(size_t)q + 1] - hq[(size_t)q] + TILE_PAIRS - 1) / TILE_PAIRS; };
@@ -1358,7 +1420,7 @@ int spade_batch_select(spade_ctx *ctx, const spade_canvas *set, const spade_tabl
     auto room = [&]() {
         return ensure(ctx, bh, PAIR_BYTES * (size_t)pmost) ||
                (cap > 0 && ensure(ctx, bo, sizeof(uint32_t) * TILE_IDS * (size_t)tmost)) ||
-               ensure(ctx, bs, sizeof(uint16_t) * (size_t)(nbins + 1) * (size_t)tmost + 4 * ((size_t)gmost + 1));
+               ensure(ctx, bs, sizeof(uint16_t) * (size_t)(nbins + 1) * (size_t)tmost);
     };
     group_by(hits_max);
     if (room()) {
@@ -1367,16 +1429,15 @@ int spade_batch_select(spade_ctx *ctx, const spade_canvas *set, const spade_tabl
         if (room()) return SPADE_E_NOMEM;
     }
     unsigned long long *hits = (unsigned long long *)bh.p;
-    uint32_t *keys = cap > 0 ? (uint32_t *)bo.p : nullptr, *dtf = (uint32_t *)bs.p;
-    uint16_t *starts = (uint16_t *)(dtf + gmost + 1);
-    // bc: bucket counts [nbmax + 1] | offsets [nbmax + 1] | query offsets [gmost + 1]
+    uint32_t *keys = cap > 0 ? (uint32_t *)bo.p : nullptr;
+    uint16_t *starts = (uint16_t *)bs.p;
+    // bc: bucket counts [nbmax + 1] | offsets [nbmax + 1]
     const size_t nbmax = (size_t)gmost * nbins;
     DevBuf &bc = ctx->scratch[S_VALS2], &cub = ctx->scratch[S_CUBTMP];
-    if (ensure(ctx, bc, sizeof(unsigned long long) * (2 * (nbmax + 1) + (size_t)gmost + 1))) return SPADE_E_NOMEM;
-    unsigned long long *tot = (unsigned long long *)bc.p, *offs = tot + (nbmax + 1), *qoff = offs + (nbmax + 1);
-    unsigned long long *h = (unsigned long long *)ensure_pinned(ctx, 12 * ((size_t)gmost + 1));
+    if (ensure(ctx, bc, sizeof(unsigned long long) * 2 * (nbmax + 1))) return SPADE_E_NOMEM;
+    unsigned long long *tot = (unsigned long long *)bc.p, *offs = tot + (nbmax + 1);
+    unsigned long long *h = (unsigned long long *)ensure_pinned(ctx, 8 * ((size_t)gmost + 1));
     if (!h) return set_error(ctx, SPADE_E_NOMEM, "pinned staging allocation failed");
-    uint32_t *htf = (uint32_t *)(h + gmost + 1);
     // the bitmap in whole blocks of 64 words
     const size_t bm_lds = sizeof(uint32_t) * 64 * (size_t)((std::max(1, (1 << L) >> 5) + 63) / 64);
     const size_t tile_lds = sizeof(uint32_t) * ((size_t)((nbins + 127) & ~63) + TILE_IDS);
@@ -1391,14 +1452,13 @@ int spade_batch_select(spade_ctx *ctx, const spade_canvas *set, const spade_tabl
         const int q0 = gq[k], q1 = gq[k + 1], ng = q1 - q0;
         const uint32_t p0 = (uint32_t)hq[(size_t)q0], p1 = (uint32_t)hq[(size_t)q1];
         const int64_t nb = (int64_t)ng * nbins;
-        htf[0] = 0;
-        for (int q = 0; q < ng; ++q) htf[q + 1] = htf[q] + (uint32_t)tiles_of(q0 + q);
-        const uint32_t ntile = htf[ng];
+        uint32_t ntile = 0;
+        for (int q = q0; q < q1; ++q) ntile += (uint32_t)tiles_of(q);
+        const uint32_t *dtf = P.tfirst + q0;
         if (ntile == 0) {
             for (int q = q0; q < q1; ++q) out_off[q + 1] = out_off[q0];
             continue;
         }
-        SPADE_HIP(ctx, hipMemcpyAsync(dtf, htf, 4 * ((size_t)ng + 1), hipMemcpyHostToDevice, st));
         const int64_t wgs = t->nchunk * BW_TASKS / (BT_THREADS / 64);
         hipLaunchKernelGGL(k_batch_hits, dim3((unsigned)std::min<int64_t>(wgs, 1 << 20)), dim3(BT_THREADS), 0, st, S,
                            t->nfin, t->nchunk, (const double *)t->x.p, (const double *)t->y.p, P.cbase, P.plist, P.pq,
@@ -1410,13 +1470,18 @@ int spade_batch_select(spade_ctx *ctx, const spade_canvas *set, const spade_tabl
                            nbins, keys, starts);
         hipLaunchKernelGGL(k_bucket_tot, dim3((nbins + 63) / 64, std::min(ng, 32768)), dim3(TILE_THREADS), 0, st, ng,
                            (const uint32_t *)dtf, (const uint16_t *)starts, nbins, tot);
-        hipLaunchKernelGGL(k_zero64, dim3(1), dim3(64), 0, st, (int64_t)1, tot + nb);
         SPADE_HIP(ctx, hipGetLastError());
-        size_t tb = 0;
-        SPADE_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(nullptr, tb, tot, offs, (int)(nb + 1), st));
-        if (ensure(ctx, cub, tb)) return SPADE_E_NOMEM;
-        SPADE_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(cub.p, tb, tot, offs, (int)(nb + 1), st));
-        hipLaunchKernelGGL(k_query_off, dim3((ng + 256) / 256), dim3(256), 0, st, ng, nbins, offs, qoff);
+        if (nb <= BUCKET_SCAN_MAX) {
+            hipLaunchKernelGGL(k_bucket_scan, dim3(1), dim3(PS_THREADS), 0, st, ng, nbins, (const unsigned long long *)tot,
+                               offs, h);
+        } else {
+            hipLaunchKernelGGL(k_zero64, dim3(1), dim3(64), 0, st, (int64_t)1, tot + nb);
+            size_t tb = 0;
+            SPADE_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(nullptr, tb, tot, offs, (int)(nb + 1), st));
+            if (ensure(ctx, cub, tb)) return SPADE_E_NOMEM;
+            SPADE_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(cub.p, tb, tot, offs, (int)(nb + 1), st));
+            hipLaunchKernelGGL(k_query_off, dim3((ng + 256) / 256), dim3(256), 0, st, ng, nbins, offs, h);
+        }
         // ids beyond cap are not written (a buffer that is too small still
         // receives the first cap ids)
         const int64_t base = out_off[q0];   // ids of the groups before
@@ -1425,7 +1490,6 @@ int spade_batch_select(spade_ctx *ctx, const spade_canvas *set, const spade_tabl
                                st, nb, offs, (const uint32_t *)dtf, (const uint16_t *)starts, (const uint32_t *)keys, L,
                                nbins, out_ids + base, cap - base);
         SPADE_HIP(ctx, hipGetLastError());
-        SPADE_HIP(ctx, hipMemcpyAsync(h, qoff, sizeof(unsigned long long) * (size_t)(ng + 1), hipMemcpyDeviceToHost, st));
         SPADE_HIP(ctx, hipStreamSynchronize(st));
         for (int q = q0; q <= q1; ++q) out_off[q] = base + (int64_t)h[q - q0];
     }

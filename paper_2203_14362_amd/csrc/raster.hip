@@ -93,13 +93,20 @@ constexpr int GSTRIDE = 16;                        // words between counters
 constexpr int NGCTR = NSHARD * 4 * GSTRIDE;        // counter block, 8 KB
 __host__ __device__ inline int gctr_at(int shard, int c) { return (shard * 4 + c) * GSTRIDE; }
 
-__global__ void k_init(unsigned *errflags, unsigned long long *bb, int64_t nbb, unsigned long long *gctr)
+// With dcd, also the row counters rcount[0, nrc) and the one canvas's
+// descriptor, whose size the caller's bounding box already gave (a launch and
+// a copy fewer before the edges).
+__global__ void k_init(unsigned *errflags, unsigned long long *bb, int64_t nbb, unsigned long long *gctr,
+                       uint32_t *rcount, int64_t nrc, CanvasDesc desc, CanvasDesc *dcd)
 {
     const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t nth = (int64_t)gridDim.x * blockDim.x;
     if (tid == 0) *errflags = 0u;
     for (int64_t i = tid; i < NGCTR; i += nth) gctr[i] = 0ull;
     for (int64_t i = tid; i < nbb; i += nth) bb[i] = ~0ull;
+    if (!dcd) return;
+    if (tid == 0) *dcd = desc;
+    for (int64_t i = tid; i < nrc; i += nth) rcount[i] = 0u;
 }
 
 __global__ __launch_bounds__(256) void k_validate(int64_t M, int64_t R, const int64_t *pro,
@@ -425,7 +432,7 @@ __device__ long long block_excl_sum(long long v, long long *wtot)
 __global__ __launch_bounds__(SCAN_THREADS) void k_rowscan(int64_t Htot, const uint32_t *rcount, int rstride,
                                                           int capA, int capB, uint32_t *row_off,
                                                           uint32_t *cursor, uint32_t *longrows,
-                                                          unsigned long long *info)
+                                                          unsigned long long *info, unsigned long long *hinfo)
 {
     __shared__ long long wtot[SCAN_THREADS / 64];
     __shared__ unsigned s_nb, s_nc;
@@ -481,10 +488,13 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_rowscan(int64_t Htot, const ui
     __syncthreads();
     if (tid == SCAN_THREADS - 1) {
         row_off[Htot] = (uint32_t)off;
-        info[0] = (unsigned long long)off;
-        info[1] = (unsigned long long)s_max;
-        info[2] = s_nb;
-        info[3] = s_nc;
+        // for the later kernels, and into the host's pinned words (no copy)
+        const unsigned long long v[4] = {(unsigned long long)off, (unsigned long long)s_max, s_nb, s_nc};
+        for (int k = 0; k < 4; ++k) {
+            info[k] = v[k];
+            __hip_atomic_store(&hinfo[k], v[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+        __threadfence_system();
     }
 }
 
@@ -1827,15 +1837,19 @@ int build_set(spade_ctx *ctx, const spade_polys *polys, int nc, const int64_t *p
     // cache-line-aligned block)
     unsigned *d_err = (unsigned *)(((uintptr_t)(d_bb + 4 * (size_t)nc) + 127) & ~(uintptr_t)127);
     unsigned long long *gctr = (unsigned long long *)((char *)d_err + CTR_HEAD);
-    hipLaunchKernelGGL(k_init, dim3((unsigned)std::min<int64_t>((4 * (int64_t)nc + 255) / 256 + 1, 1024)), dim3(256), 0,
-                       st, d_err, d_bb, 4 * (int64_t)nc, gctr);
-    SPADE_HIP(ctx, hipGetLastError());
-    if (M > 0 || R > 0 || V > 0) {
-        hipLaunchKernelGGL(k_validate, dim3(RED_BLOCKS), dim3(256), 0, st, M, R, polys->poly_ring_off,
-                           polys->ring_vtx_off, V, polys->vx, polys->vy, (int32_t *)rp.p,
-                           (double *)br.p, d_err, nc == 1 ? d_bb : nullptr);
-        SPADE_HIP(ctx, hipGetLastError());
-    }
+    // flags, box keys and counters, then the validation; with the caller's box
+    // they are queued once the canvas is sized
+    auto launch_validate = [&](uint32_t *rc0, int64_t nrc, CanvasDesc *dcd0) -> hipError_t {
+        const int64_t items = std::max<int64_t>(4 * (int64_t)nc, nrc);
+        hipLaunchKernelGGL(k_init, dim3((unsigned)std::min<int64_t>((items + 255) / 256 + 1, 1024)), dim3(256), 0, st, d_err,
+                           d_bb, 4 * (int64_t)nc, gctr, rc0, nrc, dcd0 ? cv->descs[0] : CanvasDesc{}, dcd0);
+        if (M > 0 || R > 0 || V > 0)
+            hipLaunchKernelGGL(k_validate, dim3(RED_BLOCKS), dim3(256), 0, st, M, R, polys->poly_ring_off,
+                               polys->ring_vtx_off, V, polys->vx, polys->vy, (int32_t *)rp.p,
+                               (double *)br.p, d_err, nc == 1 ? d_bb : nullptr);
+        return hipGetLastError();
+    };
+    if (!hinted) SPADE_HIP(ctx, launch_validate(nullptr, 0, nullptr));
     // Pinned staging: error flags, canvas descriptors, bounding-box keys.
     // The bounding boxes are computed before the validation verdict is read
     // (one synchronisation for both): the box kernel only reads within the
@@ -1953,8 +1967,10 @@ int build_set(spade_ctx *ctx, const spade_polys *polys, int nc, const int64_t *p
         maxW = std::max(maxW, W);
     }
     if (Htot > 0x7fffffffLL) return set_error(ctx, SPADE_E_UNSUPPORTED, "canvas set has too many rows");
-    std::memcpy(hcd, cds.data(), sizeof(CanvasDesc) * (size_t)nc);
-    SPADE_HIP(ctx, hipMemcpyAsync(dcd.p, hcd, sizeof(CanvasDesc) * (size_t)nc, hipMemcpyHostToDevice, st));
+    if (!hinted) {
+        std::memcpy(hcd, cds.data(), sizeof(CanvasDesc) * (size_t)nc);
+        SPADE_HIP(ctx, hipMemcpyAsync(dcd.p, hcd, sizeof(CanvasDesc) * (size_t)nc, hipMemcpyHostToDevice, st));
+    }
     const CanvasDesc *d_cds = (const CanvasDesc *)dcd.p;
 
     if (ensure(ctx, cv->cells, sizeof(uint32_t) * (size_t)cells_tot) ||
@@ -1963,6 +1979,7 @@ int build_set(spade_ctx *ctx, const spade_polys *polys, int nc, const int64_t *p
         return SPADE_E_NOMEM;
     cv->n_edges = V;
     if (!any) {
+        if (hinted) SPADE_HIP(ctx, launch_validate(nullptr, 0, (CanvasDesc *)dcd.p));
         SPADE_HIP(ctx, hipMemsetAsync(cv->cells.p, 0, sizeof(uint32_t) * (size_t)cells_tot, st));
         SPADE_HIP(ctx, hipMemsetAsync(cv->coarse.p, 0, sizeof(uint16_t) * ((size_t)coarse_tot + 2), st));
         if (ensure(ctx, cv->cands, 2 * sizeof(Cand)) || ensure(ctx, cv->ledges, sizeof(Edge)) ||
@@ -2028,18 +2045,21 @@ int build_set(spade_ctx *ctx, const spade_polys *polys, int nc, const int64_t *p
     // launch of their own with a stage for the longest
     const int capB = std::max(cap, 640);
 
-    hipLaunchKernelGGL(k_zero_u32, dim3(grid_for((H + 1) * rstride, 1024)), dim3(256), 0, st, (H + 1) * rstride, rcount);
+    if (hinted)
+        SPADE_HIP(ctx, launch_validate(rcount, (H + 1) * rstride, (CanvasDesc *)dcd.p));
+    else
+        hipLaunchKernelGGL(k_zero_u32, dim3(grid_for((H + 1) * rstride, 1024)), dim3(256), 0, st, (H + 1) * rstride, rcount);
     hipLaunchKernelGGL(k_edges, dim3(grid_for(2 * V)), dim3(256), 0, st, R, polys->ring_vtx_off, V,
                        polys->vx, polys->vy, (const int32_t *)rp.p, d_cds, nc, (Edge *)cv->edges.p, epoly,
                        erow0, nrows, rcount, rstride, hinted ? 1 : 0, d_err, (const unsigned long long *)d_bb,
                        hinted ? polys->bbox[0] : 0.0, hinted ? polys->bbox[1] : 0.0,
                        hinted ? polys->bbox[2] : 0.0, hinted ? polys->bbox[3] : 0.0);
     SPADE_HIP(ctx, hipGetLastError());
+    volatile uint64_t *hT = (volatile uint64_t *)ensure_pinned(ctx, 64);
+    if (!hT) return set_error(ctx, SPADE_E_NOMEM, "pinned staging allocation failed");
     hipLaunchKernelGGL(k_rowscan, dim3(1), dim3(SCAN_THREADS), 0, st, H, (const uint32_t *)rcount, rstride, cap, capB,
-                       row_off, cursor, longrows, rinfo);
+                       row_off, cursor, longrows, rinfo, (unsigned long long *)hT);
     SPADE_HIP(ctx, hipGetLastError());
-    uint64_t *hT = (uint64_t *)ensure_pinned(ctx, 64);
-    SPADE_HIP(ctx, hipMemcpyAsync(hT, rinfo, 4 * sizeof(uint64_t), hipMemcpyDeviceToHost, st));
     if (!ctx->evinfo) SPADE_HIP(ctx, hipEventCreateWithFlags(&ctx->evinfo, hipEventDisableTiming));
     SPADE_HIP(ctx, hipEventRecord(ctx->evinfo, st));
 
