@@ -232,19 +232,29 @@ __global__ __launch_bounds__(256) void k_pairs(int nq, int64_t nchunk, const dou
     }
 }
 
-// One workgroup: exclusive scans of the per-query and per-chunk counts
-// (qbase[nq], cbase[nchunk] = total), the first tile of every query, the
-// counts cleared to serve as cursors, and qbase copied to the host's words.
+// Exclusive scans of the per-query counts and the first tile of every query
+// (workgroup 0) and of the per-chunk counts (workgroup 1) (qbase[nq],
+// cbase[nchunk] = total); the counts cleared to serve as cursors, and qbase
+// copied to the host's words.
 constexpr int PS_THREADS = 1024;
+constexpr int PS_REG = 12;
 
 template <typename T, typename Get, typename Put>
 __device__ void scan_block(int64_t n, T *wsum, Get get, Put put)
 {
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int64_t per = (n + PS_THREADS - 1) / PS_THREADS, b = min(n, tid * per), e = min(n, b + per);
-    T mine = 0;
-#pragma unroll 4
-    for (int64_t i = b; i < e; ++i) mine += get(i);
+    // PS_REG values in flight, kept for the second pass when they are all
+    T v[PS_REG], mine = 0;
+    auto fetch = [&](int64_t i) {
+#pragma unroll
+        for (int k = 0; k < PS_REG; ++k) v[k] = i + k < e ? get(i + k) : (T)0;
+    };
+    for (int64_t i = b; i < e; i += PS_REG) {
+        fetch(i);
+#pragma unroll
+        for (int k = 0; k < PS_REG; ++k) mine += v[k];
+    }
     T inc = mine;
     for (int d = 1; d < 64; d <<= 1) {
         const T t = __shfl_up(inc, d, 64);
@@ -254,11 +264,14 @@ __device__ void scan_block(int64_t n, T *wsum, Get get, Put put)
     __syncthreads();
     T at = inc - mine;
     for (int w = 0; w < wv; ++w) at += wsum[w];
-#pragma unroll 4
-    for (int64_t i = b; i < e; ++i) {
-        const T v = get(i);
-        put(i, at);
-        at += v;
+    for (int64_t i = b; i < e; i += PS_REG) {
+        if (per > PS_REG) fetch(i);
+#pragma unroll
+        for (int k = 0; k < PS_REG; ++k)
+            if (i + k < e) {
+                put(i + k, at);
+                at += v[k];
+            }
     }
     if (tid == PS_THREADS - 1) put(n, at);
     __syncthreads();
@@ -271,15 +284,18 @@ __global__ __launch_bounds__(PS_THREADS) void k_pair_scan(int nq, int64_t nchunk
 {
     __shared__ unsigned long long ws[PS_THREADS / 64];
     __shared__ uint32_t wt[PS_THREADS / 64];
-    scan_block<unsigned long long>(nq, ws, [&](int64_t q) { return qn[q]; }, [&](int64_t q, unsigned long long at) {
-        qbase[q] = at;
-        __hip_atomic_store(&hbase[q], at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    });
-    scan_block<uint32_t>(nq, wt, [&](int64_t q) { return (uint32_t)((qn[q] + tile - 1) / tile); },
-                         [&](int64_t q, uint32_t at) { tfirst[q] = at; });
-    scan_block<uint32_t>(nchunk, wt, [&](int64_t c) { return cn[c]; }, [&](int64_t c, uint32_t at) { cbase[c] = at; });
-    for (int64_t q = threadIdx.x; q < nq; q += PS_THREADS) qn[q] = 0ull;
-    for (int64_t c = threadIdx.x; c < nchunk; c += PS_THREADS) cn[c] = 0u;
+    if (blockIdx.x == 0) {
+        scan_block<unsigned long long>(nq, ws, [&](int64_t q) { return qn[q]; }, [&](int64_t q, unsigned long long at) {
+            qbase[q] = at;
+            __hip_atomic_store(&hbase[q], at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        });
+        scan_block<uint32_t>(nq, wt, [&](int64_t q) { return (uint32_t)((qn[q] + tile - 1) / tile); },
+                             [&](int64_t q, uint32_t at) { tfirst[q] = at; });
+        for (int64_t q = threadIdx.x; q < nq; q += PS_THREADS) qn[q] = 0ull;
+    } else {
+        scan_block<uint32_t>(nchunk, wt, [&](int64_t c) { return cn[c]; }, [&](int64_t c, uint32_t at) { cbase[c] = at; });
+        for (int64_t c = threadIdx.x; c < nchunk; c += PS_THREADS) cn[c] = 0u;
+    }
     __threadfence_system();
 }
 
@@ -424,20 +440,24 @@ __device__ __forceinline__ uint32_t task_word(const CanvasView &v, const double4
 // p < p1.  Bound by the latency of its gathers: 3.0 ms for 130,574 (chunk,
 // query) pairs, 35 us for 805.  With 16 points per thread of a 256-thread
 // workgroup (158 registers, 2.2 wavefronts per SIMD, two barriers per pair)
-// it took 5.0 ms and 158 us.
+// it took 5.0 ms and 158 us.  BY_PAIR: a task is one pair's words instead of a
+// chunk's, for few pairs (the launch over all chunks mostly finds them
+// without any: 805 pairs of 12,208 chunks 34 us, 25 us by pair).
+template <bool BY_PAIR>
 __global__ __launch_bounds__(BT_THREADS) void k_batch_hits(SetArgs S, int64_t nfin, int64_t nchunk, const double *X,
                                                            const double *Y, const unsigned int *cbase,
-                                                           const uint32_t *plist, const uint32_t *pq, uint32_t p0,
-                                                           uint32_t p1, unsigned long long *hits)
+                                                           const uint32_t *plist, const uint32_t *pq,
+                                                           const uint32_t *pc, uint32_t p0, uint32_t p1,
+                                                           unsigned long long *hits)
 {
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int64_t ntask = nchunk * BW_TASKS;
+    const int64_t ntask = (BY_PAIR ? (int64_t)(p1 - p0) : nchunk) * BW_TASKS;
     for (int64_t task = (int64_t)blockIdx.x * (BT_THREADS / 64) + wv; task < ntask;
          task += (int64_t)gridDim.x * (BT_THREADS / 64)) {
-        const int64_t c = task / BW_TASKS;
+        const int64_t c = BY_PAIR ? (int64_t)pc[p0 + task / BW_TASKS] : task / BW_TASKS;
         const int part = (int)(task % BW_TASKS);
-        const uint32_t t0 = cbase[c], t1 = cbase[c + 1];
+        const uint32_t t0 = BY_PAIR ? 0u : cbase[c], t1 = BY_PAIR ? 1u : cbase[c + 1];
         if (t0 == t1) continue;
         double xs[BW_PTS], ys[BW_PTS];
         unsigned long long valid[BW_PTS];
@@ -450,7 +470,7 @@ __global__ __launch_bounds__(BT_THREADS) void k_batch_hits(SetArgs S, int64_t nf
         }
         const double4 cb = task_box<BW_PTS>(xs, ys);
         for (uint32_t t = t0; t < t1; ++t) {
-            const uint32_t p = plist[t];
+            const uint32_t p = BY_PAIR ? p0 + (uint32_t)(task / BW_TASKS) : plist[t];
             if (p < p0 || p >= p1) continue;
             const CanvasDesc d = S.cds[pq[p]];
             const CanvasView v = set_view(d, S.cells, S.coarse, S.cands, S.ledges, S.pspan);
@@ -1157,7 +1177,7 @@ static int make_pairs(spade_ctx *ctx, const spade_canvas *set, const spade_table
     if (nchunk > 0)
         hipLaunchKernelGGL(k_pairs<false>, g, dim3(256), 0, st, nq, nchunk, bb, cds, qn, nullptr, cn, nullptr, nullptr,
                            nullptr, nullptr);
-    hipLaunchKernelGGL(k_pair_scan, dim3(1), dim3(PS_THREADS), 0, st, nq, nchunk, qn, qbase, cn, cbase, TILE_PAIRS, P.tfirst,
+    hipLaunchKernelGGL(k_pair_scan, dim3(2), dim3(PS_THREADS), 0, st, nq, nchunk, qn, qbase, cn, cbase, TILE_PAIRS, P.tfirst,
                        h);
     SPADE_HIP(ctx, hipGetLastError());
     SPADE_HIP(ctx, hipStreamSynchronize(st));
@@ -1459,10 +1479,15 @@ int spade_batch_select(spade_ctx *ctx, const spade_canvas *set, const spade_tabl
             for (int q = q0; q < q1; ++q) out_off[q + 1] = out_off[q0];
             continue;
         }
-        const int64_t wgs = t->nchunk * BW_TASKS / (BT_THREADS / 64);
-        hipLaunchKernelGGL(k_batch_hits, dim3((unsigned)std::min<int64_t>(wgs, 1 << 20)), dim3(BT_THREADS), 0, st, S,
-                           t->nfin, t->nchunk, (const double *)t->x.p, (const double *)t->y.p, P.cbase, P.plist, P.pq,
-                           p0, p1, hits);
+        const bool by_pair = (int64_t)(p1 - p0) * 2 <= t->nchunk;
+        const int64_t wgs = (by_pair ? (int64_t)(p1 - p0) : t->nchunk) * BW_TASKS / (BT_THREADS / 64);
+        auto probe = [&](auto kern) {
+            hipLaunchKernelGGL(kern, dim3((unsigned)std::min<int64_t>(wgs, 1 << 20)), dim3(BT_THREADS), 0, st, S, t->nfin,
+                               t->nchunk, (const double *)t->x.p, (const double *)t->y.p, (const unsigned int *)P.cbase,
+                               (const uint32_t *)P.plist, (const uint32_t *)P.pq, (const uint32_t *)P.pc, p0, p1, hits);
+        };
+        if (by_pair) probe(k_batch_hits<true>);
+        else probe(k_batch_hits<false>);
         SPADE_HIP(ctx, hipGetLastError());
         if (ctx->timing && k == 0) SPADE_HIP(ctx, hipEventRecord(ctx->ev[3], st));
         hipLaunchKernelGGL(k_hit_tiles, dim3(ntile), dim3(TILE_THREADS), tile_lds, st, ng, (const uint32_t *)dtf,
