@@ -18,9 +18,11 @@
 //            workgroup copies the counts out and clears the accumulator.
 //            More polygons than that histogram holds: every point's polygon
 //            goes to a 16-bit label that k_label_hist counts.
-//   k_emit   ordered output (point ids, or (point, polygon) pairs ascending):
+//   k_emit*  ordered output (point ids, or (point, polygon) pairs ascending):
 //            the paper's two-step Map (a count pass per wavefront segment of
-//            points, a scan of the segment counts, a write pass).
+//            points that keeps every point's result, a scan of the segment
+//            counts, a write pass from the results; points in several
+//            polygons are probed again).
 #include "common.h"
 #include "exact.h"
 #include "lookup.h"
@@ -44,6 +46,7 @@ constexpr int EMIT_WDRAIN = 8;            // words of the write pass sharing one
 constexpr size_t LDS_TOTAL = 160 * 1024;
 constexpr size_t LDS_RESERVE = 2048;      // static LDS of the kernels
 constexpr size_t QUEUE_BYTES = (size_t)(CNT_THREADS / 64) * QCAP * 20;
+constexpr size_t EMIT_INDEX_BYTES = (size_t)(EMIT_THREADS / 64) * QCAP * sizeof(uint16_t);   // beside the queue, in the reserve
 
 size_t coarse_lds_budget(int64_t M)
 {
@@ -509,7 +512,8 @@ int probe_count_noalloc(spade_ctx *ctx, const spade_canvas *cv, const spade_poin
 
 // ------------------------------------------------------------ ordered emit
 
-// Write pass.  Every wavefront owns segments of EMIT_SEG consecutive points
+// Write pass that probes again, for canvases in which the count pass met a
+// point in several polygons.  Every wavefront owns segments of EMIT_SEG consecutive points
 // (grid-stride over segments), EMIT_WGROUP points per lane in flight at a
 // time.  The boundary points of a group are queued in LDS and tested a full
 // wavefront at a time (as in k_count); each lane then takes the results of
@@ -517,16 +521,13 @@ int probe_count_noalloc(spade_ctx *ctx, const spade_canvas *cv, const spade_poin
 // written in point order (ascending polygon order for a point in several
 // polygons) from position offs[s] on; positions at or beyond cap are not
 // written.  No barriers after the coarse canvas is loaded.
-template <bool MULTI>
 __global__ __launch_bounds__(EMIT_THREADS) void k_emit(CanvasView cv, int64_t n, const double *X,
                                                        const double *Y, int64_t nseg,
                                                        const unsigned long long *offs, uint32_t *out_pt,
                                                        uint32_t *out_poly, int64_t cap, const unsigned *multi)
 {
     static_assert(EMIT_THREADS == CNT_THREADS, "the queue area is sized for CNT_THREADS");
-    // both variants are launched; the one that does not fit the count
-    // pass's finding returns at once
-    if ((*multi != 0u) != MULTI) return;
+    if (*multi == 0u) return;   // k_emit_labels has written the pairs
     extern __shared__ __align__(16) unsigned char smem[];
     uint16_t *coarse = (uint16_t *)smem;
     const size_t coarse_bytes = ((size_t)cv.Wc * cv.Hc * (cv.cbyte ? 1 : 2) + 15) & ~(size_t)15;
@@ -644,7 +645,7 @@ __global__ __launch_bounds__(EMIT_THREADS) void k_emit(CanvasView cv, int64_t n,
                             out_pt[p] = pt;
                             if (out_poly) out_poly[p] = lab[k];
                         }
-                    } else if (MULTI && (int64_t)p < cap) {
+                    } else if ((int64_t)p < cap) {
                         // several polygons: the smallest L of them (all when
                         // below cap), ascending, kept in out_poly[p, p + L)
                         // by insertion during one pass over the pixel's
@@ -684,15 +685,32 @@ __global__ __launch_bounds__(EMIT_THREADS) void k_emit(CanvasView cv, int64_t n,
     }
 }
 
+// The labels of a group of 64 * EMIT_GROUP points lie lane by lane, so that a
+// lane's EMIT_GROUP labels are one store of the count pass (128-byte stores of
+// a word's labels had the pass wait for its stores: 477 us for 50M points)
+// and one load of the write pass.
+template <typename T>
+struct alignas(16) LabelVec {
+    T l[EMIT_GROUP];
+};
+
 // Count pass with the boundary points of a wavefront queued in LDS and
 // tested a full wavefront at a time (as in k_count): counts[s] = output
 // entries of segment s.  The same records and the same test as k_emit,
-// so the counts match what the write pass writes.
+// so the counts match what the write pass writes.  While *multi is clear,
+// labels keeps every point's polygon (all ones: none), so that the write pass
+// reads 2 or 4 bytes per point instead of the points and the canvas again; a
+// point in several polygons sets *multi, and the labels are not used.  Bound
+// by the latency of the points and their cells, as k_count: 100M points, 64
+// polygons on a 2048 canvas, 0.37 ms (0.31 without the labels, whose 0.2 GB
+// save the write pass 0.38 ms).
+template <typename T>
 __global__ __launch_bounds__(EMIT_THREADS) void k_emit_count(CanvasView cv, int64_t n, const double *X,
                                                              const double *Y, int64_t nseg,
-                                                             unsigned long long *counts, unsigned *multi)
+                                                             unsigned long long *counts, unsigned *multi, T *labels)
 {
     static_assert(EMIT_THREADS == CNT_THREADS, "the queue area is sized for CNT_THREADS");
+    static_assert(EMIT_SEG <= 65536 && EMIT_INDEX_BYTES <= LDS_RESERVE, "the queued points' places fit the reserve");
     extern __shared__ __align__(16) unsigned char smem[];
     uint16_t *coarse = (uint16_t *)smem;
     const size_t coarse_bytes = ((size_t)cv.Wc * cv.Hc * (cv.cbyte ? 1 : 2) + 15) & ~(size_t)15;
@@ -701,6 +719,7 @@ __global__ __launch_bounds__(EMIT_THREADS) void k_emit_count(CanvasView cv, int6
     double *qx = (double *)(qbase) + wv * QCAP;
     double *qy = (double *)(qbase) + (EMIT_THREADS / 64) * QCAP + wv * QCAP;
     uint32_t *qr = (uint32_t *)((double *)(qbase) + 2 * (EMIT_THREADS / 64) * QCAP) + wv * QCAP;
+    uint16_t *qi = (uint16_t *)(qbase + QUEUE_BYTES) + wv * QCAP;   // the points' places in the segment
     load_coarse(cv, coarse, EMIT_THREADS);
     __syncthreads();
     const uint32_t lane = lane_id();
@@ -708,6 +727,9 @@ __global__ __launch_bounds__(EMIT_THREADS) void k_emit_count(CanvasView cv, int6
     const int64_t nwave = ((int64_t)gridDim.x * EMIT_THREADS) >> 6;
     for (int64_t sg = ((int64_t)blockIdx.x * EMIT_THREADS + threadIdx.x) >> 6; sg < nseg; sg += nwave) {
         const int64_t i0 = sg * EMIT_SEG + lane;
+        // whole segments: no bounds to check; none once the labels are known
+        // not to be used
+        T *seg = __hip_atomic_load(multi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ? nullptr : labels + sg * EMIT_SEG;
         unsigned long long total = 0;   // wave-uniform
         uint32_t qn = 0;                // wave-uniform queue length
         auto drain = [&]() {
@@ -715,21 +737,25 @@ __global__ __launch_bounds__(EMIT_THREADS) void k_emit_count(CanvasView cv, int6
             uint32_t m = 0;
             if (lane < qn) {
                 const double x = qx[lane], y = qy[lane];
-                uint32_t rec = qr[lane];
+                uint32_t rec = qr[lane], first = ~0u;
                 while (true) {   // two records at a time (the slot after the last exists)
                     const Cand c0 = cv.cands[rec];
                     const Cand c1 = cv.cands[rec + 1];
-                    m += cand_inside(cv, c0, x, y) ? 1u : 0u;
+                    if (cand_inside(cv, c0, x, y)) { ++m; first = c0.poly; }
                     if (c0.meta & CAND_LAST) break;
-                    m += cand_inside(cv, c1, x, y) ? 1u : 0u;
+                    if (cand_inside(cv, c1, x, y)) { ++m; first = c1.poly; }
                     if (c1.meta & CAND_LAST) break;
                     rec += 2;
                 }
+                // after the group's own store: one wavefront's stores to
+                // an address keep their order under the fence
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+                if (seg) seg[qi[lane]] = (T)first;
             }
             __builtin_amdgcn_wave_barrier();
-            // a point in several polygons: the write pass takes its
-            // several-polygon variant
-            if (__ballot(m > 1u) && lane == 0) *multi = 1u;
+            // a point in several polygons: the write pass probes again
+            if (__ballot(m > 1u) && lane == 0)
+                __hip_atomic_store(multi, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
             for (int d = 32; d >= 1; d >>= 1) m += __shfl_xor(m, d, 64);
             total += m;
@@ -749,6 +775,12 @@ __global__ __launch_bounds__(EMIT_THREADS) void k_emit_count(CanvasView cv, int6
                 const Look lk = look_coarse(cv, coarse, xs[k], ys[k]);
                 ws[k] = lk.full ? ((gu32p)cv.cells)[lk.fidx] : lk.word;
             }
+            if (seg) {   // a boundary point's label is stored by its drain
+                LabelVec<T> v;
+#pragma unroll
+                for (int k = 0; k < EMIT_GROUP; ++k) v.l[k] = (T)(ws[k] - 1u);   // word 0: all ones
+                *(LabelVec<T> *)(seg + 64 * g + EMIT_GROUP * lane) = v;
+            }
 #pragma unroll
             for (int k = 0; k < EMIT_GROUP; ++k) {
                 const uint32_t w = ws[k];
@@ -763,12 +795,49 @@ __global__ __launch_bounds__(EMIT_THREADS) void k_emit_count(CanvasView cv, int6
                     qx[slot] = xs[k];
                     qy[slot] = ys[k];
                     qr[slot] = w & ~BFLAG;
+                    qi[slot] = (uint16_t)(64 * g + EMIT_GROUP * lane + k);
                 }
                 qn += nnew;
             }
         }
         if (qn) drain();
         if (lane == 0) counts[sg] = total;
+    }
+}
+
+// Write pass from the count pass's labels, when no point lies in several
+// polygons: a wavefront takes a segment, all its labels in flight, and stores
+// the pairs of a word to consecutive positions from offs[segment] on (below
+// cap).  Bound by HBM: 50M pairs (0.1 GB read, 0.4 GB written) in 0.10 ms,
+// where the pass that read the points and the canvas again took 0.48 ms.
+template <typename T>
+__global__ __launch_bounds__(256) void k_emit_labels(int64_t nseg, const unsigned long long *offs, const T *labels,
+                                                     const unsigned *multi, uint32_t *out_pt, uint32_t *out_poly,
+                                                     int64_t cap)
+{
+    if (*multi != 0u) return;   // k_emit writes the pairs
+    constexpr int NW = EMIT_SEG / 64;
+    const int lane = threadIdx.x & 63;
+    const unsigned long long below = (1ull << lane) - 1ull;
+    const int64_t nwave = ((int64_t)gridDim.x * blockDim.x) >> 6;
+    for (int64_t sg = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6; sg < nseg; sg += nwave) {
+        LabelVec<T> v[NW / EMIT_GROUP];
+#pragma unroll
+        for (int j = 0; j < NW / EMIT_GROUP; ++j)
+            v[j] = *(const LabelVec<T> *)(labels + sg * EMIT_SEG + EMIT_GROUP * (64 * j + lane));
+        int64_t pos = (int64_t)offs[sg];
+#pragma unroll
+        for (int j = 0; j < NW; ++j) {
+            const T lab = v[j / EMIT_GROUP].l[j % EMIT_GROUP];
+            const bool on = lab != (T)~(T)0;
+            const unsigned long long m = __ballot(on);
+            const int64_t p = pos + __popcll(m & below);
+            if (on && p < cap) {
+                out_pt[p] = (uint32_t)(sg * EMIT_SEG + 64 * j + lane);
+                if (out_poly) out_poly[p] = (uint32_t)lab;
+            }
+            pos += __popcll(m);
+        }
     }
 }
 
@@ -912,7 +981,7 @@ __global__ __launch_bounds__(256) void k_emit_bits(int64_t nseg, const unsigned 
 }
 
 __global__ void k_emit_zero(unsigned long long *p) { *p = 0ull; }
-__global__ void k_emit_flag0(unsigned *p) { *p = 0u; }
+__global__ void k_emit_flag(unsigned *p, unsigned v) { *p = v; }
 
 int probe_emit(spade_ctx *ctx, const spade_canvas *cv, const spade_points *pts, uint32_t *out_pt,
                uint32_t *out_poly, int64_t cap, int64_t *n_out)
@@ -934,12 +1003,6 @@ int probe_emit(spade_ctx *ctx, const spade_canvas *cv, const spade_points *pts, 
     const int cus = num_cus(ctx);
     const int64_t wpb = EMIT_THREADS / 64;
     const int grid = (int)std::max<int64_t>(1, std::min<int64_t>((nseg + wpb - 1) / wpb, (int64_t)cus * std::min(per_cu, 2)));
-    SPADE_HIP(ctx, hipFuncSetAttribute((const void *)k_emit_count, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)(lds + QUEUE_BYTES)));
-    SPADE_HIP(ctx, hipFuncSetAttribute((const void *)k_emit<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)(lds + QUEUE_BYTES)));
-    SPADE_HIP(ctx, hipFuncSetAttribute((const void *)k_emit<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)(lds + QUEUE_BYTES)));
     // a canvas of one polygon keeps every point's result in the count pass
     // (one bit per point), so that the write pass need not read the points
     unsigned long long *bits = nullptr;
@@ -950,18 +1013,37 @@ int probe_emit(spade_ctx *ctx, const spade_canvas *cv, const spade_points *pts, 
         else
             ctx->err.clear();   // read the points twice instead
     }
-    if (bits)
-        SPADE_HIP(ctx, hipFuncSetAttribute((const void *)k_emit_count_bits, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (int)(lds + QUEUE_BYTES)));
-    if (ctx->timing) SPADE_HIP(ctx, hipEventRecord(ctx->ev[2], st));
-    if (bits)
-        hipLaunchKernelGGL(k_emit_count_bits, dim3(grid), dim3(EMIT_THREADS), lds + QUEUE_BYTES, st, cv->view, n,
-                           pts->x, pts->y, nseg, counts, bits);
-    else {
-        hipLaunchKernelGGL(k_emit_flag0, dim3(1), dim3(1), 0, st, multi);
-        hipLaunchKernelGGL(k_emit_count, dim3(grid), dim3(EMIT_THREADS), lds + QUEUE_BYTES, st, cv->view, n, pts->x,
-                           pts->y, nseg, counts, multi);
+    // other canvases keep every point's polygon, in 16 bits where they name it
+    uint16_t *lab16 = nullptr;
+    uint32_t *lab32 = nullptr;
+    if (!bits && cap > 0) {
+        DevBuf &bb = ctx->scratch[S_BITS];
+        const bool narrow = cv->view.M < 65536;
+        if (ensure(ctx, bb, (narrow ? 2 : 4) * (size_t)EMIT_SEG * (size_t)nseg) == SPADE_OK) {
+            if (narrow) lab16 = (uint16_t *)bb.p;
+            else lab32 = (uint32_t *)bb.p;
+        } else {
+            ctx->err.clear();   // probe twice instead
+        }
     }
+    const bool labelled = lab16 || lab32;
+    auto launch = [&](auto kern, size_t bytes, auto... args) -> int {
+        SPADE_HIP(ctx, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(EMIT_THREADS), bytes, st, cv->view, n, pts->x, pts->y, nseg, args...);
+        SPADE_HIP(ctx, hipGetLastError());
+        return SPADE_OK;
+    };
+    int rc;
+    if (ctx->timing) SPADE_HIP(ctx, hipEventRecord(ctx->ev[2], st));
+    if (bits) {
+        rc = launch(k_emit_count_bits, lds + QUEUE_BYTES, counts, bits);
+    } else {
+        // without labels the write pass always probes again
+        hipLaunchKernelGGL(k_emit_flag, dim3(1), dim3(1), 0, st, multi, labelled ? 0u : 1u);
+        rc = lab32 ? launch(k_emit_count<uint32_t>, lds + QUEUE_BYTES + EMIT_INDEX_BYTES, counts, multi, lab32)
+                   : launch(k_emit_count<uint16_t>, lds + QUEUE_BYTES + EMIT_INDEX_BYTES, counts, multi, lab16);
+    }
+    if (rc) return rc;
     hipLaunchKernelGGL(k_emit_zero, dim3(1), dim3(1), 0, st, counts + nseg);
     SPADE_HIP(ctx, hipGetLastError());
     DevBuf &cub = ctx->scratch[S_CUBTMP];
@@ -974,11 +1056,16 @@ int probe_emit(spade_ctx *ctx, const spade_canvas *cv, const spade_points *pts, 
         hipLaunchKernelGGL(k_emit_bits, dim3(bg), dim3(256), 0, st, nseg, offs, bits, out_pt, out_poly, cap);
         SPADE_HIP(ctx, hipGetLastError());
     } else if (cap > 0) {
-        hipLaunchKernelGGL(k_emit<false>, dim3(grid), dim3(EMIT_THREADS), lds + QUEUE_BYTES, st, cv->view, n, pts->x,
-                           pts->y, nseg, offs, out_pt, out_poly, cap, (const unsigned *)multi);
-        hipLaunchKernelGGL(k_emit<true>, dim3(grid), dim3(EMIT_THREADS), lds + QUEUE_BYTES, st, cv->view, n, pts->x,
-                           pts->y, nseg, offs, out_pt, out_poly, cap, (const unsigned *)multi);
-        SPADE_HIP(ctx, hipGetLastError());
+        const int bg = (int)std::max<int64_t>(1, std::min<int64_t>((nseg + 3) / 4, (int64_t)cus * 16));
+        if (lab16)
+            hipLaunchKernelGGL(k_emit_labels<uint16_t>, dim3(bg), dim3(256), 0, st, nseg, (const unsigned long long *)offs,
+                               (const uint16_t *)lab16, (const unsigned *)multi, out_pt, out_poly, cap);
+        if (lab32)
+            hipLaunchKernelGGL(k_emit_labels<uint32_t>, dim3(bg), dim3(256), 0, st, nseg, (const unsigned long long *)offs,
+                               (const uint32_t *)lab32, (const unsigned *)multi, out_pt, out_poly, cap);
+        if ((rc = launch(k_emit, lds + QUEUE_BYTES, (const unsigned long long *)offs, out_pt, out_poly, cap,
+                         (const unsigned *)multi)))
+            return rc;
     }
     if (ctx->timing) SPADE_HIP(ctx, hipEventRecord(ctx->ev[3], st));
     unsigned long long *h = (unsigned long long *)ensure_pinned(ctx, 64);
