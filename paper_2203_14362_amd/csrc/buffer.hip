@@ -5,13 +5,15 @@
 // over that shape.
 //
 // Instead of rasterising the rounded rectangles, the segments are binned
-// into a uniform grid over their box widened by r: a cell lists every
-// segment whose widened box meets it (count, scan, fill).  One pass over the
+// into a uniform grid over their box widened by r: a cell that lies wholly
+// within r of a segment is full, any other lists every segment that may be
+// within r of one of its points (count, scan, fill).  One pass over the
 // points then keeps, per 1024-point segment of the stream, one result bit
 // per point: for a polygon, the canvas of the polygon answers first (coarse
 // level in LDS, full canvas, exact records, as the selection probe does);
-// a point not yet kept that lies in the grid's box is tested exactly against
-// the segments its cell lists, until one is within r.  The tests of a
+// a point not yet kept that lies in the grid's box is kept in a full cell, and
+// tested exactly against the segments that another cell lists, until one is
+// within r.  The tests of a
 // wavefront's 64 points are spread over its lanes (buf_wave_walk), so that a
 // wavefront takes about as many rounds as its points have candidates in
 // total / 64 rather than as many as its longest list.  The ordered ids are
@@ -22,6 +24,7 @@
 #include "wavewalk.h"
 
 #include <hipcub/hipcub.hpp>
+#include <rocprim/rocprim.hpp>
 
 #include <algorithm>
 #include <cmath>
@@ -30,6 +33,10 @@
 namespace spade {
 
 constexpr int BUF_GRID_MAX = 4096;            // cells per side
+constexpr double BUF_FINE = 2.0;              // finest cell: the distance over this
+constexpr double BUF_PER_CELL = 4.0;          // points per cell of a fine grid, at least
+constexpr double BUF_PER_ENTRY = 8.0;         // points per list entry of a fine grid, at least
+constexpr int64_t BUF_FILTER_MIN = 1 << 20;   // points from which a pass without exact tests pays for its launch (5 us)
 constexpr int BUF_THREADS = 1024;
 constexpr int BUF_WORDS = EMIT_SEG / 64;      // bit words per point segment
 
@@ -61,13 +68,19 @@ __device__ __forceinline__ int buf_cell(double v, double v0, double inv, int g)
     return (int)fmin(fmax(floor(u), 0.0), (double)(g - 1));
 }
 
+// The box's keys at all ones, the flags, the entry total and the length zero.
+__global__ void k_buf_init(unsigned long long *bb)
+{
+    if (threadIdx.x < 8) bb[threadIdx.x] = threadIdx.x < 4 ? ~0ull : 0ull;
+}
+
 // One segment slot per vertex: vertex v of its ring to the next one (the
 // ring's first vertex after the last when `closed`; a one-vertex ring is a
 // point).  Validates the offsets and the vertices on the way (err bit 1:
 // offsets, bit 2: a non-finite vertex) and reduces the segments' box into
 // bb (min x, -max x, min y, -max y as ordered keys); sums the segments'
 // lengths (an FP64 estimate, only for the grid's cell size) into *len.
-__global__ void k_buf_segs(int64_t R, const int64_t *rvo, int64_t V, const double *vx, const double *vy,
+__global__ __launch_bounds__(256) void k_buf_segs(int64_t R, const int64_t *rvo, int64_t V, const double *vx, const double *vy,
                            int closed, Seg *segs, uint8_t *valid, unsigned long long *bb, unsigned *err,
                            double *len)
 {
@@ -115,26 +128,57 @@ __global__ void k_buf_segs(int64_t R, const int64_t *rvo, int64_t V, const doubl
         k3 = min(k3, (unsigned long long)__shfl_xor((long long)k3, d, 64));
     }
     for (int d = 32; d > 0; d >>= 1) lsum += __shfl_xor(lsum, d, 64);
-    if ((threadIdx.x & 63) == 0 && k0 != ~0ull) {
-        atomicMin(&bb[0], k0); atomicMin(&bb[1], k1); atomicMin(&bb[2], k2); atomicMin(&bb[3], k3);
-        atomicAdd(len, lsum);
+    // one set of atomics per workgroup of 256 (all meet in one line)
+    __shared__ unsigned long long part[4][4];
+    __shared__ double plen[4];
+    const int wv = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0) {
+        part[wv][0] = k0;
+        part[wv][1] = k1;
+        part[wv][2] = k2;
+        part[wv][3] = k3;
+        plen[wv] = lsum;
     }
+    __syncthreads();
+    if (threadIdx.x < 4) {
+        const int k = threadIdx.x;
+        const unsigned long long m = min(min(part[0][k], part[1][k]), min(part[2][k], part[3][k]));
+        if (m != ~0ull) atomicMin(&bb[k], m);
+    }
+    if (threadIdx.x == 0) atomicAdd(len, plen[0] + plen[1] + plen[2] + plen[3]);
 }
 
-// Cells that may hold a point within r of each valid segment: the cells of
-// its box widened by pad whose centre lies within r + half the cell diagonal
-// of the segment (FP64 distance, with a relative margin of 1e-9 and the
-// absolute part of pad, far above its rounding and that of the point-to-cell
-// mapping), counted (FILL false, with the number of list entries summed into
-// *tot) or listed (FILL true: a copy of the segment in a per-cell slot from
-// off[] claimed with cursor[], so that a point reads its cell's candidates
-// contiguously, with no index to follow).
+// Cells that may hold a point within r of each valid segment: the cells
+// whose centre lies within r + half the cell diagonal of it (FP64 distance,
+// with a relative margin of 1e-9 and the absolute part of pad, far above its
+// rounding and that of the point-to-cell mapping).  A cell whose centre lies
+// so near to one segment that its whole square is within r (fin: r less half
+// the diagonal and the same margins; any point of the segment bounds the
+// distance from above, so rounding of the nearest one cannot make it too
+// small) is full: its points are results without a test, and it lists
+// nothing.  FILL false: cnt[c] counts the entries, or has its top bit set
+// when full, and the entries of all cells are summed into *tot.  FILL true:
+// a copy of the segment goes in a per-cell slot from off[] claimed with
+// cursor[], so that a point reads its cell's candidates contiguously, with no
+// index to follow.
+//
+// The rows of a segment's box are spread over 2^lsh lanes, and of a row only
+// the columns near the part of the segment that the row can reach are
+// visited: a long segment is the work of its own cells, not of its box's.
+constexpr uint32_t BUF_FULL = 0x80000000u;
+
 template <bool FILL>
-__global__ void k_buf_bin(int64_t V, const Seg *segs, const uint8_t *valid, BufGrid g, double pad, uint32_t *cnt,
-                          const uint32_t *off, Seg *list, unsigned long long *tot)
+__global__ __launch_bounds__(256) void k_buf_bin(int64_t V, const Seg *segs, const uint8_t *valid, BufGrid g,
+                                                 double pad, double fin, int lsh, uint32_t *cnt,
+                                                 const uint32_t *off, uint32_t *cursor, Seg *list, unsigned long long *tot)
 {
+#pragma clang fp contract(off)   // both passes decide alike
     const int64_t nth = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < V; v += nth) {
+    const double reach = (pad + 0.7071067811865476 * g.cell) * (1.0 + 1e-9);
+    const double reach2 = reach * reach, fin2 = fin > 0.0 ? fin * fin : -1.0;
+    unsigned long long nlisted = 0;
+    for (int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; w < (V << lsh); w += nth) {
+        const int64_t v = w >> lsh;
         if (!valid[v]) continue;
         const Seg s = segs[v];
         const int x0 = buf_cell(fmin(s.ax, s.bx) - pad, g.X0, g.inv, g.gx);
@@ -142,47 +186,101 @@ __global__ void k_buf_bin(int64_t V, const Seg *segs, const uint8_t *valid, BufG
         const int y0 = buf_cell(fmin(s.ay, s.by) - pad, g.Y0, g.inv, g.gy);
         const int y1 = buf_cell(fmax(s.ay, s.by) + pad, g.Y0, g.inv, g.gy);
         const double ex = s.bx - s.ax, ey = s.by - s.ay, l2 = ex * ex + ey * ey;
-        const double reach = (pad + 0.7071067811865476 * g.cell) * (1.0 + 1e-9);
-        const double reach2 = reach * reach;
-        unsigned long long nlisted = 0;
-        for (int cy = y0; cy <= y1; ++cy)
-            for (int cx = x0; cx <= x1; ++cx) {
-                const double px = g.X0 + (cx + 0.5) * g.cell, py = g.Y0 + (cy + 0.5) * g.cell;
+        for (int cy = y0 + (int)(w - (v << lsh)); cy <= y1; cy += 1 << lsh) {
+            int c0 = x0, c1 = x1;
+            const double py = g.Y0 + (cy + 0.5) * g.cell;
+            if (ey != 0.0) {
+                const double t0 = fmin(fmax((py - reach - s.ay) / ey, 0.0), 1.0);
+                const double t1 = fmin(fmax((py + reach - s.ay) / ey, 0.0), 1.0);
+                const double xa = s.ax + t0 * ex, xb = s.ax + t1 * ex;
+                const double lo = fmin(xa, xb) - reach, hi = fmax(xa, xb) + reach;
+                if (isfinite(lo) && isfinite(hi)) {
+                    c0 = max(c0, buf_cell(lo, g.X0, g.inv, g.gx) - 1);
+                    c1 = min(c1, buf_cell(hi, g.X0, g.inv, g.gx) + 1);
+                }
+            }
+            for (int cx = c0; cx <= c1; ++cx) {
+                const double px = g.X0 + (cx + 0.5) * g.cell;
                 double t = l2 > 0.0 ? ((px - s.ax) * ex + (py - s.ay) * ey) / l2 : 0.0;
                 t = fmin(fmax(t, 0.0), 1.0);
                 const double dx = px - (s.ax + t * ex), dy = py - (s.ay + t * ey);
-                if (dx * dx + dy * dy > reach2) continue;
+                const double d2 = dx * dx + dy * dy;
+                if (d2 > reach2) continue;
                 const int64_t c = (int64_t)cy * g.gx + cx;
-                if (FILL) list[off[c] + atomicAdd(&cnt[c], 1u)] = s;
-                else atomicAdd(&cnt[c], 1u);
-                ++nlisted;
+                if (FILL) {
+                    if (!(cnt[c] & BUF_FULL)) list[off[c] + atomicAdd(&cursor[c], 1u)] = s;
+                } else {
+                    if (d2 <= fin2) atomicOr(&cnt[c], BUF_FULL);
+                    else atomicAdd(&cnt[c], 1u);
+                    ++nlisted;
+                }
             }
-        if (!FILL) atomicAdd(tot, nlisted);
+        }
     }
+    if (!FILL) {
+        __shared__ unsigned long long part[4];
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) nlisted += (unsigned long long)__shfl_xor((long long)nlisted, d, 64);
+        if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = nlisted;
+        __syncthreads();
+        if (threadIdx.x == 0) atomicAdd(tot, part[0] + part[1] + part[2] + part[3]);
+    }
+}
+
+// Entries that a cell lists: none when it is full.
+struct BufListed {
+    __host__ __device__ uint32_t operator()(uint32_t c) const { return (c & BUF_FULL) ? 0u : c; }
+};
+
+// Two bits per cell, 16 cells a word: no candidate (0), candidates (1), full
+// (2).  The points read these, which stay in a chiplet's L2 (1.4 MB for 5.8M
+// cells); a table of 4-byte offsets did not, and every point's read of it
+// went past (558 us for 50M points near 24k segments, now 495).
+// Also leaves the number of list entries in *listed and clears *end (the
+// count behind the last segment of points, whose scan is the total).
+__global__ void k_buf_class(int64_t G, const uint32_t *cnt, const uint32_t *off, uint32_t *cls,
+                            unsigned long long *listed, unsigned long long *end)
+{
+    const int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (w == 0) {
+        *listed = off[G];
+        *end = 0ull;
+    }
+    if (w * 16 >= G) return;
+    uint32_t v = 0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        const uint32_t c = w * 16 + k < G ? cnt[w * 16 + k] : 0u;
+        v |= (c & BUF_FULL ? 2u : c ? 1u : 0u) << (2 * k);
+    }
+    cls[w] = v;
 }
 
 // The candidate tests of one wavefront's points, balanced over its lanes
 // (wave_round): lane i's point has the candidates list[k, k + rem) left, and
 // a point any of whose candidates in a round was within r drops the rest.
-// Returns whether this lane's point was hit.  Called by every lane of the
-// wavefront.
+// Returns whether this lane's point was hit.  Without EXACT, candidates that
+// the filter leaves open set `open` (for the whole wavefront) and count as not
+// within.  Called by every lane of the wavefront.
+template <bool EXACT>
 __device__ __forceinline__ bool buf_wave_walk(double x, double y, uint32_t k, uint32_t rem, const Seg *list,
-                                              double r, double r2, double pad, int lane)
+                                              double r, double r2, double pad, int lane, bool &open)
 {
     bool hit = false;
     while (__ballot(rem != 0u)) {
         const WaveRound w = wave_round(rem, lane);
         const uint32_t ok = __shfl(k, w.o, 64);
         const double ox = __shfl(x, w.o, 64), oy = __shfl(y, w.o, 64);
-        bool h = false;
+        int h = 0;
         if ((uint32_t)lane < w.ntake) {
             const Seg s = list[ok + ((uint32_t)lane - w.opre)];
             // outside the segment's box widened by pad: farther than r
             if (!(ox < fmin(s.ax, s.bx) - pad || ox > fmax(s.ax, s.bx) + pad || oy < fmin(s.ay, s.by) - pad ||
                   oy > fmax(s.ay, s.by) + pad))
-                h = seg_near(ox, oy, s, r, r2);
+                h = EXACT ? (seg_near(ox, oy, s, r, r2) ? 1 : 0) : seg_near_filter(ox, oy, s, r2);
         }
-        const unsigned long long hm = __ballot(h);
+        const unsigned long long hm = __ballot(h > 0);
+        if (!EXACT && __ballot(h < 0)) open = true;
         const uint32_t len = wave_round_len(w);
         if (hm & wave_round_mask(w)) {
             hit = true;
@@ -197,56 +295,148 @@ __device__ __forceinline__ bool buf_wave_walk(double x, double y, uint32_t k, ui
 
 // One result bit per point (layout of the ordered emit: word j of segment sg
 // holds points sg * EMIT_SEG + 64 j + lane) and the count per segment.
-template <bool POLY>
-__global__ __launch_bounds__(BUF_THREADS) void k_buf_bits(CanvasView cv, int64_t n, const double *X, const double *Y,
-                                                          BufGrid g, const Seg *segs, const uint32_t *off,
-                                                          const Seg *list, double r, double r2, double pad,
-                                                          int64_t nseg, unsigned long long *counts,
-                                                          unsigned long long *bits)
+//
+// Bound by the latency of a chain of three dependent loads (point, cell
+// range, candidates) and by the tests of the candidates.  A wavefront loads
+// the points and cell ranges of BUF_GROUP words together, and queues the few
+// points that have candidates in LDS, so that the candidate walk runs with
+// about 64 points rather than with those of one word.  50M points, 24k
+// segments, 50 m: 1.70 ms with cells of 150 m (every point's candidates
+// tested, one word at a time), 0.50 ms with cells of 25 m; what is left is
+// the rate of L2 requests (71M, most of them the points' cell codes).
+// The canvas's coarse level needs one workgroup per CU; without a canvas the
+// workgroups are small, so that the registers alone limit their number, and
+// the exact tests' are kept out: a first pass (EXACT false) decides by the
+// filter and leaves BUF_OPEN as the count of a segment in which a candidate
+// stayed open, a second one (EXACT and ONLY_OPEN) does those segments again.
+constexpr int BUF_GROUP = 4;                  // words in flight
+constexpr int BUF_QCAP = 64;                  // queued points per wavefront
+constexpr int BUF_QWAVE = BUF_QCAP * 22;      // x, y, cell, place: bytes per wavefront
+
+constexpr unsigned long long BUF_OPEN = ~0ull;
+
+template <bool POLY, int TH, bool EXACT, bool ONLY_OPEN>
+__global__ __launch_bounds__(TH, TH == 256 && !EXACT ? 5 : 1) void k_buf_bits(CanvasView cv, int64_t n, const double *X, const double *Y,
+                                                 BufGrid g, const uint32_t *cls, const uint32_t *off,
+                                                 const Seg *list, double r, double r2, double pad, int64_t nseg, unsigned long long *counts,
+                                                 unsigned long long *bits)
 {
+    static_assert(BUF_WORDS % BUF_GROUP == 0 && BUF_WORDS <= BUF_QCAP, "words per segment");
+    static_assert(BUF_QWAVE % 8 == 0 && EMIT_SEG <= 65536, "queue layout");
     extern __shared__ __align__(16) unsigned char smem[];
     uint16_t *coarse = (uint16_t *)smem;
+    size_t cbytes = 0;
     if (POLY) {
-        load_coarse(cv, coarse, BUF_THREADS);
+        cbytes = ((size_t)cv.Wc * cv.Hc * (cv.cbyte ? 1 : 2) + 15) & ~(size_t)15;
+        load_coarse(cv, coarse, TH);
         __syncthreads();
     }
     const int lane = threadIdx.x & 63;
-    const int64_t nwave = ((int64_t)gridDim.x * BUF_THREADS) >> 6;
-    for (int64_t sg = ((int64_t)blockIdx.x * BUF_THREADS + threadIdx.x) >> 6; sg < nseg; sg += nwave) {
-        unsigned long long total = 0, segw = 0;
-        for (int j = 0; j < BUF_WORDS; ++j) {
-            const int64_t i = sg * EMIT_SEG + 64 * j + lane;
-            const double x = i < n ? __builtin_nontemporal_load(X + i) : NAN;
-            const double y = i < n ? __builtin_nontemporal_load(Y + i) : NAN;
-            bool hit = false;
-            if (POLY) {
-                const uint32_t w = lookup(cv, coarse, x, y);
-                if (w != 0u && !(w & BFLAG)) {
-                    hit = true;
-                } else if (w & BFLAG) {
-                    uint32_t rec = w & ~BFLAG;
-                    while (true) {
-                        const Cand c = cv.cands[rec];
-                        if (cand_inside(cv, c, x, y)) { hit = true; break; }
-                        if (c.meta & CAND_LAST) break;
-                        ++rec;
-                    }
-                }
-            }
-            // NaN fails the box test
-            uint32_t k = 0u, rem = 0u;
-            if (!hit && x >= g.X0 && x <= g.X1 && y >= g.Y0 && y <= g.Y1) {
-                const int64_t c = (int64_t)buf_cell(y, g.Y0, g.inv, g.gy) * g.gx + buf_cell(x, g.X0, g.inv, g.gx);
+    const unsigned long long below = (1ull << lane) - 1ull;
+    unsigned char *q = smem + cbytes + (threadIdx.x >> 6) * BUF_QWAVE;
+    double *qx = (double *)q, *qy = qx + BUF_QCAP;
+    uint32_t *qc = (uint32_t *)(qy + BUF_QCAP);
+    uint16_t *qi = (uint16_t *)(qc + BUF_QCAP);
+    unsigned long long *qw = (unsigned long long *)q;   // a drain's result words, over the points it has read
+    auto sync = [] {   // order this wavefront's LDS accesses
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
+    const int64_t nwave = ((int64_t)gridDim.x * TH) >> 6;
+    for (int64_t sg = ((int64_t)blockIdx.x * TH + threadIdx.x) >> 6; sg < nseg; sg += nwave) {
+        if (ONLY_OPEN && counts[sg] != BUF_OPEN) continue;
+        unsigned long long segw = 0;   // lane j < BUF_WORDS: word j
+        uint32_t qn = 0;               // wave-uniform
+        bool open = false;             // wave-uniform
+        auto drain = [&]() {
+            sync();
+            double x = NAN, y = NAN;
+            uint32_t k = 0u, rem = 0u, id = 0u;
+            if (lane < (int)qn) {
+                x = qx[lane];
+                y = qy[lane];
+                id = qi[lane];
+                const uint32_t c = qc[lane];
                 k = off[c];
                 rem = off[c + 1] - k;
             }
-            if (buf_wave_walk(x, y, k, rem, list, r, r2, pad, lane)) hit = true;
-            const unsigned long long word = __ballot(hit);
-            total += (unsigned long long)__popcll(word);
-            if (lane == j) segw = word;
+            const bool hit = buf_wave_walk<EXACT>(x, y, k, rem, list, r, r2, pad, lane, open);
+            sync();
+            if (lane < BUF_WORDS) qw[lane] = 0ull;
+            sync();
+            if (hit) atomicOr(&qw[id >> 6], 1ull << (id & 63u));
+            sync();
+            if (lane < BUF_WORDS) segw |= qw[lane];
+            sync();
+            qn = 0;
+        };
+#pragma nounroll
+        for (int g0 = 0; g0 < BUF_WORDS; g0 += BUF_GROUP) {
+            double xs[BUF_GROUP], ys[BUF_GROUP];
+#pragma unroll
+            for (int k = 0; k < BUF_GROUP; ++k) {
+                const int64_t i = sg * EMIT_SEG + 64 * (g0 + k) + lane;
+                xs[k] = i < n ? __builtin_nontemporal_load(X + i) : NAN;
+                ys[k] = i < n ? __builtin_nontemporal_load(Y + i) : NAN;
+            }
+            uint32_t inside = 0;   // bit k: the polygon holds this lane's point of word k
+            if (POLY) {
+                uint32_t ws[BUF_GROUP];
+#pragma unroll
+                for (int k = 0; k < BUF_GROUP; ++k) ws[k] = lookup(cv, coarse, xs[k], ys[k]);
+#pragma unroll
+                for (int k = 0; k < BUF_GROUP; ++k) {
+                    bool in = ws[k] != 0u && !(ws[k] & BFLAG);
+                    if (ws[k] & BFLAG) {
+                        uint32_t rec = ws[k] & ~BFLAG;
+                        while (true) {
+                            const Cand c = cv.cands[rec];
+                            if (cand_inside(cv, c, xs[k], ys[k])) { in = true; break; }
+                            if (c.meta & CAND_LAST) break;
+                            ++rec;
+                        }
+                    }
+                    const unsigned long long word = __ballot(in);
+                    if (lane == g0 + k) segw |= word;
+                    if (in) inside |= 1u << k;
+                }
+            }
+            uint32_t cs[BUF_GROUP], code[BUF_GROUP];
+#pragma unroll
+            for (int k = 0; k < BUF_GROUP; ++k) {
+                // NaN fails the box test
+                const bool on = xs[k] >= g.X0 && xs[k] <= g.X1 && ys[k] >= g.Y0 && ys[k] <= g.Y1 &&
+                                !(POLY && ((inside >> k) & 1u));
+                cs[k] = on ? (uint32_t)buf_cell(ys[k], g.Y0, g.inv, g.gy) * (uint32_t)g.gx +
+                                 (uint32_t)buf_cell(xs[k], g.X0, g.inv, g.gx)
+                           : 0u;
+                code[k] = on ? cls[cs[k] >> 4] >> (2u * (cs[k] & 15u)) & 3u : 0u;
+            }
+#pragma unroll
+            for (int k = 0; k < BUF_GROUP; ++k) {
+                const unsigned long long word = __ballot(code[k] == 2u);
+                if (lane == g0 + k) segw |= word;
+                const bool on = code[k] == 1u;
+                const unsigned long long mask = __ballot(on);
+                const uint32_t nnew = (uint32_t)__popcll(mask);
+                if (nnew == 0) continue;
+                if (qn + nnew > (uint32_t)BUF_QCAP) drain();
+                if (on) {
+                    const uint32_t slot = qn + (uint32_t)__popcll(mask & below);
+                    qx[slot] = xs[k];
+                    qy[slot] = ys[k];
+                    qc[slot] = cs[k];
+                    qi[slot] = (uint16_t)(64 * (g0 + k) + lane);
+                }
+                qn += nnew;
+            }
         }
+        if (qn) drain();
+        uint32_t total = lane < BUF_WORDS ? (uint32_t)__popcll(segw) : 0u;
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) total += __shfl_xor(total, d, 64);
         if (lane < BUF_WORDS) bits[sg * BUF_WORDS + lane] = segw;
-        if (lane == 0) counts[sg] = total;
+        if (lane == 0) counts[sg] = !EXACT && open ? BUF_OPEN : total;
     }
 }
 
@@ -293,9 +483,8 @@ int buffer_select(spade_ctx *ctx, const spade_canvas *cv, const spade_points *pt
     unsigned long long *bb = (unsigned long long *)bg.p;
     unsigned *err = (unsigned *)(bb + 4);
     double *dlen = (double *)(bb + 6);
-    SPADE_HIP(ctx, hipMemsetAsync(bb, 0xff, 4 * sizeof(unsigned long long), st));
-    SPADE_HIP(ctx, hipMemsetAsync(err, 0, sizeof(unsigned), st));
-    SPADE_HIP(ctx, hipMemsetAsync(dlen, 0, sizeof(double), st));
+    hipLaunchKernelGGL(k_buf_init, dim3(1), dim3(64), 0, st, bb);
+    SPADE_HIP(ctx, hipGetLastError());
     if (R > 0) {
         const int sgrid = (int)std::max<int64_t>(1, std::min<int64_t>((std::max(V, R + 1) + 255) / 256, (int64_t)cus * 8));
         hipLaunchKernelGGL(k_buf_segs, dim3(sgrid), dim3(256), 0, st, R, geom->ring_vtx_off, V, geom->vx, geom->vy,
@@ -314,69 +503,6 @@ int buffer_select(spade_ctx *ctx, const spade_canvas *cv, const spade_points *pt
     std::memcpy(&len_sum, &h[6], sizeof len_sum);
     if (n == 0) return SPADE_OK;
 
-    // the grid over the segments' box widened by r (and a relative margin,
-    // so that rounding never drops a position within r)
-    BufGrid grid{0.0, 0.0, -1.0, -1.0, 1.0, 1.0, 1, 1};   // empty box: no point is tested
-    double pad = 0.0;
-    uint32_t *off = nullptr;
-    Seg *list = nullptr;
-    if (any) {
-        const double x0 = buf_from_key(h[0]), x1 = -buf_from_key(h[1]);
-        const double y0 = buf_from_key(h[2]), y1 = -buf_from_key(h[3]);
-        const double mag = std::fabs(x0) + std::fabs(x1) + std::fabs(y0) + std::fabs(y1);
-        pad = r * (1.0 + 0x1p-40) + mag * 0x1p-40 + 1e-300;
-        const double X0 = x0 - pad, X1 = x1 + pad, Y0 = y0 - pad, Y1 = y1 + pad;
-        const double w = X1 - X0, hgt = Y1 - Y0;
-        // cells as wide as r or the mean segment length, whichever is
-        // larger (a segment then meets a few cells, a cell a few segments),
-        // at most BUF_GRID_MAX per side
-        const double lmean = std::isfinite(len_sum) ? len_sum / (double)std::max<int64_t>(V, 1) : 0.0;
-        double cell = std::max(r, std::min(lmean, std::sqrt(w * hgt / (2.0 * (double)std::max<int64_t>(V, 1)))));
-        cell = std::max(cell, std::max(w, hgt) / BUF_GRID_MAX);
-        if (!(cell > 1e-290)) cell = 1.0;
-        grid.X0 = X0; grid.Y0 = Y0; grid.X1 = X1; grid.Y1 = Y1;
-        grid.inv = 1.0 / cell;
-        grid.cell = cell;
-        grid.gx = (int)std::min<double>(BUF_GRID_MAX, std::max(1.0, std::ceil(w * grid.inv)));
-        grid.gy = (int)std::min<double>(BUF_GRID_MAX, std::max(1.0, std::ceil(hgt * grid.inv)));
-        const int64_t G = (int64_t)grid.gx * grid.gy;
-        DevBuf &bt = ctx->scratch[S_BUF_TMP];
-        if (ensure(ctx, bg, 256 + sizeof(uint32_t) * 3 * (size_t)(G + 1))) return SPADE_E_NOMEM;
-        bb = (unsigned long long *)bg.p;
-        uint32_t *cnt = (uint32_t *)((unsigned char *)bg.p + 256);
-        off = cnt + (G + 1);
-        uint32_t *cursor = off + (G + 1);
-        unsigned long long *tot = bb + 5;
-        SPADE_HIP(ctx, hipMemsetAsync(cnt, 0, sizeof(uint32_t) * (size_t)(G + 1), st));
-        SPADE_HIP(ctx, hipMemsetAsync(tot, 0, sizeof(unsigned long long), st));
-        const int bgrid = (int)std::max<int64_t>(1, std::min<int64_t>((V + 255) / 256, (int64_t)cus * 8));
-        hipLaunchKernelGGL(k_buf_bin<false>, dim3(bgrid), dim3(256), 0, st, V, (const Seg *)segs,
-                           (const uint8_t *)valid, grid, pad, cnt, (const uint32_t *)nullptr, (Seg *)nullptr,
-                           tot);
-        SPADE_HIP(ctx, hipGetLastError());
-        size_t tb = 0;
-        SPADE_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(nullptr, tb, cnt, off, (int)(G + 1), st));
-        if (ensure(ctx, bt, std::max<size_t>(tb, 1))) return SPADE_E_NOMEM;
-        SPADE_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(bt.p, tb, cnt, off, (int)(G + 1), st));
-        // the 64-bit entry count first: the cell lists (32 bytes an entry)
-        // stay below 2^28 entries, so their 32-bit offsets are exact
-        SPADE_HIP(ctx, hipMemcpyAsync(h, tot, sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
-        SPADE_HIP(ctx, hipStreamSynchronize(st));
-        if (h[0] >= ((unsigned long long)1 << 28))
-            return set_error(ctx, SPADE_E_TOO_LARGE, "too many (segment, cell) entries: the distance is too large "
-                                                     "for the segments' spread");
-        const uint64_t total = h[0];
-        DevBuf &bl = ctx->scratch[S_BUF_LIST];
-        if (ensure(ctx, bl, sizeof(Seg) * (size_t)std::max<uint64_t>(total, 1))) return SPADE_E_NOMEM;
-        list = (Seg *)bl.p;
-        SPADE_HIP(ctx, hipMemsetAsync(cursor, 0, sizeof(uint32_t) * (size_t)(G + 1), st));
-        hipLaunchKernelGGL(k_buf_bin<true>, dim3(bgrid), dim3(256), 0, st, V, (const Seg *)segs,
-                           (const uint8_t *)valid, grid, pad, cursor, (const uint32_t *)off, list,
-                           (unsigned long long *)nullptr);
-        SPADE_HIP(ctx, hipGetLastError());
-    }
-
-    // result bits and per-segment counts, then the ordered write pass
     const int64_t nseg = (n + EMIT_SEG - 1) / EMIT_SEG;
     DevBuf &lb = ctx->scratch[S_LOOKBACK], &bbits = ctx->scratch[S_BITS];
     if (ensure(ctx, lb, sizeof(unsigned long long) * 2 * (size_t)(nseg + 1)) ||
@@ -385,26 +511,131 @@ int buffer_select(spade_ctx *ctx, const spade_canvas *cv, const spade_points *pt
     unsigned long long *counts = (unsigned long long *)lb.p;
     unsigned long long *offs = counts + (nseg + 1);
     unsigned long long *bits = (unsigned long long *)bbits.p;
+
+    // the grid over the segments' box widened by r (and a relative margin,
+    // so that rounding never drops a position within r)
+    BufGrid grid{0.0, 0.0, -1.0, -1.0, 1.0, 1.0, 1, 1};   // empty box: no point is tested
+    double pad = 0.0;
+    uint32_t *off = nullptr, *cls = nullptr;
+    Seg *list = nullptr;
+    if (any) {
+        const double x0 = buf_from_key(h[0]), x1 = -buf_from_key(h[1]);
+        const double y0 = buf_from_key(h[2]), y1 = -buf_from_key(h[3]);
+        const double mag = std::fabs(x0) + std::fabs(x1) + std::fabs(y0) + std::fabs(y1);
+        pad = r * (1.0 + 0x1p-40) + mag * 0x1p-40 + 1e-300;
+        const double X0 = x0 - pad, X1 = x1 + pad, Y0 = y0 - pad, Y1 = y1 + pad;
+        const double w = X1 - X0, hgt = Y1 - Y0;
+        // Cells as wide as r or the mean segment length, whichever is
+        // larger (a segment then meets a few cells, a cell a few segments),
+        // at most BUF_GRID_MAX per side.  With many points, finer ones, down
+        // to r / BUF_FINE, of which those inside the distance need no test:
+        // as many as leaves the lists and the cell table small beside the
+        // points (the entries a segment makes are about the area it reaches
+        // over that of a cell).  50M points, 24k segments, 50 m: r / 2 takes
+        // 0.85 ms, r / 3 1.18 (lists and table twice as large), r 1.9.
+        const double lmean = std::isfinite(len_sum) ? len_sum / (double)std::max<int64_t>(V, 1) : 0.0;
+        double cell = std::max(r, std::min(lmean, std::sqrt(w * hgt / (2.0 * (double)std::max<int64_t>(V, 1)))));
+        cell = std::max(cell, std::max(w, hgt) / BUF_GRID_MAX);
+        if (!(cell > 1e-290)) cell = 1.0;
+        const double most = std::min((double)n / BUF_PER_ENTRY, 16777216.0);
+        double fine = std::max({r / BUF_FINE, std::sqrt(w) * std::sqrt(hgt) / std::sqrt((double)n / BUF_PER_CELL),
+                                std::max(w, hgt) / BUF_GRID_MAX});
+        auto entries = [&](double c) {
+            const double reach = pad + 0.75 * c;
+            return (double)V * (2.0 * reach * lmean + 3.15 * reach * reach) / (c * c);
+        };
+        while (fine < cell && !(entries(fine) <= most)) fine *= 1.19;
+        const double coarse_cell = cell;
+        if (fine > 1e-290 && fine < cell && std::isfinite(len_sum)) cell = fine;
+        uint32_t *cnt, *cursor;
+        int64_t G;
+        int lsh, bgrid;
+        double fin;
+        while (true) {
+            grid.X0 = X0; grid.Y0 = Y0; grid.X1 = X1; grid.Y1 = Y1;
+            grid.inv = 1.0 / cell;
+            grid.cell = cell;
+            grid.gx = (int)std::min<double>(BUF_GRID_MAX, std::max(1.0, std::ceil(w * grid.inv)));
+            grid.gy = (int)std::min<double>(BUF_GRID_MAX, std::max(1.0, std::ceil(hgt * grid.inv)));
+            G = (int64_t)grid.gx * grid.gy;
+            // within r whatever the rounding: half a diagonal and the margins less
+            const double eps = mag * 0x1p-40 + 1e-300;
+            fin = r * (1.0 - 0x1p-40) - 4.0 * eps - 0.7071067811865476 * cell * (1.0 + 0x1p-19);
+            // lanes per segment: enough that few segments still fill the chip
+            lsh = 4;
+            while (lsh < 12 && (V << lsh) < (int64_t)cus * 2048) ++lsh;
+            DevBuf &bt = ctx->scratch[S_BUF_TMP];
+            if (ensure(ctx, bg, 256 + sizeof(uint32_t) * (3 * (size_t)(G + 1) + (size_t)(G / 16 + 1))))
+                return SPADE_E_NOMEM;
+            bb = (unsigned long long *)bg.p;
+            cnt = (uint32_t *)((unsigned char *)bg.p + 256);
+            cursor = cnt + (G + 1);
+            off = cursor + (G + 1);
+            cls = off + (G + 1);
+            unsigned long long *tot = bb + 5;   // cleared with the counters behind it
+            SPADE_HIP(ctx, hipMemsetAsync(tot, 0, (size_t)((unsigned char *)off - (unsigned char *)tot), st));
+            bgrid = (int)std::max<int64_t>(1, std::min<int64_t>(((V << lsh) + 255) / 256, (int64_t)cus * 8));
+            hipLaunchKernelGGL(k_buf_bin<false>, dim3(bgrid), dim3(256), 0, st, V, (const Seg *)segs,
+                               (const uint8_t *)valid, grid, pad, fin, lsh, cnt, (const uint32_t *)nullptr,
+                               (uint32_t *)nullptr, (Seg *)nullptr, tot);
+            SPADE_HIP(ctx, hipGetLastError());
+            rocprim::transform_iterator<const uint32_t *, BufListed, uint32_t> listed(cnt, BufListed{});
+            size_t tb = 0;
+            SPADE_HIP(ctx, rocprim::exclusive_scan(nullptr, tb, listed, off, 0u, (size_t)(G + 1),
+                                                   rocprim::plus<uint32_t>(), st));
+            if (ensure(ctx, bt, std::max<size_t>(tb, 1))) return SPADE_E_NOMEM;
+            SPADE_HIP(ctx, rocprim::exclusive_scan(bt.p, tb, listed, off, 0u, (size_t)(G + 1),
+                                                   rocprim::plus<uint32_t>(), st));
+            // the 64-bit entry count first: the cell lists (32 bytes an entry)
+            // stay below 2^28 entries, so their 32-bit offsets are exact
+            hipLaunchKernelGGL(k_buf_class, dim3((unsigned)((G + 4095) / 4096)), dim3(256), 0, st, G,
+                               (const uint32_t *)cnt, (const uint32_t *)off, cls, tot + 1, counts + nseg);
+            SPADE_HIP(ctx, hipGetLastError());
+            SPADE_HIP(ctx, hipMemcpyAsync(h, tot, 2 * sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
+            SPADE_HIP(ctx, hipStreamSynchronize(st));
+            if (h[0] < ((unsigned long long)1 << 28)) break;
+            if (cell == coarse_cell)
+                return set_error(ctx, SPADE_E_TOO_LARGE, "too many (segment, cell) entries: the distance is too large "
+                                                         "for the segments' spread");
+            cell = coarse_cell;   // the estimate was too low
+        }
+        const uint64_t total = h[1];
+        DevBuf &bl = ctx->scratch[S_BUF_LIST];
+        if (ensure(ctx, bl, sizeof(Seg) * (size_t)std::max<uint64_t>(total, 1))) return SPADE_E_NOMEM;
+        list = (Seg *)bl.p;
+        hipLaunchKernelGGL(k_buf_bin<true>, dim3(bgrid), dim3(256), 0, st, V, (const Seg *)segs,
+                           (const uint8_t *)valid, grid, pad, fin, lsh, cnt, (const uint32_t *)off, cursor, list,
+                           (unsigned long long *)nullptr);
+        SPADE_HIP(ctx, hipGetLastError());
+    }
+
+    // result bits and per-segment counts, then the ordered write pass
     const double r2 = r * r;
-    const int64_t wpb = BUF_THREADS / 64;
+    auto bits_pass = [&](auto kern, int threads, int per_cu, size_t lds, const CanvasView &v) -> int {
+        const int64_t wpb = threads / 64;
+        const int grid_b = (int)std::max<int64_t>(1, std::min<int64_t>((nseg + wpb - 1) / wpb, (int64_t)cus * per_cu));
+        lds += (size_t)wpb * BUF_QWAVE;
+        SPADE_HIP(ctx, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+        hipLaunchKernelGGL(kern, dim3(grid_b), dim3(threads), lds, st, v, n, pts->x, pts->y, grid,
+                           (const uint32_t *)cls, (const uint32_t *)off, (const Seg *)list, r, r2, pad, nseg, counts,
+                           bits);
+        SPADE_HIP(ctx, hipGetLastError());
+        return SPADE_OK;
+    };
     if (ctx->timing) SPADE_HIP(ctx, hipEventRecord(ctx->ev[2], st));
     if (cv) {
         const CanvasView &v = cv->view;
         const size_t lds = ((size_t)v.Wc * v.Hc * (v.cbyte ? 1 : 2) + 15) & ~(size_t)15;
-        if (lds + 2048 > 160 * 1024) return set_error(ctx, SPADE_E_HIP, "internal: coarse level exceeds the LDS");
-        const int per_cu = std::max<int>(1, (int)((160 * 1024) / (lds + 2048)));
-        const int grid_b = (int)std::max<int64_t>(1, std::min<int64_t>((nseg + wpb - 1) / wpb, (int64_t)cus * std::min(per_cu, 2)));
-        SPADE_HIP(ctx, hipFuncSetAttribute((const void *)k_buf_bits<true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-        hipLaunchKernelGGL(k_buf_bits<true>, dim3(grid_b), dim3(BUF_THREADS), lds, st, v, n, pts->x, pts->y, grid,
-                           (const Seg *)segs, (const uint32_t *)off, (const Seg *)list, r, r2, pad, nseg, counts,
-                           bits);
+        if (lds + BUF_THREADS / 64 * BUF_QWAVE > 160 * 1024)
+            return set_error(ctx, SPADE_E_HIP, "internal: coarse level exceeds the LDS");
+        if (const int rc = bits_pass(k_buf_bits<true, BUF_THREADS, true, false>, BUF_THREADS, 1, lds, v)) return rc;
+    } else if (n < BUF_FILTER_MIN) {
+        if (const int rc = bits_pass(k_buf_bits<false, 256, true, false>, 256, 4, 0, CanvasView{})) return rc;
     } else {
-        const int grid_b = (int)std::max<int64_t>(1, std::min<int64_t>((nseg + wpb - 1) / wpb, (int64_t)cus * 2));
-        hipLaunchKernelGGL(k_buf_bits<false>, dim3(grid_b), dim3(BUF_THREADS), 0, st, CanvasView{}, n, pts->x, pts->y,
-                           grid, (const Seg *)segs, (const uint32_t *)off, (const Seg *)list, r, r2, pad, nseg,
-                           counts, bits);
+        if (const int rc = bits_pass(k_buf_bits<false, 256, false, false>, 256, 5, 0, CanvasView{})) return rc;
+        if (const int rc = bits_pass(k_buf_bits<false, 256, true, true>, 256, 4, 0, CanvasView{})) return rc;
     }
-    hipLaunchKernelGGL(k_buf_zero, dim3(1), dim3(1), 0, st, counts + nseg);
+    if (!any) hipLaunchKernelGGL(k_buf_zero, dim3(1), dim3(1), 0, st, counts + nseg);
     SPADE_HIP(ctx, hipGetLastError());
     DevBuf &bt = ctx->scratch[S_BUF_TMP];
     size_t tb = 0;
