@@ -56,6 +56,17 @@ __device__ __forceinline__ bool in_disk(double x, double y, double cx, double cy
     return disk_sign_exact(x, y, cx, cy, r) >= 0;
 }
 
+// The filter of the same test alone, for a finite point: inside (1), outside
+// (0) or open (-1).
+__device__ __forceinline__ int in_disk_filter(double x, double y, double cx, double cy, double r2)
+{
+    const double dx = __dsub_rn(x, cx), dy = __dsub_rn(y, cy);
+    const double q = __dadd_rn(__dmul_rn(dx, dx), __dmul_rn(dy, dy));
+    const double s = __dsub_rn(r2, q);
+    const double bound = __dmul_rn(1.7763568394002505e-15, __dadd_rn(r2, q));   // 16 * 2^-53
+    return s > bound ? 1 : -s > bound ? 0 : -1;
+}
+
 // Sign of |a - c|^2 - |b - c|^2, exactly: which of two points is nearer to
 // c (negative: a is nearer).  Same filter and expansion construction.
 __device__ __noinline__ int dist_cmp_exact(double ax, double ay, double bx, double by, double cx, double cy)

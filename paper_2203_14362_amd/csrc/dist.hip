@@ -6,9 +6,10 @@
 //
 // The disks play the paper's constraint canvases: a grid of cells over the
 // disks' union box whose cells list the disks that can reach them (the
-// boundary index of the disk set, ascending disk ids).  Each point reads its
-// cell's list and every listed disk gets the exact closed-disk predicate, so
-// results are exact and independent of the grid.  Pairs come out ascending
+// boundary index of the disk set, ascending disk ids), those that hold the
+// whole cell marked.  A marked disk is a pair of every point of the cell, any
+// other listed one gets the exact closed-disk predicate, so results are exact
+// and independent of the grid.  Pairs come out ascending
 // by (point id, disk id) from the paper's two-step Map (count pass per
 // wavefront segment, scan, write pass), with no sort.  The disk tests of a
 // wavefront's points are spread over its lanes (wave_round), so that a
@@ -34,6 +35,17 @@ constexpr int DJ_ROUNDS = 8;                  // 64-point rounds per wavefront s
 constexpr int64_t DJ_SEG = 64 * DJ_ROUNDS;
 constexpr int DJ_GRID_MAX = 4096;             // cells per grid side
 constexpr int DJ_HIST_MAX = 8192;             // disks counted in LDS
+constexpr uint32_t DJ_FULL = 0x80000000u;     // in a cell's entry: the disk holds the whole cell
+// With many points the cells are finer than the mean radius: down to this
+// fraction of it, while the table has at most n / DJ_PER_CELL cells and the
+// lists about n / DJ_PER_ENTRY entries (both cost a pass each, the points
+// the tests that they save).
+constexpr double DJ_FINE = 4.0, DJ_PER_CELL = 8.0, DJ_PER_ENTRY = 8.0;
+constexpr unsigned DJ_LIST_SORT = 64;         // longest list ordered by one lane
+constexpr int DJ_QCAP = 64;                   // queued points per wavefront
+constexpr int DJ_QWAVE = DJ_QCAP * 28;        // x, y, entries, place: bytes per wavefront
+constexpr uint32_t DJ_STAGE = 512;            // pairs listed per wavefront before they are stored
+constexpr int DJ_GROUP = 4;                   // words of points in flight
 
 struct DiskGrid {
     double X0, Y0, sx, sy;   // cell (floor((x - X0) * sx), floor((y - Y0) * sy))
@@ -53,7 +65,7 @@ __device__ __forceinline__ double radius_of(const DiskArgs &D, int64_t j)
 
 // Validation and union box: flags bit 0 = a non-finite centre or radius or a
 // negative radius; box as order keys (min x, -max x, min y, -max y) of the
-// disks' extents, and the sum of radii.
+// disks' extents, and the sums of the radii and of their squares.
 __device__ __forceinline__ unsigned long long okey_d(double v)
 {
     const unsigned long long b = (unsigned long long)__double_as_longlong(v);
@@ -64,9 +76,9 @@ __global__ __launch_bounds__(256) void k_disks_box(int64_t n, DiskArgs D, unsign
                                                    double *rsum)
 {
     __shared__ unsigned long long s[4][256];
-    __shared__ double sr[256];
+    __shared__ double sr[256], sq[256];
     unsigned long long k0 = ~0ull, k1 = ~0ull, k2 = ~0ull, k3 = ~0ull;
-    double rs = 0.0;
+    double rs = 0.0, rq = 0.0;
     unsigned nb = 0;
     for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < n; j += (int64_t)gridDim.x * blockDim.x) {
         const double cx = D.cx[j], cy = D.cy[j], r = radius_of(D, j);
@@ -74,20 +86,26 @@ __global__ __launch_bounds__(256) void k_disks_box(int64_t n, DiskArgs D, unsign
         k0 = min(k0, okey_d(cx - r)); k1 = min(k1, okey_d(-(cx + r)));
         k2 = min(k2, okey_d(cy - r)); k3 = min(k3, okey_d(-(cy + r)));
         rs += r;
+        rq += r * r;
     }
     if (nb) atomicOr(bad, 1u);
     s[0][threadIdx.x] = k0; s[1][threadIdx.x] = k1; s[2][threadIdx.x] = k2; s[3][threadIdx.x] = k3;
     sr[threadIdx.x] = rs;
+    sq[threadIdx.x] = rq;
     __syncthreads();
     for (int w = 128; w > 0; w >>= 1) {
         if ((int)threadIdx.x < w) {
             for (int q = 0; q < 4; ++q) s[q][threadIdx.x] = min(s[q][threadIdx.x], s[q][threadIdx.x + w]);
             sr[threadIdx.x] += sr[threadIdx.x + w];
+            sq[threadIdx.x] += sq[threadIdx.x + w];
         }
         __syncthreads();
     }
     if (threadIdx.x < 4) atomicMin(&bb[threadIdx.x], s[threadIdx.x][0]);
-    if (threadIdx.x == 0) atomicAdd(rsum, sr[0]);
+    if (threadIdx.x == 0) {
+        atomicAdd(rsum, sr[0]);
+        atomicAdd(rsum + 1, sq[0]);
+    }
 }
 
 // Cells a disk can reach: its box widened by one cell (so that rounding in a
@@ -102,65 +120,148 @@ __device__ __forceinline__ void disk_cells(const DiskGrid &g, double cx, double 
     r1 = (int)fmin((double)(g.H - 1), floor((cy + r - g.Y0) * g.sy) + 1.0);
 }
 
-__device__ __forceinline__ bool cell_reached(const DiskGrid &g, double cx, double cy, double r, int c, int rr)
+// Whether the disk reaches the cell (0: no, 1: yes) or holds all of it (2).
+// lim scales r^2 for the second: below 1 by far more than the rounding of the
+// corners, or negative where a cell is too small beside its coordinates for
+// the quarter cell to cover the rounding of a point's index.
+__device__ __forceinline__ int cell_reached(const DiskGrid &g, double ux, double uy, double cx, double cy, double r,
+                                            double lim, int c, int rr)
 {
+#pragma clang fp contract(off)   // the count and the fill pass decide alike
     // the cell's square enlarged by a quarter cell on every side
-    const double x0 = g.X0 + ((double)c - 0.25) / g.sx, x1 = g.X0 + ((double)c + 1.25) / g.sx;
-    const double y0 = g.Y0 + ((double)rr - 0.25) / g.sy, y1 = g.Y0 + ((double)rr + 1.25) / g.sy;
+    const double x0 = g.X0 + ((double)c - 0.25) * ux, x1 = g.X0 + ((double)c + 1.25) * ux;
+    const double y0 = g.Y0 + ((double)rr - 0.25) * uy, y1 = g.Y0 + ((double)rr + 1.25) * uy;
     const double dx = fmax(fmax(x0 - cx, cx - x1), 0.0), dy = fmax(fmax(y0 - cy, cy - y1), 0.0);
-    return dx * dx + dy * dy <= r * r * 1.0000001;
+    if (!(dx * dx + dy * dy <= r * r * 1.0000001)) return 0;
+    const double fx = fmax(x1 - cx, cx - x0), fy = fmax(y1 - cy, cy - y0);
+    const double f2 = fx * fx + fy * fy, l2 = r * r * lim;
+    return l2 > 1e-280 && f2 <= l2 && f2 < 1e280 ? 2 : 1;
 }
 
-// COUNT: cells per disk.  Otherwise keys (cell << 32 | disk) from off[j].
-template <bool FILL>
-__global__ __launch_bounds__(256) void k_disk_cells(int64_t n, DiskArgs D, DiskGrid g, unsigned long long *count,
-                                                    const unsigned long long *off, unsigned long long *keys)
+// The cells of every disk, a wavefront per disk (the cells of its box are
+// spread over the lanes, so that a disk much larger than the others is not
+// one lane's loop).  CELL_COUNT: cells per disk, and the entries of every
+// cell; CELL_KEYS: the disk's keys cell << 32 | disk (DJ_FULL set where the
+// disk holds the whole cell) from off[j]; CELL_LIST: entries into the cells'
+// lists, in any order.
+enum { CELL_COUNT, CELL_KEYS, CELL_LIST };
+
+template <int STEP>
+__global__ __launch_bounds__(256) void k_disk_cells(int64_t n, DiskArgs D, DiskGrid g, double ux, double uy,
+                                                    double lim, unsigned long long *count, uint32_t *ccnt,
+                                                    const unsigned long long *off, unsigned long long *keys,
+                                                    const uint2 *cells, uint32_t *cell_disk, double2 *centre)
 {
-    for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < n; j += (int64_t)gridDim.x * blockDim.x) {
+    const int lane = threadIdx.x & 63;
+    const unsigned long long below = (1ull << lane) - 1ull;
+    const int64_t nwave = ((int64_t)gridDim.x * blockDim.x) >> 6;
+    for (int64_t j = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6; j < n; j += nwave) {
         const double cx = D.cx[j], cy = D.cy[j], r = radius_of(D, j);
+        if (STEP == CELL_COUNT && lane == 0) centre[j] = double2{cx, cy};
         int c0, c1, r0, r1;
         disk_cells(g, cx, cy, r, c0, c1, r0, r1);
-        unsigned long long m = 0, at = FILL ? off[j] : 0ull;
-        for (int rr = r0; rr <= r1; ++rr)
-            for (int c = c0; c <= c1; ++c) {
-                if (!cell_reached(g, cx, cy, r, c, rr)) continue;
-                if (FILL) keys[at++] = ((unsigned long long)((int64_t)rr * g.W + c) << 32) | (unsigned long long)j;
-                else ++m;
+        unsigned long long at = STEP == CELL_KEYS ? off[j] : 0ull;
+        const int wide = c1 - c0 + 1;
+        const int64_t all = wide > 0 && r1 >= r0 ? (int64_t)wide * (r1 - r0 + 1) : 0;
+        for (int64_t t0 = 0; t0 < all; t0 += 64) {
+            const int64_t t = t0 + lane;
+            const int rr = r0 + (int)(t / wide), c = c0 + (int)(t % wide);
+            const int in = t < all ? cell_reached(g, ux, uy, cx, cy, r, lim, c, rr) : 0;
+            const unsigned long long m = __ballot(in != 0);
+            const int64_t cell = (int64_t)rr * g.W + c;
+            const uint32_t e = (uint32_t)j | (in == 2 ? DJ_FULL : 0u);
+            if (in) {
+                if (STEP == CELL_COUNT) atomicAdd(&ccnt[cell], 1u);
+                if (STEP == CELL_KEYS)
+                    keys[at + __popcll(m & below)] = ((unsigned long long)cell << 32) | (unsigned long long)e;
+                if (STEP == CELL_LIST) cell_disk[cells[cell].x + atomicAdd(&ccnt[cell], 1u)] = e;
             }
-        if (!FILL) count[j] = m;
+            at += __popcll(m);
+        }
+        if (STEP == CELL_COUNT && lane == 0) count[j] = at;
     }
 }
 
-// cell_off[c] = first sorted key of cell c (c = 0 .. ncell).
-__global__ void k_dcell_off(int64_t nk, const unsigned long long *skeys, int64_t ncell, uint32_t *cell_off,
-                            uint32_t *cell_disk)
+// cells[c].x = off[c] (c = 0 .. ncell), *longest = the most entries of a
+// cell if that is more than 32 (nothing asks below; an atomic per wavefront
+// took 50 us); clears the counters for the lists.
+__global__ __launch_bounds__(256) void k_dcell_start(int64_t ncell, const uint32_t *off, uint32_t *ccnt, uint2 *cells,
+                                                     unsigned *longest)
 {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i <= nk; i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t ki = i < nk ? (int64_t)(skeys[i] >> 32) : ncell;
-        const int64_t kp = i == 0 ? -1 : (int64_t)(skeys[i - 1] >> 32);
-        for (int64_t c = kp + 1; c <= ki; ++c) cell_off[c] = (uint32_t)i;
-        if (i < nk) cell_disk[i] = (uint32_t)skeys[i];
+    const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    uint32_t m = 0;
+    if (c < ncell) {
+        m = ccnt[c];
+        ccnt[c] = 0u;
     }
+    if (c <= ncell) cells[c] = uint2{off[c], 0u};
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, d, 64));
+    if ((threadIdx.x & 63) == 0 && m > 32u &&
+        m > __hip_atomic_load(longest, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+        atomicMax(longest, m);
+}
+
+// The entries of sorted keys.
+__global__ void k_dcell_list(int64_t nk, const unsigned long long *skeys, uint32_t *cell_disk)
+{
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nk; i += (int64_t)gridDim.x * blockDim.x)
+        cell_disk[i] = (uint32_t)skeys[i];
+}
+
+// cells[c].y = which of the cell's first 32 entries hold all of it; first,
+// with sort, the entries in order of their disks (insertion: the lists are
+// short).
+__global__ void k_dcell_full(int64_t ncell, uint2 *cells, uint32_t *cell_disk, int sort)
+{
+    const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (c >= ncell) return;
+    const uint32_t k = cells[c].x, have = cells[c + 1].x - k, m = min(have, 32u);
+    if (sort)
+        for (uint32_t i = 1; i < have; ++i) {
+            const uint32_t e = cell_disk[k + i];
+            uint32_t p = i;
+            for (; p > 0; --p) {
+                const uint32_t q = cell_disk[k + p - 1];
+                if ((q & ~DJ_FULL) < (e & ~DJ_FULL)) break;
+                cell_disk[k + p] = q;
+            }
+            if (p != i) cell_disk[k + p] = e;
+        }
+    uint32_t full = 0;
+    for (uint32_t i = 0; i < m; ++i) full |= (cell_disk[k + i] >> 31) << i;
+    if (full) cells[c].y = full;
 }
 
 struct DiskCanvas {
     DiskGrid g;
-    const uint32_t *cell_off, *cell_disk;
+    const uint2 *cells;          // first entry, entries that hold the cell; one past the last cell
+    const uint32_t *cell_disk;   // the cells' entries: disk ids ascending, DJ_FULL
+    const double2 *centre;       // the disks' centres, one load each
+    unsigned longest;            // most entries of a cell (0: at most 32)
     DiskArgs D;
 };
 
-// The candidates of point (x, y): its cell's disks cell_disk[k, k + rem)
-// (none outside the disks' box; NaN fails the test too).
-__device__ __forceinline__ void disk_range(const DiskCanvas &K, double x, double y, uint32_t &k, uint32_t &rem)
+// The cell of a point, or -1 outside the disks' box (NaN fails the test too).
+__device__ __forceinline__ int disk_cell(const DiskCanvas &K, double x, double y)
 {
-    k = 0u;
-    rem = 0u;
-    if (!(K.g.bx0 <= x && x <= K.g.bx1 && K.g.by0 <= y && y <= K.g.by1)) return;
+    if (!(K.g.bx0 <= x && x <= K.g.bx1 && K.g.by0 <= y && y <= K.g.by1)) return -1;
     const int c = min((int)((x - K.g.X0) * K.g.sx), K.g.W - 1);
     const int r = min((int)((y - K.g.Y0) * K.g.sy), K.g.H - 1);
-    const int64_t cell = (int64_t)max(r, 0) * K.g.W + max(c, 0);
-    k = K.cell_off[cell];
-    rem = K.cell_off[cell + 1] - k;
+    return max(r, 0) * K.g.W + max(c, 0);   // at most DJ_GRID_MAX^2 cells
+}
+
+// A cell's record and its neighbour's in one load.
+struct alignas(8) CellPair {
+    uint2 a, b;
+};
+
+// The candidates of point (x, y): its cell's disks cell_disk[k, k + rem).
+__device__ __forceinline__ void disk_range(const DiskCanvas &K, double x, double y, uint32_t &k, uint32_t &rem)
+{
+    const int cell = disk_cell(K, x, y);
+    k = cell < 0 ? 0u : K.cells[cell].x;
+    rem = cell < 0 ? 0u : K.cells[cell + 1].x - k;
 }
 
 // The (point, disk) pairs of a wavefront's points with the disk tests
@@ -184,8 +285,12 @@ __device__ __forceinline__ void disk_wave_walk(const DiskCanvas &K, double x, do
         uint32_t j = 0u;
         if ((uint32_t)lane < w.ntake) {
             j = K.cell_disk[ok + ((uint32_t)lane - w.opre)];
-            const double rj = radius_of(K.D, j);
-            h = in_disk(ox, oy, K.D.cx[j], K.D.cy[j], rj, rj * rj);
+            h = (j & DJ_FULL) != 0u;
+            j &= ~DJ_FULL;
+            if (!h) {
+                const double rj = radius_of(K.D, j);
+                h = in_disk(ox, oy, K.D.cx[j], K.D.cy[j], rj, rj * rj);
+            }
         }
         const unsigned long long hm = __ballot(h);
         if (h) pair(w.o, obase + ocnt + (uint32_t)__popcll(hm & wave_round_before(w, lane)), j);
@@ -196,16 +301,255 @@ __device__ __forceinline__ void disk_wave_walk(const DiskCanvas &K, double x, do
     }
 }
 
-// MODE 0: counts per wavefront segment (and, with pcount, the pairs of every
-// point, so that the write pass walks each point's candidates once); 1: pairs
-// written from offs[s] on (positions at or beyond cap are not written); 2:
-// per-disk counts.
+// Which of the first 32 entries of this lane's cell (from k on) whose bits are
+// in pm hold its point, the tests balanced over the lanes (wave_round).
+// Without EXACT, a test that the floating-point filter leaves open sets `open`
+// (for the whole wavefront) and counts as outside.  Called by every lane of
+// the wavefront.
+template <bool EXACT>
+__device__ __forceinline__ uint32_t disk_mask_walk(const DiskCanvas &K, double x, double y, uint32_t k, uint32_t pm,
+                                                   int lane, bool &open)
+{
+    uint32_t hits = 0u, rem = (uint32_t)__popc(pm);
+    while (__ballot(rem != 0u)) {
+        const WaveRound w = wave_round(rem, lane);
+        const uint32_t ok = __shfl(k, w.o, 64);
+        uint32_t opm = __shfl(pm, w.o, 64);
+        const double ox = __shfl(x, w.o, 64), oy = __shfl(y, w.o, 64);
+        int h = 0;
+        if ((uint32_t)lane < w.ntake) {
+            for (uint32_t t = (uint32_t)lane - w.opre; t != 0u; --t) opm &= opm - 1u;
+            const uint32_t j = K.cell_disk[ok + (uint32_t)__ffs(opm) - 1u] & ~DJ_FULL;
+            const double rj = radius_of(K.D, j);
+            const double2 c = K.centre[j];
+            h = EXACT ? (in_disk(ox, oy, c.x, c.y, rj, rj * rj) ? 1 : 0) : in_disk_filter(ox, oy, c.x, c.y, rj * rj);
+        }
+        const unsigned long long hm = __ballot(h > 0);
+        if (!EXACT && __ballot(h < 0)) open = true;
+        const uint32_t len = wave_round_len(w);
+        uint32_t got = len ? (uint32_t)(hm >> w.pre) : 0u;
+        for (uint32_t t = 0; t < len; ++t) {
+            const uint32_t low = pm & (0u - pm);
+            if (got & 1u) hits |= low;
+            got >>= 1;
+            pm ^= low;
+        }
+        rem -= len;
+    }
+    return hits;
+}
+
+// Count pass: pairs per wavefront segment, and with pm every point's pairs as
+// (first entry of its cell, mask of the entries that hold it), or (all ones,
+// number) for a cell of more than 32 entries, so that the write pass reads 8
+// bytes per point and tests nothing.  A point's entries that hold its whole
+// cell are pairs as they stand; points with others are queued in LDS and
+// tested 64 at a time.  Bound by the rate of L2 requests (the cells, and an
+// entry and a centre per test): 30M points, 10,000 disks of 300 m, 0.52 ms
+// with cells of 75 m (0.95 with cells of 300 m and every candidate tested a
+// word at a time).  The exact test costs registers (106 against 90), so a
+// first pass (EXACT false) decides by the filter and leaves DJ_OPEN as the
+// count of a segment in which a test stayed open, a second one (EXACT and
+// ONLY_OPEN) does those segments again.
+constexpr unsigned long long DJ_OPEN = ~0ull;
+constexpr int64_t DJ_FILTER_MIN = 1 << 20;   // points from which the second launch (5 us) pays
+
+template <bool EXACT, bool ONLY_OPEN>
+__global__ __launch_bounds__(DJ_THREADS) void k_dj_count(DiskCanvas K, int64_t n, const double *X, const double *Y,
+                                                         int64_t nseg, unsigned long long *counts, uint2 *pm)
+{
+    static_assert(DJ_ROUNDS % DJ_GROUP == 0 && DJ_SEG <= 65536 && DJ_QWAVE % 8 == 0, "queue layout");
+    __shared__ __align__(16) unsigned char smem[DJ_THREADS / 64 * DJ_QWAVE];
+    const int lane = threadIdx.x & 63;
+    const unsigned long long below = (1ull << lane) - 1ull;
+    unsigned char *q = smem + (threadIdx.x >> 6) * DJ_QWAVE;
+    double *qx = (double *)q, *qy = qx + DJ_QCAP;
+    uint32_t *qk = (uint32_t *)(qy + DJ_QCAP), *qf = qk + DJ_QCAP, *qi = qf + DJ_QCAP;
+    const int64_t nwave = ((int64_t)gridDim.x * DJ_THREADS) >> 6;
+    for (int64_t sg = ((int64_t)blockIdx.x * DJ_THREADS + threadIdx.x) >> 6; sg < nseg; sg += nwave) {
+        if (ONLY_OPEN && counts[sg] != DJ_OPEN) continue;
+        const int64_t i0 = sg * DJ_SEG;
+        bool open = false;              // wave-uniform
+        unsigned long long total = 0;   // this lane's pairs
+        uint32_t qn = 0;                // wave-uniform
+        auto drain = [&]() {
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            double x = NAN, y = NAN;
+            uint32_t k = 0u, rem = 0u, full = 0u, id = 0u;
+            if (lane < (int)qn) {
+                x = qx[lane];
+                y = qy[lane];
+                k = qk[lane];
+                full = qf[lane];
+                id = qi[lane] & 0xffffu;
+                rem = qi[lane] >> 16;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            const bool many = rem > 32u;
+            const uint32_t all = rem >= 32u ? ~0u : (1u << rem) - 1u;
+            uint32_t hits = full | disk_mask_walk<EXACT>(K, x, y, k, many ? 0u : all & ~full, lane, open);
+            uint32_t m = (uint32_t)__popc(hits);
+            if (!EXACT && __ballot(many)) open = true;
+            if (EXACT && __ballot(many)) {
+                uint32_t cnt;
+                disk_range(K, x, y, k, rem);   // the queue holds no more than 33
+                disk_wave_walk(K, x, y, k, many ? rem : 0u, 0u, lane, cnt, [](int, uint32_t, uint32_t) {});
+                if (many) {
+                    k = ~0u;
+                    hits = m = cnt;
+                }
+            }
+            if (lane < (int)qn) {
+                total += m;
+                if (pm) pm[i0 + id] = uint2{k, hits};
+            }
+            qn = 0;
+        };
+#pragma nounroll
+        for (int g0 = 0; g0 < DJ_ROUNDS; g0 += DJ_GROUP) {
+            double xs[DJ_GROUP], ys[DJ_GROUP];
+#pragma unroll
+            for (int k = 0; k < DJ_GROUP; ++k) {
+                const int64_t i = i0 + 64 * (g0 + k) + lane;
+                xs[k] = i < n ? __builtin_nontemporal_load(X + i) : NAN;
+                ys[k] = i < n ? __builtin_nontemporal_load(Y + i) : NAN;
+            }
+            uint2 a[DJ_GROUP];
+            uint32_t rem[DJ_GROUP];
+#pragma unroll
+            for (int k = 0; k < DJ_GROUP; ++k) {
+                const int c = disk_cell(K, xs[k], ys[k]);
+                const CellPair p = c >= 0 ? *(const CellPair *)(K.cells + c) : CellPair{{0u, 0u}, {0u, 0u}};
+                a[k] = p.a;
+                rem[k] = p.b.x - p.a.x;
+            }
+#pragma unroll
+            for (int k = 0; k < DJ_GROUP; ++k) {
+                const bool test = rem[k] > 32u || (uint32_t)__popc(a[k].y) != rem[k];
+                const int64_t i = i0 + 64 * (g0 + k) + lane;
+                if (!test) {
+                    total += rem[k];
+                    if (pm && i < n) pm[i] = a[k];
+                }
+                const unsigned long long mask = __ballot(test);
+                const uint32_t nnew = (uint32_t)__popcll(mask);
+                if (nnew == 0) continue;
+                if (qn + nnew > (uint32_t)DJ_QCAP) drain();
+                if (test) {
+                    const uint32_t slot = qn + (uint32_t)__popcll(mask & below);
+                    qx[slot] = xs[k];
+                    qy[slot] = ys[k];
+                    qk[slot] = a[k].x;
+                    qf[slot] = a[k].y;
+                    qi[slot] = (uint32_t)(64 * (g0 + k) + lane) | (min(rem[k], 33u) << 16);
+                }
+                qn += nnew;
+            }
+        }
+        if (qn) drain();
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) total += (unsigned long long)__shfl_xor((long long)total, d, 64);
+        if (lane == 0) counts[sg] = !EXACT && open ? DJ_OPEN : total;
+    }
+}
+
+// Write pass from the count pass's masks.  The entries of a segment's pairs
+// are listed in LDS in their order and then looked up and stored 64 at a
+// time: 24M pairs of 30M points in 176 us, where every lane looking up and storing
+// its own point's pairs one after the other took 240 us.  A word with more
+// pairs than the list is stored by its lanes; points of cells with more than
+// 32 entries are walked again.
+__global__ __launch_bounds__(DJ_THREADS) void k_dj_write(DiskCanvas K, int64_t n, const double *X, const double *Y,
+                                                         int64_t nseg, const unsigned long long *offs,
+                                                         const uint2 *pm, uint32_t *out_pt, uint32_t *out_disk,
+                                                         int64_t cap)
+{
+    __shared__ uint2 stage[DJ_THREADS / 64][DJ_STAGE];
+    const int lane = threadIdx.x & 63;
+    uint2 *list = stage[threadIdx.x >> 6];
+    const int64_t nwave = ((int64_t)gridDim.x * DJ_THREADS) >> 6;
+    for (int64_t sg = ((int64_t)blockIdx.x * DJ_THREADS + threadIdx.x) >> 6; sg < nseg; sg += nwave) {
+        const int64_t i0 = sg * DJ_SEG + lane;
+        uint2 e[DJ_ROUNDS];
+#pragma unroll
+        for (int k = 0; k < DJ_ROUNDS; ++k) e[k] = i0 + 64 * k < n ? pm[i0 + 64 * k] : uint2{0u, 0u};
+        int64_t pos = (int64_t)offs[sg];   // of the list's first pair
+        uint32_t have = 0;                 // pairs listed
+        auto flush = [&]() {
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            for (uint32_t t = (uint32_t)lane; t < have; t += 64) {
+                const uint2 v = list[t];
+                const uint32_t j = K.cell_disk[v.x] & ~DJ_FULL;
+                if (pos + t < cap) {
+                    out_pt[pos + t] = v.y;
+                    out_disk[pos + t] = j;
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            pos += have;
+            have = 0;
+        };
+#pragma unroll
+        for (int k = 0; k < DJ_ROUNDS; ++k) {
+            const int64_t i = i0 + 64 * k;
+            const bool many = e[k].x == ~0u;
+            uint32_t bits = many ? 0u : e[k].y;
+            const uint32_t m = many ? e[k].y : (uint32_t)__popc(bits);
+            uint32_t inc = m;
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const uint32_t t = __shfl_up(inc, d, 64);
+                if (lane >= d) inc += t;
+            }
+            const uint32_t tot = __shfl(inc, 63, 64);
+            const bool direct = tot > DJ_STAGE || __ballot(many) != 0ull;
+            if (direct || have + tot > DJ_STAGE) flush();
+            uint32_t at = have + inc - m;
+            while (bits) {
+                const uint32_t x = e[k].x + (uint32_t)__ffs(bits) - 1u;
+                bits &= bits - 1u;
+                if (!direct) {
+                    list[at] = uint2{x, (uint32_t)i};
+                } else if (pos + at < cap) {
+                    out_pt[pos + at] = (uint32_t)i;
+                    out_disk[pos + at] = K.cell_disk[x] & ~DJ_FULL;
+                }
+                ++at;
+            }
+            if (!direct) {
+                have += tot;
+                continue;
+            }
+            if (__ballot(many)) {
+                const double x = many ? X[i] : NAN, y = many ? Y[i] : NAN;
+                uint32_t c0, rem, m2;
+                disk_range(K, x, y, c0, rem);
+                const int64_t w0 = sg * DJ_SEG + 64 * k;
+                disk_wave_walk(K, x, y, c0, rem, inc - m, lane, m2, [&](int o, uint32_t slot, uint32_t j) {
+                    if (pos + slot < cap) {
+                        out_pt[pos + slot] = (uint32_t)(w0 + o);
+                        out_disk[pos + slot] = j;
+                    }
+                });
+            }
+            pos += tot;
+        }
+        if (have) flush();
+    }
+}
+
+// Walks that keep nothing.  MODE 1: pairs written from offs[s] on (positions
+// at or beyond cap are not written), where the count pass's masks had no
+// room; 2: per-disk counts.
 template <int MODE>
 __global__ __launch_bounds__(DJ_THREADS) void k_djoin(DiskCanvas K, int64_t n, const double *X, const double *Y,
-                                                      int64_t nseg, unsigned long long *counts,
-                                                      const unsigned long long *offs, uint32_t *out_pt,
+                                                      int64_t nseg, const unsigned long long *offs, uint32_t *out_pt,
                                                       uint32_t *out_disk, int64_t cap, int64_t ndisk,
-                                                      unsigned long long *dcount, uint32_t *pcount)
+                                                      unsigned long long *dcount)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     uint32_t *hist = (uint32_t *)smem;
@@ -237,13 +581,7 @@ __global__ __launch_bounds__(DJ_THREADS) void k_djoin(DiskCanvas K, int64_t n, c
                 });
                 continue;
             }
-            const int64_t ip = i0 + 64 * k;
-            if (MODE == 1 && pcount) {
-                m = ip < n ? pcount[ip] : 0u;   // the count pass's pairs of this point
-            } else {
-                disk_wave_walk(K, xs[k], ys[k], c0, rem, 0u, lane, m, [](int, uint32_t, uint32_t) {});
-                if (MODE == 0 && pcount && ip < n) pcount[ip] = m;
-            }
+            disk_wave_walk(K, xs[k], ys[k], c0, rem, 0u, lane, m, [](int, uint32_t, uint32_t) {});
             uint32_t inc = m;
 #pragma unroll
             for (int d = 1; d < 64; d <<= 1) {
@@ -251,7 +589,7 @@ __global__ __launch_bounds__(DJ_THREADS) void k_djoin(DiskCanvas K, int64_t n, c
                 if (lane >= d) inc += t;
             }
             const uint32_t tot = __shfl(inc, 63, 64);
-            if (MODE == 1 && tot) {
+            if (tot) {
                 // again, writing each pair at pos + (pairs of earlier lanes) + rank
                 const int64_t w0 = sg * DJ_SEG + 64 * k;
                 uint32_t m2;
@@ -266,7 +604,6 @@ __global__ __launch_bounds__(DJ_THREADS) void k_djoin(DiskCanvas K, int64_t n, c
             }
             pos += tot;
         }
-        if (MODE == 0 && lane == 0) counts[sg] = pos;
     }
     if (MODE == 2 && ldsh) {
         __syncthreads();
@@ -295,7 +632,7 @@ static int dj_bits(uint64_t v)
 
 // Builds the disk canvas in ctx scratch (cell lists valid until the next
 // call on ctx).
-static int build_disk_canvas(spade_ctx *ctx, const spade_disks *dk, DiskCanvas &K)
+static int build_disk_canvas(spade_ctx *ctx, const spade_disks *dk, int64_t npts, DiskCanvas &K)
 {
     hipStream_t st = ctx->stream;
     const int64_t n = dk->n;
@@ -307,9 +644,9 @@ static int build_disk_canvas(spade_ctx *ctx, const spade_disks *dk, DiskCanvas &
     if (ensure(ctx, bb, 128)) return SPADE_E_NOMEM;
     unsigned long long *dbb = (unsigned long long *)bb.p;
     unsigned *bad = (unsigned *)(dbb + 4);
-    double *rsum = (double *)(dbb + 6);
-    // box keys start at all-ones, the flag and the radius sum at zero
-    hipLaunchKernelGGL(k_dj_zero, dim3(1), dim3(64), 0, st, (int64_t)8, dbb);
+    double *rsum = (double *)(dbb + 6);   // radii, squares
+    // box keys start at all-ones; the flag, the sums and the longest list at zero
+    hipLaunchKernelGGL(k_dj_zero, dim3(1), dim3(64), 0, st, (int64_t)9, dbb);
     SPADE_HIP(ctx, hipGetLastError());
     SPADE_HIP(ctx, hipMemsetAsync(dbb, 0xff, 32, st));
     hipLaunchKernelGGL(k_disks_box, dim3(dj_grid(n, 1024)), dim3(256), 0, st, n, K.D, dbb, bad, rsum);
@@ -325,64 +662,102 @@ static int build_disk_canvas(spade_ctx *ctx, const spade_disks *dk, DiskCanvas &
         std::memcpy(&d, &b, sizeof d);
         return d;
     };
-    double mr;
+    double mr, rsq;
     std::memcpy(&mr, h + 6, sizeof mr);
-    mr /= (double)n;
+    std::memcpy(&rsq, h + 7, sizeof rsq);
     DiskGrid &g = K.g;
     g.bx0 = from_key(h[0]);
     g.bx1 = -from_key(h[1]);
     g.by0 = from_key(h[2]);
     g.by1 = -from_key(h[3]);
     // cells about the mean radius on a side (at most DJ_GRID_MAX per side,
-    // at least one), so a disk reaches a few cells
-    const double w = g.bx1 - g.bx0, hgt = g.by1 - g.by0;
-    const double cell = std::max(mr, std::max(w, hgt) / DJ_GRID_MAX);
+    // at least one), so a disk reaches a few cells; with many points, finer
+    // ones.  An estimate of the finer lists' entries: the cells that meet a
+    // disk widened by a cell's quarter and half its diagonal.
+    const double w = g.bx1 - g.bx0, hgt = g.by1 - g.by0, sum_r = mr;
+    mr /= (double)n;
+    auto entries = [&](double c) {
+        return 3.15 * (rsq + 2.2 * c * sum_r + 1.21 * c * c * (double)n) / (c * c);
+    };
+    const double least = std::max(w, hgt) / DJ_GRID_MAX;
+    double cell = std::max(mr, least);
+    double fine = std::max({mr / DJ_FINE, least, std::sqrt(w) * std::sqrt(hgt) / std::sqrt((double)npts / DJ_PER_CELL)});
+    while (fine < cell && !(entries(fine) <= std::min((double)npts / DJ_PER_ENTRY, 268435456.0))) fine *= 1.19;
+    if (fine > 0.0 && fine < cell) cell = fine;
     g.W = (w > 0 && cell > 0) ? (int)std::min<double>(DJ_GRID_MAX, std::max(1.0, std::ceil(w / cell))) : 1;
     g.H = (hgt > 0 && cell > 0) ? (int)std::min<double>(DJ_GRID_MAX, std::max(1.0, std::ceil(hgt / cell))) : 1;
     g.X0 = g.bx0;
     g.Y0 = g.by0;
     g.sx = w > 0 ? g.W / w : 0.0;
     g.sy = hgt > 0 ? g.H / hgt : 0.0;
+    const double ux = w > 0 ? w / g.W : 0.0, uy = hgt > 0 ? hgt / g.H : 0.0;
+    const double mag = std::fabs(g.bx0) + std::fabs(g.bx1) + std::fabs(g.by0) + std::fabs(g.by1);
+    const double lim = std::min(ux, uy) > mag * 0x1p-40 ? 1.0 - 1e-7 : -1.0;
     const int64_t ncell = (int64_t)g.W * g.H;
-    // (cell, disk) keys: count, scan, fill, sort
-    DevBuf &bc = ctx->scratch[S_NROWS], &bo = ctx->scratch[S_ROWOFF];
-    if (ensure(ctx, bc, 8 * (size_t)(n + 1)) || ensure(ctx, bo, 8 * (size_t)(n + 1))) return SPADE_E_NOMEM;
+    // Cell lists: count, scan, fill in any order, order each list.  Where a
+    // list is longer than DJ_LIST_SORT entries, (cell, disk) keys are sorted
+    // instead (30 launches for a million of them: 140 us, against 25).
+    DevBuf &bc = ctx->scratch[S_NROWS], &bo = ctx->scratch[S_ROWOFF], &bw = ctx->scratch[S_VALS2];
+    if (ensure(ctx, bc, 8 * (size_t)(n + 1)) || ensure(ctx, bo, 8 * (size_t)(n + 1)) ||
+        ensure(ctx, bw, sizeof(double2) * (size_t)n + (sizeof(uint2) + 2 * sizeof(uint32_t)) * (size_t)(ncell + 1)))
+        return SPADE_E_NOMEM;
     unsigned long long *cnt = (unsigned long long *)bc.p, *off = (unsigned long long *)bo.p;
-    hipLaunchKernelGGL(k_disk_cells<false>, dim3(dj_grid(n)), dim3(256), 0, st, n, K.D, g, cnt, nullptr, nullptr);
+    double2 *centre = (double2 *)bw.p;
+    uint2 *cells = (uint2 *)(centre + n);
+    uint32_t *ccnt = (uint32_t *)(cells + (ncell + 1)), *coff = ccnt + (ncell + 1);
+    unsigned *longest = (unsigned *)(dbb + 8);
+    const int64_t most = (int64_t)0x7fffffff / 64;   // a wavefront per disk
+    const dim3 dgrid(dj_grid(std::min(n, most) * 64)), cgrid((unsigned)(ncell / 256 + 1));
+    auto disks = [&](auto kern, unsigned long long *keys, uint32_t *list) {
+        hipLaunchKernelGGL(kern, dgrid, dim3(256), 0, st, n, K.D, g, ux, uy, lim, cnt, ccnt,
+                           (const unsigned long long *)off, keys, (const uint2 *)cells, list, centre);
+    };
+    DevBuf &cub = ctx->scratch[S_CUBTMP];
+    size_t tb = 0, tc = 0;
+    SPADE_HIP(ctx, hipMemsetAsync(ccnt, 0, sizeof(uint32_t) * (size_t)(ncell + 1), st));
+    disks(k_disk_cells<CELL_COUNT>, nullptr, nullptr);
     hipLaunchKernelGGL(k_dj_zero, dim3(1), dim3(64), 0, st, (int64_t)1, cnt + n);
     SPADE_HIP(ctx, hipGetLastError());
-    DevBuf &cub = ctx->scratch[S_CUBTMP];
-    size_t tb = 0;
     SPADE_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(nullptr, tb, cnt, off, (int)(n + 1), st));
-    if (ensure(ctx, cub, std::max<size_t>(tb, 1))) return SPADE_E_NOMEM;
+    SPADE_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(nullptr, tc, ccnt, coff, (int)(ncell + 1), st));
+    if (ensure(ctx, cub, std::max<size_t>({tb, tc, 1}))) return SPADE_E_NOMEM;
     SPADE_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(cub.p, tb, cnt, off, (int)(n + 1), st));
+    SPADE_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(cub.p, tc, ccnt, coff, (int)(ncell + 1), st));
+    hipLaunchKernelGGL(k_dcell_start, cgrid, dim3(256), 0, st, ncell, (const uint32_t *)coff, ccnt, cells, longest);
+    SPADE_HIP(ctx, hipGetLastError());
     SPADE_HIP(ctx, hipMemcpyAsync(h, off + n, 8, hipMemcpyDeviceToHost, st));
+    SPADE_HIP(ctx, hipMemcpyAsync(h + 1, longest, 4, hipMemcpyDeviceToHost, st));
     SPADE_HIP(ctx, hipStreamSynchronize(st));
     const int64_t nk = (int64_t)h[0];
     if (nk >= (int64_t)0xffffffffLL) return set_error(ctx, SPADE_E_UNSUPPORTED, "too many (cell, disk) entries");
-    DevBuf &bk = ctx->scratch[S_KEYS], &bk2 = ctx->scratch[S_KEYS2], &bl = ctx->scratch[S_VALS];
-    if (ensure(ctx, bk, 8 * (size_t)std::max<int64_t>(nk, 1)) || ensure(ctx, bk2, 8 * (size_t)std::max<int64_t>(nk, 1)) ||
-        ensure(ctx, bl, 4 * (size_t)(ncell + 1) + 4 * (size_t)std::max<int64_t>(nk, 1) + 64))
-        return SPADE_E_NOMEM;
-    uint32_t *cell_off = (uint32_t *)bl.p;
-    uint32_t *cell_disk = cell_off + (ncell + 1);
-    if (nk > 0) {
-        hipLaunchKernelGGL(k_disk_cells<true>, dim3(dj_grid(n)), dim3(256), 0, st, n, K.D, g, nullptr, off,
-                           (unsigned long long *)bk.p);
+    const bool sorted = (unsigned)h[1] > DJ_LIST_SORT;
+    DevBuf &bl = ctx->scratch[S_VALS];
+    if (ensure(ctx, bl, 4 * (size_t)std::max<int64_t>(nk, 1) + 64)) return SPADE_E_NOMEM;
+    uint32_t *cell_disk = (uint32_t *)bl.p;
+    if (sorted) {
+        DevBuf &bk = ctx->scratch[S_KEYS], &bk2 = ctx->scratch[S_KEYS2];
+        if (ensure(ctx, bk, 8 * (size_t)nk) || ensure(ctx, bk2, 8 * (size_t)nk)) return SPADE_E_NOMEM;
+        disks(k_disk_cells<CELL_KEYS>, (unsigned long long *)bk.p, nullptr);
         SPADE_HIP(ctx, hipGetLastError());
+        // by cell alone: the keys are filled disk by disk and the sort is stable
         const int kb = 32 + std::max(1, dj_bits((uint64_t)ncell));
         tb = 0;
         SPADE_HIP(ctx, hipcub::DeviceRadixSort::SortKeys(nullptr, tb, (const unsigned long long *)bk.p,
-                                                         (unsigned long long *)bk2.p, (int)nk, 0, kb, st));
+                                                         (unsigned long long *)bk2.p, (int)nk, 32, kb, st));
         if (ensure(ctx, cub, std::max<size_t>(tb, 1))) return SPADE_E_NOMEM;
         SPADE_HIP(ctx, hipcub::DeviceRadixSort::SortKeys(cub.p, tb, (const unsigned long long *)bk.p,
-                                                         (unsigned long long *)bk2.p, (int)nk, 0, kb, st));
+                                                         (unsigned long long *)bk2.p, (int)nk, 32, kb, st));
+        hipLaunchKernelGGL(k_dcell_list, dim3(dj_grid(nk)), dim3(256), 0, st, nk, (const unsigned long long *)bk2.p,
+                           cell_disk);
+    } else {
+        disks(k_disk_cells<CELL_LIST>, nullptr, cell_disk);
     }
-    hipLaunchKernelGGL(k_dcell_off, dim3(dj_grid(nk + 1)), dim3(256), 0, st, nk, (const unsigned long long *)bk2.p,
-                       ncell, cell_off, cell_disk);
+    hipLaunchKernelGGL(k_dcell_full, cgrid, dim3(256), 0, st, ncell, cells, cell_disk, sorted ? 0 : 1);
     SPADE_HIP(ctx, hipGetLastError());
-    K.cell_off = cell_off;
+    K.cells = cells;
     K.cell_disk = cell_disk;
+    K.centre = centre;
+    K.longest = (unsigned)h[1];
     return SPADE_OK;
 }
 
@@ -422,7 +797,7 @@ int distance_join(spade_ctx *ctx, const spade_points *pts, const spade_disks *dk
         return SPADE_OK;
     }
     DiskCanvas K;
-    if ((rc = build_disk_canvas(ctx, dk, K))) return rc;
+    if ((rc = build_disk_canvas(ctx, dk, n, K))) return rc;
     const int64_t nseg = (n + DJ_SEG - 1) / DJ_SEG;
     const int cus = num_cus_dj(ctx->device);
     const int grid = (int)std::max<int64_t>(1, std::min<int64_t>((nseg + DJ_THREADS / 64 - 1) / (DJ_THREADS / 64),
@@ -431,8 +806,7 @@ int distance_join(spade_ctx *ctx, const spade_points *pts, const spade_disks *dk
     if (counting) {
         const size_t lds = m <= DJ_HIST_MAX ? 4 * (size_t)m : 16;
         hipLaunchKernelGGL(k_djoin<2>, dim3(grid), dim3(DJ_THREADS), lds, st, K, n, pts->x, pts->y, nseg, nullptr,
-                           nullptr, nullptr, nullptr, (int64_t)0, m, (unsigned long long *)out_counts,
-                           (uint32_t *)nullptr);
+                           nullptr, nullptr, (int64_t)0, m, (unsigned long long *)out_counts);
         SPADE_HIP(ctx, hipGetLastError());
         if (ctx->timing) SPADE_HIP(ctx, hipEventRecord(ctx->ev[3], st));
         SPADE_HIP(ctx, hipStreamSynchronize(st));
@@ -441,16 +815,24 @@ int distance_join(spade_ctx *ctx, const spade_points *pts, const spade_disks *dk
     DevBuf &lb = ctx->scratch[S_LOOKBACK];
     if (ensure(ctx, lb, sizeof(unsigned long long) * 2 * (size_t)(nseg + 1))) return SPADE_E_NOMEM;
     unsigned long long *counts = (unsigned long long *)lb.p, *offs = counts + (nseg + 1);
-    // pairs per point, kept by the count pass for the write pass (without the
-    // room, the write pass counts again)
+    // every point's pairs, kept by the count pass for the write pass (without
+    // the room, the write pass tests again)
     DevBuf &pb = ctx->scratch[S_BITS];
-    uint32_t *pcount = nullptr;
+    uint2 *pm = nullptr;
     if (cap > 0) {
-        if (ensure(ctx, pb, sizeof(uint32_t) * (size_t)n) == SPADE_OK) pcount = (uint32_t *)pb.p;
+        if (ensure(ctx, pb, sizeof(uint2) * (size_t)n) == SPADE_OK) pm = (uint2 *)pb.p;
         else ctx->err.clear();
     }
-    hipLaunchKernelGGL(k_djoin<0>, dim3(grid), dim3(DJ_THREADS), 0, st, K, n, pts->x, pts->y, nseg, counts, nullptr,
-                       nullptr, nullptr, (int64_t)0, m, nullptr, pcount);
+    auto count = [&](auto kern, int per_cu) {
+        hipLaunchKernelGGL(kern, dim3(std::min(grid, cus * per_cu)), dim3(DJ_THREADS), 0, st, K, n, pts->x, pts->y, nseg,
+                           counts, pm);
+    };
+    if (n < DJ_FILTER_MIN || K.longest > 32) {   // longer lists always take the exact walk
+        count(k_dj_count<true, false>, 4);
+    } else {
+        count(k_dj_count<false, false>, 5);
+        count(k_dj_count<true, true>, 4);
+    }
     hipLaunchKernelGGL(k_dj_zero, dim3(1), dim3(64), 0, st, (int64_t)1, counts + nseg);
     SPADE_HIP(ctx, hipGetLastError());
     DevBuf &cub = ctx->scratch[S_CUBTMP];
@@ -459,8 +841,12 @@ int distance_join(spade_ctx *ctx, const spade_points *pts, const spade_disks *dk
     if (ensure(ctx, cub, std::max<size_t>(tb, 1))) return SPADE_E_NOMEM;
     SPADE_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(cub.p, tb, counts, offs, (int)(nseg + 1), st));
     if (cap > 0) {
-        hipLaunchKernelGGL(k_djoin<1>, dim3(grid), dim3(DJ_THREADS), 0, st, K, n, pts->x, pts->y, nseg, nullptr, offs,
-                           out_pt, out_disk, cap, m, nullptr, pcount);
+        if (pm)
+            hipLaunchKernelGGL(k_dj_write, dim3(std::min(grid, cus * 5)), dim3(DJ_THREADS), 0, st, K, n, pts->x, pts->y, nseg,
+                               (const unsigned long long *)offs, (const uint2 *)pm, out_pt, out_disk, cap);
+        else
+            hipLaunchKernelGGL(k_djoin<1>, dim3(grid), dim3(DJ_THREADS), 0, st, K, n, pts->x, pts->y, nseg, offs, out_pt,
+                               out_disk, cap, m, nullptr);
         SPADE_HIP(ctx, hipGetLastError());
     }
     if (ctx->timing) SPADE_HIP(ctx, hipEventRecord(ctx->ev[3], st));
