@@ -562,7 +562,7 @@ int buffer_select(spade_ctx *ctx, const spade_canvas *cv, const spade_points *pt
             const double eps = mag * 0x1p-40 + 1e-300;
             fin = r * (1.0 - 0x1p-40) - 4.0 * eps - 0.7071067811865476 * cell * (1.0 + 0x1p-19);
             // lanes per segment: enough that few segments still fill the chip
-            lsh = 4;
+            lsh = 0;
             while (lsh < 12 && (V << lsh) < (int64_t)cus * 2048) ++lsh;
             DevBuf &bt = ctx->scratch[S_BUF_TMP];
             if (ensure(ctx, bg, 256 + sizeof(uint32_t) * (3 * (size_t)(G + 1) + (size_t)(G / 16 + 1))))

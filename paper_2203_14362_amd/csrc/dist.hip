@@ -40,6 +40,7 @@ constexpr uint32_t DJ_FULL = 0x80000000u;     // in a cell's entry: the disk hol
 // fraction of it, while the table has at most n / DJ_PER_CELL cells and the
 // lists about n / DJ_PER_ENTRY entries (both cost a pass each, the points
 // the tests that they save).
+constexpr double DJ_COVER = 0.0625;           // disks over a position on average, at least, for that
 constexpr double DJ_FINE = 4.0, DJ_PER_CELL = 8.0, DJ_PER_ENTRY = 8.0;
 constexpr unsigned DJ_LIST_SORT = 64;         // longest list ordered by one lane
 constexpr int DJ_QCAP = 64;                   // queued points per wavefront
@@ -140,45 +141,47 @@ __device__ __forceinline__ int cell_reached(const DiskGrid &g, double ux, double
 
 // The cells of every disk, a wavefront per disk (the cells of its box are
 // spread over the lanes, so that a disk much larger than the others is not
-// one lane's loop).  CELL_COUNT: cells per disk, and the entries of every
-// cell; CELL_KEYS: the disk's keys cell << 32 | disk (DJ_FULL set where the
-// disk holds the whole cell) from off[j]; CELL_LIST: entries into the cells'
-// lists, in any order.
+// one lane's loop).  CELL_COUNT: the entries of every cell, and *total of
+// all; CELL_LIST: the entries into the cells' lists, in any order; CELL_KEYS:
+// the same as keys, cell << 32 | disk << 1 | the disk holds the whole cell.
 enum { CELL_COUNT, CELL_KEYS, CELL_LIST };
 
 template <int STEP>
 __global__ __launch_bounds__(256) void k_disk_cells(int64_t n, DiskArgs D, DiskGrid g, double ux, double uy,
-                                                    double lim, unsigned long long *count, uint32_t *ccnt,
-                                                    const unsigned long long *off, unsigned long long *keys,
-                                                    const uint2 *cells, uint32_t *cell_disk, double2 *centre)
+                                                    double lim, uint32_t *ccnt, unsigned long long *keys,
+                                                    const uint2 *cells, uint32_t *cell_disk, double2 *centre,
+                                                    unsigned long long *total)
 {
+    unsigned long long mine = 0;   // wave-uniform
     const int lane = threadIdx.x & 63;
-    const unsigned long long below = (1ull << lane) - 1ull;
     const int64_t nwave = ((int64_t)gridDim.x * blockDim.x) >> 6;
     for (int64_t j = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6; j < n; j += nwave) {
         const double cx = D.cx[j], cy = D.cy[j], r = radius_of(D, j);
         if (STEP == CELL_COUNT && lane == 0) centre[j] = double2{cx, cy};
         int c0, c1, r0, r1;
         disk_cells(g, cx, cy, r, c0, c1, r0, r1);
-        unsigned long long at = STEP == CELL_KEYS ? off[j] : 0ull;
         const int wide = c1 - c0 + 1;
         const int64_t all = wide > 0 && r1 >= r0 ? (int64_t)wide * (r1 - r0 + 1) : 0;
         for (int64_t t0 = 0; t0 < all; t0 += 64) {
             const int64_t t = t0 + lane;
             const int rr = r0 + (int)(t / wide), c = c0 + (int)(t % wide);
             const int in = t < all ? cell_reached(g, ux, uy, cx, cy, r, lim, c, rr) : 0;
-            const unsigned long long m = __ballot(in != 0);
             const int64_t cell = (int64_t)rr * g.W + c;
-            const uint32_t e = (uint32_t)j | (in == 2 ? DJ_FULL : 0u);
             if (in) {
-                if (STEP == CELL_COUNT) atomicAdd(&ccnt[cell], 1u);
+                const uint32_t p = atomicAdd(&ccnt[cell], 1u);
                 if (STEP == CELL_KEYS)
-                    keys[at + __popcll(m & below)] = ((unsigned long long)cell << 32) | (unsigned long long)e;
-                if (STEP == CELL_LIST) cell_disk[cells[cell].x + atomicAdd(&ccnt[cell], 1u)] = e;
+                    keys[cells[cell].x + p] = ((unsigned long long)cell << 32) | ((unsigned long long)j << 1) |
+                                              (in == 2 ? 1ull : 0ull);
+                if (STEP == CELL_LIST) cell_disk[cells[cell].x + p] = (uint32_t)j | (in == 2 ? DJ_FULL : 0u);
             }
-            at += __popcll(m);
+            mine += __popcll(__ballot(in != 0));
         }
-        if (STEP == CELL_COUNT && lane == 0) count[j] = at;
+    }
+    if (STEP == CELL_COUNT) {
+        __shared__ unsigned long long part[4];
+        if (lane == 0) part[threadIdx.x >> 6] = mine;
+        __syncthreads();
+        if (threadIdx.x == 0) atomicAdd(total, part[0] + part[1] + part[2] + part[3]);
     }
 }
 
@@ -206,7 +209,7 @@ __global__ __launch_bounds__(256) void k_dcell_start(int64_t ncell, const uint32
 __global__ void k_dcell_list(int64_t nk, const unsigned long long *skeys, uint32_t *cell_disk)
 {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nk; i += (int64_t)gridDim.x * blockDim.x)
-        cell_disk[i] = (uint32_t)skeys[i];
+        cell_disk[i] = (uint32_t)(skeys[i] & 0xffffffffull) >> 1 | (skeys[i] & 1ull ? DJ_FULL : 0u);
 }
 
 // cells[c].y = which of the cell's first 32 entries hold all of it; first,
@@ -260,8 +263,9 @@ struct alignas(8) CellPair {
 __device__ __forceinline__ void disk_range(const DiskCanvas &K, double x, double y, uint32_t &k, uint32_t &rem)
 {
     const int cell = disk_cell(K, x, y);
-    k = cell < 0 ? 0u : K.cells[cell].x;
-    rem = cell < 0 ? 0u : K.cells[cell + 1].x - k;
+    const CellPair p = cell < 0 ? CellPair{{0u, 0u}, {0u, 0u}} : *(const CellPair *)(K.cells + cell);
+    k = p.a.x;
+    rem = p.b.x - p.a.x;
 }
 
 // The (point, disk) pairs of a wavefront's points with the disk tests
@@ -645,8 +649,8 @@ static int build_disk_canvas(spade_ctx *ctx, const spade_disks *dk, int64_t npts
     unsigned long long *dbb = (unsigned long long *)bb.p;
     unsigned *bad = (unsigned *)(dbb + 4);
     double *rsum = (double *)(dbb + 6);   // radii, squares
-    // box keys start at all-ones; the flag, the sums and the longest list at zero
-    hipLaunchKernelGGL(k_dj_zero, dim3(1), dim3(64), 0, st, (int64_t)9, dbb);
+    // box keys start at all-ones; the flag, the sums, the longest list and the entries at zero
+    hipLaunchKernelGGL(k_dj_zero, dim3(1), dim3(64), 0, st, (int64_t)10, dbb);
     SPADE_HIP(ctx, hipGetLastError());
     SPADE_HIP(ctx, hipMemsetAsync(dbb, 0xff, 32, st));
     hipLaunchKernelGGL(k_disks_box, dim3(dj_grid(n, 1024)), dim3(256), 0, st, n, K.D, dbb, bad, rsum);
@@ -683,7 +687,11 @@ static int build_disk_canvas(spade_ctx *ctx, const spade_disks *dk, int64_t npts
     double cell = std::max(mr, least);
     double fine = std::max({mr / DJ_FINE, least, std::sqrt(w) * std::sqrt(hgt) / std::sqrt((double)npts / DJ_PER_CELL)});
     while (fine < cell && !(entries(fine) <= std::min((double)npts / DJ_PER_ENTRY, 268435456.0))) fine *= 1.19;
-    if (fine > 0.0 && fine < cell) cell = fine;
+    // Few disks: most cells list nothing, and a small table stays in the L1
+    // (100 disks of 500 m over 60 km, 30M points: counts 330 us with cells of
+    // 500 m, 430 with 125).
+    const bool few = !(3.15 * rsq >= DJ_COVER * w * hgt);
+    if (!few && fine > 0.0 && fine < cell) cell = fine;
     g.W = (w > 0 && cell > 0) ? (int)std::min<double>(DJ_GRID_MAX, std::max(1.0, std::ceil(w / cell))) : 1;
     g.H = (hgt > 0 && cell > 0) ? (int)std::min<double>(DJ_GRID_MAX, std::max(1.0, std::ceil(hgt / cell))) : 1;
     g.X0 = g.bx0;
@@ -697,40 +705,34 @@ static int build_disk_canvas(spade_ctx *ctx, const spade_disks *dk, int64_t npts
     // Cell lists: count, scan, fill in any order, order each list.  Where a
     // list is longer than DJ_LIST_SORT entries, (cell, disk) keys are sorted
     // instead (30 launches for a million of them: 140 us, against 25).
-    DevBuf &bc = ctx->scratch[S_NROWS], &bo = ctx->scratch[S_ROWOFF], &bw = ctx->scratch[S_VALS2];
-    if (ensure(ctx, bc, 8 * (size_t)(n + 1)) || ensure(ctx, bo, 8 * (size_t)(n + 1)) ||
-        ensure(ctx, bw, sizeof(double2) * (size_t)n + (sizeof(uint2) + 2 * sizeof(uint32_t)) * (size_t)(ncell + 1)))
+    DevBuf &bw = ctx->scratch[S_VALS2];
+    if (ensure(ctx, bw, sizeof(double2) * (size_t)n + (sizeof(uint2) + 2 * sizeof(uint32_t)) * (size_t)(ncell + 1)))
         return SPADE_E_NOMEM;
-    unsigned long long *cnt = (unsigned long long *)bc.p, *off = (unsigned long long *)bo.p;
     double2 *centre = (double2 *)bw.p;
     uint2 *cells = (uint2 *)(centre + n);
     uint32_t *ccnt = (uint32_t *)(cells + (ncell + 1)), *coff = ccnt + (ncell + 1);
     unsigned *longest = (unsigned *)(dbb + 8);
-    const int64_t most = (int64_t)0x7fffffff / 64;   // a wavefront per disk
-    const dim3 dgrid(dj_grid(std::min(n, most) * 64)), cgrid((unsigned)(ncell / 256 + 1));
+    const dim3 dgrid(dj_grid(n * 64, 2048)), cgrid((unsigned)(ncell / 256 + 1));
     auto disks = [&](auto kern, unsigned long long *keys, uint32_t *list) {
-        hipLaunchKernelGGL(kern, dgrid, dim3(256), 0, st, n, K.D, g, ux, uy, lim, cnt, ccnt,
-                           (const unsigned long long *)off, keys, (const uint2 *)cells, list, centre);
+        hipLaunchKernelGGL(kern, dgrid, dim3(256), 0, st, n, K.D, g, ux, uy, lim, ccnt, keys,
+                           (const uint2 *)cells, list, centre, dbb + 9);
     };
     DevBuf &cub = ctx->scratch[S_CUBTMP];
-    size_t tb = 0, tc = 0;
+    size_t tb = 0;
     SPADE_HIP(ctx, hipMemsetAsync(ccnt, 0, sizeof(uint32_t) * (size_t)(ncell + 1), st));
     disks(k_disk_cells<CELL_COUNT>, nullptr, nullptr);
-    hipLaunchKernelGGL(k_dj_zero, dim3(1), dim3(64), 0, st, (int64_t)1, cnt + n);
     SPADE_HIP(ctx, hipGetLastError());
-    SPADE_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(nullptr, tb, cnt, off, (int)(n + 1), st));
-    SPADE_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(nullptr, tc, ccnt, coff, (int)(ncell + 1), st));
-    if (ensure(ctx, cub, std::max<size_t>({tb, tc, 1}))) return SPADE_E_NOMEM;
-    SPADE_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(cub.p, tb, cnt, off, (int)(n + 1), st));
-    SPADE_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(cub.p, tc, ccnt, coff, (int)(ncell + 1), st));
+    SPADE_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(nullptr, tb, ccnt, coff, (int)(ncell + 1), st));
+    if (ensure(ctx, cub, std::max<size_t>(tb, 1))) return SPADE_E_NOMEM;
+    SPADE_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(cub.p, tb, ccnt, coff, (int)(ncell + 1), st));
     hipLaunchKernelGGL(k_dcell_start, cgrid, dim3(256), 0, st, ncell, (const uint32_t *)coff, ccnt, cells, longest);
     SPADE_HIP(ctx, hipGetLastError());
-    SPADE_HIP(ctx, hipMemcpyAsync(h, off + n, 8, hipMemcpyDeviceToHost, st));
-    SPADE_HIP(ctx, hipMemcpyAsync(h + 1, longest, 4, hipMemcpyDeviceToHost, st));
+    SPADE_HIP(ctx, hipMemcpyAsync(h, dbb + 8, 16, hipMemcpyDeviceToHost, st));
     SPADE_HIP(ctx, hipStreamSynchronize(st));
-    const int64_t nk = (int64_t)h[0];
+    const unsigned most_listed = (unsigned)h[0];
+    const int64_t nk = (int64_t)h[1];
     if (nk >= (int64_t)0xffffffffLL) return set_error(ctx, SPADE_E_UNSUPPORTED, "too many (cell, disk) entries");
-    const bool sorted = (unsigned)h[1] > DJ_LIST_SORT;
+    const bool sorted = most_listed > DJ_LIST_SORT;
     DevBuf &bl = ctx->scratch[S_VALS];
     if (ensure(ctx, bl, 4 * (size_t)std::max<int64_t>(nk, 1) + 64)) return SPADE_E_NOMEM;
     uint32_t *cell_disk = (uint32_t *)bl.p;
@@ -739,14 +741,13 @@ static int build_disk_canvas(spade_ctx *ctx, const spade_disks *dk, int64_t npts
         if (ensure(ctx, bk, 8 * (size_t)nk) || ensure(ctx, bk2, 8 * (size_t)nk)) return SPADE_E_NOMEM;
         disks(k_disk_cells<CELL_KEYS>, (unsigned long long *)bk.p, nullptr);
         SPADE_HIP(ctx, hipGetLastError());
-        // by cell alone: the keys are filled disk by disk and the sort is stable
         const int kb = 32 + std::max(1, dj_bits((uint64_t)ncell));
         tb = 0;
         SPADE_HIP(ctx, hipcub::DeviceRadixSort::SortKeys(nullptr, tb, (const unsigned long long *)bk.p,
-                                                         (unsigned long long *)bk2.p, (int)nk, 32, kb, st));
+                                                         (unsigned long long *)bk2.p, (int)nk, 0, kb, st));
         if (ensure(ctx, cub, std::max<size_t>(tb, 1))) return SPADE_E_NOMEM;
         SPADE_HIP(ctx, hipcub::DeviceRadixSort::SortKeys(cub.p, tb, (const unsigned long long *)bk.p,
-                                                         (unsigned long long *)bk2.p, (int)nk, 32, kb, st));
+                                                         (unsigned long long *)bk2.p, (int)nk, 0, kb, st));
         hipLaunchKernelGGL(k_dcell_list, dim3(dj_grid(nk)), dim3(256), 0, st, nk, (const unsigned long long *)bk2.p,
                            cell_disk);
     } else {
@@ -757,7 +758,7 @@ static int build_disk_canvas(spade_ctx *ctx, const spade_disks *dk, int64_t npts
     K.cells = cells;
     K.cell_disk = cell_disk;
     K.centre = centre;
-    K.longest = (unsigned)h[1];
+    K.longest = most_listed;
     return SPADE_OK;
 }
 

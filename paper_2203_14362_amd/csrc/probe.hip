@@ -725,11 +725,13 @@ __global__ __launch_bounds__(EMIT_THREADS) void k_emit_count(CanvasView cv, int6
     const uint32_t lane = lane_id();
     const unsigned long long below = (1ull << lane) - 1ull;
     const int64_t nwave = ((int64_t)gridDim.x * EMIT_THREADS) >> 6;
+    bool several = false;   // a point lies in several polygons
     for (int64_t sg = ((int64_t)blockIdx.x * EMIT_THREADS + threadIdx.x) >> 6; sg < nseg; sg += nwave) {
         const int64_t i0 = sg * EMIT_SEG + lane;
         // whole segments: no bounds to check; none once the labels are known
         // not to be used
-        T *seg = __hip_atomic_load(multi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ? nullptr : labels + sg * EMIT_SEG;
+        several = several || __hip_atomic_load(multi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u;
+        T *seg = several ? nullptr : labels + sg * EMIT_SEG;
         unsigned long long total = 0;   // wave-uniform
         uint32_t qn = 0;                // wave-uniform queue length
         auto drain = [&]() {
@@ -753,9 +755,12 @@ __global__ __launch_bounds__(EMIT_THREADS) void k_emit_count(CanvasView cv, int6
                 if (seg) seg[qi[lane]] = (T)first;
             }
             __builtin_amdgcn_wave_barrier();
-            // a point in several polygons: the write pass probes again
-            if (__ballot(m > 1u) && lane == 0)
-                __hip_atomic_store(multi, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            // a point in several polygons: the write pass probes again (told
+            // once per wavefront: the stores of all of them meet in one place)
+            if (!several && __ballot(m > 1u)) {
+                several = true;
+                if (lane == 0) __hip_atomic_store(multi, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
 #pragma unroll
             for (int d = 32; d >= 1; d >>= 1) m += __shfl_xor(m, d, 64);
             total += m;
