@@ -201,6 +201,11 @@ void free_buf(DevBuf &b);
 // synchronisation.
 int build_canvas(spade_ctx *ctx, const spade_polys *polys, spade_canvas *cv, bool defer = false);
 int build_flush(spade_ctx *ctx, spade_canvas *cv);
+
+// The boundary-pixel counters of a build that build_flush has not copied yet
+// (shards of them, stride words apart), or null: cv->n_boundary is valid.
+const unsigned long long *build_boundary(const spade_canvas *cv, int *shards, int *stride);
+
 // Completes a deferred build; returns BUILD_AGAIN when the single row pass
 // ran out of capacity (grown by now: build again, non-deferred).
 constexpr int BUILD_AGAIN = 1;

@@ -704,13 +704,15 @@ struct alignas(16) LabelVec {
 // by the latency of the points and their cells, as k_count: 100M points, 64
 // polygons on a 2048 canvas, 0.37 ms (0.31 without the labels, whose 0.2 GB
 // save the write pass 0.38 ms).
-template <typename T>
+template <typename T, bool LABELS>
 __global__ __launch_bounds__(EMIT_THREADS) void k_emit_count(CanvasView cv, int64_t n, const double *X,
                                                              const double *Y, int64_t nseg,
-                                                             unsigned long long *counts, unsigned *multi, T *labels)
+                                                             unsigned long long *counts, unsigned *multi, T *labels,
+                                                             const unsigned *skip)
 {
     static_assert(EMIT_THREADS == CNT_THREADS, "the queue area is sized for CNT_THREADS");
     static_assert(EMIT_SEG <= 65536 && EMIT_INDEX_BYTES <= LDS_RESERVE, "the queued points' places fit the reserve");
+    if (LABELS == (*skip != 0u)) return;
     extern __shared__ __align__(16) unsigned char smem[];
     uint16_t *coarse = (uint16_t *)smem;
     const size_t coarse_bytes = ((size_t)cv.Wc * cv.Hc * (cv.cbyte ? 1 : 2) + 15) & ~(size_t)15;
@@ -730,8 +732,8 @@ __global__ __launch_bounds__(EMIT_THREADS) void k_emit_count(CanvasView cv, int6
         const int64_t i0 = sg * EMIT_SEG + lane;
         // whole segments: no bounds to check; none once the labels are known
         // not to be used
-        several = several || __hip_atomic_load(multi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u;
-        T *seg = several ? nullptr : labels + sg * EMIT_SEG;
+        if (LABELS) several = several || __hip_atomic_load(multi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u;
+        T *seg = !LABELS || several ? nullptr : labels + sg * EMIT_SEG;
         unsigned long long total = 0;   // wave-uniform
         uint32_t qn = 0;                // wave-uniform queue length
         auto drain = [&]() {
@@ -740,24 +742,25 @@ __global__ __launch_bounds__(EMIT_THREADS) void k_emit_count(CanvasView cv, int6
             if (lane < qn) {
                 const double x = qx[lane], y = qy[lane];
                 uint32_t rec = qr[lane], first = ~0u;
-                while (true) {   // two records at a time (the slot after the last exists)
-                    const Cand c0 = cv.cands[rec];
-                    const Cand c1 = cv.cands[rec + 1];
-                    if (cand_inside(cv, c0, x, y)) { ++m; first = c0.poly; }
-                    if (c0.meta & CAND_LAST) break;
-                    if (cand_inside(cv, c1, x, y)) { ++m; first = c1.poly; }
-                    if (c1.meta & CAND_LAST) break;
-                    rec += 2;
+                if (LABELS) {   // one record at a time: two spill registers
+                    while (true) {
+                        const Cand c0 = cv.cands[rec];
+                        if (cand_inside(cv, c0, x, y)) { ++m; first = c0.poly; }
+                        if (c0.meta & CAND_LAST) break;
+                        ++rec;
+                    }
+                } else {
+                    test_records(cv, rec, x, y, [&](uint32_t) { ++m; });
                 }
                 // after the group's own store: one wavefront's stores to
                 // an address keep their order under the fence
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-                if (seg) seg[qi[lane]] = (T)first;
+                if (LABELS && seg) seg[qi[lane]] = (T)first;
             }
             __builtin_amdgcn_wave_barrier();
             // a point in several polygons: the write pass probes again (told
             // once per wavefront: the stores of all of them meet in one place)
-            if (!several && __ballot(m > 1u)) {
+            if (LABELS && !several && __ballot(m > 1u)) {
                 several = true;
                 if (lane == 0) __hip_atomic_store(multi, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
@@ -780,7 +783,7 @@ __global__ __launch_bounds__(EMIT_THREADS) void k_emit_count(CanvasView cv, int6
                 const Look lk = look_coarse(cv, coarse, xs[k], ys[k]);
                 ws[k] = lk.full ? ((gu32p)cv.cells)[lk.fidx] : lk.word;
             }
-            if (seg) {   // a boundary point's label is stored by its drain
+            if (LABELS && seg) {   // a boundary point's label is stored by its drain
                 LabelVec<T> v;
 #pragma unroll
                 for (int k = 0; k < EMIT_GROUP; ++k) v.l[k] = (T)(ws[k] - 1u);   // word 0: all ones
@@ -800,7 +803,7 @@ __global__ __launch_bounds__(EMIT_THREADS) void k_emit_count(CanvasView cv, int6
                     qx[slot] = xs[k];
                     qy[slot] = ys[k];
                     qr[slot] = w & ~BFLAG;
-                    qi[slot] = (uint16_t)(64 * g + EMIT_GROUP * lane + k);
+                    if (LABELS) qi[slot] = (uint16_t)(64 * g + EMIT_GROUP * lane + k);
                 }
                 qn += nnew;
             }
@@ -986,7 +989,18 @@ __global__ __launch_bounds__(256) void k_emit_bits(int64_t nseg, const unsigned 
 }
 
 __global__ void k_emit_zero(unsigned long long *p) { *p = 0ull; }
-__global__ void k_emit_flag(unsigned *p, unsigned v) { *p = v; }
+
+// Whether the pairs' count pass keeps labels: p[0], set later by a point in
+// several polygons, and p[1] start at 0 if so, else at 1.
+__global__ void k_emit_flag(unsigned *p, int labelled, const unsigned long long *bnd, int shards, int stride,
+                            unsigned long long known, unsigned long long most)
+{
+    if (bnd) {
+        known = 0;
+        for (int k = 0; k < shards; ++k) known += bnd[k * stride];
+    }
+    p[0] = p[1] = labelled && known <= most ? 0u : 1u;
+}
 
 int probe_emit(spade_ctx *ctx, const spade_canvas *cv, const spade_points *pts, uint32_t *out_pt,
                uint32_t *out_poly, int64_t cap, int64_t *n_out)
@@ -1043,10 +1057,22 @@ int probe_emit(spade_ctx *ctx, const spade_canvas *cv, const spade_points *pts, 
     if (bits) {
         rc = launch(k_emit_count_bits, lds + QUEUE_BYTES, counts, bits);
     } else {
-        // without labels the write pass always probes again
-        hipLaunchKernelGGL(k_emit_flag, dim3(1), dim3(1), 0, st, multi, labelled ? 0u : 1u);
-        rc = lab32 ? launch(k_emit_count<uint32_t>, lds + QUEUE_BYTES + EMIT_INDEX_BYTES, counts, multi, lab32)
-                   : launch(k_emit_count<uint16_t>, lds + QUEUE_BYTES + EMIT_INDEX_BYTES, counts, multi, lab16);
+        // Where more than an eighth of the canvas are boundary pixels (a
+        // twentieth in a tessellation), polygons overlap or most points need
+        // records, and the count pass without labels is the faster one (20M
+        // points, 12 overlapping polygons: 0.47 ms, with labels 0.61; 50M
+        // points, 256 zones: 0.37 ms with them, which save a second probe of
+        // 0.48).  The pass that is not chosen returns at once.
+        int shards, stride;
+        const unsigned long long *bnd = build_boundary(cv, &shards, &stride);
+        hipLaunchKernelGGL(k_emit_flag, dim3(1), dim3(1), 0, st, multi, labelled ? 1 : 0, bnd, shards, stride,
+                           (unsigned long long)cv->n_boundary, (unsigned long long)cv->view.W * cv->view.H / 8);
+        rc = SPADE_OK;
+        const size_t qb = lds + QUEUE_BYTES;
+        const unsigned *skip = multi + 1;
+        if (lab16) rc = launch(k_emit_count<uint16_t, true>, qb + EMIT_INDEX_BYTES, counts, multi, lab16, skip);
+        if (lab32) rc = launch(k_emit_count<uint32_t, true>, qb + EMIT_INDEX_BYTES, counts, multi, lab32, skip);
+        if (!rc) rc = launch(k_emit_count<uint16_t, false>, qb, counts, multi, lab16, skip);
     }
     if (rc) return rc;
     hipLaunchKernelGGL(k_emit_zero, dim3(1), dim3(1), 0, st, counts + nseg);

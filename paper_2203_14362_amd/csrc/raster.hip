@@ -1766,6 +1766,14 @@ int build_flush(spade_ctx *ctx, spade_canvas *cv)
     return SPADE_OK;
 }
 
+const unsigned long long *build_boundary(const spade_canvas *cv, int *shards, int *stride)
+{
+    *shards = NSHARD;
+    *stride = gctr_at(1, 0);
+    if (!cv->pending || !cv->pend_src) return nullptr;
+    return (const unsigned long long *)((const char *)cv->pend_src + CTR_HEAD) + gctr_at(0, 3);
+}
+
 int build_finish(spade_ctx *ctx, spade_canvas *cv)
 {
     if (!cv->pending) return SPADE_OK;
