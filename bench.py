@@ -196,7 +196,7 @@ def leg_c2_pairs(ctx, dx, dy, dp, N):
     return {"workload": "join pairs: the headline 100M points x 260 polygons", "pairs": npairs,
             "ms_per_call": round(float(np.mean(ms)), 4), "probe_ms": round(pm, 4),
             "pairs_per_s": round(npairs / (float(np.mean(ms)) / 1e3), 1),
-            "roofline": roofline("k_emit_count + k_emit", 16.0 * N + 8.0 * npairs, pm,
+            "roofline": roofline("k_emit_count + k_emit_labels", 16.0 * N + 8.0 * npairs, pm,
                                  bytes_rule="16 B/point + 8 B/pair"),
             "gpu_matches_oracle_digest": parity}
 

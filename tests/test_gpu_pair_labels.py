@@ -30,11 +30,13 @@ def _check(ctx, x, y, polys):
 
 
 @pytest.mark.parametrize("n", [1, 63, 64, 65, 511, 513, 2047, 2048, 2049, 4097, 100_003])
-@pytest.mark.parametrize("overlap", [False, True])
+@pytest.mark.parametrize("overlap", [0.0, 0.004, 0.1, 0.5])
 def test_pairs_match_oracle(ctx, n, overlap):
+    """No overlap, one found on the way (few pixels in several polygons), and
+    ones that the canvas shows beforehand."""
     polys = gen.rect_grid(12, 9, 0.0, 0.0, 1.0, 1.0)
     if overlap:
-        polys = gen.concat_polys(polys, gen.star_polygon(60, 0.1, (6.0, 4.5), L=9.0, seed=4))
+        polys = gen.concat_polys(polys, gen.star_polygon(60, overlap, (6.0, 4.5), L=9.0, seed=4))
     _check(ctx, *_points(n, 12, 9, n), polys)
 
 
