@@ -20,12 +20,9 @@
 
 #include "disk.h"
 #include "exact.h"
+#include "segfilter.h"
 
 namespace spade {
-
-struct Seg {
-    double ax, ay, bx, by;
-};
 
 // In-place compression of a non-overlapping expansion e[0..m) (increasing
 // magnitude) into a non-adjacent one with the same value; returns its
@@ -187,40 +184,6 @@ __device__ __forceinline__ bool seg_near(double px, double py, const Seg &s, dou
     if (dot_sign(px, py, s.bx, s.by, s.ax, s.ay) <= 0)                                      // t >= L
         return in_disk(px, py, s.bx, s.by, r, r2);
     return perp_sign(px, py, s, r, r2) >= 0;
-}
-
-// The floating-point decisions of the same test for a finite point: within
-// (1), not within (0), or open (-1).  Without the exact test's calls a kernel
-// needs half the registers (k_buf_bits: 64 for 128) and keeps twice the
-// wavefronts.  The nearest point's region is chosen from rounded dot
-// products: where that choice is uncertain, the squared distances of the two
-// regions differ by less than 1e-29 of themselves, so the margins of 1e-12
-// decide only what both agree on; the cross product is enclosed by its
-// rounding bound as in perp_sign.
-__device__ __forceinline__ int seg_near_filter(double px, double py, const Seg &s, double r2)
-{
-    const double ex = s.bx - s.ax, ey = s.by - s.ay;
-    double dx = px - s.ax, dy = py - s.ay;
-    const double l2 = ex * ex + ey * ey, u = dx * ex + dy * ey;
-    double lo, hi, rhs = r2;
-    if (u > 0.0 && u < l2) {
-        const double c1 = ex * dy, c2 = ey * dx;
-        const double c = fabs(c1 - c2), ec = 6.7e-16 * (fabs(c1) + fabs(c2));
-        const double a = fmax(c - ec, 0.0), b = c + ec;
-        lo = a * a;
-        hi = b * b;
-        rhs = r2 * l2;
-    } else {
-        if (u > 0.0) {
-            dx = px - s.bx;
-            dy = py - s.by;
-        }
-        lo = hi = dx * dx + dy * dy;
-    }
-    if (!(rhs > 1e-250 && hi < 1e250)) return -1;
-    if (hi * (1.0 + 1e-12) < rhs * (1.0 - 1e-12)) return 1;
-    if (lo * (1.0 - 1e-12) > rhs * (1.0 + 1e-12)) return 0;
-    return -1;
 }
 
 }  // namespace spade
