@@ -112,7 +112,10 @@ int spade_ctx_create(int device, void *stream, spade_ctx **out);
 /* Destroy a context and free its scratch memory (NULL is a no-op). */
 void spade_ctx_destroy(spade_ctx *ctx);
 
-/* Change the stream later calls are ordered on (NULL = null stream). */
+/* Change the stream later calls are ordered on (NULL = null stream).  An
+ * asynchronous count that is still queued on the earlier stream uses the
+ * context's scratch: later work on the new stream runs after it (unless the
+ * new stream is being captured). */
 int spade_ctx_set_stream(spade_ctx *ctx, void *stream);
 
 /* Message for the last failing call on ctx ("" if none).  Valid until the

@@ -104,6 +104,13 @@ static int check_ctx(spade_ctx *ctx)
     return SPADE_OK;
 }
 
+bool capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &c) != hipSuccess) (void)hipGetLastError();
+    return c != hipStreamCaptureStatusNone;
+}
+
 static int check_points(spade_ctx *ctx, const spade_points *pts)
 {
     if (!pts) return set_error(ctx, SPADE_E_INVALID, "points is NULL");
@@ -186,6 +193,7 @@ void spade_ctx_destroy(spade_ctx *ctx)
     if (ctx->join) (void)hipEventDestroy(ctx->join);
     if (ctx->join2) (void)hipEventDestroy(ctx->join2);
     if (ctx->evinfo) (void)hipEventDestroy(ctx->evinfo);
+    if (ctx->evqueued) (void)hipEventDestroy(ctx->evqueued);
     if (ctx->side) (void)hipStreamDestroy(ctx->side);
     if (ctx->side2) (void)hipStreamDestroy(ctx->side2);
     if (ctx->capture) (void)hipStreamDestroy(ctx->capture);
@@ -196,6 +204,16 @@ int spade_ctx_set_stream(spade_ctx *ctx, void *stream)
 {
     if (!ctx) return SPADE_E_INVALID;
     SPADE_CTX_LOCK(ctx);
+    // A count that was only queued uses the context's scratch until it has
+    // run: work on another stream goes behind it.  (Not into a graph that the
+    // caller captures, where the event has no place.)
+    if (ctx->queued && (hipStream_t)stream != ctx->stream && !capturing((hipStream_t)stream)) {
+        (void)hipSetDevice(ctx->device);   // the null stream is the current device's
+        ctx->queued = hipEventQuery(ctx->evqueued) != hipSuccess;
+        if (ctx->queued && hipStreamWaitEvent((hipStream_t)stream, ctx->evqueued, 0) != hipSuccess)
+            (void)hipEventSynchronize(ctx->evqueued);
+        (void)hipGetLastError();
+    }
     ctx->stream = (hipStream_t)stream;
     return SPADE_OK;
 }
@@ -392,11 +410,9 @@ int spade_layered_build(spade_ctx *ctx, const spade_polys *polys, int32_t res, s
     return SPADE_OK;
 }
 
-int spade_canvas_join_count_async(spade_ctx *ctx, const spade_canvas *cv, const spade_points *pts,
-                                  uint64_t *out_counts)
+// Queues a count (ctx locked).
+static int queue_count(spade_ctx *ctx, const spade_canvas *cv, const spade_points *pts, uint64_t *out_counts)
 {
-    if (!ctx) return SPADE_E_INVALID;
-    SPADE_CTX_LOCK(ctx);
     int rc = check_ctx(ctx);
     if (rc) return rc;
     if (!cv) return set_error(ctx, SPADE_E_INVALID, "canvas is NULL");
@@ -405,6 +421,19 @@ int spade_canvas_join_count_async(spade_ctx *ctx, const spade_canvas *cv, const 
     if (cv->view.M > 0 && !out_counts) return set_error(ctx, SPADE_E_INVALID, "out_counts is NULL");
     if (cv != ctx->plain) ctx->timed_raster = false;
     return probe_count(ctx, cv, pts, out_counts);
+}
+
+int spade_canvas_join_count_async(spade_ctx *ctx, const spade_canvas *cv, const spade_points *pts,
+                                  uint64_t *out_counts)
+{
+    if (!ctx) return SPADE_E_INVALID;
+    SPADE_CTX_LOCK(ctx);
+    const int rc = queue_count(ctx, cv, pts, out_counts);
+    if (rc || capturing(ctx->stream)) return rc;
+    if (!ctx->evqueued) SPADE_HIP(ctx, hipEventCreateWithFlags(&ctx->evqueued, hipEventDisableTiming));
+    SPADE_HIP(ctx, hipEventRecord(ctx->evqueued, ctx->stream));
+    ctx->queued = true;
+    return SPADE_OK;
 }
 
 int spade_canvas_join_count_noalloc(spade_ctx *ctx, const spade_canvas *cv, const spade_points *pts,
@@ -428,7 +457,7 @@ int spade_canvas_join_count(spade_ctx *ctx, const spade_canvas *cv, const spade_
 {
     if (!ctx) return SPADE_E_INVALID;
     SPADE_CTX_LOCK(ctx);
-    int rc = spade_canvas_join_count_async(ctx, cv, pts, out_counts);
+    int rc = queue_count(ctx, cv, pts, out_counts);
     if (rc) return rc;
     SPADE_HIP(ctx, hipStreamSynchronize(ctx->stream));
     return SPADE_OK;
@@ -589,7 +618,7 @@ int spade_join_count(spade_ctx *ctx, const spade_points *pts, const spade_polys 
     int rc = check_points(ctx, pts);
     if (rc) return rc;
     return plain_query(ctx, polys, [&](spade_canvas *cv) {
-        return spade_canvas_join_count_async(ctx, cv, pts, out_counts);
+        return queue_count(ctx, cv, pts, out_counts);
     });
 }
 

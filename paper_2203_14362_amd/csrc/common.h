@@ -150,6 +150,8 @@ struct spade_ctx {
     hipStream_t side2 = nullptr;
     hipEvent_t fork = nullptr, join = nullptr, join2 = nullptr;
     hipEvent_t evinfo = nullptr;            // a build's row totals reached the host
+    hipEvent_t evqueued = nullptr;          // behind the last call that was only queued,
+    bool queued = false;                    // which may still run (its scratch is in use)
     hipStream_t capture = nullptr;          // internal stream graphs are captured on
     bool graphs = true;                     // replay repeated canvas builds from graphs
     int64_t graph_captures = 0, graph_replays = 0;
@@ -194,6 +196,7 @@ int plain_canvas(spade_ctx *ctx, const spade_polys *polys, spade_canvas **cvo);
 void jobs_shutdown(spade_ctx *ctx);
 size_t jobs_bytes(const spade_ctx *ctx);
 void free_buf(DevBuf &b);
+bool capturing(hipStream_t s);   // a caller records s into a graph
 
 // `defer`: leave the build's counters and flags on the device instead of
 // waiting for them; build_flush queues their copy to the host (after the

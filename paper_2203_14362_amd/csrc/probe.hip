@@ -343,15 +343,8 @@ static int launch_count(spade_ctx *ctx, const spade_canvas *cv, const spade_poin
     const int64_t rounds = (n + LH_ROUND - 1) / LH_ROUND;
     const int hgrid = (int)std::min<int64_t>(std::max<int64_t>(rounds, 1), cus);
     const int nw = (int)((M + 1) / 2);
-    if (scratch && !ldshist && M <= LABEL_MAX_POLYS && n > 0 && n <= (int64_t)0xffffffffLL) {
-        // not into a caller's graph, whose replays would outlive the buffers
-        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(st, &cap) != hipSuccess) (void)hipGetLastError();
-        scratch = cap == hipStreamCaptureStatusNone;
-    } else {
-        scratch = false;
-    }
-    if (scratch) {
+    // not into a caller's graph, whose replays would outlive the buffers
+    if (scratch && !ldshist && M <= LABEL_MAX_POLYS && n > 0 && n <= (int64_t)0xffffffffLL && !capturing(st)) {
         DevBuf &bl = ctx->scratch[S_BITS], &bs = ctx->scratch[S_LOOKBACK];
         if (ensure(ctx, bl, sizeof(uint16_t) * (size_t)(rounds * LH_ROUND)) == SPADE_OK &&
             ensure(ctx, bs, sizeof(uint32_t) * (size_t)nw * (size_t)hgrid) == SPADE_OK) {
