@@ -1005,9 +1005,17 @@ __global__ __launch_bounds__(KNN_THREADS) void k_knn_pow2(int64_t n, const doubl
         if (h[k]) atomicAdd(&bins[k], (unsigned long long)h[k]);
 }
 
-// The points of circle 2^J from the words whose innermost circle reaches it,
-// in no particular order: ids and keys (FP64 squared distance).  A wavefront
-// looks at 64 words, one per lane; one global atomic per workgroup.
+// The points of circle 2^J from the words whose innermost circle reaches it:
+// ids and keys (FP64 squared distance).  A wavefront looks at 64 words, one
+// per lane.  TAKE_ANY: the workgroups' points in no particular order (one
+// atomic per workgroup; the sort in LDS orders by key and id).  For the sort
+// by key alone the ids have to come ascending, or the exact comparison of a
+// run of equal distances (a place with many points) would be quadratic:
+// TAKE_COUNT gives the points per workgroup, TAKE_AT writes them from the
+// scanned counts on.
+enum { TAKE_ANY, TAKE_COUNT, TAKE_AT };
+
+template <int STEP>
 __global__ __launch_bounds__(KNN_THREADS) void k_knn_take(int64_t n, const double *X, const double *Y, double px,
                                                           double py, int J, const int16_t *wmin, uint32_t *count,
                                                           uint32_t cap, uint32_t *ids, unsigned long long *keys)
@@ -1039,8 +1047,12 @@ __global__ __launch_bounds__(KNN_THREADS) void k_knn_take(int64_t n, const doubl
         if (w < wv) pre += wsum[w];
         total += wsum[w];
     }
+    if (STEP == TAKE_COUNT) {
+        if (threadIdx.x == 0) count[blockIdx.x] = total;
+        return;
+    }
     if (total == 0u) return;   // uniform over the workgroup
-    if (threadIdx.x == 0) s_base = atomicAdd(count, total);
+    if (threadIdx.x == 0) s_base = STEP == TAKE_AT ? count[blockIdx.x] : atomicAdd(count, total);
     __syncthreads();
     const uint32_t first = s_base + pre + incl - c;   // of this lane's word
     for (unsigned long long m = __ballot(mine != 0ull); m; m &= m - 1) {
@@ -1261,10 +1273,27 @@ int knn_select(spade_ctx *ctx, const spade_points *pts, double px, double py, in
     DevBuf &bc = ctx->scratch[S_VALS2], &bk = ctx->scratch[S_KEYS];
     if (ensure(ctx, bc, 4 * (size_t)std::max<int64_t>(cum, 1)) || ensure(ctx, bk, 8 * (size_t)std::max<int64_t>(cum, 1)))
         return SPADE_E_NOMEM;
+    DevBuf &cub = ctx->scratch[S_CUBTMP];
+    size_t tb = 0;
     if (jsel <= KNN_JMAX && cum <= n / 32) {
-        hipLaunchKernelGGL(k_knn_take, dim3((unsigned)((n + 64 * KNN_THREADS - 1) / (64 * KNN_THREADS))), dim3(KNN_THREADS),
-                           0, st, n, pts->x, pts->y, px, py, jsel, (const int16_t *)wmin, (uint32_t *)(dbins + KNN_BINS),
-                           (uint32_t)cum, (uint32_t *)bc.p, (unsigned long long *)bk.p);
+        const unsigned wgs = (unsigned)((n + 64 * KNN_THREADS - 1) / (64 * KNN_THREADS));
+        auto take = [&](auto kern, uint32_t *count) {
+            hipLaunchKernelGGL(kern, dim3(wgs), dim3(KNN_THREADS), 0, st, n, pts->x, pts->y, px, py, jsel,
+                               (const int16_t *)wmin, count, (uint32_t)cum, (uint32_t *)bc.p, (unsigned long long *)bk.p);
+        };
+        if (cum <= KS_MAX) {
+            take(k_knn_take<TAKE_ANY>, (uint32_t *)(dbins + KNN_BINS));
+        } else {
+            DevBuf &bn = ctx->scratch[S_LOOKBACK];
+            if (ensure(ctx, bn, sizeof(uint32_t) * 2 * (size_t)wgs)) return SPADE_E_NOMEM;
+            uint32_t *cnt = (uint32_t *)bn.p, *at = cnt + wgs;
+            SPADE_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(nullptr, tb, cnt, at, (int)wgs, st));
+            if (ensure(ctx, cub, std::max<size_t>(tb, 1))) return SPADE_E_NOMEM;
+            take(k_knn_take<TAKE_COUNT>, cnt);
+            SPADE_HIP(ctx, hipGetLastError());
+            SPADE_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(cub.p, tb, cnt, at, (int)wgs, st));
+            take(k_knn_take<TAKE_AT>, at);
+        }
     } else {
         int rc = select_disk(ctx, pts, px, py, rsel, (uint32_t *)bc.p, cum, &m);
         if (rc) return rc;
@@ -1286,8 +1315,7 @@ int knn_select(spade_ctx *ctx, const spade_points *pts, double px, double py, in
     }
     DevBuf &bk2 = ctx->scratch[S_KEYS2], &bi = ctx->scratch[S_VALS];
     if (ensure(ctx, bk2, 8 * (size_t)m) || ensure(ctx, bi, 4 * (size_t)m)) return SPADE_E_NOMEM;
-    DevBuf &cub = ctx->scratch[S_CUBTMP];
-    size_t tb = 0;
+    tb = 0;
     SPADE_HIP(ctx, hipcub::DeviceRadixSort::SortPairs(nullptr, tb, (const unsigned long long *)bk.p,
                                                       (unsigned long long *)bk2.p, (const uint32_t *)bc.p,
                                                       (uint32_t *)bi.p, (int)m, 0, 64, st));
