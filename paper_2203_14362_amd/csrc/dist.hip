@@ -686,12 +686,15 @@ static int build_disk_canvas(spade_ctx *ctx, const spade_disks *dk, int64_t npts
     const double least = std::max(w, hgt) / DJ_GRID_MAX;
     double cell = std::max(mr, least);
     double fine = std::max({mr / DJ_FINE, least, std::sqrt(w) * std::sqrt(hgt) / std::sqrt((double)npts / DJ_PER_CELL)});
-    while (fine < cell && !(entries(fine) <= std::min((double)npts / DJ_PER_ENTRY, 268435456.0))) fine *= 1.19;
+    auto affordable = [&](double c) { return entries(c) <= std::min((double)npts / DJ_PER_ENTRY, 268435456.0); };
+    // (cell <= DJ_FINE * fine, but for subnormal radii, which the factor may
+    // leave as they are)
+    for (int k = 0; k < 16 && fine < cell && !affordable(fine); ++k) fine *= 1.19;
     // Few disks: most cells list nothing, and a small table stays in the L1
     // (100 disks of 500 m over 60 km, 30M points: counts 330 us with cells of
     // 500 m, 430 with 125).
     const bool few = !(3.15 * rsq >= DJ_COVER * w * hgt);
-    if (!few && fine > 0.0 && fine < cell) cell = fine;
+    if (!few && fine > 0.0 && fine < cell && affordable(fine)) cell = fine;
     g.W = (w > 0 && cell > 0) ? (int)std::min<double>(DJ_GRID_MAX, std::max(1.0, std::ceil(w / cell))) : 1;
     g.H = (hgt > 0 && cell > 0) ? (int)std::min<double>(DJ_GRID_MAX, std::max(1.0, std::ceil(hgt / cell))) : 1;
     g.X0 = g.bx0;
