@@ -384,9 +384,12 @@ int spade_batch_rebuild(spade_ctx *ctx, const spade_polys *polys, int32_t nq, co
  * the count pass alone).  Evaluated with the paper's two-step Map
  * (Sec. 5.1): a count pass, then a write pass.  The count pass keeps each
  * (table chunk, query) overlap's match bits (512 bytes per overlap) so that
- * the write pass needs no second probe; queries whose overlaps would exceed
- * the byte count in the environment variable SPADE_HIT_MASK_LIMIT (default
- * 512 MiB) are taken in groups that do not (0: one query at a time). */
+ * the write pass needs no second probe, and 16 KiB of ids per overlap to
+ * order them, both for whole groups of four overlaps of a query.  Queries
+ * whose match bits would exceed the byte count in the environment variable
+ * SPADE_HIT_MASK_LIMIT (default 512 MiB, so 16 GiB of ids) are taken in
+ * groups that do not (0: one query at a time), and in smaller ones when the
+ * device has less memory. */
 int spade_batch_select(spade_ctx *ctx, const spade_canvas *set, const spade_table *t,
                        uint32_t *out_ids, int64_t cap, int64_t *out_off);
 

@@ -1405,13 +1405,16 @@ int spade_batch_select(spade_ctx *ctx, const spade_canvas *set, const spade_tabl
     auto bins_at = [&](int l) { return (int)(((uint64_t)std::max<int64_t>(t->n - 1, 0) >> l) + 1); };
     while (L > SORT_LMIN && (int64_t)nq * bins_at(L) < 2 * cus && bins_at(L - 1) <= TILE_BINS) --L;
     const int nbins = bins_at(L);
-    // The queries are taken in groups: the hit words of a group's pairs (512
-    // bytes each) fit the limit (SPADE_HIT_MASK_LIMIT bytes, default 512 MiB:
-    // 2^20 pairs, whose tiles then take 16 GiB) and its buckets 2^26, or it is
-    // one query.  Nearly always one group.
+    // The queries are taken in groups.  A group's pairs, every query's rounded
+    // up to whole tiles (a tile's keys take 64 KB however few pairs or ids it
+    // has), have hit words of 512 bytes within the limit
+    // (SPADE_HIT_MASK_LIMIT bytes, default 512 MiB: 2^20 pairs, so 2^18 tiles,
+    // whose keys take 16 GiB), and its buckets are at most 2^26; or it is one
+    // query.  Nearly always one group.
     size_t hits_max = (size_t)512 << 20;
     if (const char *e = getenv("SPADE_HIT_MASK_LIMIT")) hits_max = (size_t)strtoull(e, nullptr, 10);
     constexpr size_t PAIR_BYTES = sizeof(unsigned long long) * BW_WORDS;
+    constexpr size_t TILE_BYTES = PAIR_BYTES * TILE_PAIRS;
     constexpr int64_t BUCKETS = (int64_t)1 << 26;
     DevBuf &bh = ctx->scratch[S_KEYS2], &bo = ctx->scratch[S_ENTF], &bs = ctx->scratch[S_LOOKBACK];
     const std::vector<int64_t> &hq = P.qfirst;   // first pair of every query
@@ -1425,8 +1428,7 @@ int spade_batch_select(spade_ctx *ctx, const spade_canvas *set, const spade_tabl
         int64_t tiles = 0;
         for (int q = 0; q < nq; ++q) {
             const int qb = gq.back();
-            if (q > qb && ((size_t)(hq[(size_t)q + 1] - hq[(size_t)qb]) * PAIR_BYTES > limit ||
-                           (int64_t)(q + 1 - qb) * nbins > BUCKETS)) {
+            if (q > qb && ((size_t)(tiles + tiles_of(q)) * TILE_BYTES > limit || (int64_t)(q + 1 - qb) * nbins > BUCKETS)) {
                 gq.push_back(q);
                 tiles = 0;
             }
@@ -1443,10 +1445,11 @@ int spade_batch_select(spade_ctx *ctx, const spade_canvas *set, const spade_tabl
                ensure(ctx, bs, sizeof(uint16_t) * (size_t)(nbins + 1) * (size_t)tmost);
     };
     group_by(hits_max);
-    if (room()) {
-        ctx->err.clear();   // one query at a time needs the least
-        group_by(0);
-        if (room()) return SPADE_E_NOMEM;
+    while (room()) {
+        if (gmost == 1 || hits_max < TILE_BYTES) return SPADE_E_NOMEM;   // one query at a time needs the least
+        ctx->err.clear();
+        hits_max = std::min(hits_max, (size_t)tmost * TILE_BYTES) / 2;
+        group_by(hits_max);
     }
     unsigned long long *hits = (unsigned long long *)bh.p;
     uint32_t *keys = cap > 0 ? (uint32_t *)bo.p : nullptr;
