@@ -1479,6 +1479,7 @@ int spade_batch_select(spade_ctx *ctx, const spade_canvas *set, const spade_tabl
         for (int q = q0; q < q1; ++q) ntile += (uint32_t)tiles_of(q);
         const uint32_t *dtf = P.tfirst + q0;
         if (ntile == 0) {
+            if (ctx->timing && k == 0) SPADE_HIP(ctx, hipEventRecord(ctx->ev[3], st));
             for (int q = q0; q < q1; ++q) out_off[q + 1] = out_off[q0];
             continue;
         }

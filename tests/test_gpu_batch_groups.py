@@ -1,5 +1,6 @@
 """Batch selection in groups: the scratch of many queries of one table chunk each
-stays within what the limit on hit words allows."""
+stays within what the limit on hit words allows, and a first group without any
+(chunk, query) overlap leaves a valid timing."""
 import numpy as np
 import pytest
 import torch
@@ -43,3 +44,18 @@ def test_scratch_of_many_small_queries(own, monkeypatch):
     monkeypatch.delenv("SPADE_HIT_MASK_LIMIT")
     ids2, off2 = own.batch_select(b, t)
     assert np.array_equal(off, off2) and torch.equal(ids, ids2)
+
+
+@pytest.mark.parametrize("limit", [None, "0"])
+def test_timing_without_overlaps(own, monkeypatch, limit):
+    if limit is not None:
+        monkeypatch.setenv("SPADE_HIT_MASK_LIMIT", limit)
+    p = torch.rand(5000, device="cuda", dtype=torch.float64)
+    t = own.table(p, p.flip(0).contiguous())
+    far = _squares(3, 0.1, 6)
+    far["vx"] = far["vx"] + 7.0
+    b = own.batch(far, np.arange(4))
+    own.set_timing(True)
+    ids, off = own.batch_select(b, t)
+    assert ids.numel() == 0 and not off.any()
+    assert 0.0 <= own.last_timing()[1] < 1000.0
