@@ -112,6 +112,7 @@ struct spade_canvas {
     spade::DevBuf dcds;                       // device copy
     spade::CanvasView view{};                 // probe view of canvas 0
     int64_t n_boundary = 0;
+    int64_t n_overlap = 0;                    // pixels inside several polygons
     int64_t n_cands = 0;
     int64_t n_elist = 0;
     int64_t n_edges = 0;
@@ -205,9 +206,10 @@ bool capturing(hipStream_t s);   // a caller records s into a graph
 int build_canvas(spade_ctx *ctx, const spade_polys *polys, spade_canvas *cv, bool defer = false);
 int build_flush(spade_ctx *ctx, spade_canvas *cv);
 
-// The boundary-pixel counters of a build that build_flush has not copied yet
-// (shards of them, stride words apart), or null: cv->n_boundary is valid.
-const unsigned long long *build_boundary(const spade_canvas *cv, int *shards, int *stride);
+// The counters of the pixels inside several polygons of a build that
+// build_flush has not copied yet (shards of them, stride words apart), or
+// null: cv->n_overlap is valid.
+const unsigned long long *build_overlap(const spade_canvas *cv, int *shards, int *stride);
 
 // Completes a deferred build; returns BUILD_AGAIN when the single row pass
 // ran out of capacity (grown by now: build again, non-deferred).

@@ -981,18 +981,30 @@ __global__ __launch_bounds__(256) void k_emit_bits(int64_t nseg, const unsigned 
     }
 }
 
-__global__ void k_emit_zero(unsigned long long *p) { *p = 0ull; }
-
-// Whether the pairs' count pass keeps labels: p[0], set later by a point in
-// several polygons, and p[1] start at 0 if so, else at 1.
-__global__ void k_emit_flag(unsigned *p, int labelled, const unsigned long long *bnd, int shards, int stride,
-                            unsigned long long known, unsigned long long most)
+// Clears the count behind the last segment, whose scan is the total, and says
+// whether the pairs' count pass keeps labels: p[0], set later by a point in
+// several polygons, and p[1] start at 0 if so, else at 1.  No labels where the
+// pixels that the raster found inside several polygons would hold one of n
+// evenly spread points: the write pass would have to probe again, and the
+// count pass without labels is the faster one (12 overlapping polygons, 30M
+// points: 224 us, with labels 344; the call 940 us and 1,055).  Everywhere else they pay, however many of the pixels are
+// boundary ones (calls of 30M points: 260 zones, 5 % of the pixels, 660 us
+// with labels and 930 probing twice; 29 %, 2.1 and 4.0 ms; 40,000 cells, 14 %,
+// 7.1 and 13.2 ms; 40,000 rectangles of a pixel each, 1.9 and 3.1 ms).  One
+// wavefront; over: the counters of a build not read yet, else null.
+__global__ __launch_bounds__(64) void k_emit_start(unsigned long long *end, unsigned *p, int labelled,
+                                                   const unsigned long long *over, int shards, int stride,
+                                                   unsigned long long known, unsigned long long n,
+                                                   unsigned long long pixels)
 {
-    if (bnd) {
-        known = 0;
-        for (int k = 0; k < shards; ++k) known += bnd[k * stride];
+    if (over) {
+        known = 0ull;
+        for (int k = threadIdx.x; k < shards; k += 64) known += over[k * stride];
+        for (int d = 32; d > 0; d >>= 1) known += (unsigned long long)__shfl_xor((long long)known, d, 64);
     }
-    p[0] = p[1] = labelled && known <= most ? 0u : 1u;
+    if (threadIdx.x != 0) return;
+    *end = 0ull;
+    if (p) p[0] = p[1] = labelled && known * n < pixels ? 0u : 1u;
 }
 
 int probe_emit(spade_ctx *ctx, const spade_canvas *cv, const spade_points *pts, uint32_t *out_pt,
@@ -1045,22 +1057,16 @@ int probe_emit(spade_ctx *ctx, const spade_canvas *cv, const spade_points *pts, 
         SPADE_HIP(ctx, hipGetLastError());
         return SPADE_OK;
     };
-    int rc;
+    int rc = SPADE_OK, shards = 0, stride = 0;
     if (ctx->timing) SPADE_HIP(ctx, hipEventRecord(ctx->ev[2], st));
+    const unsigned long long *over = bits ? nullptr : build_overlap(cv, &shards, &stride);
+    hipLaunchKernelGGL(k_emit_start, dim3(1), dim3(64), 0, st, counts + nseg, bits ? nullptr : multi, labelled ? 1 : 0, over,
+                       shards, stride, (unsigned long long)cv->n_overlap, (unsigned long long)n,
+                       (unsigned long long)cv->view.W * (unsigned long long)cv->view.H);
+    SPADE_HIP(ctx, hipGetLastError());
     if (bits) {
         rc = launch(k_emit_count_bits, lds + QUEUE_BYTES, counts, bits);
-    } else {
-        // Where more than an eighth of the canvas are boundary pixels (a
-        // twentieth in a tessellation), polygons overlap or most points need
-        // records, and the count pass without labels is the faster one (20M
-        // points, 12 overlapping polygons: 0.47 ms, with labels 0.61; 50M
-        // points, 256 zones: 0.37 ms with them, which save a second probe of
-        // 0.48).  The pass that is not chosen returns at once.
-        int shards, stride;
-        const unsigned long long *bnd = build_boundary(cv, &shards, &stride);
-        hipLaunchKernelGGL(k_emit_flag, dim3(1), dim3(1), 0, st, multi, labelled ? 1 : 0, bnd, shards, stride,
-                           (unsigned long long)cv->n_boundary, (unsigned long long)cv->view.W * cv->view.H / 8);
-        rc = SPADE_OK;
+    } else {   // the pass that is not chosen returns at once
         const size_t qb = lds + QUEUE_BYTES;
         const unsigned *skip = multi + 1;
         if (lab16) rc = launch(k_emit_count<uint16_t, true>, qb + EMIT_INDEX_BYTES, counts, multi, lab16, skip);
@@ -1068,8 +1074,6 @@ int probe_emit(spade_ctx *ctx, const spade_canvas *cv, const spade_points *pts, 
         if (!rc) rc = launch(k_emit_count<uint16_t, false>, qb, counts, multi, lab16, skip);
     }
     if (rc) return rc;
-    hipLaunchKernelGGL(k_emit_zero, dim3(1), dim3(1), 0, st, counts + nseg);
-    SPADE_HIP(ctx, hipGetLastError());
     DevBuf &cub = ctx->scratch[S_CUBTMP];
     size_t tb = 0;
     SPADE_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(nullptr, tb, counts, offs, (int)(nseg + 1), st));

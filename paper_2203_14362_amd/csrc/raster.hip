@@ -92,6 +92,8 @@ constexpr int NSHARD = 16;
 constexpr int GSTRIDE = 16;                        // words between counters
 constexpr int NGCTR = NSHARD * 4 * GSTRIDE;        // counter block, 8 KB
 __host__ __device__ inline int gctr_at(int shard, int c) { return (shard * 4 + c) * GSTRIDE; }
+// the pixels inside several polygons: the word behind the boundary pixels'
+__host__ __device__ inline int gctr_overlap_at(int shard) { return gctr_at(shard, 3) + 1; }
 
 // With dcd, also the row counters rcount[0, nrc) and the one canvas's
 // descriptor, whose size the caller's bounding box already gave (a launch and
@@ -1314,7 +1316,7 @@ __device__ void process_row(const RowArgs &A, const RowData &D, RowShared &L, in
     // phase 3: classify pixels.  sx := 0 (no polygon), label + 1, or for a
     // boundary pixel BFLAG | (label + 1 of its single interior claimant, or 0);
     // sa := per-column record counters, starting with the claimant record.
-    uint32_t nb = 0, multi = 0;
+    uint32_t nb = 0, nover = 0;   // boundary pixels, pixels inside several polygons
     for (int c = tid; c < W; c += row_threads()) {
         const int32_t bc = L.sa[cix(c)], cc = L.sb[cix(c)];
         const uint32_t xc = L.sx_get(cix(c));
@@ -1323,10 +1325,10 @@ __device__ void process_row(const RowArgs &A, const RowData &D, RowShared &L, in
         L.sa[cix(c)] = (bnd && cc == 1) ? 1 : 0;
         L.sb[cix(c)] = 0;
         nb += bnd ? 1u : 0u;
-        multi |= (cc >= 2) ? 1u : 0u;
+        nover += (cc >= 2) ? 1u : 0u;
     }
     atomicAdd(s_nbp, nb);
-    if (multi) atomicOr(s_multi, 1u);
+    if (nover) atomicAdd(s_multi, nover);
     __syncthreads();
     const bool rmulti = *s_multi != 0;
     if (rmulti) {
@@ -1357,6 +1359,7 @@ __device__ void process_row(const RowArgs &A, const RowData &D, RowShared &L, in
             const unsigned long long b1 = atomicAdd(&A.gctr[gctr_at(sh, 1)], *s_nloc);
             const unsigned long long b2 = atomicAdd(&A.gctr[gctr_at(sh, 2)], (unsigned long long)npart_r);
             atomicAdd(&A.gctr[gctr_at(sh, 3)], (unsigned long long)*s_nbp);
+            if (rmulti) atomicAdd(&A.gctr[gctr_overlap_at(sh)], (unsigned long long)*s_multi);
             const bool over = b0 + nrec > A.cap_rec || b1 + *s_nloc > A.cap_loc || b2 + npart_r > A.cap_part;
             if (over) atomicOr(A.errflags, 32u);
             s_base[0] = (unsigned long long)sh * A.cap_rec + b0;
@@ -1777,12 +1780,20 @@ int build_flush(spade_ctx *ctx, spade_canvas *cv)
     return SPADE_OK;
 }
 
-const unsigned long long *build_boundary(const spade_canvas *cv, int *shards, int *stride)
+static uint64_t overlap_total(const void *hcb)
+{
+    const uint64_t *hc = (const uint64_t *)((const char *)hcb + CTR_HEAD);
+    uint64_t t = 0;
+    for (int k = 0; k < NSHARD; ++k) t += hc[gctr_overlap_at(k)];
+    return t;
+}
+
+const unsigned long long *build_overlap(const spade_canvas *cv, int *shards, int *stride)
 {
     *shards = NSHARD;
-    *stride = gctr_at(1, 0);
+    *stride = gctr_overlap_at(1) - gctr_overlap_at(0);
     if (!cv->pending || !cv->pend_src) return nullptr;
-    return (const unsigned long long *)((const char *)cv->pend_src + CTR_HEAD) + gctr_at(0, 3);
+    return (const unsigned long long *)((const char *)cv->pend_src + CTR_HEAD) + gctr_overlap_at(0);
 }
 
 int build_finish(spade_ctx *ctx, spade_canvas *cv)
@@ -1807,6 +1818,7 @@ int build_finish(spade_ctx *ctx, spade_canvas *cv)
     }
     if (int rc = flag_error(ctx, ef)) return rc;
     cv->n_boundary = (int64_t)counter_total(hc, 3);
+    cv->n_overlap = (int64_t)overlap_total(hc);
     cv->n_cands = (int64_t)nrec;
     cv->n_elist = (int64_t)(nloc + npart);
     return SPADE_OK;
@@ -2004,7 +2016,7 @@ int build_set(spade_ctx *ctx, const spade_polys *polys, int nc, const int64_t *p
         if (ensure(ctx, cv->cands, 2 * sizeof(Cand)) || ensure(ctx, cv->ledges, sizeof(Edge)) ||
             ensure(ctx, cv->pspan, sizeof(double2)))
             return SPADE_E_NOMEM;
-        cv->n_boundary = cv->n_cands = cv->n_elist = 0;
+        cv->n_boundary = cv->n_overlap = cv->n_cands = cv->n_elist = 0;
         finish_views(cv);
         if (hinted) {
             // the validation verdict is still to be read
@@ -2367,6 +2379,7 @@ int build_set(spade_ctx *ctx, const spade_polys *polys, int nc, const int64_t *p
         SPADE_HIP(ctx, hipStreamSynchronize(st));
         ef = counter_flags(hc);
         if (ef & (1u | 2u | 4u | 64u | 128u)) return flag_error(ctx, ef);   // a hinted build's verdict
+        cv->n_overlap = (int64_t)overlap_total(hc);   // of every row, also of one without room
         if (!(ef & 32u)) {
             done_single = true;
             nrec = counter_total(hc, 0); nloc = counter_total(hc, 1);
