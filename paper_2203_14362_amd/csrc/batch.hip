@@ -802,17 +802,21 @@ __global__ __launch_bounds__(PS_THREADS) void k_bucket_scan(int nq, int nbins, c
 // 2.8 + 6.2 + 5.5 + 0.5 ms.
 
 constexpr int PW_BYTES = 4096;                          // LDS pool of a wavefront of the write pass
-constexpr uint32_t PW_LONG = PW_BYTES / sizeof(uint32_t);   // lists that may not fit it
+// Longer lists go through a bitmap.  200,000 points in n polygons each, layered
+// (ids in any order), by insertion and by bitmap: n = 40 425 and 516 us, 48 484
+// and 539, 64 1,655 and 587, 100 1,821 and 779.
+constexpr uint32_t PW_LONG = 48;
+constexpr int PL_WORDS = 2048;                          // its words of 32 ids per wavefront
 constexpr size_t PAIR_HITS_MAX = (size_t)16 << 30;
 
 // Count pass over chunks [c0, c1).  hits, when given, keeps the points that
 // matched: hits[(t - cbase[c0]) * BW_WORDS + j] for entry t of the chunks'
-// query lists and word j.  *longest is raised to the longest list.
+// query lists and word j.  *some_long is set by a list longer than PW_LONG.
 __global__ __launch_bounds__(BT_THREADS) void k_batch_pcount(SetArgs S, int64_t nfin, int64_t c0, int64_t c1,
                                                              const double *X, const double *Y, const uint32_t *ids,
                                                              const unsigned int *cbase, const uint32_t *plist,
                                                              const uint32_t *pq, uint32_t *pcnt,
-                                                             unsigned long long *hits, uint32_t *longest)
+                                                             unsigned long long *hits, uint32_t *some_long)
 {
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -878,30 +882,48 @@ __global__ __launch_bounds__(BT_THREADS) void k_batch_pcount(SetArgs S, int64_t 
 #pragma unroll
         for (int u = 0; u < BW_PTS; ++u) {
             if (cnt[u]) pcnt[ids[i0 + 64 * u]] = cnt[u];
-            if (cnt[u] > PW_LONG) atomicMax(longest, cnt[u]);
+            if (cnt[u] > PW_LONG) *some_long = 1u;
         }
     }
+}
+
+// fn(polygon id) for every match of point (x, y) with the canvas d that is
+// known to have one: only the record of a boundary pixel that has no other is
+// then the match without a test.
+template <typename Fn>
+__device__ __forceinline__ void point_matches(const SetArgs &S, const CanvasDesc &d, double x, double y, Fn fn)
+{
+    const CanvasView v = set_view(d, S.cells, S.coarse, S.cands, S.ledges, S.pspan);
+    const uint32_t w = lookup(v, v.coarse, x, y);
+    uint32_t rec = w & ~BFLAG, label = w - 1u;
+    bool more = (w & BFLAG) != 0, first = true, in = true;
+    do {
+        if (more) {
+            const Cand cd = v.cands[rec++];
+            label = cd.poly;
+            more = !(cd.meta & CAND_LAST);
+            in = (first && !more) || cand_inside(v, cd, x, y);
+            first = false;
+        }
+        if (in) fn(caller_id(S, d.poly_base + label));
+    } while (more);
 }
 
 // Write pass over chunks [c0, c1), from the count pass's hit words: a
 // wavefront takes 64 table points, one per lane, whose lists are gathered in
 // its pool in LDS in ascending polygon id (an insertion per match), as many
 // points at a time as the pool holds, and stored.  Only the points that
-// matched look their canvas word up again, and the only record of a boundary
-// pixel is then the match without another test.  LONG: the lists longer than
-// the pool, gathered in place in the output by a launch of their own (which
-// ends at once when there is none, so that the usual launch needs no
-// registers for it).  Positions at or beyond cap are not written.
-template <typename T, bool LONG>
+// matched look their canvas word up again.  Positions at or beyond cap are not
+// written.
+template <typename T>
 __global__ __launch_bounds__(BT_THREADS) void k_batch_pwrite(SetArgs S, int64_t nfin, int64_t c0, int64_t c1,
                                                              const double *X, const double *Y, const uint32_t *ids,
                                                              const unsigned int *cbase, const uint32_t *plist,
                                                              const uint32_t *pq, const unsigned long long *hits,
-                                                             const unsigned long long *offs, const uint32_t *longest,
-                                                             uint32_t *out_poly, int64_t cap)
+                                                             const unsigned long long *offs, uint32_t *out_poly, int64_t cap)
 {
     constexpr uint32_t POOL = PW_BYTES / sizeof(T);
-    if (LONG && *longest <= POOL) return;
+    static_assert(PW_LONG <= POOL, "the pool holds a list");
     __shared__ T pools[BT_THREADS / 64][POOL];
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -922,49 +944,7 @@ __global__ __launch_bounds__(BT_THREADS) void k_batch_pwrite(SetArgs S, int64_t 
             o = (int64_t)offs[id];
             n = o < cap ? (uint32_t)(offs[id + 1] - (unsigned long long)o) : 0u;
         }
-        // fn(polygon id) for every match of the points `of`
-        auto matches = [&](unsigned long long of, auto fn) {
-            for (uint32_t t = t0; t < t1; ++t) {
-                const unsigned long long m = hits[(size_t)(t - tb) * BW_WORDS + word % BW_WORDS] & of;
-                if (m == 0ull) continue;
-                const CanvasDesc &d = S.cds[pq[plist[t]]];
-                const CanvasView v = set_view(d, S.cells, S.coarse, S.cands, S.ledges, S.pspan);
-                if (!((m >> lane) & 1ull)) continue;
-                const uint32_t w = lookup(v, v.coarse, x, y);
-                uint32_t rec = w & ~BFLAG, label = w - 1u;
-                bool more = (w & BFLAG) != 0, first = true, in = true;
-                do {
-                    if (more) {
-                        const Cand cd = v.cands[rec++];
-                        label = cd.poly;
-                        more = !(cd.meta & CAND_LAST);
-                        in = (first && !more) || cand_inside(v, cd, x, y);
-                        first = false;
-                    }
-                    if (in) fn(caller_id(S, d.poly_base + label));
-                } while (more);
-            }
-        };
-        if (LONG) {
-            const bool mine = n > POOL;
-            if (!__ballot(mine)) continue;
-            // the smallest of a list that cap cuts off are kept
-            const uint32_t keep = (uint32_t)min<int64_t>(n, cap - o);
-            uint32_t *list = out_poly + o, j = 0u;
-            matches(__ballot(mine), [&](uint32_t id) {
-                uint32_t at = j;
-                if (j < keep) ++j;
-                else if (list[keep - 1] > id) at = keep - 1;
-                else return;
-                while (at > 0u && list[at - 1] > id) {
-                    list[at] = list[at - 1];
-                    --at;
-                }
-                list[at] = id;
-            });
-            continue;
-        }
-        const uint32_t np = n > POOL ? 0u : n;
+        const uint32_t np = n > PW_LONG ? 0u : n;
         const uint32_t excl = wave_incl_sum(np) - np;
         unsigned long long todo = __ballot(np != 0u);
         while (todo) {
@@ -973,18 +953,99 @@ __global__ __launch_bounds__(BT_THREADS) void k_batch_pwrite(SetArgs S, int64_t 
             T *list = pool + (now ? excl - base : 0u);
             uint32_t j = 0u;
             const unsigned long long of = __ballot(now);
-            matches(of, [&](uint32_t id) {
-                if (j >= np) return;
-                uint32_t at = j++;
-                while (at > 0u && (uint32_t)list[at - 1] > id) {
-                    list[at] = list[at - 1];
-                    --at;
-                }
-                list[at] = (T)id;
-            });
+            for (uint32_t t = t0; t < t1; ++t) {
+                const unsigned long long m = hits[(size_t)(t - tb) * BW_WORDS + word % BW_WORDS] & of;
+                if (m == 0ull) continue;
+                const CanvasDesc &d = S.cds[pq[plist[t]]];
+                if (!((m >> lane) & 1ull)) continue;
+                point_matches(S, d, x, y, [&](uint32_t id) {
+                    if (j >= np) return;
+                    uint32_t at = j++;
+                    while (at > 0u && (uint32_t)list[at - 1] > id) {
+                        list[at] = list[at - 1];
+                        --at;
+                    }
+                    list[at] = (T)id;
+                });
+            }
             if (now)
                 for (uint32_t k = 0; k < np && o + k < cap; ++k) out_poly[o + k] = (uint32_t)list[k];
             todo &= ~of;
+        }
+    }
+}
+
+// The lists longer than PW_LONG (ends at once when there is none): a wavefront
+// takes one point at a time, its lanes the canvases of the point's chunk, and
+// marks the matches in a bitmap of ids in LDS, whose set bits, read in order,
+// are the list, a window of ids after the other.  Linear in the list, where an
+// insertion is quadratic: 600 polygons over each of 16,384 points, the call 1.9
+// ms, by insertion 210.  Bound by the latency of the matches' lookups.
+__global__ __launch_bounds__(BT_THREADS) void k_batch_plong(SetArgs S, int64_t nfin, int64_t c0, int64_t c1,
+                                                            const double *X, const double *Y, const uint32_t *ids,
+                                                            const unsigned int *cbase, const uint32_t *plist,
+                                                            const uint32_t *pq, const unsigned long long *hits,
+                                                            const unsigned long long *offs, const uint32_t *some_long,
+                                                            uint32_t npoly, uint32_t *out_poly, int64_t cap)
+{
+    if (*some_long == 0u) return;
+    __shared__ uint32_t maps[BT_THREADS / 64][PL_WORDS];
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    uint32_t *map = maps[wv];
+    auto sync = [] {   // order this wavefront's LDS accesses
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
+    const uint32_t tb = cbase[c0];
+    for (int64_t word = c0 * BW_WORDS + (int64_t)blockIdx.x * (BT_THREADS / 64) + wv; word < c1 * BW_WORDS;
+         word += (int64_t)gridDim.x * (BT_THREADS / 64)) {
+        const int64_t c = word / BW_WORDS;
+        const uint32_t t0 = cbase[c], t1 = cbase[c + 1];
+        if (t0 == t1) continue;
+        const int64_t i = word * 64 + lane;
+        int64_t o = 0;
+        uint32_t n = 0u;
+        if (i < nfin) {
+            const uint32_t id = ids[i];
+            o = (int64_t)offs[id];
+            n = o < cap ? (uint32_t)(offs[id + 1] - (unsigned long long)o) : 0u;
+        }
+        for (unsigned long long todo = __ballot(n > PW_LONG); todo; todo &= todo - 1) {
+            const int b = __ffsll((long long)todo) - 1;
+            const double x = X[word * 64 + b], y = Y[word * 64 + b];
+            int64_t pos = __shfl(o, b, 64);
+            uint32_t w0 = 0u;   // first id of the window, a multiple of 32
+            while (w0 < npoly && pos < cap) {
+                const uint32_t left = (npoly - w0 + 31u) / 32u;
+                const int nw = (int)(left < (uint32_t)PL_WORDS ? left : (uint32_t)PL_WORDS);
+                for (int k = lane; k < (nw + 63) / 64 * 64; k += 64) map[k] = 0u;
+                sync();
+                uint32_t next = npoly;   // the smallest id past the window
+                for (uint32_t t = t0 + lane; t < t1; t += 64) {
+                    if (!((hits[(size_t)(t - tb) * BW_WORDS + word % BW_WORDS] >> b) & 1ull)) continue;
+                    point_matches(S, S.cds[pq[plist[t]]], x, y, [&](uint32_t id) {
+                        if (id < w0) return;
+                        const uint32_t k = (id - w0) / 32u;
+                        if (k < (uint32_t)nw) atomicOr(&map[k], 1u << (id & 31u));
+                        else next = min(next, id);
+                    });
+                }
+                sync();
+                for (int k0 = 0; k0 < nw; k0 += 64) {
+                    uint32_t m = map[k0 + lane];
+                    const uint32_t cnt = (uint32_t)__popc(m), incl = wave_incl_sum(cnt);
+                    int64_t p = pos + (incl - cnt);
+                    const uint32_t first = w0 + 32u * (uint32_t)(k0 + lane);
+                    for (; m != 0u; m &= m - 1u, ++p)
+                        if (p < cap) out_poly[p] = first + (uint32_t)(__ffs((int)m) - 1);
+                    pos += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+                }
+                sync();
+#pragma unroll
+                for (int d = 32; d > 0; d >>= 1) next = min(next, (uint32_t)__shfl_xor((int)next, d, 64));
+                w0 = next < npoly ? next & ~31u : npoly;
+            }
         }
     }
 }
@@ -1705,7 +1766,7 @@ int spade_batch_join_pairs(spade_ctx *ctx, const spade_canvas *set, const spade_
     DevBuf &bc = ctx->scratch[S_VALS2], &bo = ctx->scratch[S_ENTC], &cub = ctx->scratch[S_CUBTMP];
     if (ensure(ctx, bc, sizeof(uint32_t) * (size_t)(n + 2)) || ensure(ctx, bo, sizeof(unsigned long long) * (size_t)(n + 1)))
         return SPADE_E_NOMEM;
-    uint32_t *pcnt = (uint32_t *)bc.p, *longest = pcnt + (n + 1);
+    uint32_t *pcnt = (uint32_t *)bc.p, *some_long = pcnt + (n + 1);
     unsigned long long *offs = (unsigned long long *)bo.p;
     const auto counts64 = rocprim::make_transform_iterator((const uint32_t *)pcnt, Widen());
     size_t tb = 0;
@@ -1741,7 +1802,7 @@ int spade_batch_join_pairs(spade_ctx *ctx, const spade_canvas *set, const spade_
     auto count = [&](int64_t c0, int64_t c1, unsigned long long *keep) {
         hipLaunchKernelGGL(k_batch_pcount, task_grid(c1 - c0, BW_TASKS), dim3(BT_THREADS), 0, st, S, t->nfin, c0, c1,
                            (const double *)t->x.p, (const double *)t->y.p, (const uint32_t *)t->ids.p, P.cbase, P.plist,
-                           P.pq, pcnt, keep, longest);
+                           P.pq, pcnt, keep, some_long);
     };
     count(0, t->nchunk, group == t->nchunk ? hits : nullptr);
     SPADE_HIP(ctx, hipGetLastError());
@@ -1751,20 +1812,16 @@ int spade_batch_join_pairs(spade_ctx *ctx, const spade_canvas *set, const spade_
         for (int64_t c0 = 0; c0 < t->nchunk; c0 += group) {
             const int64_t c1 = std::min(t->nchunk, c0 + group);
             if (group < t->nchunk) count(c0, c1, hits);
-            auto write = [&](auto kern) {
+            auto write = [&](auto kern, auto... args) {
                 hipLaunchKernelGGL(kern, task_grid(c1 - c0, BW_WORDS), dim3(BT_THREADS), 0, st, S, t->nfin, c0, c1,
                                    (const double *)t->x.p, (const double *)t->y.p, (const uint32_t *)t->ids.p, P.cbase,
-                                   P.plist, P.pq, (const unsigned long long *)hits, (const unsigned long long *)offs,
-                                   (const uint32_t *)longest, out_poly, cap);
+                                   P.plist, P.pq, (const unsigned long long *)hits, (const unsigned long long *)offs, args...,
+                                   out_poly, cap);
             };
             // 16-bit lists hold the polygon ids of at most 2^16 polygons
-            if (M <= 65536) {
-                write(k_batch_pwrite<uint16_t, false>);
-                write(k_batch_pwrite<uint16_t, true>);
-            } else {
-                write(k_batch_pwrite<uint32_t, false>);
-                write(k_batch_pwrite<uint32_t, true>);
-            }
+            if (M <= 65536) write(k_batch_pwrite<uint16_t>);
+            else write(k_batch_pwrite<uint32_t>);
+            write(k_batch_plong, (const uint32_t *)some_long, (uint32_t)M);
         }
         hipLaunchKernelGGL(k_pair_points, dim3(grid_of(n)), dim3(256), 0, st, n, (const unsigned long long *)offs, out_pt,
                            cap);
