@@ -10,7 +10,8 @@
 // paper's two-step Map (Sec. 5.1): a selection's probe pass keeps every pair's
 // match bits, whose ids are counted per window of ids and put in order window
 // by window; a join's count pass sizes every point's output range, a scan
-// places the ranges in id order and a write pass fills them.  The join-count
+// places the ranges in id order and a write pass fills them (few pairs are
+// sorted as keys instead).  The join-count
 // needs no pair list: its single probe launch finds each chunk's queries
 // itself.
 #include "common.h"
@@ -808,6 +809,16 @@ constexpr int PW_BYTES = 4096;                          // LDS pool of a wavefro
 constexpr uint32_t PW_LONG = 48;
 constexpr int PL_WORDS = 2048;                          // its words of 32 ids per wavefront
 constexpr size_t PAIR_HITS_MAX = (size_t)16 << 30;
+// Sorted keys while the (chunk, query) overlaps have at most as many points as
+// the table, in a table of PK_LARGE points or more, and a PK_PART of them in a
+// smaller one.  Lists and places of all points, and keys: one polygon, 30M
+// points, 3,570 pairs 460 and 104 us, 11.3M pairs 1,206 and 586; 18M points,
+// 0.36M to 6.8M pairs 336 to 723 and 218 to 427; 8M points, 0.37M pairs 216 and
+// 212; 5M points, overlaps of a 20th of them 166 and 152, a tenth 172 and 187,
+// a half 239 and 298 (a library sort of some 100,000 keys takes many launches).
+// Where every point meets several queries lists are better: 30M points, 78M
+// pairs 3.2 and 4.8 ms.
+constexpr int64_t PK_LARGE = (int64_t)1 << 23, PK_PART = 16;
 
 // Count pass over chunks [c0, c1).  hits, when given, keeps the points that
 // matched: hits[(t - cbase[c0]) * BW_WORDS + j] for entry t of the chunks'
@@ -1076,6 +1087,101 @@ __global__ __launch_bounds__(256) void k_pair_points(int64_t n, const unsigned l
         } else {
             for (unsigned long long k = id ? offs[min(n, id)] : 0ull; k < e && (int64_t)k < cap; ++k) out_pt[k] = (uint32_t)id;
         }
+    }
+}
+
+// The pairs of few (chunk, query) pairs as 64-bit keys (id << pbits | polygon
+// id), in any order, to be sorted: for a table that is large beside them, the
+// counts and places of all its points cost more.  A workgroup takes a pair, its
+// wavefronts the pair's tasks as in k_batch_hits, and reserves its keys once
+// (11.3M pairs of 30M points, 3,094 overlaps: 134 us; with an atomic per
+// wavefront 582, bound by that address).  *cursor counts all of them; keys at
+// or beyond room are not written.
+constexpr int PK_THREADS = 64 * BW_TASKS;
+
+__global__ __launch_bounds__(PK_THREADS) void k_batch_pkeys(SetArgs S, int64_t nfin, const double *X, const double *Y,
+                                                            const uint32_t *ids, const uint32_t *pq, const uint32_t *pc,
+                                                            uint32_t np, int pbits, unsigned long long *cursor,
+                                                            unsigned long long *keys, unsigned long long room)
+{
+    __shared__ uint32_t wsum[BW_TASKS];
+    __shared__ unsigned long long s_at;
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    for (uint32_t p = blockIdx.x; p < np; p += gridDim.x) {
+        const int64_t i0 = (int64_t)pc[p] * CHUNK + wv * (64 * BW_PTS) + lane;
+        double xs[BW_PTS], ys[BW_PTS];
+#pragma unroll
+        for (int u = 0; u < BW_PTS; ++u) {
+            xs[u] = i0 + 64 * u < nfin ? X[i0 + 64 * u] : NAN;
+            ys[u] = i0 + 64 * u < nfin ? Y[i0 + 64 * u] : NAN;
+        }
+        const CanvasDesc d = S.cds[pq[p]];
+        const CanvasView v = set_view(d, S.cells, S.coarse, S.cands, S.ledges, S.pspan);
+        const uint32_t cw = task_word(v, task_box<BW_PTS>(xs, ys), lane);
+        uint32_t ws[BW_PTS];
+        if (cw != NO_WORD) {
+#pragma unroll
+            for (int u = 0; u < BW_PTS; ++u) ws[u] = i0 + 64 * u < nfin ? cw : 0u;
+        } else {
+            Look lk[BW_PTS];
+#pragma unroll
+            for (int u = 0; u < BW_PTS; ++u) lk[u] = look_coarse(v, v.coarse, xs[u], ys[u]);
+#pragma unroll
+            for (int u = 0; u < BW_PTS; ++u) ws[u] = lk[u].full ? ((gu32p)v.cells)[lk[u].fidx] : lk[u].word;
+        }
+        auto records = [&](int u, auto fn) {
+            for (uint32_t rec = ws[u] & ~BFLAG;; ++rec) {
+                const Cand cd = v.cands[rec];
+                if (cand_inside(v, cd, xs[u], ys[u])) fn(cd.poly);
+                if (cd.meta & CAND_LAST) break;
+            }
+        };
+        // a boundary point in one polygon or none gets that word; in several it
+        // keeps its own and is tested again
+        uint32_t mine = 0u;
+#pragma unroll
+        for (int u = 0; u < BW_PTS; ++u) {
+            uint32_t got = ws[u] != 0u ? 1u : 0u;
+            if (ws[u] & BFLAG) {
+                uint32_t one = 0u;
+                got = 0u;
+                records(u, [&](uint32_t label) { ++got; one = label + 1u; });
+                if (got <= 1u) ws[u] = one;
+            }
+            mine += got;
+        }
+        const uint32_t incl = wave_incl_sum(mine);
+        if (lane == 63) wsum[wv] = incl;
+        __syncthreads();
+        uint32_t pre = 0u, total = 0u;
+#pragma unroll
+        for (int w = 0; w < BW_TASKS; ++w) {
+            pre += w < wv ? wsum[w] : 0u;
+            total += wsum[w];
+        }
+        if (threadIdx.x == 0) s_at = total != 0u ? atomicAdd(cursor, (unsigned long long)total) : 0ull;
+        __syncthreads();
+        unsigned long long at = s_at + pre + (incl - mine);
+        auto put = [&](int u, uint32_t label) {
+            if (at < room) keys[at] = ((unsigned long long)ids[i0 + 64 * u] << pbits) | caller_id(S, d.poly_base + label);
+            ++at;
+        };
+        if (mine != 0u && keys != nullptr)
+#pragma unroll
+            for (int u = 0; u < BW_PTS; ++u) {
+                if (ws[u] & BFLAG) records(u, [&](uint32_t label) { put(u, label); });
+                else if (ws[u] != 0u) put(u, ws[u] - 1u);
+            }
+    }
+}
+
+__global__ void k_split_keys(int64_t n, const unsigned long long *keys, int pbits, uint32_t *pt, uint32_t *pg)
+{
+    const unsigned long long m = (1ull << pbits) - 1ull;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        pt[i] = (uint32_t)(keys[i] >> pbits);
+        pg[i] = (uint32_t)(keys[i] & m);
     }
 }
 
@@ -1741,6 +1847,58 @@ int spade_batch_join_count(spade_ctx *ctx, const spade_canvas *set, const spade_
     return SPADE_OK;
 }
 
+// Join pairs by sorted keys, as far as room keys hold them (several polygons
+// of a query may hold a point); done is left false when they don't, or when the
+// memory is not there.
+static int sorted_pairs(spade_ctx *ctx, const spade_table *t, const SetArgs &S, const Pairs &P, int64_t M,
+                        unsigned long long room, uint32_t *out_pt, uint32_t *out_poly, int64_t cap, int64_t *n_out,
+                        bool &done)
+{
+    hipStream_t st = ctx->stream;
+    DevBuf &bk = ctx->scratch[S_ENTC], &bs = ctx->scratch[S_KEYS2], &bc = ctx->scratch[S_VALS2], &cub = ctx->scratch[S_CUBTMP];
+    const int pbits = bits_of((uint64_t)(M - 1)), idbits = std::max(1, bits_of((uint64_t)(t->n - 1)));
+    if (ensure(ctx, bc, sizeof(unsigned long long))) return SPADE_E_NOMEM;
+    unsigned long long *cursor = (unsigned long long *)bc.p, *keys = nullptr, *sorted = nullptr;
+    if (cap > 0 && P.np > 0) {
+        if (ensure(ctx, bk, 8 * (size_t)room) || ensure(ctx, bs, 8 * (size_t)room)) {
+            ctx->err.clear();
+            return SPADE_OK;
+        }
+        keys = (unsigned long long *)bk.p;
+        sorted = (unsigned long long *)bs.p;
+    }
+    unsigned long long *h = (unsigned long long *)ensure_pinned(ctx, 64);
+    if (!h) return set_error(ctx, SPADE_E_NOMEM, "pinned staging allocation failed");
+    hipLaunchKernelGGL(k_zero64, dim3(1), dim3(64), 0, st, (int64_t)1, cursor);
+    if (ctx->timing) SPADE_HIP(ctx, hipEventRecord(ctx->ev[2], st));
+    if (P.np > 0)
+        hipLaunchKernelGGL(k_batch_pkeys, dim3((unsigned)std::min<int64_t>(P.np, 1 << 20)), dim3(PK_THREADS), 0, st, S,
+                           t->nfin, (const double *)t->x.p, (const double *)t->y.p, (const uint32_t *)t->ids.p, P.pq, P.pc,
+                           (uint32_t)P.np, pbits, cursor, keys, room);
+    SPADE_HIP(ctx, hipGetLastError());
+    SPADE_HIP(ctx, hipMemcpyAsync(h, cursor, sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
+    SPADE_HIP(ctx, hipStreamSynchronize(st));
+    const int64_t total = (int64_t)h[0];
+    if (cap > 0 && h[0] > room) return SPADE_OK;
+    if (cap > 0 && total > 0) {
+        size_t tb = 0;
+        SPADE_HIP(ctx, hipcub::DeviceRadixSort::SortKeys(nullptr, tb, (const unsigned long long *)keys, sorted, (int)total, 0,
+                                                         pbits + idbits, st));
+        if (ensure(ctx, cub, std::max<size_t>(tb, 1))) return SPADE_E_NOMEM;
+        SPADE_HIP(ctx, hipcub::DeviceRadixSort::SortKeys(cub.p, tb, (const unsigned long long *)keys, sorted, (int)total, 0,
+                                                         pbits + idbits, st));
+        const int64_t nw = std::min(total, cap);
+        hipLaunchKernelGGL(k_split_keys, dim3(grid_of(nw)), dim3(256), 0, st, nw, (const unsigned long long *)sorted, pbits,
+                           out_pt, out_poly);
+        SPADE_HIP(ctx, hipGetLastError());
+    }
+    if (ctx->timing) SPADE_HIP(ctx, hipEventRecord(ctx->ev[3], st));
+    SPADE_HIP(ctx, hipStreamSynchronize(st));
+    *n_out = total;
+    done = true;
+    return total > cap ? set_error(ctx, SPADE_E_CAPACITY, "output capacity too small") : SPADE_OK;
+}
+
 int spade_batch_join_pairs(spade_ctx *ctx, const spade_canvas *set, const spade_table *t, uint32_t *out_pt,
                            uint32_t *out_poly, int64_t cap, int64_t *n_out)
 {
@@ -1760,10 +1918,15 @@ int spade_batch_join_pairs(spade_ctx *ctx, const spade_canvas *set, const spade_
     int rc = make_pairs(ctx, set, t, P);
     if (rc) return rc;
     const SetArgs S = set_args(set);
-    // counts by point id, and their places (64-bit: a join may hold more than
-    // 2^32 pairs)
     const int64_t n = t->n;
     DevBuf &bc = ctx->scratch[S_VALS2], &bo = ctx->scratch[S_ENTC], &cub = ctx->scratch[S_CUBTMP];
+    if (P.np * CHUNK <= (n >= PK_LARGE ? n : n / PK_PART)) {
+        bool done = false;
+        rc = sorted_pairs(ctx, t, S, P, M, (unsigned long long)(P.np * CHUNK), out_pt, out_poly, cap, n_out, done);
+        if (rc || done) return rc;
+    }
+    // counts by point id, and their places (64-bit: a join may hold more than
+    // 2^32 pairs)
     if (ensure(ctx, bc, sizeof(uint32_t) * (size_t)(n + 2)) || ensure(ctx, bo, sizeof(unsigned long long) * (size_t)(n + 1)))
         return SPADE_E_NOMEM;
     uint32_t *pcnt = (uint32_t *)bc.p, *some_long = pcnt + (n + 1);
