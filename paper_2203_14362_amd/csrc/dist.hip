@@ -238,7 +238,8 @@ __global__ void k_dcell_full(int64_t ncell, uint2 *cells, uint32_t *cell_disk, i
 
 struct DiskCanvas {
     DiskGrid g;
-    const uint2 *cells;          // first entry, entries that hold the cell; one past the last cell
+    const uint32_t *off;         // the cells' first entries; one past the last cell
+    const uint2 *cells;          // the same, and which of the first 32 entries hold the cell
     const uint32_t *cell_disk;   // the cells' entries: disk ids ascending, DJ_FULL
     const double2 *centre;       // the disks' centres, one load each
     unsigned longest;            // most entries of a cell (0: at most 32)
@@ -260,12 +261,15 @@ struct alignas(8) CellPair {
 };
 
 // The candidates of point (x, y): its cell's disks cell_disk[k, k + rem).
+// From the offsets alone, half the table: counts of 100 disks over 30M points
+// 212 us, 255 from the cells' records.
 __device__ __forceinline__ void disk_range(const DiskCanvas &K, double x, double y, uint32_t &k, uint32_t &rem)
 {
     const int cell = disk_cell(K, x, y);
-    const CellPair p = cell < 0 ? CellPair{{0u, 0u}, {0u, 0u}} : *(const CellPair *)(K.cells + cell);
-    k = p.a.x;
-    rem = p.b.x - p.a.x;
+    k = rem = 0u;
+    if (cell < 0) return;
+    k = K.off[cell];
+    rem = K.off[cell + 1] - k;
 }
 
 // The (point, disk) pairs of a wavefront's points with the disk tests
@@ -758,6 +762,7 @@ static int build_disk_canvas(spade_ctx *ctx, const spade_disks *dk, int64_t npts
     }
     hipLaunchKernelGGL(k_dcell_full, cgrid, dim3(256), 0, st, ncell, cells, cell_disk, sorted ? 0 : 1);
     SPADE_HIP(ctx, hipGetLastError());
+    K.off = coff;
     K.cells = cells;
     K.cell_disk = cell_disk;
     K.centre = centre;
