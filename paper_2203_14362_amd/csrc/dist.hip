@@ -41,8 +41,11 @@ constexpr uint32_t DJ_FULL = 0x80000000u;     // in a cell's entry: the disk hol
 // lists about n / DJ_PER_ENTRY entries (both cost a pass each, the points
 // the tests that they save).
 constexpr double DJ_COVER = 0.0625;           // disks over a position on average, at least, for that
+constexpr double DJ_STACK = 32.0;             // and at most (longer lists have no masks)
 constexpr double DJ_FINE = 4.0, DJ_PER_CELL = 8.0, DJ_PER_ENTRY = 8.0;
-constexpr unsigned DJ_LIST_SORT = 64;         // longest list ordered by one lane
+constexpr unsigned DJ_LIST_SORT = 16;         // longest list ordered by one lane
+constexpr unsigned DJ_LIST_WAVE = 256;        // by a wavefront
+constexpr unsigned DJ_LIST_WG = 2048;         // by a workgroup
 constexpr int DJ_QCAP = 64;                   // queued points per wavefront
 constexpr int DJ_QWAVE = DJ_QCAP * 28;        // x, y, entries, place: bytes per wavefront
 constexpr uint32_t DJ_STAGE = 512;            // pairs listed per wavefront before they are stored
@@ -141,68 +144,158 @@ __device__ __forceinline__ int cell_reached(const DiskGrid &g, double ux, double
 
 // The cells of every disk, a wavefront per disk (the cells of its box are
 // spread over the lanes, so that a disk much larger than the others is not
-// one lane's loop).  CELL_COUNT: the entries of every cell, and *total of
-// all; CELL_LIST: the entries into the cells' lists, in any order; CELL_KEYS:
+// one lane's loop).  CELL_COUNT: the entries of every cell, and of all in
+// total's shards (2,048 workgroups adding to one word took 20 us of 28);
+// CELL_LIST: the entries into the cells' lists, in any order; CELL_KEYS:
 // the same as keys, cell << 32 | disk << 1 | the disk holds the whole cell.
+// FEW: at most DJ_FEW_CELLS cells, where many disks meet in one; a workgroup
+// counts its disks in LDS and adds to a cell once (500 disks on one spot: 8
+// and 22 us for counts and lists with an atomic per entry, 6 and 8 so).
 enum { CELL_COUNT, CELL_KEYS, CELL_LIST };
+constexpr int DJ_SHARDS = 16, DJ_SHARD_WORDS = 16;
+constexpr int DJ_FEW_CELLS = 4096;
 
-template <int STEP>
+template <int STEP, bool FEW>
 __global__ __launch_bounds__(256) void k_disk_cells(int64_t n, DiskArgs D, DiskGrid g, double ux, double uy,
                                                     double lim, uint32_t *ccnt, unsigned long long *keys,
                                                     const uint2 *cells, uint32_t *cell_disk, double2 *centre,
                                                     unsigned long long *total)
 {
-    unsigned long long mine = 0;   // wave-uniform
+    __shared__ uint32_t hist[FEW ? DJ_FEW_CELLS : 1], base[FEW ? DJ_FEW_CELLS : 1];
     const int lane = threadIdx.x & 63;
     const int64_t nwave = ((int64_t)gridDim.x * blockDim.x) >> 6;
-    for (int64_t j = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6; j < n; j += nwave) {
-        const double cx = D.cx[j], cy = D.cy[j], r = radius_of(D, j);
-        if (STEP == CELL_COUNT && lane == 0) centre[j] = double2{cx, cy};
-        int c0, c1, r0, r1;
-        disk_cells(g, cx, cy, r, c0, c1, r0, r1);
-        const int wide = c1 - c0 + 1;
-        const int64_t all = wide > 0 && r1 >= r0 ? (int64_t)wide * (r1 - r0 + 1) : 0;
-        for (int64_t t0 = 0; t0 < all; t0 += 64) {
-            const int64_t t = t0 + lane;
-            const int rr = r0 + (int)(t / wide), c = c0 + (int)(t % wide);
-            const int in = t < all ? cell_reached(g, ux, uy, cx, cy, r, lim, c, rr) : 0;
-            const int64_t cell = (int64_t)rr * g.W + c;
-            if (in) {
-                const uint32_t p = atomicAdd(&ccnt[cell], 1u);
-                if (STEP == CELL_KEYS)
-                    keys[cells[cell].x + p] = ((unsigned long long)cell << 32) | ((unsigned long long)j << 1) |
-                                              (in == 2 ? 1ull : 0ull);
-                if (STEP == CELL_LIST) cell_disk[cells[cell].x + p] = (uint32_t)j | (in == 2 ? DJ_FULL : 0u);
+    // fn(disk, cell, reached or held) for the cells of this wavefront's disks
+    auto disks = [&](auto fn) {
+        for (int64_t j = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6; j < n; j += nwave) {
+            const double cx = D.cx[j], cy = D.cy[j], r = radius_of(D, j);
+            if (STEP == CELL_COUNT && lane == 0) centre[j] = double2{cx, cy};
+            int c0, c1, r0, r1;
+            disk_cells(g, cx, cy, r, c0, c1, r0, r1);
+            const int wide = c1 - c0 + 1;
+            const int64_t all = wide > 0 && r1 >= r0 ? (int64_t)wide * (r1 - r0 + 1) : 0;
+            for (int64_t t0 = 0; t0 < all; t0 += 64) {
+                const int64_t t = t0 + lane;
+                const int rr = r0 + (int)(t / wide), c = c0 + (int)(t % wide);
+                const int in = t < all ? cell_reached(g, ux, uy, cx, cy, r, lim, c, rr) : 0;
+                fn(j, (int64_t)rr * g.W + c, in);
             }
-            mine += __popcll(__ballot(in != 0));
         }
+    };
+    auto put = [&](int64_t j, int64_t cell, int in, uint32_t p) {
+        if (STEP == CELL_KEYS)
+            keys[cells[cell].x + p] =
+                ((unsigned long long)cell << 32) | ((unsigned long long)j << 1) | (in == 2 ? 1ull : 0ull);
+        if (STEP == CELL_LIST) cell_disk[cells[cell].x + p] = (uint32_t)j | (in == 2 ? DJ_FULL : 0u);
+    };
+    unsigned long long sum = 0;   // wave-uniform
+    if (FEW) {
+        const int ncell = g.W * g.H;
+        for (int c = threadIdx.x; c < ncell; c += 256) hist[c] = 0u;
+        __syncthreads();
+        disks([&](int64_t, int64_t cell, int in) {
+            if (in) atomicAdd(&hist[cell], 1u);
+            sum += __popcll(__ballot(in != 0));
+        });
+        __syncthreads();
+        for (int c = threadIdx.x; c < ncell; c += 256) {
+            const uint32_t h = hist[c];
+            base[c] = h ? atomicAdd(&ccnt[c], h) : 0u;
+            hist[c] = 0u;
+        }
+        __syncthreads();
+        if (STEP != CELL_COUNT)
+            disks([&](int64_t j, int64_t cell, int in) {
+                if (in) put(j, cell, in, base[cell] + atomicAdd(&hist[cell], 1u));
+            });
+    } else {
+        disks([&](int64_t j, int64_t cell, int in) {
+            if (in) put(j, cell, in, atomicAdd(&ccnt[cell], 1u));
+            sum += __popcll(__ballot(in != 0));
+        });
     }
     if (STEP == CELL_COUNT) {
         __shared__ unsigned long long part[4];
-        if (lane == 0) part[threadIdx.x >> 6] = mine;
+        if (lane == 0) part[threadIdx.x >> 6] = sum;
         __syncthreads();
-        if (threadIdx.x == 0) atomicAdd(total, part[0] + part[1] + part[2] + part[3]);
+        if (threadIdx.x == 0)
+            atomicAdd(&total[(blockIdx.x % DJ_SHARDS) * DJ_SHARD_WORDS], part[0] + part[1] + part[2] + part[3]);
     }
 }
 
 // cells[c].x = off[c] (c = 0 .. ncell), *longest = the most entries of a
-// cell if that is more than 32 (nothing asks below; an atomic per wavefront
-// took 50 us); clears the counters for the lists.
+// cell if that is more than DJ_LIST_SORT (nothing asks below; an atomic per
+// wavefront took 50 us); clears the counters for the lists.  The cells of more than
+// DJ_LIST_SORT entries are listed in longs, *nlong of them, in any order, and
+// the entries of all cells summed from their shards.
 __global__ __launch_bounds__(256) void k_dcell_start(int64_t ncell, const uint32_t *off, uint32_t *ccnt, uint2 *cells,
-                                                     unsigned *longest)
+                                                     uint32_t *longs, unsigned *nlong, unsigned *longest,
+                                                     const unsigned long long *shards, unsigned long long *total)
 {
     const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int lane = threadIdx.x & 63;
     uint32_t m = 0;
     if (c < ncell) {
         m = ccnt[c];
         ccnt[c] = 0u;
     }
     if (c <= ncell) cells[c] = uint2{off[c], 0u};
+    if (c == 0) {
+        unsigned long long t = 0ull;
+#pragma unroll
+        for (int k = 0; k < DJ_SHARDS; ++k) t += shards[k * DJ_SHARD_WORDS];
+        *total = t;
+    }
+    const unsigned long long big = __ballot(m > DJ_LIST_SORT);
+    if (big) {
+        unsigned at = 0;
+        if (lane == 0) at = atomicAdd(nlong, (unsigned)__popcll(big));
+        at = (unsigned)__shfl((int)at, 0, 64) + (unsigned)__popcll(big & ((1ull << lane) - 1ull));
+        if (m > DJ_LIST_SORT) longs[at] = (uint32_t)c;
+    }
 #pragma unroll
     for (int d = 32; d > 0; d >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, d, 64));
-    if ((threadIdx.x & 63) == 0 && m > 32u &&
-        m > __hip_atomic_load(longest, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+    if (lane == 0 && m > DJ_LIST_SORT && m > __hip_atomic_load(longest, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
         atomicMax(longest, m);
+}
+
+// The entries of the listed cells (at most DJ_LIST_WG each) in order of their
+// disks: an entry's place is the count of smaller ones, four to an LDS read.  A
+// wavefront takes a cell, the workgroup together one of more than DJ_LIST_WAVE.
+__global__ __launch_bounds__(256) void k_dcell_sort(const unsigned *nlong, const uint32_t *longs, const uint2 *cells,
+                                                    uint32_t *cell_disk)
+{
+    static_assert(4 * DJ_LIST_WAVE <= DJ_LIST_WG && DJ_LIST_WAVE % 4 == 0, "the wavefronts' lists share the stage");
+    __shared__ __align__(16) uint32_t e[DJ_LIST_WG];
+    const unsigned nl = *nlong, wv = threadIdx.x >> 6;
+    auto order = [&](uint32_t *s, uint32_t k, uint32_t n, uint32_t first, uint32_t step, auto sync) {
+        const uint32_t n4 = (n + 3u) & ~3u;
+        for (uint32_t i = first; i < n4; i += step) s[i] = i < n ? cell_disk[k + i] : ~0u;   // past every disk
+        sync();
+        for (uint32_t i = first; i < n; i += step) {
+            const uint32_t v = s[i] & ~DJ_FULL;
+            uint32_t at = 0u;
+#pragma unroll 4
+            for (uint32_t j = 0; j < n4; j += 4) {
+                const uint4 q = *(const uint4 *)(s + j);
+                at += ((q.x & ~DJ_FULL) < v) + ((q.y & ~DJ_FULL) < v) + ((q.z & ~DJ_FULL) < v) + ((q.w & ~DJ_FULL) < v);
+            }
+            cell_disk[k + at] = s[i];
+        }
+        sync();
+    };
+    auto wave_sync = [] {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
+    for (unsigned q = blockIdx.x * 4 + wv; q < nl; q += gridDim.x * 4) {
+        const uint32_t c = longs[q], k = cells[c].x, n = cells[c + 1].x - k;
+        if (n <= DJ_LIST_WAVE) order(e + wv * DJ_LIST_WAVE, k, n, threadIdx.x & 63u, 64u, wave_sync);
+    }
+    __syncthreads();
+    for (unsigned q = blockIdx.x; q < nl; q += gridDim.x) {
+        const uint32_t c = longs[q], k = cells[c].x, n = cells[c + 1].x - k;
+        if (n > DJ_LIST_WAVE) order(e, k, n, threadIdx.x, 256u, [] { __syncthreads(); });
+    }
 }
 
 // The entries of sorted keys.
@@ -212,27 +305,48 @@ __global__ void k_dcell_list(int64_t nk, const unsigned long long *skeys, uint32
         cell_disk[i] = (uint32_t)(skeys[i] & 0xffffffffull) >> 1 | (skeys[i] & 1ull ? DJ_FULL : 0u);
 }
 
-// cells[c].y = which of the cell's first 32 entries hold all of it; first,
-// with sort, the entries in order of their disks (insertion: the lists are
-// short).
-__global__ void k_dcell_full(int64_t ncell, uint2 *cells, uint32_t *cell_disk, int sort)
+// cells[c].y = which of the cell's entries hold all of it, for a cell of at
+// most 32; first, with sort, the entries of a cell of at most DJ_LIST_SORT in
+// order of their disks, a lane per cell, by insertion in LDS (in place, 51 us
+// for lists of 24: a step waits for a load).
+__global__ __launch_bounds__(128) void k_dcell_full(int64_t ncell, uint2 *cells, uint32_t *cell_disk, int sort)
 {
+    __shared__ uint32_t s[DJ_LIST_SORT][128];
     const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int t = threadIdx.x;
     if (c >= ncell) return;
-    const uint32_t k = cells[c].x, have = cells[c + 1].x - k, m = min(have, 32u);
-    if (sort)
-        for (uint32_t i = 1; i < have; ++i) {
-            const uint32_t e = cell_disk[k + i];
-            uint32_t p = i;
-            for (; p > 0; --p) {
-                const uint32_t q = cell_disk[k + p - 1];
-                if ((q & ~DJ_FULL) < (e & ~DJ_FULL)) break;
-                cell_disk[k + p] = q;
-            }
-            if (p != i) cell_disk[k + p] = e;
-        }
+    const uint32_t k = cells[c].x, have = cells[c + 1].x - k, m = have > 32u ? 0u : have;
     uint32_t full = 0;
-    for (uint32_t i = 0; i < m; ++i) full |= (cell_disk[k + i] >> 31) << i;
+    if (sort && have <= DJ_LIST_SORT) {
+        bool moved = false;
+        uint32_t last = 0;   // the entry before, in order
+        for (uint32_t i0 = 0; i0 < have; i0 += 4) {
+            uint32_t in[4];
+#pragma unroll
+            for (uint32_t u = 0; u < 4; ++u) in[u] = i0 + u < have ? cell_disk[k + i0 + u] : 0u;
+#pragma unroll
+            for (uint32_t u = 0; u < 4; ++u) {
+                if (i0 + u >= have) break;
+                const uint32_t e = in[u];
+                uint32_t p = i0 + u;
+                if (p == 0 || (last & ~DJ_FULL) < (e & ~DJ_FULL)) {
+                    last = e;
+                } else {
+                    moved = true;
+                    for (; p > 0 && (s[p - 1][t] & ~DJ_FULL) > (e & ~DJ_FULL); --p) s[p][t] = s[p - 1][t];
+                }
+                s[p][t] = e;
+            }
+        }
+        for (uint32_t i = 0; i < have; ++i) {
+            const uint32_t e = s[i][t];
+            if (moved) cell_disk[k + i] = e;
+            full |= (e >> 31) << i;
+        }
+    } else {
+#pragma unroll 8
+        for (uint32_t i = 0; i < m; ++i) full |= (cell_disk[k + i] >> 31) << i;
+    }
     if (full) cells[c].y = full;
 }
 
@@ -242,7 +356,8 @@ struct DiskCanvas {
     const uint2 *cells;          // the same, and which of the first 32 entries hold the cell
     const uint32_t *cell_disk;   // the cells' entries: disk ids ascending, DJ_FULL
     const double2 *centre;       // the disks' centres, one load each
-    unsigned longest;            // most entries of a cell (0: at most 32)
+    unsigned longest;            // most entries of a cell (0: at most DJ_LIST_SORT)
+    bool together;               // points of short and long lists are walked together
     DiskArgs D;
 };
 
@@ -318,16 +433,22 @@ template <bool EXACT>
 __device__ __forceinline__ uint32_t disk_mask_walk(const DiskCanvas &K, double x, double y, uint32_t k, uint32_t pm,
                                                    int lane, bool &open)
 {
-    uint32_t hits = 0u, rem = (uint32_t)__popc(pm);
+    uint32_t hits = 0u, rem = (uint32_t)__popc(pm), done = 0u;
+    // without entries that hold the cell, the masks have no gaps
+    const bool gaps = __ballot((pm & (pm + 1u)) != 0u) != 0ull;
     while (__ballot(rem != 0u)) {
         const WaveRound w = wave_round(rem, lane);
         const uint32_t ok = __shfl(k, w.o, 64);
-        uint32_t opm = __shfl(pm, w.o, 64);
+        uint32_t opm = __shfl(gaps ? pm : done, w.o, 64);
         const double ox = __shfl(x, w.o, 64), oy = __shfl(y, w.o, 64);
         int h = 0;
         if ((uint32_t)lane < w.ntake) {
-            for (uint32_t t = (uint32_t)lane - w.opre; t != 0u; --t) opm &= opm - 1u;
-            const uint32_t j = K.cell_disk[ok + (uint32_t)__ffs(opm) - 1u] & ~DJ_FULL;
+            uint32_t at = opm + (uint32_t)lane - w.opre;
+            if (gaps) {   // few bits where disks hold cells
+                for (uint32_t t = (uint32_t)lane - w.opre; t != 0u; --t) opm &= opm - 1u;
+                at = (uint32_t)__ffs(opm) - 1u;
+            }
+            const uint32_t j = K.cell_disk[ok + at] & ~DJ_FULL;
             const double rj = radius_of(K.D, j);
             const double2 c = K.centre[j];
             h = EXACT ? (in_disk(ox, oy, c.x, c.y, rj, rj * rj) ? 1 : 0) : in_disk_filter(ox, oy, c.x, c.y, rj * rj);
@@ -336,11 +457,16 @@ __device__ __forceinline__ uint32_t disk_mask_walk(const DiskCanvas &K, double x
         if (!EXACT && __ballot(h < 0)) open = true;
         const uint32_t len = wave_round_len(w);
         uint32_t got = len ? (uint32_t)(hm >> w.pre) : 0u;
-        for (uint32_t t = 0; t < len; ++t) {
-            const uint32_t low = pm & (0u - pm);
-            if (got & 1u) hits |= low;
-            got >>= 1;
-            pm ^= low;
+        if (gaps) {
+            for (uint32_t t = 0; t < len; ++t) {
+                const uint32_t low = pm & (0u - pm);
+                if (got & 1u) hits |= low;
+                got >>= 1;
+                pm ^= low;
+            }
+        } else if (len) {
+            hits |= (got & (~0u >> (32u - len))) << done;
+            done += len;
         }
         rem -= len;
     }
@@ -349,8 +475,8 @@ __device__ __forceinline__ uint32_t disk_mask_walk(const DiskCanvas &K, double x
 
 // Count pass: pairs per wavefront segment, and with pm every point's pairs as
 // (first entry of its cell, mask of the entries that hold it), or (all ones,
-// number) for a cell of more than 32 entries, so that the write pass reads 8
-// bytes per point and tests nothing.  A point's entries that hold its whole
+// number) for a cell of more than 32 entries and the points tested with such
+// ones, so that the write pass reads 8 bytes per point and tests nothing else.  A point's entries that hold its whole
 // cell are pairs as they stand; points with others are queued in LDS and
 // tested 64 at a time.  Bound by the rate of L2 requests (the cells, and an
 // entry and a centre per test): 30M points, 10,000 disks of 300 m, 0.52 ms
@@ -395,12 +521,18 @@ __global__ __launch_bounds__(DJ_THREADS) void k_dj_count(DiskCanvas K, int64_t n
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
-            const bool many = rem > 32u;
+            // Points of lists of more than 32 are walked and counted, and with
+            // few points or no cells inside disks (whose masks save tests) the
+            // others of the queue with them: 300,000 points near 2,000 disks,
+            // lists of both kinds, 62 us, two walks 120; 30M points near disks
+            // of all sizes, the call 1.56 ms and 1.43.
+            const bool some = __ballot(rem > 32u) != 0ull;
+            const bool many = some && (rem > 32u || K.together);
             const uint32_t all = rem >= 32u ? ~0u : (1u << rem) - 1u;
             uint32_t hits = full | disk_mask_walk<EXACT>(K, x, y, k, many ? 0u : all & ~full, lane, open);
             uint32_t m = (uint32_t)__popc(hits);
-            if (!EXACT && __ballot(many)) open = true;
-            if (EXACT && __ballot(many)) {
+            if (!EXACT && some) open = true;
+            if (EXACT && some) {
                 uint32_t cnt;
                 disk_range(K, x, y, k, rem);   // the queue holds no more than 33
                 disk_wave_walk(K, x, y, k, many ? rem : 0u, 0u, lane, cnt, [](int, uint32_t, uint32_t) {});
@@ -639,8 +771,8 @@ static int dj_bits(uint64_t v)
 }
 
 // Builds the disk canvas in ctx scratch (cell lists valid until the next
-// call on ctx).
-static int build_disk_canvas(spade_ctx *ctx, const spade_disks *dk, int64_t npts, DiskCanvas &K)
+// call on ctx).  Counts need no order in the lists and no masks.
+static int build_disk_canvas(spade_ctx *ctx, const spade_disks *dk, int64_t npts, bool counting, DiskCanvas &K)
 {
     hipStream_t st = ctx->stream;
     const int64_t n = dk->n;
@@ -649,12 +781,15 @@ static int build_disk_canvas(spade_ctx *ctx, const spade_disks *dk, int64_t npts
     K.D.r = dk->r;
     K.D.r_all = dk->r_all;
     DevBuf &bb = ctx->scratch[S_BLOCKRED];
-    if (ensure(ctx, bb, 128)) return SPADE_E_NOMEM;
+    // box keys (4 words) | flag, long lists | - | sums of radii, of squares |
+    // longest list | entries | - | shards of the entries
+    const int64_t words = 16 + DJ_SHARDS * DJ_SHARD_WORDS;
+    if (ensure(ctx, bb, 8 * (size_t)words)) return SPADE_E_NOMEM;
     unsigned long long *dbb = (unsigned long long *)bb.p;
-    unsigned *bad = (unsigned *)(dbb + 4);
-    double *rsum = (double *)(dbb + 6);   // radii, squares
-    // box keys start at all-ones; the flag, the sums, the longest list and the entries at zero
-    hipLaunchKernelGGL(k_dj_zero, dim3(1), dim3(64), 0, st, (int64_t)10, dbb);
+    unsigned *bad = (unsigned *)(dbb + 4), *nlong = bad + 1;
+    double *rsum = (double *)(dbb + 6);
+    // box keys start at all-ones, the others at zero
+    hipLaunchKernelGGL(k_dj_zero, dim3(1), dim3(256), 0, st, words, dbb);
     SPADE_HIP(ctx, hipGetLastError());
     SPADE_HIP(ctx, hipMemsetAsync(dbb, 0xff, 32, st));
     hipLaunchKernelGGL(k_disks_box, dim3(dj_grid(n, 1024)), dim3(256), 0, st, n, K.D, dbb, bad, rsum);
@@ -697,8 +832,10 @@ static int build_disk_canvas(spade_ctx *ctx, const spade_disks *dk, int64_t npts
     // Few disks: most cells list nothing, and a small table stays in the L1
     // (100 disks of 500 m over 60 km, 30M points: counts 330 us with cells of
     // 500 m, 430 with 125).
-    const bool few = !(3.15 * rsq >= DJ_COVER * w * hgt);
-    if (!few && fine > 0.0 && fine < cell && affordable(fine)) cell = fine;
+    const bool few = !(3.15 * rsq >= DJ_COVER * w * hgt), stacked = !(3.15 * rsq <= DJ_STACK * w * hgt);
+    const bool finer = !few && !stacked && fine > 0.0 && fine < cell && affordable(fine);
+    if (finer) cell = fine;
+    K.together = !finer || npts < DJ_FILTER_MIN;
     g.W = (w > 0 && cell > 0) ? (int)std::min<double>(DJ_GRID_MAX, std::max(1.0, std::ceil(w / cell))) : 1;
     g.H = (hgt > 0 && cell > 0) ? (int)std::min<double>(DJ_GRID_MAX, std::max(1.0, std::ceil(hgt / cell))) : 1;
     g.X0 = g.bx0;
@@ -709,44 +846,48 @@ static int build_disk_canvas(spade_ctx *ctx, const spade_disks *dk, int64_t npts
     const double mag = std::fabs(g.bx0) + std::fabs(g.bx1) + std::fabs(g.by0) + std::fabs(g.by1);
     const double lim = std::min(ux, uy) > mag * 0x1p-40 ? 1.0 - 1e-7 : -1.0;
     const int64_t ncell = (int64_t)g.W * g.H;
-    // Cell lists: count, scan, fill in any order, order each list.  Where a
-    // list is longer than DJ_LIST_SORT entries, (cell, disk) keys are sorted
-    // instead (30 launches for a million of them: 140 us, against 25).
+    // Cell lists: count, scan, fill in any order, order each list, by one lane
+    // or a workgroup.  Where a list is longer than DJ_LIST_WG entries, (cell,
+    // disk) keys are sorted instead (30 launches for a million of them: 140 us,
+    // against 25).
     DevBuf &bw = ctx->scratch[S_VALS2];
-    if (ensure(ctx, bw, sizeof(double2) * (size_t)n + (sizeof(uint2) + 2 * sizeof(uint32_t)) * (size_t)(ncell + 1)))
+    if (ensure(ctx, bw, sizeof(double2) * (size_t)n + (sizeof(uint2) + 3 * sizeof(uint32_t)) * (size_t)(ncell + 1)))
         return SPADE_E_NOMEM;
     double2 *centre = (double2 *)bw.p;
     uint2 *cells = (uint2 *)(centre + n);
     uint32_t *ccnt = (uint32_t *)(cells + (ncell + 1)), *coff = ccnt + (ncell + 1);
+    uint32_t *longs = coff + (ncell + 1);
     unsigned *longest = (unsigned *)(dbb + 8);
-    const dim3 dgrid(dj_grid(n * 64, 2048)), cgrid((unsigned)(ncell / 256 + 1));
+    const bool few_cells = ncell <= DJ_FEW_CELLS;
+    const dim3 dgrid(few_cells ? dj_grid(n * 16, 384) : dj_grid(n * 64, 2048)), cgrid((unsigned)(ncell / 256 + 1));
     auto disks = [&](auto kern, unsigned long long *keys, uint32_t *list) {
         hipLaunchKernelGGL(kern, dgrid, dim3(256), 0, st, n, K.D, g, ux, uy, lim, ccnt, keys,
-                           (const uint2 *)cells, list, centre, dbb + 9);
+                           (const uint2 *)cells, list, centre, dbb + 16);
     };
     DevBuf &cub = ctx->scratch[S_CUBTMP];
     size_t tb = 0;
     SPADE_HIP(ctx, hipMemsetAsync(ccnt, 0, sizeof(uint32_t) * (size_t)(ncell + 1), st));
-    disks(k_disk_cells<CELL_COUNT>, nullptr, nullptr);
+    disks(few_cells ? k_disk_cells<CELL_COUNT, true> : k_disk_cells<CELL_COUNT, false>, nullptr, nullptr);
     SPADE_HIP(ctx, hipGetLastError());
     SPADE_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(nullptr, tb, ccnt, coff, (int)(ncell + 1), st));
     if (ensure(ctx, cub, std::max<size_t>(tb, 1))) return SPADE_E_NOMEM;
     SPADE_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(cub.p, tb, ccnt, coff, (int)(ncell + 1), st));
-    hipLaunchKernelGGL(k_dcell_start, cgrid, dim3(256), 0, st, ncell, (const uint32_t *)coff, ccnt, cells, longest);
+    hipLaunchKernelGGL(k_dcell_start, cgrid, dim3(256), 0, st, ncell, (const uint32_t *)coff, ccnt, cells, longs,
+                       nlong, longest, (const unsigned long long *)(dbb + 16), dbb + 9);
     SPADE_HIP(ctx, hipGetLastError());
     SPADE_HIP(ctx, hipMemcpyAsync(h, dbb + 8, 16, hipMemcpyDeviceToHost, st));
     SPADE_HIP(ctx, hipStreamSynchronize(st));
     const unsigned most_listed = (unsigned)h[0];
     const int64_t nk = (int64_t)h[1];
     if (nk >= (int64_t)0xffffffffLL) return set_error(ctx, SPADE_E_UNSUPPORTED, "too many (cell, disk) entries");
-    const bool sorted = most_listed > DJ_LIST_SORT;
+    const bool sorted = !counting && most_listed > DJ_LIST_WG;
     DevBuf &bl = ctx->scratch[S_VALS];
     if (ensure(ctx, bl, 4 * (size_t)std::max<int64_t>(nk, 1) + 64)) return SPADE_E_NOMEM;
     uint32_t *cell_disk = (uint32_t *)bl.p;
     if (sorted) {
         DevBuf &bk = ctx->scratch[S_KEYS], &bk2 = ctx->scratch[S_KEYS2];
         if (ensure(ctx, bk, 8 * (size_t)nk) || ensure(ctx, bk2, 8 * (size_t)nk)) return SPADE_E_NOMEM;
-        disks(k_disk_cells<CELL_KEYS>, (unsigned long long *)bk.p, nullptr);
+        disks(few_cells ? k_disk_cells<CELL_KEYS, true> : k_disk_cells<CELL_KEYS, false>, (unsigned long long *)bk.p, nullptr);
         SPADE_HIP(ctx, hipGetLastError());
         const int kb = 32 + std::max(1, dj_bits((uint64_t)ncell));
         tb = 0;
@@ -758,9 +899,14 @@ static int build_disk_canvas(spade_ctx *ctx, const spade_disks *dk, int64_t npts
         hipLaunchKernelGGL(k_dcell_list, dim3(dj_grid(nk)), dim3(256), 0, st, nk, (const unsigned long long *)bk2.p,
                            cell_disk);
     } else {
-        disks(k_disk_cells<CELL_LIST>, nullptr, cell_disk);
+        disks(few_cells ? k_disk_cells<CELL_LIST, true> : k_disk_cells<CELL_LIST, false>, nullptr, cell_disk);
+        if (!counting && most_listed > DJ_LIST_SORT)
+            hipLaunchKernelGGL(k_dcell_sort, dim3(1024), dim3(256), 0, st, (const unsigned *)nlong, (const uint32_t *)longs,
+                               (const uint2 *)cells, cell_disk);
     }
-    hipLaunchKernelGGL(k_dcell_full, cgrid, dim3(256), 0, st, ncell, cells, cell_disk, sorted ? 0 : 1);
+    if (!counting)
+        hipLaunchKernelGGL(k_dcell_full, dim3((unsigned)((ncell + 127) / 128)), dim3(128), 0, st, ncell, cells, cell_disk,
+                           sorted ? 0 : 1);
     SPADE_HIP(ctx, hipGetLastError());
     K.off = coff;
     K.cells = cells;
@@ -806,7 +952,7 @@ int distance_join(spade_ctx *ctx, const spade_points *pts, const spade_disks *dk
         return SPADE_OK;
     }
     DiskCanvas K;
-    if ((rc = build_disk_canvas(ctx, dk, n, K))) return rc;
+    if ((rc = build_disk_canvas(ctx, dk, n, counting, K))) return rc;
     const int64_t nseg = (n + DJ_SEG - 1) / DJ_SEG;
     const int cus = num_cus_dj(ctx->device);
     const int grid = (int)std::max<int64_t>(1, std::min<int64_t>((nseg + DJ_THREADS / 64 - 1) / (DJ_THREADS / 64),
