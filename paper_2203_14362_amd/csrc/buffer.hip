@@ -223,7 +223,10 @@ __global__ __launch_bounds__(256) void k_buf_bin(int64_t V, const Seg *segs, con
         for (int d = 32; d > 0; d >>= 1) nlisted += (unsigned long long)__shfl_xor((long long)nlisted, d, 64);
         if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = nlisted;
         __syncthreads();
-        if (threadIdx.x == 0) atomicAdd(tot, part[0] + part[1] + part[2] + part[3]);
+        // (2,048 workgroups adding to one word take 20 us, and with few
+        // segments most have nothing to add)
+        const unsigned long long sum = part[0] + part[1] + part[2] + part[3];
+        if (threadIdx.x == 0 && sum != 0ull) atomicAdd(tot, sum);
     }
 }
 
