@@ -1238,18 +1238,16 @@ __device__ __forceinline__ bool knn_close(unsigned long long a, unsigned long lo
     return fabs(qa - qb) <= 1.7763568394002505e-15 * (qa + qb);
 }
 
-// Runs of consecutive keys too close to tell apart, starting before `upto`,
-// are re-ordered by the exact comparison (ids break exact ties); one thread
-// per run, insertion sort.
-__global__ void k_knn_fix(int64_t m, int64_t upto, const unsigned long long *key, uint32_t *ids, const double *X,
-                          const double *Y, double px, double py)
+// Runs of consecutive keys too close to tell apart, starting among the first
+// kk, are re-ordered by the exact comparison (ids break exact ties); one thread
+// per run, insertion sort.  Every run's ids go to out, the first kk of all.
+__global__ void k_knn_fix(int64_t m, int64_t kk, const unsigned long long *key, uint32_t *ids, const double *X,
+                          const double *Y, double px, double py, uint32_t *out)
 {
-    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < upto && t < m;
-         t += (int64_t)gridDim.x * blockDim.x) {
+    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < kk; t += (int64_t)gridDim.x * blockDim.x) {
         if (t > 0 && knn_close(key[t - 1], key[t])) continue;   // not a run start
         int64_t e = t + 1;
         while (e < m && knn_close(key[e - 1], key[e])) ++e;
-        if (e - t < 2) continue;
         for (int64_t a = t + 1; a < e; ++a) {
             const uint32_t v = ids[a];
             int64_t b = a;
@@ -1262,19 +1260,19 @@ __global__ void k_knn_fix(int64_t m, int64_t upto, const unsigned long long *key
             }
             ids[b] = v;
         }
+        for (int64_t a = t; a < min(e, kk); ++a) out[a] = ids[a];
     }
 }
 
-// Few candidates (m <= KS_MAX) are ordered by one workgroup in LDS: a bitonic
-// sort of (key, id), the runs of keys too close to tell apart as in k_knn_fix,
-// and the first kk ids written out.  The library sort and the kernels around
-// it took five launches for the 1,000 to 4,000 candidates of k = 1,000.
+// Few candidates (m <= KS_MAX) are sorted by (key, id) by one workgroup in
+// LDS, a bitonic sort in place of the library's five launches for the 1,000 to
+// 4,000 candidates of k = 1,000.  The runs of close keys are k_knn_fix's, whose
+// comparisons need more than one CU: 3,000 lattice points in runs of up to 36,
+// 439 us in this workgroup, 135 in a launch of its own.
 constexpr int KS_THREADS = 1024;
 constexpr int KS_MAX = 4096;
 
-__global__ __launch_bounds__(KS_THREADS) void k_knn_order(int m, int kk, const unsigned long long *keys,
-                                                          const uint32_t *ids, const double *X, const double *Y,
-                                                          double px, double py, uint32_t *out)
+__global__ __launch_bounds__(KS_THREADS) void k_knn_order(int m, unsigned long long *keys, uint32_t *ids)
 {
     __shared__ unsigned long long sk[KS_MAX];
     __shared__ uint32_t sid[KS_MAX];
@@ -1300,25 +1298,10 @@ __global__ __launch_bounds__(KS_THREADS) void k_knn_order(int m, int kk, const u
             }
             __syncthreads();
         }
-    for (int i = t; i < m && i <= kk; i += KS_THREADS) {
-        if (i > 0 && knn_close(sk[i - 1], sk[i])) continue;   // not a run start
-        int e = i + 1;
-        while (e < m && knn_close(sk[e - 1], sk[e])) ++e;
-        for (int a = i + 1; a < e; ++a) {
-            const uint32_t v = sid[a];
-            int b = a;
-            while (b > i) {
-                const uint32_t u = sid[b - 1];
-                const int c = dist_cmp(X[u], Y[u], X[v], Y[v], px, py);
-                if (c < 0 || (c == 0 && u < v)) break;
-                sid[b] = u;
-                --b;
-            }
-            sid[b] = v;
-        }
+    for (int i = t; i < m; i += KS_THREADS) {
+        keys[i] = sk[i];
+        ids[i] = sid[i];
     }
-    __syncthreads();
-    for (int i = t; i < kk; i += KS_THREADS) out[i] = sid[i];
 }
 
 int knn_select(spade_ctx *ctx, const spade_points *pts, double px, double py, int64_t k, uint32_t *out_ids,
@@ -1458,29 +1441,26 @@ int knn_select(spade_ctx *ctx, const spade_points *pts, double px, double py, in
     SPADE_HIP(ctx, hipGetLastError());
     // order by distance, exactly; the first k are the result
     const int64_t kk = std::min<int64_t>(k, m);
+    unsigned long long *sorted = (unsigned long long *)bk.p;
+    uint32_t *sids = (uint32_t *)bc.p;
     if (m <= KS_MAX) {
-        hipLaunchKernelGGL(k_knn_order, dim3(1), dim3(KS_THREADS), 0, st, (int)m, (int)kk,
-                           (const unsigned long long *)bk.p, (const uint32_t *)bc.p, pts->x, pts->y, px, py, out_ids);
-        SPADE_HIP(ctx, hipGetLastError());
-        if (ctx->timing) SPADE_HIP(ctx, hipEventRecord(ctx->ev[3], st));
-        SPADE_HIP(ctx, hipStreamSynchronize(st));
-        *n_out = kk;
-        return SPADE_OK;
+        hipLaunchKernelGGL(k_knn_order, dim3(1), dim3(KS_THREADS), 0, st, (int)m, sorted, sids);
+    } else {
+        DevBuf &bk2 = ctx->scratch[S_KEYS2], &bi = ctx->scratch[S_VALS];
+        if (ensure(ctx, bk2, 8 * (size_t)m) || ensure(ctx, bi, 4 * (size_t)m)) return SPADE_E_NOMEM;
+        sorted = (unsigned long long *)bk2.p;
+        sids = (uint32_t *)bi.p;
+        tb = 0;
+        SPADE_HIP(ctx, hipcub::DeviceRadixSort::SortPairs(nullptr, tb, (const unsigned long long *)bk.p, sorted,
+                                                          (const uint32_t *)bc.p, sids, (int)m, 0, 64, st));
+        if (ensure(ctx, cub, std::max<size_t>(tb, 1))) return SPADE_E_NOMEM;
+        SPADE_HIP(ctx, hipcub::DeviceRadixSort::SortPairs(cub.p, tb, (const unsigned long long *)bk.p, sorted,
+                                                          (const uint32_t *)bc.p, sids, (int)m, 0, 64, st));
     }
-    DevBuf &bk2 = ctx->scratch[S_KEYS2], &bi = ctx->scratch[S_VALS];
-    if (ensure(ctx, bk2, 8 * (size_t)m) || ensure(ctx, bi, 4 * (size_t)m)) return SPADE_E_NOMEM;
-    tb = 0;
-    SPADE_HIP(ctx, hipcub::DeviceRadixSort::SortPairs(nullptr, tb, (const unsigned long long *)bk.p,
-                                                      (unsigned long long *)bk2.p, (const uint32_t *)bc.p,
-                                                      (uint32_t *)bi.p, (int)m, 0, 64, st));
-    if (ensure(ctx, cub, std::max<size_t>(tb, 1))) return SPADE_E_NOMEM;
-    SPADE_HIP(ctx, hipcub::DeviceRadixSort::SortPairs(cub.p, tb, (const unsigned long long *)bk.p,
-                                                      (unsigned long long *)bk2.p, (const uint32_t *)bc.p,
-                                                      (uint32_t *)bi.p, (int)m, 0, 64, st));
-    hipLaunchKernelGGL(k_knn_fix, dim3(dj_grid(kk + 1)), dim3(256), 0, st, m, kk + 1,
-                       (const unsigned long long *)bk2.p, (uint32_t *)bi.p, pts->x, pts->y, px, py);
     SPADE_HIP(ctx, hipGetLastError());
-    SPADE_HIP(ctx, hipMemcpyAsync(out_ids, bi.p, 4 * (size_t)kk, hipMemcpyDeviceToDevice, st));
+    hipLaunchKernelGGL(k_knn_fix, dim3(dj_grid(kk)), dim3(256), 0, st, m, kk, (const unsigned long long *)sorted, sids,
+                       pts->x, pts->y, px, py, out_ids);
+    SPADE_HIP(ctx, hipGetLastError());
     if (ctx->timing) SPADE_HIP(ctx, hipEventRecord(ctx->ev[3], st));
     SPADE_HIP(ctx, hipStreamSynchronize(st));
     *n_out = kk;
