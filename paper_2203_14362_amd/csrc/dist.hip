@@ -1160,19 +1160,14 @@ __global__ __launch_bounds__(KNN_THREADS) void k_knn_pow2(int64_t n, const doubl
 }
 
 // The points of circle 2^J from the words whose innermost circle reaches it:
-// ids and keys (FP64 squared distance).  A wavefront looks at 64 words, one
-// per lane.  TAKE_ANY: the workgroups' points in no particular order (one
-// atomic per workgroup; the sort in LDS orders by key and id).  For the sort
-// by key alone the ids have to come ascending, or the exact comparison of a
-// run of equal distances (a place with many points) would be quadratic:
-// TAKE_COUNT gives the points per workgroup, TAKE_AT writes them from the
-// scanned counts on.
-enum { TAKE_ANY, TAKE_COUNT, TAKE_AT };
-
-template <int STEP>
+// ids and keys (FP64 squared distance), a workgroup's in id order, the
+// workgroups in no particular one.  A wavefront looks at 64 words, one per
+// lane; one global atomic per workgroup.  seg, when given, keeps where every
+// workgroup's points lie, and tot their number.
 __global__ __launch_bounds__(KNN_THREADS) void k_knn_take(int64_t n, const double *X, const double *Y, double px,
                                                           double py, int J, const int16_t *wmin, uint32_t *count,
-                                                          uint32_t cap, uint32_t *ids, unsigned long long *keys)
+                                                          uint32_t cap, uint32_t *ids, unsigned long long *keys,
+                                                          uint32_t *seg, uint32_t *tot)
 {
     __shared__ uint32_t wsum[KNN_THREADS / 64];
     __shared__ uint32_t s_base;
@@ -1201,12 +1196,12 @@ __global__ __launch_bounds__(KNN_THREADS) void k_knn_take(int64_t n, const doubl
         if (w < wv) pre += wsum[w];
         total += wsum[w];
     }
-    if (STEP == TAKE_COUNT) {
-        if (threadIdx.x == 0) count[blockIdx.x] = total;
-        return;
-    }
+    if (tot && threadIdx.x == 0) tot[blockIdx.x] = total;
     if (total == 0u) return;   // uniform over the workgroup
-    if (threadIdx.x == 0) s_base = STEP == TAKE_AT ? count[blockIdx.x] : atomicAdd(count, total);
+    if (threadIdx.x == 0) {
+        s_base = atomicAdd(count, total);
+        if (seg) seg[blockIdx.x] = s_base;
+    }
     __syncthreads();
     const uint32_t first = s_base + pre + incl - c;   // of this lane's word
     for (unsigned long long m = __ballot(mine != 0ull); m; m &= m - 1) {
@@ -1218,6 +1213,21 @@ __global__ __launch_bounds__(KNN_THREADS) void k_knn_take(int64_t n, const doubl
             ids[at] = (uint32_t)i;
             keys[at] = (unsigned long long)__double_as_longlong(dist2(X[i], Y[i], px, py));
         }
+    }
+}
+
+// The workgroups' points in id order: those of k_knn_take's workgroup b, at
+// seg[b], to at[b].  The sort by key is stable, so a run of equal distances (a
+// place with many points) then has its ids ascending and costs the exact
+// comparison one step per point; out of order it would be quadratic.
+__global__ __launch_bounds__(64) void k_knn_place(const uint32_t *seg, const uint32_t *tot, const uint32_t *at,
+                                                  const uint32_t *ids, const unsigned long long *keys, uint32_t *oids,
+                                                  unsigned long long *okeys)
+{
+    const uint32_t n = tot[blockIdx.x], from = n ? seg[blockIdx.x] : 0u, to = at[blockIdx.x];
+    for (uint32_t i = threadIdx.x; i < n; i += 64) {
+        oids[to + i] = ids[from + i];
+        okeys[to + i] = keys[from + i];
     }
 }
 
@@ -1403,33 +1413,40 @@ int knn_select(spade_ctx *ctx, const spade_points *pts, double px, double py, in
         rsel = C.r[sel];
     }
     // The candidates: the points of that circle, with their keys.  Few of them
-    // (one in 32 points) come from the words of points that reach the circle;
-    // more, and the circles of the bounding box, from a distance selection
-    // over all points.
+    // (one in 32 points, in 128 where they have to be put in id order; in no
+    // spatial order two thirds of the words have one of one in 60) come from
+    // the words of points that reach the circle; more, and the circles of the
+    // bounding box, from a distance selection over all points.
     int64_t m = cum;
     DevBuf &bc = ctx->scratch[S_VALS2], &bk = ctx->scratch[S_KEYS];
     if (ensure(ctx, bc, 4 * (size_t)std::max<int64_t>(cum, 1)) || ensure(ctx, bk, 8 * (size_t)std::max<int64_t>(cum, 1)))
         return SPADE_E_NOMEM;
-    DevBuf &cub = ctx->scratch[S_CUBTMP];
+    // (sorted by the library, the candidates lie in bi and bk2 in id order)
+    DevBuf &bk2 = ctx->scratch[S_KEYS2], &bi = ctx->scratch[S_VALS], &cub = ctx->scratch[S_CUBTMP];
+    const bool take = jsel <= KNN_JMAX && cum <= n / (cum > KS_MAX ? 128 : 32), placed = take && cum > KS_MAX;
+    if (cum > KS_MAX && (ensure(ctx, bk2, 8 * (size_t)cum) || ensure(ctx, bi, 4 * (size_t)cum))) return SPADE_E_NOMEM;
     size_t tb = 0;
-    if (jsel <= KNN_JMAX && cum <= n / 32) {
+    if (take) {
         const unsigned wgs = (unsigned)((n + 64 * KNN_THREADS - 1) / (64 * KNN_THREADS));
-        auto take = [&](auto kern, uint32_t *count) {
-            hipLaunchKernelGGL(kern, dim3(wgs), dim3(KNN_THREADS), 0, st, n, pts->x, pts->y, px, py, jsel,
-                               (const int16_t *)wmin, count, (uint32_t)cum, (uint32_t *)bc.p, (unsigned long long *)bk.p);
-        };
-        if (cum <= KS_MAX) {
-            take(k_knn_take<TAKE_ANY>, (uint32_t *)(dbins + KNN_BINS));
-        } else {
+        uint32_t *seg = nullptr, *tot = nullptr, *at = nullptr;
+        if (placed) {
             DevBuf &bn = ctx->scratch[S_LOOKBACK];
-            if (ensure(ctx, bn, sizeof(uint32_t) * 2 * (size_t)wgs)) return SPADE_E_NOMEM;
-            uint32_t *cnt = (uint32_t *)bn.p, *at = cnt + wgs;
-            SPADE_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(nullptr, tb, cnt, at, (int)wgs, st));
+            if (ensure(ctx, bn, sizeof(uint32_t) * 3 * (size_t)wgs)) return SPADE_E_NOMEM;
+            seg = (uint32_t *)bn.p;
+            tot = seg + wgs;
+            at = tot + wgs;
+            SPADE_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(nullptr, tb, tot, at, (int)wgs, st));
             if (ensure(ctx, cub, std::max<size_t>(tb, 1))) return SPADE_E_NOMEM;
-            take(k_knn_take<TAKE_COUNT>, cnt);
-            SPADE_HIP(ctx, hipGetLastError());
-            SPADE_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(cub.p, tb, cnt, at, (int)wgs, st));
-            take(k_knn_take<TAKE_AT>, at);
+        }
+        hipLaunchKernelGGL(k_knn_take, dim3(wgs), dim3(KNN_THREADS), 0, st, n, pts->x, pts->y, px, py, jsel,
+                           (const int16_t *)wmin, (uint32_t *)(dbins + KNN_BINS), (uint32_t)cum, (uint32_t *)bc.p,
+                           (unsigned long long *)bk.p, seg, tot);
+        SPADE_HIP(ctx, hipGetLastError());
+        if (placed) {
+            SPADE_HIP(ctx, hipcub::DeviceScan::ExclusiveSum(cub.p, tb, tot, at, (int)wgs, st));
+            hipLaunchKernelGGL(k_knn_place, dim3(wgs), dim3(64), 0, st, (const uint32_t *)seg, (const uint32_t *)tot,
+                               (const uint32_t *)at, (const uint32_t *)bc.p, (const unsigned long long *)bk.p,
+                               (uint32_t *)bi.p, (unsigned long long *)bk2.p);
         }
     } else {
         int rc = select_disk(ctx, pts, px, py, rsel, (uint32_t *)bc.p, cum, &m);
@@ -1446,16 +1463,14 @@ int knn_select(spade_ctx *ctx, const spade_points *pts, double px, double py, in
     if (m <= KS_MAX) {
         hipLaunchKernelGGL(k_knn_order, dim3(1), dim3(KS_THREADS), 0, st, (int)m, sorted, sids);
     } else {
-        DevBuf &bk2 = ctx->scratch[S_KEYS2], &bi = ctx->scratch[S_VALS];
-        if (ensure(ctx, bk2, 8 * (size_t)m) || ensure(ctx, bi, 4 * (size_t)m)) return SPADE_E_NOMEM;
-        sorted = (unsigned long long *)bk2.p;
-        sids = (uint32_t *)bi.p;
+        const unsigned long long *keys = (const unsigned long long *)(placed ? bk2.p : bk.p);
+        const uint32_t *ids = (const uint32_t *)(placed ? bi.p : bc.p);
+        sorted = (unsigned long long *)(placed ? bk.p : bk2.p);
+        sids = (uint32_t *)(placed ? bc.p : bi.p);
         tb = 0;
-        SPADE_HIP(ctx, hipcub::DeviceRadixSort::SortPairs(nullptr, tb, (const unsigned long long *)bk.p, sorted,
-                                                          (const uint32_t *)bc.p, sids, (int)m, 0, 64, st));
+        SPADE_HIP(ctx, hipcub::DeviceRadixSort::SortPairs(nullptr, tb, keys, sorted, ids, sids, (int)m, 0, 64, st));
         if (ensure(ctx, cub, std::max<size_t>(tb, 1))) return SPADE_E_NOMEM;
-        SPADE_HIP(ctx, hipcub::DeviceRadixSort::SortPairs(cub.p, tb, (const unsigned long long *)bk.p, sorted,
-                                                          (const uint32_t *)bc.p, sids, (int)m, 0, 64, st));
+        SPADE_HIP(ctx, hipcub::DeviceRadixSort::SortPairs(cub.p, tb, keys, sorted, ids, sids, (int)m, 0, 64, st));
     }
     SPADE_HIP(ctx, hipGetLastError());
     hipLaunchKernelGGL(k_knn_fix, dim3(dj_grid(kk)), dim3(256), 0, st, m, kk, (const unsigned long long *)sorted, sids,

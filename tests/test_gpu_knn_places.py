@@ -1,5 +1,5 @@
 """kNN around places that hold many points: tens of thousands of equal distances
-among more candidates than one workgroup orders and fewer than a 32nd of the
+among more candidates than one workgroup orders and fewer than a 128th of the
 points, so that they are taken from the words that reach the circle and ordered
 by the library sort.  The ids are exact and equal the oracle's, in its order;
 the time of a call shows work that grows with the square of a place."""
@@ -16,17 +16,18 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("at", [(0.0, 0.0), (3.0, 4.0)])   # the query point itself, five units off
 def test_crowded_place(ctx, at):
-    n, many, k = 1_300_001, 30_000, 39_000
+    n, many, k = 5_300_001, 30_000, 39_000
     rng = np.random.default_rng(11)
     x, y = rng.uniform(100, 200, n), rng.uniform(100, 200, n)
     place = rng.permutation(n)[:40_000]
     x[place[:many]], y[place[:many]] = at
-    # four more places at one distance, and points around them
+    # four more places at one distance, and points around them (all within the
+    # circle of radius 8)
     for j, (a, b) in enumerate([(6.0, 0.0), (0.0, 6.0), (-6.0, 0.0), (0.0, -6.0)]):
         p = place[many + 1500 * j:many + 1500 * (j + 1)]
         x[p], y[p] = a, b
     rest = place[many + 6000:]
-    x[rest], y[rest] = rng.uniform(-6, 6, rest.size), rng.uniform(-6, 6, rest.size)
+    x[rest], y[rest] = rng.uniform(-5.6, 5.6, rest.size), rng.uniform(-5.6, 5.6, rest.size)
     dx, dy = torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda()
     torch.cuda.synchronize()
     t = time.perf_counter()
