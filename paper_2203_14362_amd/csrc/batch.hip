@@ -809,16 +809,16 @@ constexpr int PW_BYTES = 4096;                          // LDS pool of a wavefro
 constexpr uint32_t PW_LONG = 48;
 constexpr int PL_WORDS = 2048;                          // its words of 32 ids per wavefront
 constexpr size_t PAIR_HITS_MAX = (size_t)16 << 30;
-// Sorted keys while the (chunk, query) overlaps have at most as many points as
-// the table, in a table of PK_LARGE points or more, and a PK_PART of them in a
-// smaller one.  Lists and places of all points, and keys: one polygon, 30M
+// Sorted keys while the (chunk, query) overlaps have at most PK_OVER times the
+// table's points, in a table of PK_LARGE points or more, and a PK_PART of them
+// in a smaller one.  Lists and places of all points, and keys: one polygon, 30M
 // points, 3,570 pairs 460 and 104 us, 11.3M pairs 1,206 and 586; 18M points,
 // 0.36M to 6.8M pairs 336 to 723 and 218 to 427; 8M points, 0.37M pairs 216 and
 // 212; 5M points, overlaps of a 20th of them 166 and 152, a tenth 172 and 187,
 // a half 239 and 298 (a library sort of some 100,000 keys takes many launches).
-// Where every point meets several queries lists are better: 30M points, 78M
-// pairs 3.2 and 4.8 ms.
-constexpr int64_t PK_LARGE = (int64_t)1 << 23, PK_PART = 16;
+// Every point in one polygon (64 cells), 30M points 2.4 and 1.3 ms.  Where points
+// meet several queries lists are better: 30M points, 78M pairs 3.2 and 4.8 ms.
+constexpr int64_t PK_LARGE = (int64_t)1 << 23, PK_PART = 16, PK_OVER = 2;
 
 // Count pass over chunks [c0, c1).  hits, when given, keeps the points that
 // matched: hits[(t - cbase[c0]) * BW_WORDS + j] for entry t of the chunks'
@@ -1920,9 +1920,10 @@ int spade_batch_join_pairs(spade_ctx *ctx, const spade_canvas *set, const spade_
     const SetArgs S = set_args(set);
     const int64_t n = t->n;
     DevBuf &bc = ctx->scratch[S_VALS2], &bo = ctx->scratch[S_ENTC], &cub = ctx->scratch[S_CUBTMP];
-    if (P.np * CHUNK <= (n >= PK_LARGE ? n : n / PK_PART)) {
+    if (P.np * CHUNK <= (n >= PK_LARGE ? n * PK_OVER : n / PK_PART)) {
         bool done = false;
-        rc = sorted_pairs(ctx, t, S, P, M, (unsigned long long)(P.np * CHUNK), out_pt, out_poly, cap, n_out, done);
+        const int64_t room = std::min<int64_t>({P.np * CHUNK, n + n / 8, INT32_MAX});
+        rc = sorted_pairs(ctx, t, S, P, M, (unsigned long long)room, out_pt, out_poly, cap, n_out, done);
         if (rc || done) return rc;
     }
     // counts by point id, and their places (64-bit: a join may hold more than
