@@ -609,9 +609,20 @@ __global__ __launch_bounds__(TILE_THREADS, 8) void k_hit_tiles(int nq, const uin
     for (int k = 0; k < PER; ++k)
         if ((on >> k) & 1u) sorted[bins[rb[k] >> 14] + (rb[k] & 0x3fffu)] = v[k];
     __syncthreads();
-    if (!keys) return;   // counts only
     uint32_t *dst = keys + (size_t)tile * TILE_IDS;
     for (uint32_t i = tid; i < total; i += TILE_THREADS) dst[i] = sorted[i];
+}
+
+// Counts alone: tot[q] += the ids of pair p of query q, a wavefront per pair.
+__global__ __launch_bounds__(256) void k_hit_count(uint32_t p0, uint32_t p1, uint32_t q0, const uint32_t *pq,
+                                                   const unsigned long long *hits, unsigned long long *tot)
+{
+    static_assert(BW_WORDS == 64, "a word per lane");
+    const int lane = threadIdx.x & 63;
+    for (uint32_t p = p0 + ((blockIdx.x * 256 + threadIdx.x) >> 6); p < p1; p += gridDim.x * 4) {
+        const uint32_t c = wave_incl_sum((uint32_t)__popcll(hits[(size_t)(p - p0) * BW_WORDS + lane]));
+        if (lane == 63 && c != 0u) atomicAdd(&tot[pq[p] - q0], (unsigned long long)c);
+    }
 }
 
 // Bucket totals: tot[q * nbins + b] = ids of query q in window b, summed over
@@ -1571,7 +1582,7 @@ int spade_batch_select(spade_ctx *ctx, const spade_canvas *set, const spade_tabl
     int L = std::min(idbits, SORT_LBITS);
     auto bins_at = [&](int l) { return (int)(((uint64_t)std::max<int64_t>(t->n - 1, 0) >> l) + 1); };
     while (L > SORT_LMIN && (int64_t)nq * bins_at(L) < 2 * cus && bins_at(L - 1) <= TILE_BINS) --L;
-    const int nbins = bins_at(L);
+    const int nbins = cap > 0 ? bins_at(L) : 1;   // counts alone need no windows
     // The queries are taken in groups.  A group's pairs, every query's rounded
     // up to whole tiles (a tile's keys take 64 KB however few pairs or ids it
     // has), have hit words of 512 bytes within the limit
@@ -1608,8 +1619,8 @@ int spade_batch_select(spade_ctx *ctx, const spade_canvas *set, const spade_tabl
     };
     auto room = [&]() {
         return ensure(ctx, bh, PAIR_BYTES * (size_t)pmost) ||
-               (cap > 0 && ensure(ctx, bo, sizeof(uint32_t) * TILE_IDS * (size_t)tmost)) ||
-               ensure(ctx, bs, sizeof(uint16_t) * (size_t)(nbins + 1) * (size_t)tmost);
+               (cap > 0 && (ensure(ctx, bo, sizeof(uint32_t) * TILE_IDS * (size_t)tmost) ||
+                            ensure(ctx, bs, sizeof(uint16_t) * (size_t)(nbins + 1) * (size_t)tmost)));
     };
     group_by(hits_max);
     while (room()) {
@@ -1619,7 +1630,7 @@ int spade_batch_select(spade_ctx *ctx, const spade_canvas *set, const spade_tabl
         group_by(hits_max);
     }
     unsigned long long *hits = (unsigned long long *)bh.p;
-    uint32_t *keys = cap > 0 ? (uint32_t *)bo.p : nullptr;
+    uint32_t *keys = (uint32_t *)bo.p;
     uint16_t *starts = (uint16_t *)bs.p;
     // bc: bucket counts [nbmax + 1] | offsets [nbmax + 1]
     const size_t nbmax = (size_t)gmost * nbins;
@@ -1661,11 +1672,17 @@ int spade_batch_select(spade_ctx *ctx, const spade_canvas *set, const spade_tabl
         else probe(k_batch_hits<false>);
         SPADE_HIP(ctx, hipGetLastError());
         if (ctx->timing && k == 0) SPADE_HIP(ctx, hipEventRecord(ctx->ev[3], st));
-        hipLaunchKernelGGL(k_hit_tiles, dim3(ntile), dim3(TILE_THREADS), tile_lds, st, ng, (const uint32_t *)dtf,
-                           (const unsigned long long *)P.qbase + q0, p0, P.pc, hits, (const uint32_t *)t->ids.p, L,
-                           nbins, keys, starts);
-        hipLaunchKernelGGL(k_bucket_tot, dim3((nbins + 63) / 64, std::min(ng, 32768)), dim3(TILE_THREADS), 0, st, ng,
-                           (const uint32_t *)dtf, (const uint16_t *)starts, nbins, tot);
+        if (cap > 0) {
+            hipLaunchKernelGGL(k_hit_tiles, dim3(ntile), dim3(TILE_THREADS), tile_lds, st, ng, (const uint32_t *)dtf,
+                               (const unsigned long long *)P.qbase + q0, p0, P.pc, hits, (const uint32_t *)t->ids.p, L,
+                               nbins, keys, starts);
+            hipLaunchKernelGGL(k_bucket_tot, dim3((nbins + 63) / 64, std::min(ng, 32768)), dim3(TILE_THREADS), 0, st, ng,
+                               (const uint32_t *)dtf, (const uint16_t *)starts, nbins, tot);
+        } else {
+            hipLaunchKernelGGL(k_zero64, dim3(grid_of(ng, 4096)), dim3(256), 0, st, (int64_t)ng, tot);
+            hipLaunchKernelGGL(k_hit_count, dim3((unsigned)std::min<int64_t>((p1 - p0 + 3) / 4, 1 << 16)), dim3(256), 0, st,
+                               p0, p1, (uint32_t)q0, (const uint32_t *)P.pq, (const unsigned long long *)hits, tot);
+        }
         SPADE_HIP(ctx, hipGetLastError());
         if (nb <= BUCKET_SCAN_MAX) {
             hipLaunchKernelGGL(k_bucket_scan, dim3(1), dim3(PS_THREADS), 0, st, ng, nbins, (const unsigned long long *)tot,
