@@ -1025,16 +1025,17 @@ __device__ __forceinline__ int run_end(const RowData &D, const RowShared &L, int
 }
 
 // Claimant records of the runs in rows where interiors overlap: every boundary
-// column inside a run's interior spans gets (S = 1, no edges).  A lane takes an
-// entry and the span behind it; long spans are walked by the whole wavefront,
-// one after the other, the others by their lanes.  The entries go round the
-// wavefronts in polygon order, so that a column's claimants come nearly in
-// that order, which the pairs' write pass orders by insertion.  Bound by its
-// LDS reads.  A thread per run, walking all its spans column after column,
-// left the row to its longest run: build and count of 260 overlapping polygons
-// 2.15 ms, now 0.68; of 300 large ones 43.8 ms, now 11.0; of 20,000 small
-// ones 388 us, now 358 (a wavefront per run: 443).
-constexpr int CLAIM_WIDE = 32;
+// column inside a run's interior spans gets (S = 1, no edges).  A lane holds an
+// entry and the span behind it; spans of CLAIM_WIDE columns are walked by the
+// wavefront, the others by CLAIM_LANES lanes each.  In entry order, so that a
+// column's claimants come nearly in polygon order, which the pairs' write pass
+// orders by insertion.  Bound by its LDS reads.  A thread per run, walking all
+// its spans column after column, left the row to its longest run: build and
+// count of 260 overlapping polygons 2.15 ms, now 0.66; of 300 large ones
+// 43.8 ms, now 11.0; of 20,000 small ones 388 us, now 357 (16 lanes: 379, a
+// wavefront per run: 443).  With a lane per narrow span the pairs of 20,000
+// overlapping polygons took 36.3 ms for 30M points, now 35.4 (16 lanes: 35.2).
+constexpr int CLAIM_WIDE = 64, CLAIM_LANES = 8;
 
 template <bool EMIT>
 __device__ void claimant_records(const RowArgs &A, const RowData &D, const RowShared &L, uint64_t rec_base_r, int W)
@@ -1064,14 +1065,23 @@ __device__ void claimant_records(const RowArgs &A, const RowData &D, const RowSh
             lo = max((int)(D.c[q] & 0xffff), (int)(pm & PM_COL));
             len = (q + 1 < D.n && D.poly[q + 1] == poly ? (int)(D.c[q + 1] & 0xffff) : W) - lo;
         }
-        for (unsigned long long m = __ballot(len >= CLAIM_WIDE); m; m &= m - 1) {
-            const int b = __ffsll((long long)m) - 1;
-            const int l0 = __builtin_amdgcn_readlane(lo, b), n = __builtin_amdgcn_readlane(len, b);
-            const uint32_t k = (uint32_t)__builtin_amdgcn_readlane((int)poly, b);
-            for (int col = lane; col < n; col += 64) claim(l0 + col, k);
+        const unsigned long long any = __ballot(len > 0), wide = __ballot(len >= CLAIM_WIDE);
+        constexpr int AT_ONCE = 64 / CLAIM_LANES;
+        for (int b = 0; b < 64; b += AT_ONCE) {
+            const unsigned long long these = ((1ull << AT_ONCE) - 1ull) << b;
+            if (!(any & these)) continue;
+            for (unsigned long long m = wide & these; m; m &= m - 1) {
+                const int w = __ffsll((long long)m) - 1;
+                const int l0 = __builtin_amdgcn_readlane(lo, w), n = __builtin_amdgcn_readlane(len, w);
+                const uint32_t k = (uint32_t)__builtin_amdgcn_readlane((int)poly, w);
+                for (int col = lane; col < n; col += 64) claim(l0 + col, k);
+            }
+            const int from = b + lane / CLAIM_LANES;
+            const int l0 = __shfl(lo, from, 64), n = __shfl(len, from, 64);
+            const uint32_t k = __shfl(poly, from, 64);
+            if (n < CLAIM_WIDE)
+                for (int col = lane % CLAIM_LANES; col < n; col += CLAIM_LANES) claim(l0 + col, k);
         }
-        if (len < CLAIM_WIDE)
-            for (int col = 0; col < len; ++col) claim(lo + col, poly);
     }
 }
 

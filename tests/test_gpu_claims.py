@@ -1,5 +1,5 @@
 """Claimant records of rows where interiors overlap: combs of teeth whose
-widths in pixels lie about the limit from which a wavefront walks a span, at
+widths in pixels lie about the limits from which 8 lanes or a wavefront walk a span, at
 offsets that shift them across lanes, with rows of fewer and of more entries
 than a wavefront and than the staging.  Pairs are whole numbers decided
 exactly, compared with the oracle's."""
@@ -24,7 +24,7 @@ def _comb(width, gap, shift, top):
     return np.asarray(ring + [(0.0, 0.0)])
 
 
-@pytest.mark.parametrize("width", [1.5, 31, 32, 33, 63, 64, 65, 500])
+@pytest.mark.parametrize("width", [1.5, 7, 8, 9, 31, 32, 33, 63, 64, 65, 500])
 def test_comb_spans(width):
     rings = [_comb(width, 2.0 + k, 3.0 + k, 20.0 + k) for k in range(5)]
     rings += [np.array([[100.0 + 7 * k, -20.0], [900.0 - 5 * k, -20.0], [900.0 - 5 * k, 30.0], [100.0 + 7 * k, 30.0]])
