@@ -88,8 +88,9 @@ typedef struct {
  * and spade_canvas_build size the canvas without waiting for the device;
  * the device still validates the offsets and the box before any kernel
  * depends on them, and a box that does not contain every vertex, like any
- * other invalid input, fails the call with SPADE_E_INVALID.  Canvas sets
- * (the batch calls) ignore it. */
+ * other invalid input, fails the call with SPADE_E_INVALID.  A batch of one
+ * query takes it the same way; larger batches, jobs and layered sets do not read
+ * it. */
 typedef struct {
     int64_t n_polys;
     int64_t n_rings;

@@ -11,9 +11,8 @@
 // match bits, whose ids are counted per window of ids and put in order window
 // by window; a join's count pass sizes every point's output range, a scan
 // places the ranges in id order and a write pass fills them (few pairs are
-// sorted as keys instead).  The join-count
-// needs no pair list: its single probe launch finds each chunk's queries
-// itself.
+// sorted as keys instead).  The join-count needs no pair list: its single probe
+// launch finds each chunk's queries itself.
 #include "common.h"
 #include "exact.h"
 #include "lookup.h"
@@ -376,10 +375,9 @@ __device__ __forceinline__ uint32_t wave_incl_sum(uint32_t v)
 // of 64 consecutive table points, one point per lane and word, and needs no
 // barrier.  The table is in Z order, so a task's box is small: most of the
 // (task, canvas) tests end at the box or at the canvas's coarse blocks under
-// it.  Few points per lane keep the registers low enough for eight
-// five or six wavefronts per SIMD, which is what hides the chain of dependent
-// reads (descriptor, coarse word, canvas word, record, edges) that bounds a
-// probe.
+// it.  Few points per lane keep the registers low enough for six wavefronts per
+// SIMD, which is what hides the chain of dependent reads (descriptor, coarse
+// word, canvas word, record, edges) that bounds a probe.
 constexpr int BW_PTS = 4;                        // words of 64 points per task
 constexpr int BW_TASKS = CHUNK / (64 * BW_PTS);  // tasks per chunk
 constexpr int BW_WORDS = CHUNK / 64;             // result words per chunk

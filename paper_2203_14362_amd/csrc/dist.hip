@@ -476,15 +476,15 @@ __device__ __forceinline__ uint32_t disk_mask_walk(const DiskCanvas &K, double x
 // Count pass: pairs per wavefront segment, and with pm every point's pairs as
 // (first entry of its cell, mask of the entries that hold it), or (all ones,
 // number) for a cell of more than 32 entries and the points tested with such
-// ones, so that the write pass reads 8 bytes per point and tests nothing else.  A point's entries that hold its whole
-// cell are pairs as they stand; points with others are queued in LDS and
-// tested 64 at a time.  Bound by the rate of L2 requests (the cells, and an
-// entry and a centre per test): 30M points, 10,000 disks of 300 m, 0.52 ms
-// with cells of 75 m (0.95 with cells of 300 m and every candidate tested a
-// word at a time).  The exact test costs registers (106 against 90), so a
-// first pass (EXACT false) decides by the filter and leaves DJ_OPEN as the
-// count of a segment in which a test stayed open, a second one (EXACT and
-// ONLY_OPEN) does those segments again.
+// ones, so that the write pass reads 8 bytes per point and tests nothing else.
+// A point's entries that hold its whole cell are pairs as they stand; points
+// with others are queued in LDS and tested 64 at a time.  Bound by the rate of
+// L2 requests (the cells, and an entry and a centre per test): 30M points,
+// 10,000 disks of 300 m, 0.52 ms with cells of 75 m (0.95 with cells of 300 m
+// and every candidate tested a word at a time).  The exact test costs registers
+// (106 against 90), so a first pass (EXACT false) decides by the filter and
+// leaves DJ_OPEN as the count of a segment in which a test stayed open, a second
+// one (EXACT and ONLY_OPEN) does those segments again.
 constexpr unsigned long long DJ_OPEN = ~0ull;
 constexpr int64_t DJ_FILTER_MIN = 1 << 20;   // points from which the second launch (5 us) pays
 

@@ -985,13 +985,14 @@ __global__ __launch_bounds__(256) void k_emit_bits(int64_t nseg, const unsigned 
 // whether the pairs' count pass keeps labels: p[0], set later by a point in
 // several polygons, and p[1] start at 0 if so, else at 1.  No labels where the
 // pixels that the raster found inside several polygons would hold one of n
-// evenly spread points: the write pass would have to probe again, and the
-// count pass without labels is the faster one (12 overlapping polygons, 30M
-// points: 224 us, with labels 344; the call 940 us and 1,055).  Everywhere else they pay, however many of the pixels are
-// boundary ones (calls of 30M points: 260 zones, 5 % of the pixels, 660 us
-// with labels and 930 probing twice; 29 %, 2.1 and 4.0 ms; 40,000 cells, 14 %,
-// 7.1 and 13.2 ms; 40,000 rectangles of a pixel each, 1.9 and 3.1 ms).  One
-// wavefront; over: the counters of a build not read yet, else null.
+// evenly spread points: the write pass would have to probe again, and the count
+// pass without labels is the faster one (12 overlapping polygons, 30M points:
+// 224 us, with labels 344; the call 940 us and 1,055).  Everywhere else they
+// pay, however many of the pixels are boundary ones (calls of 30M points: 260
+// zones, 5 % of the pixels, 660 us with labels and 930 probing twice; 29 %, 2.1
+// and 4.0 ms; 40,000 cells, 14 %, 7.1 and 13.2 ms; 40,000 rectangles of a pixel
+// each, 1.9 and 3.1 ms).  One wavefront; over: the counters of a build not read
+// yet, else null.
 __global__ __launch_bounds__(64) void k_emit_start(unsigned long long *end, unsigned *p, int labelled,
                                                    const unsigned long long *over, int shards, int stride,
                                                    unsigned long long known, unsigned long long n,
