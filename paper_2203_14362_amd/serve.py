@@ -432,14 +432,18 @@ class SpadeExecutor:
         """Device bytes a request holds while in flight (upper estimate):
         canvas words and coarse level (about three words per pixel), edges,
         their row entries and the boundary index sized from them (64-byte
-        records), outputs."""
+        records), outputs, and for a selection what orders its ids: the match
+        bits, keys and window starts (20 KiB) of every chunk of 4,096 table
+        points that its box meets, those on its sides included."""
         V = n_vertices(req.polys)
         px = min(max(self.ppv * V, 64 * 64), 4096 * 4096)
         b = 12 * px + 1024 * V + (1 << 20)
         if req.kind == "select":
             if V:
                 vx, vy = np.asarray(req.polys["vx"]), np.asarray(req.polys["vy"])
-                b += 4 * self._points_in_box(vx.min(), vx.max(), vy.min(), vy.max())
+                pts = self._points_in_box(vx.min(), vx.max(), vy.min(), vy.max())
+                chunks = pts / 4096
+                b += 4 * pts + 20480 * int(chunks + 4 * chunks ** 0.5 + 16)
         else:
             b += 8 * int(req.polys["n_polys"])
         return int(b)
